@@ -242,6 +242,8 @@ static void fill_decode_common(kvc_ctx* ctx, kvc::DecodeArgs& a) {
     a.pred = nullptr;
     a.max_blocks = a.n_seq = a.k = a.n_layers = 0;
     a.pool_blocks_per_layer = 0;
+    a.by_ppb = kvc::make_fast_div((uint32_t)ctx->g.ppb);
+    a.by_per_layer = a.by_k = kvc::make_fast_div(1);
 }
 
 int kvc_decompress_blocks(kvc_ctx* ctx, void* d_cache_out, int64_t n_out_blocks, const int32_t* d_pool_block_ids,
@@ -288,6 +290,8 @@ int kvc_gather_decompress(kvc_ctx* ctx, void* d_out, const int32_t* d_block_tabl
     a.k = k;
     a.n_layers = n_layers;
     a.pool_blocks_per_layer = pool_blocks_per_layer;
+    a.by_per_layer = kvc::make_fast_div((uint32_t)(n_seq * k));  // at most n_blocks, which is below 2^26
+    a.by_k = kvc::make_fast_div((uint32_t)k);
     return hip_ok(kvc::launch_decompress(a, static_cast<hipStream_t>(stream))) ? KVC_OK : KVC_ERR_HIP;
 }
 

@@ -33,9 +33,6 @@ typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 #ifndef KVC_NT_STORE
 #define KVC_NT_STORE 1
 #endif
-#ifndef KVC_NT_POOL
-#define KVC_NT_POOL 0
-#endif
 
 // 128-bit global accesses of streamed data (each byte is touched once)
 __device__ __forceinline__ uint4 load_stream(const uint4* p) {
@@ -672,27 +669,28 @@ __device__ __forceinline__ uint4 dequant8_biased(const uint32_t pb[8], float s, 
                       __builtin_bit_cast(uint32_t, h[2]), __builtin_bit_cast(uint32_t, h[3]));
 }
 
-// This lane's 8 values of its quad's packet in group set p, read from the staged payload: the bits
-// above each value's sign flag (hb) and the flag as 0 / -1 (sg): delta = hb ^ sg.
-template <int NP>
-__device__ __forceinline__ void unpack8(const DecodeArgs& a, const uint32_t* stage, const uint32_t* ginfo, int p, bool special, uint32_t hdr,
+// This lane's 8 values of its quad's packet in group set p, read from the staged payload.  gi: the packet's
+// body offset and code, as the header scan left them.  A value's zig-zag code u comes back in two parts,
+// sg = 0 or -1 from its lowest bit, and hb: u >> 1 (delta = hb ^ sg), or u itself if TWICE (2 delta = hb ^ sg;
+// the field then begins at the value's own bit, which saves the four offsets by one).  SPECIAL: the page has
+// zero-run or run packets (few pages do, and the others are decoded without the tests for them).
+template <int NP, bool TWICE, bool SPECIAL>
+__device__ __forceinline__ void unpack8(const DecodeArgs& a, const uint32_t* stage, uint32_t gi, uint32_t hdr,
                                         uint32_t (&hb)[8], int (&sg)[8]) {
     (void)hdr;
     (void)a;  // only the bounds-checking build reads it
-    const int lane = lane_id();
-    const uint32_t qi = (uint32_t)lane & 3u;
-    const uint32_t gi = ginfo[p * 16 + (lane >> 2)];
+    const uint32_t qi = (uint32_t)lane_id() & 3u;
     uint32_t c = gi & 15u;
     const uint32_t goff = gi >> 4;
-    uint32_t B = goff + qi * c;
-    if (special && c == 9) B = goff;
+    uint32_t B = goff + __umul24(qi, c);
+    if (SPECIAL && c == 9) B = goff;
     const uint32_t sh = (B & 3u) << 3;
     const uint32_t* p0 = stage + (B >> 2);
     KVC_CHECK(a.st, (B >> 2) + 2 < (uint32_t)Slot<NP>::kWords && B >= hdr);  // bodies start after the header bytes
     const uint32_t d0 = p0[0], d1 = p0[1], d2 = p0[2];
     uint32_t lo = __builtin_amdgcn_alignbit(d1, d0, sh);
     uint32_t hi = __builtin_amdgcn_alignbit(d2, d1, sh);
-    if (special) {
+    if (SPECIAL) {
         if (c == 9) {  // run packet: the body byte, 32 times
             lo = __builtin_amdgcn_perm(lo, lo, 0u);
             hi = lo;
@@ -704,142 +702,182 @@ __device__ __forceinline__ void unpack8(const DecodeArgs& a, const uint32_t* sta
         }
     }
     const uint32_t mid = shr_nibbles(lo, hi, c);  // values 4..7 start at bit 4c
-    // value k sits at bits [k*c, k*c + c); delta = (u >> 1) ^ -(u & 1) taken straight from the fields
-    const uint32_t w1 = c - 1u;
+    // value k sits at bits [k*c, k*c + c)
+    constexpr uint32_t kLow = TWICE ? 0u : 1u;
+    const uint32_t w = c - kLow;
     const uint32_t o1 = c, o2 = c << 1, o3 = o2 + c;
-    hb[0] = __builtin_amdgcn_ubfe(lo, 1u, w1), sg[0] = __builtin_amdgcn_sbfe((int)lo, 0u, 1u);
-    hb[1] = __builtin_amdgcn_ubfe(lo, o1 + 1u, w1), sg[1] = __builtin_amdgcn_sbfe((int)lo, o1, 1u);
-    hb[2] = __builtin_amdgcn_ubfe(lo, o2 + 1u, w1), sg[2] = __builtin_amdgcn_sbfe((int)lo, o2, 1u);
-    hb[3] = __builtin_amdgcn_ubfe(lo, o3 + 1u, w1), sg[3] = __builtin_amdgcn_sbfe((int)lo, o3, 1u);
-    hb[4] = __builtin_amdgcn_ubfe(mid, 1u, w1), sg[4] = __builtin_amdgcn_sbfe((int)mid, 0u, 1u);
-    hb[5] = __builtin_amdgcn_ubfe(mid, o1 + 1u, w1), sg[5] = __builtin_amdgcn_sbfe((int)mid, o1, 1u);
-    hb[6] = __builtin_amdgcn_ubfe(mid, o2 + 1u, w1), sg[6] = __builtin_amdgcn_sbfe((int)mid, o2, 1u);
-    hb[7] = __builtin_amdgcn_ubfe(mid, o3 + 1u, w1), sg[7] = __builtin_amdgcn_sbfe((int)mid, o3, 1u);
+    hb[0] = __builtin_amdgcn_ubfe(lo, kLow, w), sg[0] = __builtin_amdgcn_sbfe((int)lo, 0u, 1u);
+    hb[1] = __builtin_amdgcn_ubfe(lo, o1 + kLow, w), sg[1] = __builtin_amdgcn_sbfe((int)lo, o1, 1u);
+    hb[2] = __builtin_amdgcn_ubfe(lo, o2 + kLow, w), sg[2] = __builtin_amdgcn_sbfe((int)lo, o2, 1u);
+    hb[3] = __builtin_amdgcn_ubfe(lo, o3 + kLow, w), sg[3] = __builtin_amdgcn_sbfe((int)lo, o3, 1u);
+    hb[4] = __builtin_amdgcn_ubfe(mid, kLow, w), sg[4] = __builtin_amdgcn_sbfe((int)mid, 0u, 1u);
+    hb[5] = __builtin_amdgcn_ubfe(mid, o1 + kLow, w), sg[5] = __builtin_amdgcn_sbfe((int)mid, o1, 1u);
+    hb[6] = __builtin_amdgcn_ubfe(mid, o2 + kLow, w), sg[6] = __builtin_amdgcn_sbfe((int)mid, o2, 1u);
+    hb[7] = __builtin_amdgcn_ubfe(mid, o3 + kLow, w), sg[7] = __builtin_amdgcn_sbfe((int)mid, o3, 1u);
 }
-
-// A page on its way through the decoder: the descriptor's fields, the outcome of its validation and,
-// for the packed modes, the payload as it arrives from the pool (16 bytes per lane and round).
-template <class P>
-struct DecPage {
-    uint64_t off;
-    float s;
-    uint32_t n16, mode;
-    bool ok;
-    uint4 pay[P::kRounds];
-};
 
 template <class P>
 __device__ __forceinline__ bool is_packed_mode(uint32_t mode) {
     return mode == KVC_MODE_DELTA || mode == KVC_MODE_RLE || mode == KVC_MODE_PACK || (P::kChan && mode == KVC_MODE_CHAN);
 }
 
-// Take the descriptor apart, validate it against the pool and the page geometry, and start the
-// payload loads of a packed page.  Nothing here waits for those loads.
+// Lane-wise second half of the resolution: fetch the descriptor, validate it against the pool and the page
+// geometry.  Sticky status bits of bad indices and descriptors are set here.
 template <class P>
-__device__ __forceinline__ DecPage<P> dec_open(const DecodeArgs& a, uint4 dw) {
+__device__ __forceinline__ DecLanes dec_open(const DecodeArgs& a, const DecPlace& t) {
     const Extent x = page_extent<P>(a.g);
-    const int lane = lane_id();
-    DecPage<P> pg;
-    pg.off = (uint64_t)dw.x | ((uint64_t)dw.y << 32);
-    pg.s = __uint_as_float(dw.z);
-    pg.n16 = dw.w & 0xFFFFu;
-    pg.mode = (dw.w >> 16) & 0xFFu;
-    bool ok = (pg.off & 15u) == 0 && (pg.off >> 4) + pg.n16 <= a.pool_units;
-    if (pg.mode == KVC_MODE_RAW)
-        ok = ok && pg.n16 == x.E >> 3;
-    else if (pg.mode == KVC_MODE_INT8)
-        ok = ok && pg.n16 == x.E >> 4;
-    else if (is_packed_mode<P>(pg.mode))
-        ok = ok && pg.n16 * 16u >= x.hdr && pg.n16 < x.E >> 4;
-    else
-        ok = false;
-    pg.ok = ok;
-#pragma unroll
-    for (int z = 0; z < P::kRounds; ++z) pg.pay[z] = make_uint4(0u, 0u, 0u, 0u);
-    if (ok && is_packed_mode<P>(pg.mode)) {
-        const uint4* pl4 = reinterpret_cast<const uint4*>(a.pool + pg.off);
-#pragma unroll
-        for (int z = 0; z < P::kRounds; ++z) {
-#if KVC_NT_POOL
-            if ((uint32_t)lane + 64 * z < pg.n16) pg.pay[z] = load_stream(pl4 + lane + 64 * z);
-#else
-            if ((uint32_t)lane + 64 * z < pg.n16) pg.pay[z] = pl4[lane + 64 * z];
-#endif
-        }
-    }
-    return pg;
+    const bool placed = t.live && t.db >= 0 && t.db < a.n_out_blocks;
+    const uint64_t di = (uint64_t)t.pb * (uint64_t)a.g.ppb + t.pg;
+    const bool wanted = placed && (t.bad_index || t.pb >= 0);
+    const bool readable = wanted && !t.bad_index && di < a.n_desc;
+    uint4 dw = make_uint4(0u, 0u, 0u, 0u);
+    if (readable) dw = reinterpret_cast<const uint4*>(a.desc)[di];
+    DecLanes r;
+    r.db = t.db;
+    r.pg = t.pg;
+    r.off = (uint64_t)dw.x | ((uint64_t)dw.y << 32);
+    r.s = __uint_as_float(dw.z);
+    const uint32_t n16 = dw.w & 0xFFFFu, mode = (dw.w >> 16) & 0xFFu;
+    const bool raw = mode == KVC_MODE_RAW;
+    const bool in_pool = (r.off & 15u) == 0 && (r.off >> 4) + n16 <= a.pool_units;
+    const bool sized = raw ? n16 == x.E >> 3 : mode == KVC_MODE_INT8 ? n16 == x.E >> 4 : is_packed_mode<P>(mode) && n16 * 16u >= x.hdr && n16 < x.E >> 4;
+    const bool ok = readable && in_pool && sized;
+    const uint32_t kind = ok ? (raw ? kDecRaw : kDecPayload) : wanted ? kDecZero : kDecSkip;
+    r.meta = n16 | (mode << 16) | (kind << 24);
+    uint32_t st = 0;
+    if (t.live && ((t.db >= 0 && !placed) || (wanted && !readable))) st = KVC_ST_BAD_INDEX;
+    if (readable && !ok) st = KVC_ST_CORRUPT;
+    if (st) atomicOr(&a.st->status, st);
+    return r;
 }
 
-// Decode an opened page into dst.  false = validation failed, dst zeroed.
-template <class P>
-__device__ __forceinline__ bool dec_finish(const DecodeArgs& a, const DecPage<P>& pg, uint16_t* __restrict__ dst,
-                                           uint32_t* stage, uint32_t* ginfo) {
-    constexpr int NP = P::kPasses, kG = P::kGroups;
-    const Extent x = page_extent<P>(a.g);
-    const int lane = lane_id();
-    const float s = pg.s;
-    const uint32_t n16 = pg.n16, mode = pg.mode;
-    char* dst_b = reinterpret_cast<char*>(a.out) + wave_uniform((int64_t)(dst - a.out) * 2);  // wave-uniform page base
-    const LanePos lp = lane_pos<P>(a.g);
-    if (!pg.ok) {
-        zero_page(dst, a.g);
-        return false;
-    }
-    const uint4* pl4 = reinterpret_cast<const uint4*>(a.pool + pg.off);
-    if (mode == KVC_MODE_RAW) {  // stored-uncompressed bypass
+// Lane i's value in scalar registers (a batch of one page holds the same values in every lane).
+template <int PPW>
+__device__ __forceinline__ uint32_t of_lane(uint32_t v, int i) {
+    return (uint32_t)(PPW == 1 ? __builtin_amdgcn_readfirstlane((int)v) : __builtin_amdgcn_readlane((int)v, i));
+}
+template <int PPW>
+__device__ __forceinline__ uint64_t of_lane(uint64_t v, int i) {
+    return (uint64_t)of_lane<PPW>((uint32_t)v, i) | ((uint64_t)of_lane<PPW>((uint32_t)(v >> 32), i) << 32);
+}
+
+// 16 bytes from global memory straight to LDS: lane l's go to lds + 16 l (the destination is wave-uniform).
+__device__ __forceinline__ void load_to_lds16(const void* g, void* lds) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g, (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+}
+
+// Whether INT8 payloads go through LDS too.  With several pages per wave their loads have to be under way before
+// the first page is stored; with one page per wave they are read straight from the pool, pass by pass, which is
+// 1.5 % faster for whole launches of INT8 pages (262,144 pages of 4 KB: 285 us, 289 us through LDS).
+template <int PPW>
+constexpr bool kStageInt8 = PPW > 1;
+
+// Start the payload loads of the batch: page i's payload goes to LDS slot i, 16 bytes per lane and round,
+// without a stop in registers.  Payload bytes past the page's own are not read.
+template <class P, int PPW>
+__device__ __forceinline__ void dec_fetch(const DecodeArgs& a, const DecLanes& L, uint32_t (*slots)[Slot<P::kPasses>::kWords]) {
+    const uint32_t lane = (uint32_t)lane_id();
+    const bool staged = (L.meta >> 24) == kDecPayload && (kStageInt8<PPW> || ((L.meta >> 16) & 0xFFu) != KVC_MODE_INT8);
+    const uint32_t n_own = staged ? L.meta & 0xFFFFu : 0u;
 #pragma unroll
-        for (int p = 0; p < NP; ++p)
-            if (lane_live<P>(x, p)) *reinterpret_cast<uint4*>(dst_b + pass_base_off<P, false>(a.g, p) + pass_lane_off<P, false>(a.g, lp, p)) = pl4[p * 64 + lane];
-        return true;
-    }
-    const float neg128s = -128.0f * s;
-    if (mode == KVC_MODE_INT8) {
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            if (!lane_live<P>(x, p)) continue;
-            const uint2 v = reinterpret_cast<const uint2*>(pl4)[p * 64 + lane];
-            uint32_t pb[8];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                pb[k] = ((v.x >> (8 * k)) + 128u);
-                pb[4 + k] = ((v.y >> (8 * k)) + 128u);
-            }
-            store_stream(reinterpret_cast<uint4*>(dst_b + pass_base_off<P, false>(a.g, p) + pass_lane_off<P, false>(a.g, lp, p)), dequant8_biased(pb, s, neg128s));
-        }
-        return true;
-    }
-    // packed modes: stage the payload in LDS (fewer than kE/16 16-byte units)
-    {
-        uint4* st4 = reinterpret_cast<uint4*>(stage);
+    for (int i = 0; i < PPW; ++i) {
+        const uint32_t n16 = of_lane<PPW>(n_own, i);
+        const uint8_t* src = a.pool + of_lane<PPW>(L.off, i);
 #pragma unroll
         for (int z = 0; z < P::kRounds; ++z)
-            if ((uint32_t)lane + 64 * z < n16) st4[lane + 64 * z] = pg.pay[z];
+            if (lane + 64u * z < n16) load_to_lds16(src + (lane + 64u * z) * 16u, reinterpret_cast<uint4*>(slots[i]) + 64 * z);
     }
+}
+
+// The fetched payloads of this wave are in LDS.  (Waited for before the first output store is issued: loads
+// and stores retire in one order, so a payload waited for after a store would wait for the store too.)
+__device__ __forceinline__ void dec_fetched() {
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), the other counters unchanged
     wave_sync();
-    // header: a lane takes the code of group g (64 groups per round); body offsets are a prefix sum of
-    // body sizes
+}
+
+// How the header scan deals packet groups to lanes: pages whose groups divide the wave share a scan.
+template <class P>
+struct HeaderDeal {
+    static constexpr int kG = P::kGroups;
+    static constexpr int kSeg = 64 % kG == 0 ? kG : 64;  // lanes per page
+    static constexpr int kPages = 64 / kSeg;             // pages per scan
+    static constexpr int kRounds = (kG + 63) / 64;       // scans per page
+};
+
+// Scan the headers of the SCAN <= HeaderDeal<P>::kPages pages from page i0 on: info = body offset << 4 | code of
+// the lane's group (one per round).  `bad` / `special`: ballots of the lanes whose page fails validation, and of
+// the lanes whose group is a zero-run or run packet.
+template <class P, int PPW, int SCAN>
+__device__ __forceinline__ void dec_headers(const Extent& x, const DecLanes& L, int i0, const uint32_t (*slots)[Slot<P::kPasses>::kWords],
+                                            uint32_t (&info)[HeaderDeal<P>::kRounds], uint64_t& bad, uint64_t& special) {
+    using H = HeaderDeal<P>;
+    constexpr int kG = P::kGroups;
+    const int lane = lane_id();
+    const int pi = i0 + min(lane / H::kSeg, SCAN - 1);  // this lane's page
+    const uint32_t meta = SCAN == 1 ? of_lane<PPW>(L.meta, i0) : (uint32_t)__builtin_amdgcn_ds_bpermute(pi << 2, (int)L.meta);
+    const uint32_t n16 = meta & 0xFFFFu, mode = (meta >> 16) & 0xFFu;
+    const uint32_t* stage = SCAN == 1 ? slots[i0] : slots[pi];
     uint32_t total = x.hdr;
-    bool bad = false, special = false;
+    bool wrong = false, rare = false;
 #pragma unroll
-    for (int g0 = 0; g0 < kG; g0 += 64) {
-        const int g = g0 + lane;
-        const bool in_slot = kG % 64 == 0 || g < kG;                         // the group has an entry in ginfo
-        const bool live = P::kPartial ? (uint32_t)g < (x.E >> 5) : in_slot;  // ... and exists in this page
-        const uint32_t c_own = live ? (stage[g >> 3] >> ((g & 7) << 2)) & 15u : 1u;
-        const uint32_t size_own = !live ? 0u : (c_own == 9) ? 1u : (c_own << 2);
-        const uint32_t incl = wave_incl_scan_dpp(size_own);
-        // (a group beyond a short page: a one-bit literal at the payload's end, read but never stored)
-        if (in_slot) ginfo[g] = ((total + incl - size_own) << 4) | c_own;
-        total += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-        bad = bad || c_own > 9 || (mode == KVC_MODE_DELTA && (c_own == 0 || c_own == 9));
-        special = special || c_own == 0 || c_own == 9;
+    for (int r = 0; r < H::kRounds; ++r) {
+        const int g = r * 64 + lane % H::kSeg;
+        const bool in_page = P::kPartial ? (uint32_t)g < (x.E >> 5) : (kG % H::kSeg == 0 || g < kG);
+        // (a group beyond the page: a one-bit literal at the payload's end, read but never stored)
+        const uint32_t c = in_page ? (stage[g >> 3] >> ((g & 7) << 2)) & 15u : 1u;
+        const uint32_t size = !in_page ? 0u : c == 9 ? 1u : c << 2;
+        uint32_t incl;
+        if (H::kSeg == 64) {
+            incl = wave_incl_scan_dpp(size);
+        } else {
+            incl = row16_incl_scan_dpp(size);
+            if (H::kSeg == 32) incl += dpp<0x142, 0xA>(0, incl);  // odd rows add the row before
+        }
+        info[r] = ((total + incl - size) << 4) | c;
+        wrong = wrong || c > 9 || (mode == KVC_MODE_DELTA && (c == 0 || c == 9));
+        rare = rare || c == 0 || c == 9;
+        if (r + 1 < H::kRounds)
+            total += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        else
+            wrong = wrong || (lane % H::kSeg == H::kSeg - 1 && ((total + incl + 15u) >> 4) != n16);
     }
-    special = __builtin_amdgcn_ballot_w64(special) != 0;  // any zero-run / run packet in the page
-    if (__builtin_amdgcn_ballot_w64(bad) != 0 || ((total + 15u) >> 4) != n16) {
-        zero_page(dst, a.g);
-        return false;
+    const bool packed = (meta >> 24) == kDecPayload && mode != KVC_MODE_INT8;
+    bad = __builtin_amdgcn_ballot_w64(packed && wrong);
+    special = __builtin_amdgcn_ballot_w64(packed && rare);
+}
+
+// Decode an INT8 payload at src (the staged copy, or the pool itself) into the page at dst_b.
+template <class P>
+__device__ __forceinline__ void dec_int8(const DecodeArgs& a, const Extent& x, const LanePos& lp, float s, char* dst_b, const uint2* src) {
+#pragma unroll
+    for (int p = 0; p < P::kPasses; ++p) {
+        if (!lane_live<P>(x, p)) continue;
+        const uint2 v = src[p * 64 + lane_id()];
+        const uint32_t lo = v.x ^ 0x80808080u, hi = v.y ^ 0x80808080u;  // + 128 in every byte: the sign bits change
+        uint32_t pb[8];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            pb[k] = lo >> (8 * k);
+            pb[4 + k] = hi >> (8 * k);
+        }
+        store_stream(reinterpret_cast<uint4*>(dst_b + pass_base_off<P, false>(a.g, p) + pass_lane_off<P, false>(a.g, lp, p)), dequant8_biased(pb, s, -128.0f * s));
     }
-    wave_sync();
+}
+
+// Decode one staged packed payload into the page at dst_b.  seg0: the first lane of the page's part of `info`.
+// SPECIAL: the page may hold zero-run and run packets.
+template <class P, bool SPECIAL>
+__device__ __forceinline__ void dec_page(const DecodeArgs& a, const Extent& x, const LanePos& lp, uint32_t mode, float s, char* dst_b, const uint32_t* stage,
+                                         const uint32_t (&info)[HeaderDeal<P>::kRounds], int seg0) {
+    constexpr int NP = P::kPasses;
+    const int lane = lane_id();
+    const float neg128s = -128.0f * s;
+    // info of the group this lane's quad unpacks in group set p: lane seg0 + (16 p + quad) mod 64 of its scan
+    auto group_info = [&](int p) {
+        const uint32_t from = (uint32_t)(seg0 + (p * 16) % 64 + (lane >> 2)) << 2;
+        return (uint32_t)__builtin_amdgcn_ds_bpermute((int)from, (int)info[(p * 16) / 64]);
+    };
     if constexpr (P::kChan && P::kD == 64) {
         if (mode == KVC_MODE_CHAN) {
             // Mode 5 with eight octets (see the encoder): group set s holds, for this lane, pair 2s + h of its
@@ -853,7 +891,7 @@ __device__ __forceinline__ bool dec_finish(const DecodeArgs& a, const DecPage<P>
             for (int sset = 0; sset < 2; ++sset) {
                 uint32_t hb[8];
                 int sg[8];
-                unpack8<NP>(a, stage, ginfo, sset, special, x.hdr, hb, sg);
+                unpack8<NP, false, SPECIAL>(a, stage, group_info(sset), x.hdr, hb, sg);
                 uint32_t b[8];
 #pragma unroll
                 for (int m = 0; m < 8; ++m) b[m] = (hb[m] ^ (uint32_t)sg[m]) + 128u;
@@ -873,54 +911,57 @@ __device__ __forceinline__ bool dec_finish(const DecodeArgs& a, const DecPage<P>
                 store_stream(reinterpret_cast<uint4*>(dst_b + pass_base_off<P, true>(a.g, p) + pass_lane_off<P, true>(a.g, lp, p)),
                              dequant8_biased(pb, s, neg128s));
             }
-            return true;
+            return;
         }
-    } else if (P::kChan && mode == KVC_MODE_CHAN) {
-        // Mode 5: of a run of 16 octets, group set j holds channels 2j, 2j + 1 of the lane's octet,
-        // tokens 4p + (lane & 3) for p = 0..3 (value 2p + e of the packet = pass p, channel 2j + e).  The
-        // biased codes of a set are kept as bytes, so that pass p then finds its eight codes at fixed
-        // byte positions.
+    } else if constexpr (P::kChan) {
+        if (mode == KVC_MODE_CHAN) {
+            // Mode 5: of a run of 16 octets, group set j holds channels 2j, 2j + 1 of the lane's octet,
+            // tokens 4p + (lane & 3) for p = 0..3 (value 2p + e of the packet = pass p, channel 2j + e).  The
+            // biased codes of a set are kept as bytes, so that pass p then finds its eight codes at fixed
+            // byte positions.
 #pragma unroll
-        for (int h = 0; h < NP / 4; ++h) {
-            uint32_t packed[4][2];
+            for (int h = 0; h < NP / 4; ++h) {
+                uint32_t packed[4][2];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint32_t hb[8];
-                int sg[8];
-                unpack8<NP>(a, stage, ginfo, 4 * h + j, special, x.hdr, hb, sg);
-                uint32_t b[8];
+                for (int j = 0; j < 4; ++j) {
+                    uint32_t hb[8];
+                    int sg[8];
+                    unpack8<NP, false, SPECIAL>(a, stage, group_info(4 * h + j), x.hdr, hb, sg);
+                    uint32_t b[8];
 #pragma unroll
-                for (int m = 0; m < 8; ++m) b[m] = (hb[m] ^ (uint32_t)sg[m]) + 128u;
-                packed[j][0] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u), __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), 0x05040100u);
-                packed[j][1] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[7], b[6], 0x0c0c0400u), __builtin_amdgcn_perm(b[5], b[4], 0x0c0c0400u), 0x05040100u);
-            }
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                uint32_t pb[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const int m = 2 * p + (k & 1);  // value index inside group set k / 2
-                    pb[k] = packed[k >> 1][m >> 2] >> (8 * (m & 3));
+                    for (int m = 0; m < 8; ++m) b[m] = (hb[m] ^ (uint32_t)sg[m]) + 128u;
+                    packed[j][0] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u), __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), 0x05040100u);
+                    packed[j][1] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[7], b[6], 0x0c0c0400u), __builtin_amdgcn_perm(b[5], b[4], 0x0c0c0400u), 0x05040100u);
                 }
-                store_stream(reinterpret_cast<uint4*>(dst_b + pass_base_off<P, true>(a.g, 4 * h + p) + pass_lane_off<P, true>(a.g, lp, 4 * h + p)),
-                             dequant8_biased(pb, s, neg128s));
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    uint32_t pb[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const int m = 2 * p + (k & 1);  // value index inside group set k / 2
+                        pb[k] = packed[k >> 1][m >> 2] >> (8 * (m & 3));
+                    }
+                    store_stream(reinterpret_cast<uint4*>(dst_b + pass_base_off<P, true>(a.g, 4 * h + p) + pass_lane_off<P, true>(a.g, lp, 4 * h + p)),
+                                 dequant8_biased(pb, s, neg128s));
+                }
             }
+            return;
         }
-        return true;
     }
+    const bool no_delta = mode == KVC_MODE_PACK;
     uint32_t carry = 0;  // what a row that continues from the pass before had summed up there
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        uint32_t hb[8];  // bits above the sign flag
-        int sg[8];       // 0 or -1 from the sign flag
-        unpack8<NP>(a, stage, ginfo, p, special, x.hdr, hb, sg);
-        uint32_t pb[8];
-        if (mode == KVC_MODE_PACK) {  // no delta step was taken: the fields are the codes
+        uint32_t hb[8];  // a value's zig-zag code
+        int sg[8];       // 0 or -1 from its sign flag
+        unpack8<NP, true, SPECIAL>(a, stage, group_info(p), x.hdr, hb, sg);
+        uint32_t pb[8];  // biased codes in byte 1: ((2 q) << 7) + (128 << 8)
+        if (no_delta) {  // no delta step was taken: the fields are the codes
 #pragma unroll
-            for (int k = 0; k < 8; ++k) pb[k] = (hb[k] ^ (uint32_t)sg[k]) + 128u;
+            for (int k = 0; k < 8; ++k) pb[k] = ((hb[k] ^ (uint32_t)sg[k]) << 7) + 0x8000u;
         } else {
-            // prefix sum along the channel index: in the lane first (each step is one xor-add), then
-            // the lanes of the token row before this one
+            // prefix sum along the channel index, of twice the deltas: in the lane first (each step is one
+            // xor-add), then the lanes of the token row before this one
             uint32_t pre[8];
             pre[0] = hb[0] ^ (uint32_t)sg[0];
 #pragma unroll
@@ -928,47 +969,86 @@ __device__ __forceinline__ bool dec_finish(const DecodeArgs& a, const DecPage<P>
             const uint32_t tot = pre[7];
             const uint32_t incl = row_incl_scan<P>(lp, p, tot, carry);
             if (!P::kAligned) carry = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-            const uint32_t base = incl - tot + 128u;  // +128: biased codes, see dequant8_biased
+            const uint32_t base = ((incl - tot) << 7) + 0x8000u;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) pb[k] = pre[k] + base;
+            for (int k = 0; k < 8; ++k) pb[k] = (pre[k] << 7) + base;
         }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) pb[k] >>= 8;
         if (lane_live<P>(x, p))
             store_stream(reinterpret_cast<uint4*>(dst_b + pass_base_off<P, false>(a.g, p) + pass_lane_off<P, false>(a.g, lp, p)), dequant8_biased(pb, s, neg128s));
     }
-    return true;
+}
+
+// Decode the pages of a batch whose payloads dec_fetch has begun to load.
+template <class P, int PPW>
+__device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L, const LanePos& lp, uint32_t (*slots)[Slot<P::kPasses>::kWords]) {
+    using H = HeaderDeal<P>;
+    static_assert(PPW % H::kPages == 0 || PPW == 1, "a header scan covers whole pages of the batch");
+    constexpr int kScan = PPW < H::kPages ? PPW : H::kPages;  // pages taken from one scan
+    const Extent x = page_extent<P>(a.g);
+    dec_fetched();
+#pragma unroll 1
+    for (int i0 = 0; i0 < PPW; i0 += kScan) {
+        uint32_t info[H::kRounds];
+        uint64_t bad, special;
+        dec_headers<P, PPW, kScan>(x, L, i0, slots, info, bad, special);
+#pragma unroll 1
+        for (int j = 0; j < kScan; ++j) {
+            const int i = i0 + j;
+            const uint32_t meta = of_lane<PPW>(L.meta, i);
+            const uint32_t kind = meta >> 24;
+            if (kind == kDecSkip) continue;
+            uint16_t* dst = a.out + page_base(a.g, (int64_t)(int32_t)of_lane<PPW>((uint32_t)L.db, i), (int)of_lane<PPW>(L.pg, i));
+            constexpr uint64_t kSegMask = H::kSeg == 64 ? ~0ull : (1ull << (H::kSeg & 63)) - 1;
+            const bool bad_header = ((bad >> (j * H::kSeg)) & kSegMask) != 0;
+            if (kind == kDecZero || bad_header) {
+                zero_page(dst, a.g);
+                if (bad_header && lane_id() == 0) atomicOr(&a.st->status, KVC_ST_CORRUPT);
+                continue;
+            }
+            char* dst_b = reinterpret_cast<char*>(dst);
+            if (kind == kDecRaw) {  // stored-uncompressed bypass
+                // (a pass is stored before the next is loaded: whole launches of raw pages are 1.5 % faster so than
+                // with all loads ahead of all stores)
+                const uint4* src = reinterpret_cast<const uint4*>(a.pool + of_lane<PPW>(L.off, i));
+#pragma unroll
+                for (int p = 0; p < P::kPasses; ++p)
+                    if (lane_live<P>(x, p)) *reinterpret_cast<uint4*>(dst_b + pass_base_off<P, false>(a.g, p) + pass_lane_off<P, false>(a.g, lp, p)) = src[p * 64 + lane_id()];
+                continue;
+            }
+            const uint32_t mode = (meta >> 16) & 0xFFu;
+            const float s = __uint_as_float(of_lane<PPW>(__float_as_uint(L.s), i));
+            if (mode == KVC_MODE_INT8) {
+                if constexpr (kStageInt8<PPW>)
+                    dec_int8<P>(a, x, lp, s, dst_b, reinterpret_cast<const uint2*>(slots[i]));
+                else
+                    dec_int8<P>(a, x, lp, s, dst_b, reinterpret_cast<const uint2*>(a.pool + of_lane<PPW>(L.off, i)));
+                continue;
+            }
+            if (((special >> (j * H::kSeg)) & kSegMask) != 0)
+                dec_page<P, true>(a, x, lp, mode, s, dst_b, slots[i], info, j * H::kSeg);
+            else
+                dec_page<P, false>(a, x, lp, mode, s, dst_b, slots[i], info, j * H::kSeg);
+        }
+    }
 }
 
 template <class P, int WAVES, int PPW>
 __global__ __launch_bounds__(WAVES * 64) void k_decompress(DecodeArgs a) {
-    __shared__ __align__(16) uint32_t s_stage[WAVES][Slot<P::kPasses>::kWords];
-    __shared__ uint32_t s_ginfo[WAVES][P::kGroups];
+    __shared__ __align__(16) uint32_t s_stage[WAVES][PPW][Slot<P::kPasses>::kWords];
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t t0 = ((int64_t)task_block_index<1>() * WAVES + wave) * PPW;
-    TaskPos pos = task_pos(t0, a.g.ppb);
-    // A page's memory chain is ids -> descriptor -> payload, each a full trip to HBM.  The wave walks
-    // it for all of its PPW pages side by side: every descriptor load is issued before the first is
-    // looked at, then every payload load before the first page is decoded.
-    DecTask task[PPW];
-    uint4 dw[PPW];
-    DecPage<P> pg[PPW];
-#pragma unroll
-    for (int i = 0; i < PPW; ++i) {
-        task[i] = resolve_dec_task(a, t0 + i, pos);
-        task_advance(pos, a.g.ppb);
-        if (task[i].kind == 1) dw[i] = reinterpret_cast<const uint4*>(a.desc)[task[i].desc_idx];
-    }
-#pragma unroll
-    for (int i = 0; i < PPW; ++i)
-        if (task[i].kind == 1) pg[i] = dec_open<P>(a, dw[i]);
-#pragma unroll
-    for (int i = 0; i < PPW; ++i) {
-        if (task[i].kind == 2) zero_page(task[i].dst, a.g);
-        if (task[i].kind == 1 && !dec_finish<P>(a, pg[i], task[i].dst, s_stage[wave], s_ginfo[wave])) {
-            if (lane == 0) atomicOr(&a.st->status, KVC_ST_CORRUPT);
-        }
-        wave_sync();
-    }
+    if (t0 >= a.n_pages) return;
+    // A page's memory chain is ids -> descriptor -> payload, each a full trip to HBM.  The wave walks it for
+    // all of its PPW pages at once: lane i resolves page i, then all payload loads are issued, straight to
+    // LDS, and the pages are decoded one after the other.
+    const LanePos lp = lane_pos<P>(a.g);
+    // (a batch of one page is resolved on the scalar unit: every lane has the same task)
+    const DecLanes L = dec_open<P>(a, PPW == 1 ? dec_locate(a, true, (uint32_t)t0) : dec_locate(a, lane < PPW && t0 + lane < a.n_pages, (uint32_t)t0 + (uint32_t)lane));
+    dec_fetch<P, PPW>(a, L, s_stage[wave]);
+    dec_batch<P, PPW>(a, L, lp, s_stage[wave]);
 }
 
 // Transfer engines of the prefetch window (Algorithm 1: at most Omega_max transfers outstanding): a
@@ -977,13 +1057,14 @@ __global__ __launch_bounds__(WAVES * 64) void k_decompress(DecodeArgs a) {
 // (pages of up to four passes whose rows do not cross passes: held within 128 VGPRs, so that four waves fit a SIMD)
 template <class P, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::kPasses <= 4 && P::kAligned ? 4 : 1))) void k_decompress_window(DecodeArgs a, WindowArgs w) {
-    __shared__ __align__(16) uint32_t s_stage[WAVES][Slot<P::kPasses>::kWords];
-    __shared__ uint32_t s_ginfo[WAVES][P::kGroups];
+    constexpr int kSide = 4;
+    __shared__ __align__(16) uint32_t s_stage[WAVES][kSide][Slot<P::kPasses>::kWords];
     __shared__ uint32_t s_turn[2];
     __shared__ int32_t s_q[WAVES][2][64];
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ppb = a.g.ppb;
+    const LanePos lp = lane_pos<P>(a.g);
     if (blockIdx.x >= w.hdr->engines) return;  // the window was opened for fewer engines than the grid holds
     WindowTurn none;
     none.first = none.count = 0;
@@ -1000,31 +1081,20 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
       for (uint32_t i = 0; i < turn.count; ++i) {
         const int32_t slot = __builtin_amdgcn_readfirstlane(s_q[wave][0][i]);
         const int32_t pb = __builtin_amdgcn_readfirstlane(s_q[wave][1][i]);
-        // a wave takes the block's pages wave, wave + WAVES, ... four at a time: all four descriptor loads
-        // are issued before the first is looked at, then all payload loads before the first page is decoded
-        constexpr int kSide = 4;
+        // a wave takes the block's pages wave, wave + WAVES, ... kSide at a time: lane j resolves the j-th of
+        // them, and all payload loads are issued before the first page is decoded
         for (int pg0 = wave; pg0 < ppb; pg0 += kSide * WAVES) {
-            DecTask task[kSide];
-            uint4 dw[kSide];
-            DecPage<P> dp[kSide];
-#pragma unroll
-            for (int j = 0; j < kSide; ++j) {
-                const int pg = pg0 + j * WAVES;
-                task[j].kind = 0;  // past the block: no task
-                if (pg < ppb) task[j] = place_dec_task(a, pb, slot, pg, false);
-                if (task[j].kind == 1) dw[j] = reinterpret_cast<const uint4*>(a.desc)[task[j].desc_idx];
-            }
-#pragma unroll
-            for (int j = 0; j < kSide; ++j)
-                if (task[j].kind == 1) dp[j] = dec_open<P>(a, dw[j]);
-#pragma unroll
-            for (int j = 0; j < kSide; ++j) {
-                if (task[j].kind == 2) zero_page(task[j].dst, a.g);
-                if (task[j].kind == 1 && !dec_finish<P>(a, dp[j], task[j].dst, s_stage[wave], s_ginfo[wave])) {
-                    if (lane == 0) atomicOr(&a.st->status, KVC_ST_CORRUPT);
-                }
-                wave_sync();
-            }
+            DecPlace t;
+            t.pg = (uint32_t)(pg0 + lane * WAVES);
+            t.live = lane < kSide && (int)t.pg < ppb;
+            t.bad_index = false;
+            t.pb = pb;
+            t.db = slot;
+            const DecLanes L = dec_open<P>(a, t);
+            dec_fetch<P, kSide>(a, L, s_stage[wave]);
+            dec_batch<P, kSide>(a, L, lp, s_stage[wave]);
+            wave_sync();
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the slots have been read before they are filled again
         }
       }
       turn = window_next(w, s_turn, turn);
@@ -1043,7 +1113,10 @@ constexpr int enc_waves_large(int np) { return np >= 5 ? KVC_ENC_WAVES_LONG : np
 // the smallest pages), so the pages are encoded side by side instead of several in a row.  The cursor
 // then takes an atomic per four pages, which only a large call would feel.
 constexpr int enc_ppw_small(int np) { return np == 1 ? 4 : np == 2 ? 2 : 1; }
-// a page of one or two passes is too small to cover its own memory chain: a wave walks several side by side
+// Pages per decoder wave: a page of one or two passes is too small to cover its own memory chain, so a wave
+// takes the pages that share a header scan, resolved one per lane.  Measured (half a million pages, us): one
+// pass 180 / 112 / 117 with 1 / 4 / 8 pages, two passes 283 / 276 / 294 with 1 / 2 / 4, four passes 1075 / 1083 /
+// 1109 (a million pages) with 1 / 2 / 4: there the launch moves 5.8 TB/s, what a copy does, with any of them.
 constexpr int dec_ppw(int np) { return np == 1 ? 4 : np == 2 ? 2 : 1; }
 // calls of at most this many pages take the low-latency launch shape
 #ifndef KVC_ENC_SMALL_PAGES

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "kvc.h"
+#include "kvc_fastdiv.h"
 
 namespace kvc {
 
@@ -57,6 +58,8 @@ struct DecodeArgs {
     const int32_t* pred;
     int32_t max_blocks, n_seq, k, n_layers;
     int64_t pool_blocks_per_layer;
+    // divisions of the task resolution: by ppb, and in the gather form by n_seq * k and by k
+    FastDiv by_ppb, by_per_layer, by_k;
 };
 
 constexpr int kMaxPrefetchK = 32;  // predictions per sequence the slot-reuse policy can plan

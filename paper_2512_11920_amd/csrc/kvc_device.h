@@ -265,70 +265,63 @@ __device__ __forceinline__ EncTask resolve_enc_task(const EncodeArgs& a, int64_t
     return r;
 }
 
-// Page task of the decoder.  kind: 0 skip, 1 decode desc_idx into dst, 2 zero-fill dst (bad index).
-struct DecTask {
-    int kind;
-    uint64_t desc_idx;
-    uint16_t* dst;
+// Page tasks of the decoder, one per lane: lane i of a wave holds what there is to know about page i of the
+// wave's batch, so that the ids, the table entries and the descriptors of all its pages are fetched by one
+// load each.  (Resolved one page after the other, with wave-uniform values, every descriptor was waited for
+// before the next one was asked for: at 1 KB pages a wave of four pages spent 70 % of its cycles in those waits.)
+enum DecKind : uint32_t {
+    kDecSkip = 0,     // nothing to do
+    kDecPayload = 1,  // packed or INT8 payload
+    kDecRaw = 2,      // stored uncompressed
+    kDecZero = 3,     // bad index or descriptor: the page is zero-filled
+};
+struct DecLanes {
+    uint64_t off;   // byte offset of the payload in the pool
+    int32_t db;     // output block
+    uint32_t pg;    // page inside the block
+    float s;
+    uint32_t meta;  // n16 | mode << 16 | DecKind << 24
 };
 
-// Second half of the resolution: pool block pb (< 0: nothing stored there) into output block db.
-__device__ __forceinline__ DecTask place_dec_task(const DecodeArgs& a, int64_t pb, int64_t db, int pg, bool bad_index) {
-    DecTask r;
-    r.kind = 0;
-    r.desc_idx = 0;
-    r.dst = nullptr;
-    const Geometry& g = a.g;
-    if (db < 0 || db >= a.n_out_blocks) {
-        if (db >= 0 && lane_id() == 0) atomicOr(&a.st->status, KVC_ST_BAD_INDEX);
-        return r;
-    }
-    r.dst = a.out + page_base(g, db, pg);
-    if (!bad_index && pb < 0) return r;  // skip
-    r.desc_idx = (uint64_t)pb * (uint64_t)g.ppb + (uint64_t)pg;
-    if (bad_index || r.desc_idx >= a.n_desc) {
-        if (lane_id() == 0) atomicOr(&a.st->status, KVC_ST_BAD_INDEX);
-        r.kind = 2;
-        return r;
-    }
-    r.kind = 1;
-    return r;
-}
+// Where a page task comes from and goes to, before the descriptor is looked at.
+struct DecPlace {
+    bool live, bad_index;  // live = false: no task (the other fields are meaningless)
+    int64_t pb;            // pool block (< 0: nothing stored)
+    int32_t db;            // output block (< 0: skip)
+    uint32_t pg;           // page inside the block
+};
 
-__device__ __forceinline__ DecTask resolve_dec_task(const DecodeArgs& a, int64_t t, const TaskPos& pos) {
-    if (t >= a.n_pages) {
-        DecTask r;
-        r.kind = 0;
-        r.desc_idx = 0;
-        r.dst = nullptr;
-        return r;
-    }
-    const int64_t blk = pos.blk;
-    int64_t pb, db;
-    bool bad_index = false;
+// lane-wise: page task t of the call (t < 2^31)
+__device__ __forceinline__ DecPlace dec_locate(const DecodeArgs& a, bool live, uint32_t t) {
+    DecPlace r;
+    r.live = live;
+    r.bad_index = false;
+    const uint32_t blk = fast_div(t, a.by_ppb);
+    r.pg = t - blk * (uint32_t)a.g.ppb;
+    r.db = (int32_t)blk;
+    r.pb = -1;
     if (a.block_table) {  // translate (layer, sequence, predicted logical block) -> pool block
         const uint32_t per_layer = (uint32_t)a.n_seq * (uint32_t)a.k;  // blocks of one call fit 31 bits
-        const uint32_t layer_u = (uint32_t)blk / per_layer;
-        const uint32_t sj = (uint32_t)blk - layer_u * per_layer;
-        const int64_t sq = sj / (uint32_t)a.k;
-        const int64_t layer = layer_u;
-        const int32_t lb = wave_uniform(a.pred[sj]);
-        db = blk;
-        pb = -1;
-        if (lb >= a.max_blocks) {
-            bad_index = true;
-        } else if (lb >= 0) {
-            const int32_t e = wave_uniform(a.block_table[sq * a.max_blocks + lb]);
-            if (e >= a.pool_blocks_per_layer)
-                bad_index = true;
-            else if (e >= 0)
-                pb = layer * a.pool_blocks_per_layer + e;
+        const uint32_t layer = fast_div(blk, a.by_per_layer);
+        const uint32_t sj = blk - layer * per_layer;
+        const uint32_t sq = fast_div(sj, a.by_k);
+        if (live) {
+            const int32_t lb = a.pred[sj];
+            r.bad_index = lb >= a.max_blocks;
+            if (lb >= 0 && !r.bad_index) {
+                const int32_t e = a.block_table[(int64_t)sq * a.max_blocks + lb];
+                r.bad_index = e >= a.pool_blocks_per_layer;
+                if (e >= 0) r.pb = (int64_t)layer * a.pool_blocks_per_layer + e;
+            }
         }
     } else {
-        pb = a.pool_ids ? (int64_t)wave_uniform(a.pool_ids[blk]) : blk;
-        db = a.dst_ids ? (int64_t)wave_uniform(a.dst_ids[blk]) : blk;
+        int32_t pb = (int32_t)blk, db = (int32_t)blk;
+        if (live && a.pool_ids) pb = a.pool_ids[blk];
+        if (live && a.dst_ids) db = a.dst_ids[blk];
+        r.pb = pb;
+        r.db = db;
     }
-    return place_dec_task(a, pb, db, pos.pg, bad_index);
+    return r;
 }
 
 __device__ __forceinline__ void zero_page(uint16_t* dst, const Geometry& g) {
