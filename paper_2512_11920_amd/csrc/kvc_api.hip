@@ -352,6 +352,7 @@ static int prefetch_impl(kvc_ctx* ctx, void* d_l2, int32_t* d_tags, int32_t* d_f
     p.fill_half = fill_half;
     p.policy = ctx->prefetch_policy;
     p.pool_blocks_per_layer = pool_blocks_per_layer;
+    p.by_n_seq = kvc::make_fast_div((uint32_t)n_seq);
     p.tags = d_tags;
     p.fetch = d_fetch;
     p.loc = d_loc;

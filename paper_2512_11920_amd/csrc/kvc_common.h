@@ -72,6 +72,7 @@ struct PlanArgs {
     int32_t max_blocks, n_seq, k, layer_begin, layer_end, n_layers, fill_half;
     int32_t policy;              // 0: slot j for prediction j; 1: keep wanted blocks, fill unwanted slots
     int64_t pool_blocks_per_layer;
+    FastDiv by_n_seq;
     int32_t* tags;   // [2][n_layers*n_seq*k]
     int32_t* fetch;  // [n_layers*n_seq*k]
     int32_t* loc;    // [n_layers*n_seq*k]
