@@ -112,10 +112,13 @@ __global__ __launch_bounds__(64) void k_prefetch_plan(PlanArgs a) {
     if (live && lb >= 0 && lb < a.max_blocks) want = in_l1 ? -2 : (e < 0 || bad) ? -1 : (int32_t)((int64_t)l * a.pool_blocks_per_layer + e);
 
     // this row's part of a ballot, bit j2 = lane j2 of the row
+    // (the half of the ballot by masks: of a selection the compiler may make a 64-bit shift by a lane's own amount)
     const int lane0 = lane - j;
+    const uint32_t upper = 0u - (uint32_t)(lane >> 5);
     auto of_row = [&](bool c) {
         const uint64_t m = __builtin_amdgcn_ballot_w64(c);
-        return ((lane0 < 32 ? (uint32_t)m : (uint32_t)(m >> 32)) >> (lane0 & 31)) & (KMAX == 32 ? ~0u : (1u << (KMAX & 31)) - 1u);
+        const uint32_t half = ((uint32_t)m & ~upper) | ((uint32_t)(m >> 32) & upper);
+        return KMAX == 32 ? half : (half >> (lane0 & 31)) & ((1u << (KMAX & 31)) - 1u);
     };
     auto of_row_lane = [&](int32_t v, int j2) { return __builtin_amdgcn_ds_bpermute((lane0 + j2) << 2, v); };
     int32_t wants[KMAX];
