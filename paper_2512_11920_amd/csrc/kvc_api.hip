@@ -16,6 +16,7 @@ static __device__ __align__(256) unsigned char scratch[kStaticWindowBytes];
 struct kvc_ctx {
     int prefetch_policy = 0;
     int window_capacity = 0;      // window engines this device holds at once (0: unknown); an upper bound on useful omega
+    int wide_capacity = 0;        // ... and wide engines (0: unknown)
     void* static_work = nullptr;  // device address of `scratch` on this context's device
     kvc_config cfg;
     kvc::Geometry g;
@@ -104,7 +105,8 @@ int kvc_create(kvc_ctx** out, const kvc_config* cfg) {
         delete c;
         return KVC_ERR_HIP;
     }
-    c->window_capacity = kvc::window_engine_capacity(c->g);
+    c->window_capacity = kvc::window_engine_capacity(c->g, false);
+    c->wide_capacity = kvc::window_engine_capacity(c->g, true);
     *out = c;
     return KVC_OK;
 }
@@ -378,13 +380,14 @@ static int prefetch_impl(kvc_ctx* ctx, void* d_l2, int32_t* d_tags, int32_t* d_f
     w.fetch = d_fetch + first;
     w.n_now = (int32_t)n_now;
     w.per_layer = n_seq * k;
+    w.by_per_layer = kvc::make_fast_div((uint32_t)w.per_layer);
     w.layer_begin = layer_begin;
     w.n_layers_call = layer_end - layer_begin;
     w.n_layers = n_layers;
     w.omega = omega;
     w.notify = d_notify;
     if (!hip_ok(kvc::launch_window_build(w, s))) return KVC_ERR_HIP;
-    return hip_ok(kvc::launch_decompress_window(a, w, omega, s)) ? KVC_OK : KVC_ERR_HIP;
+    return hip_ok(kvc::launch_decompress_window(a, w, omega, ctx->wide_capacity, s)) ? KVC_OK : KVC_ERR_HIP;
 }
 
 int kvc_prefetch_layers(kvc_ctx* ctx, void* d_l2, int32_t* d_tags, int32_t* d_fetch, int32_t* d_loc,

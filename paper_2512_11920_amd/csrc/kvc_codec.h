@@ -669,6 +669,33 @@ __device__ __forceinline__ uint4 dequant8_biased(const uint32_t pb[8], float s, 
                       __builtin_bit_cast(uint32_t, h[2]), __builtin_bit_cast(uint32_t, h[3]));
 }
 
+// Stores of the decoder's output at base + off (wave-uniform) + lane_off.  Plain launches stream it out; under the
+// prefetch window (WT) the stores write through the XCD's L2 (device scope), so that a block is published by
+// waiting for its stores, without a write-back of the whole L2.
+template <bool WT>
+__device__ __forceinline__ void store_out(char* base, int64_t off, uint32_t lane_off, const uint4& v) {
+    if constexpr (WT) {
+        uint4v w;
+        w.x = v.x; w.y = v.y; w.z = v.z; w.w = v.w;
+        // aux: 16 = sc1, device scope; 2 = nt.  The uniform offset goes into the resource and not into the store's scalar
+        // offset: a store of more than 64 bits needs a wait state before its data registers are written again, and
+        // with a scalar offset the compiler leaves it out, taking the store to be safe -- on this chip it is not (one
+        // page in a hundred came out with the first dword of some lanes replaced by what was computed next).
+        __builtin_amdgcn_raw_buffer_store_b128(w, __builtin_amdgcn_make_buffer_rsrc(base + off, 0, -1, 0x00020000), (int)lane_off, 0, 16 | 2);
+    } else {
+        store_stream(reinterpret_cast<uint4*>(base + off + lane_off), v);
+    }
+}
+template <bool WT>
+__device__ __forceinline__ void zero_out(uint16_t* dst, const Geometry& g) {
+    if constexpr (WT) {
+        for (int o = lane_id(); o < (g.E >> 3); o += 64)
+            store_out<true>(reinterpret_cast<char*>(dst), 0, (uint32_t)elem_off(g, o * 8) * 2u, make_uint4(0u, 0u, 0u, 0u));
+    } else {
+        zero_page(dst, g);
+    }
+}
+
 // This lane's 8 values of its quad's packet in group set p, read from the staged payload.  gi: the packet's
 // body offset and code, as the header scan left them.  A value's zig-zag code u comes back in two parts,
 // sg = 0 or -1 from its lowest bit, and hb: u >> 1 (delta = hb ^ sg), or u itself if TWICE (2 delta = hb ^ sg;
@@ -751,14 +778,14 @@ __device__ __forceinline__ DecLanes dec_open(const DecodeArgs& a, const DecPlace
     return r;
 }
 
-// Lane i's value in scalar registers (a batch of one page holds the same values in every lane).
-template <int PPW>
+// Lane i's value in scalar registers.  UNIFORM: every lane holds the same page task.
+template <bool UNIFORM>
 __device__ __forceinline__ uint32_t of_lane(uint32_t v, int i) {
-    return (uint32_t)(PPW == 1 ? __builtin_amdgcn_readfirstlane((int)v) : __builtin_amdgcn_readlane((int)v, i));
+    return (uint32_t)(UNIFORM ? __builtin_amdgcn_readfirstlane((int)v) : __builtin_amdgcn_readlane((int)v, i));
 }
-template <int PPW>
+template <bool UNIFORM>
 __device__ __forceinline__ uint64_t of_lane(uint64_t v, int i) {
-    return (uint64_t)of_lane<PPW>((uint32_t)v, i) | ((uint64_t)of_lane<PPW>((uint32_t)(v >> 32), i) << 32);
+    return (uint64_t)of_lane<UNIFORM>((uint32_t)v, i) | ((uint64_t)of_lane<UNIFORM>((uint32_t)(v >> 32), i) << 32);
 }
 
 // 16 bytes from global memory straight to LDS: lane l's go to lds + 16 l (the destination is wave-uniform).
@@ -772,17 +799,17 @@ __device__ __forceinline__ void load_to_lds16(const void* g, void* lds) {
 template <int PPW>
 constexpr bool kStageInt8 = PPW > 1;
 
-// Start the payload loads of the batch: page i's payload goes to LDS slot i, 16 bytes per lane and round,
-// without a stop in registers.  Payload bytes past the page's own are not read.
-template <class P, int PPW>
-__device__ __forceinline__ void dec_fetch(const DecodeArgs& a, const DecLanes& L, uint32_t (*slots)[Slot<P::kPasses>::kWords]) {
+// Start the payload loads of PPW pages, those of lanes first .. first + PPW - 1: the i-th goes to LDS slot i, 16
+// bytes per lane and round, without a stop in registers.  Payload bytes past the page's own are not read.
+template <class P, int PPW, bool UNIFORM>
+__device__ __forceinline__ void dec_fetch(const DecodeArgs& a, const DecLanes& L, int first, uint32_t (*slots)[Slot<P::kPasses>::kWords]) {
     const uint32_t lane = (uint32_t)lane_id();
     const bool staged = (L.meta >> 24) == kDecPayload && (kStageInt8<PPW> || ((L.meta >> 16) & 0xFFu) != KVC_MODE_INT8);
     const uint32_t n_own = staged ? L.meta & 0xFFFFu : 0u;
 #pragma unroll
     for (int i = 0; i < PPW; ++i) {
-        const uint32_t n16 = of_lane<PPW>(n_own, i);
-        const uint8_t* src = a.pool + of_lane<PPW>(L.off, i);
+        const uint32_t n16 = of_lane<UNIFORM>(n_own, first + i);
+        const uint8_t* src = a.pool + of_lane<UNIFORM>(L.off, first + i);
 #pragma unroll
         for (int z = 0; z < P::kRounds; ++z)
             if (lane + 64u * z < n16) load_to_lds16(src + (lane + 64u * z) * 16u, reinterpret_cast<uint4*>(slots[i]) + 64 * z);
@@ -805,17 +832,17 @@ struct HeaderDeal {
     static constexpr int kRounds = (kG + 63) / 64;       // scans per page
 };
 
-// Scan the headers of the SCAN <= HeaderDeal<P>::kPages pages from page i0 on: info = body offset << 4 | code of
+// Scan the headers of SCAN <= HeaderDeal<P>::kPages pages, those of slots i0 .. and lanes first + i0 ..: info = body offset << 4 | code of
 // the lane's group (one per round).  `bad` / `special`: ballots of the lanes whose page fails validation, and of
 // the lanes whose group is a zero-run or run packet.
-template <class P, int PPW, int SCAN>
-__device__ __forceinline__ void dec_headers(const Extent& x, const DecLanes& L, int i0, const uint32_t (*slots)[Slot<P::kPasses>::kWords],
+template <class P, bool UNIFORM, int SCAN>
+__device__ __forceinline__ void dec_headers(const Extent& x, const DecLanes& L, int first, int i0, const uint32_t (*slots)[Slot<P::kPasses>::kWords],
                                             uint32_t (&info)[HeaderDeal<P>::kRounds], uint64_t& bad, uint64_t& special) {
     using H = HeaderDeal<P>;
     constexpr int kG = P::kGroups;
     const int lane = lane_id();
     const int pi = i0 + min(lane / H::kSeg, SCAN - 1);  // this lane's page
-    const uint32_t meta = SCAN == 1 ? of_lane<PPW>(L.meta, i0) : (uint32_t)__builtin_amdgcn_ds_bpermute(pi << 2, (int)L.meta);
+    const uint32_t meta = SCAN == 1 ? of_lane<UNIFORM>(L.meta, first + i0) : (uint32_t)__builtin_amdgcn_ds_bpermute((first + pi) << 2, (int)L.meta);
     const uint32_t n16 = meta & 0xFFFFu, mode = (meta >> 16) & 0xFFu;
     const uint32_t* stage = SCAN == 1 ? slots[i0] : slots[pi];
     uint32_t total = x.hdr;
@@ -848,7 +875,7 @@ __device__ __forceinline__ void dec_headers(const Extent& x, const DecLanes& L, 
 }
 
 // Decode an INT8 payload at src (the staged copy, or the pool itself) into the page at dst_b.
-template <class P>
+template <class P, bool WT>
 __device__ __forceinline__ void dec_int8(const DecodeArgs& a, const Extent& x, const LanePos& lp, float s, char* dst_b, const uint2* src) {
 #pragma unroll
     for (int p = 0; p < P::kPasses; ++p) {
@@ -861,13 +888,13 @@ __device__ __forceinline__ void dec_int8(const DecodeArgs& a, const Extent& x, c
             pb[k] = lo >> (8 * k);
             pb[4 + k] = hi >> (8 * k);
         }
-        store_stream(reinterpret_cast<uint4*>(dst_b + pass_base_off<P, false>(a.g, p) + pass_lane_off<P, false>(a.g, lp, p)), dequant8_biased(pb, s, -128.0f * s));
+        store_out<WT>(dst_b, pass_base_off<P, false>(a.g, p), pass_lane_off<P, false>(a.g, lp, p), dequant8_biased(pb, s, -128.0f * s));
     }
 }
 
 // Decode one staged packed payload into the page at dst_b.  seg0: the first lane of the page's part of `info`.
 // SPECIAL: the page may hold zero-run and run packets.
-template <class P, bool SPECIAL>
+template <class P, bool SPECIAL, bool WT>
 __device__ __forceinline__ void dec_page(const DecodeArgs& a, const Extent& x, const LanePos& lp, uint32_t mode, float s, char* dst_b, const uint32_t* stage,
                                          const uint32_t (&info)[HeaderDeal<P>::kRounds], int seg0) {
     constexpr int NP = P::kPasses;
@@ -908,8 +935,7 @@ __device__ __forceinline__ void dec_page(const DecodeArgs& a, const Extent& x, c
 #pragma unroll
                 for (int k = 0; k < 8; ++k)  // channel k = pair k / 2 = 2 (k / 4) + (k / 2) % 2, value 2p + k % 2 of the dword
                     pb[k] = (((k >> 1) & 1) ? pair_hi[k >> 2] : pair_lo[k >> 2]) >> (8 * (2 * p + (k & 1)));
-                store_stream(reinterpret_cast<uint4*>(dst_b + pass_base_off<P, true>(a.g, p) + pass_lane_off<P, true>(a.g, lp, p)),
-                             dequant8_biased(pb, s, neg128s));
+                store_out<WT>(dst_b, pass_base_off<P, true>(a.g, p), pass_lane_off<P, true>(a.g, lp, p), dequant8_biased(pb, s, neg128s));
             }
             return;
         }
@@ -941,8 +967,7 @@ __device__ __forceinline__ void dec_page(const DecodeArgs& a, const Extent& x, c
                         const int m = 2 * p + (k & 1);  // value index inside group set k / 2
                         pb[k] = packed[k >> 1][m >> 2] >> (8 * (m & 3));
                     }
-                    store_stream(reinterpret_cast<uint4*>(dst_b + pass_base_off<P, true>(a.g, 4 * h + p) + pass_lane_off<P, true>(a.g, lp, 4 * h + p)),
-                                 dequant8_biased(pb, s, neg128s));
+                    store_out<WT>(dst_b, pass_base_off<P, true>(a.g, 4 * h + p), pass_lane_off<P, true>(a.g, lp, 4 * h + p), dequant8_biased(pb, s, neg128s));
                 }
             }
             return;
@@ -976,13 +1001,13 @@ __device__ __forceinline__ void dec_page(const DecodeArgs& a, const Extent& x, c
 #pragma unroll
         for (int k = 0; k < 8; ++k) pb[k] >>= 8;
         if (lane_live<P>(x, p))
-            store_stream(reinterpret_cast<uint4*>(dst_b + pass_base_off<P, false>(a.g, p) + pass_lane_off<P, false>(a.g, lp, p)), dequant8_biased(pb, s, neg128s));
+            store_out<WT>(dst_b, pass_base_off<P, false>(a.g, p), pass_lane_off<P, false>(a.g, lp, p), dequant8_biased(pb, s, neg128s));
     }
 }
 
-// Decode the pages of a batch whose payloads dec_fetch has begun to load.
-template <class P, int PPW>
-__device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L, const LanePos& lp, uint32_t (*slots)[Slot<P::kPasses>::kWords]) {
+// Decode the pages whose payloads dec_fetch has begun to load.
+template <class P, int PPW, bool UNIFORM, bool WT>
+__device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L, int first, const LanePos& lp, uint32_t (*slots)[Slot<P::kPasses>::kWords]) {
     using H = HeaderDeal<P>;
     static_assert(PPW % H::kPages == 0 || PPW == 1, "a header scan covers whole pages of the batch");
     constexpr int kScan = PPW < H::kPages ? PPW : H::kPages;  // pages taken from one scan
@@ -992,18 +1017,19 @@ __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L
     for (int i0 = 0; i0 < PPW; i0 += kScan) {
         uint32_t info[H::kRounds];
         uint64_t bad, special;
-        dec_headers<P, PPW, kScan>(x, L, i0, slots, info, bad, special);
+        if (kScan == 1 && (of_lane<UNIFORM>(L.meta, first + i0) >> 24) == kDecSkip) continue;
+        dec_headers<P, UNIFORM, kScan>(x, L, first, i0, slots, info, bad, special);
 #pragma unroll 1
         for (int j = 0; j < kScan; ++j) {
             const int i = i0 + j;
-            const uint32_t meta = of_lane<PPW>(L.meta, i);
+            const uint32_t meta = of_lane<UNIFORM>(L.meta, first + i);
             const uint32_t kind = meta >> 24;
             if (kind == kDecSkip) continue;
-            uint16_t* dst = a.out + page_base(a.g, (int64_t)(int32_t)of_lane<PPW>((uint32_t)L.db, i), (int)of_lane<PPW>(L.pg, i));
+            uint16_t* dst = a.out + page_base(a.g, (int64_t)(int32_t)of_lane<UNIFORM>((uint32_t)L.db, first + i), (int)of_lane<UNIFORM>(L.pg, first + i));
             constexpr uint64_t kSegMask = H::kSeg == 64 ? ~0ull : (1ull << (H::kSeg & 63)) - 1;
             const bool bad_header = ((bad >> (j * H::kSeg)) & kSegMask) != 0;
             if (kind == kDecZero || bad_header) {
-                zero_page(dst, a.g);
+                zero_out<WT>(dst, a.g);
                 if (bad_header && lane_id() == 0) atomicOr(&a.st->status, KVC_ST_CORRUPT);
                 continue;
             }
@@ -1011,25 +1037,31 @@ __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L
             if (kind == kDecRaw) {  // stored-uncompressed bypass
                 // (a pass is stored before the next is loaded: whole launches of raw pages are 1.5 % faster so than
                 // with all loads ahead of all stores)
-                const uint4* src = reinterpret_cast<const uint4*>(a.pool + of_lane<PPW>(L.off, i));
+                const uint4* src = reinterpret_cast<const uint4*>(a.pool + of_lane<UNIFORM>(L.off, first + i));
 #pragma unroll
                 for (int p = 0; p < P::kPasses; ++p)
-                    if (lane_live<P>(x, p)) *reinterpret_cast<uint4*>(dst_b + pass_base_off<P, false>(a.g, p) + pass_lane_off<P, false>(a.g, lp, p)) = src[p * 64 + lane_id()];
+                    if (lane_live<P>(x, p)) {
+                        const uint4 v = src[p * 64 + lane_id()];
+                        if (WT)
+                            store_out<true>(dst_b, pass_base_off<P, false>(a.g, p), pass_lane_off<P, false>(a.g, lp, p), v);
+                        else
+                            *reinterpret_cast<uint4*>(dst_b + pass_base_off<P, false>(a.g, p) + pass_lane_off<P, false>(a.g, lp, p)) = v;
+                    }
                 continue;
             }
             const uint32_t mode = (meta >> 16) & 0xFFu;
-            const float s = __uint_as_float(of_lane<PPW>(__float_as_uint(L.s), i));
+            const float s = __uint_as_float(of_lane<UNIFORM>(__float_as_uint(L.s), first + i));
             if (mode == KVC_MODE_INT8) {
                 if constexpr (kStageInt8<PPW>)
-                    dec_int8<P>(a, x, lp, s, dst_b, reinterpret_cast<const uint2*>(slots[i]));
+                    dec_int8<P, WT>(a, x, lp, s, dst_b, reinterpret_cast<const uint2*>(slots[i]));
                 else
-                    dec_int8<P>(a, x, lp, s, dst_b, reinterpret_cast<const uint2*>(a.pool + of_lane<PPW>(L.off, i)));
+                    dec_int8<P, WT>(a, x, lp, s, dst_b, reinterpret_cast<const uint2*>(a.pool + of_lane<UNIFORM>(L.off, first + i)));
                 continue;
             }
             if (((special >> (j * H::kSeg)) & kSegMask) != 0)
-                dec_page<P, true>(a, x, lp, mode, s, dst_b, slots[i], info, j * H::kSeg);
+                dec_page<P, true, WT>(a, x, lp, mode, s, dst_b, slots[i], info, j * H::kSeg);
             else
-                dec_page<P, false>(a, x, lp, mode, s, dst_b, slots[i], info, j * H::kSeg);
+                dec_page<P, false, WT>(a, x, lp, mode, s, dst_b, slots[i], info, j * H::kSeg);
         }
     }
 }
@@ -1047,62 +1079,74 @@ __global__ __launch_bounds__(WAVES * 64) void k_decompress(DecodeArgs a) {
     const LanePos lp = lane_pos<P>(a.g);
     // (a batch of one page is resolved on the scalar unit: every lane has the same task)
     const DecLanes L = dec_open<P>(a, PPW == 1 ? dec_locate(a, true, (uint32_t)t0) : dec_locate(a, lane < PPW && t0 + lane < a.n_pages, (uint32_t)t0 + (uint32_t)lane));
-    dec_fetch<P, PPW>(a, L, s_stage[wave]);
-    dec_batch<P, PPW>(a, L, lp, s_stage[wave]);
+    dec_fetch<P, PPW, PPW == 1>(a, L, 0, s_stage[wave]);
+    dec_batch<P, PPW, PPW == 1, false>(a, L, 0, lp, s_stage[wave]);
 }
 
 // Transfer engines of the prefetch window (Algorithm 1: at most Omega_max transfers outstanding): a
-// workgroup takes the next issued block from the queue, its waves decode the block's pages, and the
-// completion is reported before the next block is taken.
+// workgroup takes the next issued blocks from the queue (a turn), its waves decode them one block after the other,
+// and the completion is reported before the next turn is taken.  An engine is latency, not bandwidth: few of them
+// are at work, each on one block.  So the waves share a block's pages as far as they go round (wave w takes pages w,
+// w + WAVES, ...; WIDE engines have a wave for each of 16 pages), and what can be known ahead is fetched for the
+// whole turn at once: queue entries, pool blocks and all descriptors, one page task per lane, before the first
+// payload.  SIDE: pages of one block that a wave has in flight together.
 // (pages of up to four passes whose rows do not cross passes: held within 128 VGPRs, so that four waves fit a SIMD)
-template <class P, int WAVES>
+template <class P, int WAVES, int SIDE>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::kPasses <= 4 && P::kAligned ? 4 : 1))) void k_decompress_window(DecodeArgs a, WindowArgs w) {
-    constexpr int kSide = 4;
-    __shared__ __align__(16) uint32_t s_stage[WAVES][kSide][Slot<P::kPasses>::kWords];
+    __shared__ __align__(16) uint32_t s_stage[WAVES][SIDE][Slot<P::kPasses>::kWords];
     __shared__ uint32_t s_turn[2];
-    __shared__ int32_t s_q[WAVES][2][64];
+    __shared__ int32_t s_q[WAVES][2][kMaxWindowTurn];
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ppb = a.g.ppb;
     const LanePos lp = lane_pos<P>(a.g);
     if (blockIdx.x >= w.hdr->engines) return;  // the window was opened for fewer engines than the grid holds
+    // a wave's page tasks of a block, rounded up to whole batches of SIDE pages (tasks past the block do nothing)
+    const int per_wave = (ppb + WAVES - 1) / WAVES;
+    const int per_block = (per_wave + SIDE - 1) / SIDE * SIDE;
+    const uint32_t n_issued = w.hdr->n_issued, chunk = w.hdr->chunk;
+    uint32_t mine = 0;
     WindowTurn none;
     none.first = none.count = 0;
-    WindowTurn turn = window_next(w, s_turn, none);
+    WindowTurn turn = window_next<true>(w, s_turn, none, s_q[0][0], mine, n_issued, chunk);
     while (turn.count) {
-      // the turn's queue entries (at most 64) and the pool blocks they name, fetched one per lane and parked
-      // in the wave's row of LDS: two trips to memory per turn instead of two per block
-      if ((uint32_t)lane < turn.count) {
-          const int32_t slot_l = w.queue[turn.first + lane];
-          s_q[wave][0][lane] = slot_l;
-          s_q[wave][1][lane] = a.pool_ids[slot_l];
-      }
-      wave_sync();
-      for (uint32_t i = 0; i < turn.count; ++i) {
-        const int32_t slot = __builtin_amdgcn_readfirstlane(s_q[wave][0][i]);
-        const int32_t pb = __builtin_amdgcn_readfirstlane(s_q[wave][1][i]);
-        // a wave takes the block's pages wave, wave + WAVES, ... kSide at a time: lane j resolves the j-th of
-        // them, and all payload loads are issued before the first page is decoded
-        for (int pg0 = wave; pg0 < ppb; pg0 += kSide * WAVES) {
-            DecPlace t;
-            t.pg = (uint32_t)(pg0 + lane * WAVES);
-            t.live = lane < kSide && (int)t.pg < ppb;
-            t.bad_index = false;
-            t.pb = pb;
-            t.db = slot;
-            const DecLanes L = dec_open<P>(a, t);
-            dec_fetch<P, kSide>(a, L, s_stage[wave]);
-            dec_batch<P, kSide>(a, L, lp, s_stage[wave]);
-            wave_sync();
-            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the slots have been read before they are filled again
+        // the turn's queue entries and the pool blocks they name, one per lane, parked in the wave's row of LDS
+        if ((uint32_t)lane < turn.count) {
+            const int32_t slot_l = w.queue[turn.first + lane];
+            s_q[wave][0][lane] = slot_l;
+            s_q[wave][1][lane] = a.pool_ids[slot_l];
         }
-      }
-      turn = window_next(w, s_turn, turn);
+        wave_sync();
+        const int tasks = (int)turn.count * per_block;  // in block order
+        for (int t0 = 0; t0 < tasks; t0 += 64 / SIDE * SIDE) {
+            const int t = t0 + lane;
+            const uint32_t b = min((uint32_t)t / (uint32_t)per_block, turn.count - 1u);
+            DecPlace pl;
+            pl.pg = (uint32_t)(wave + (t - (int)b * per_block) * WAVES);
+            pl.live = lane < 64 / SIDE * SIDE && t < tasks && (int)pl.pg < ppb;
+            pl.bad_index = false;
+            pl.pb = s_q[wave][1][b];
+            pl.db = s_q[wave][0][b];
+            const DecLanes L = dec_open<P>(a, pl);
+            for (int j = 0; j < 64 / SIDE * SIDE && t0 + j < tasks; j += SIDE) {
+                dec_fetch<P, SIDE, false>(a, L, j, s_stage[wave]);
+                dec_batch<P, SIDE, false, true>(a, L, j, lp, s_stage[wave]);
+                wave_sync();
+                __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the slots have been read before they are filled again
+            }
+        }
+        turn = window_next<false>(w, s_turn, turn, s_q[0][0], mine, n_issued, chunk);
     }
 }
 
 // Launch shapes by page size (NP passes of 1 KB): waves per workgroup, pages per wave.
 constexpr int kCodecWaves = 4;
+// Transfer engines of the prefetch window.  Up to as many engines as the device holds of the wide kind (512 at 16 x 128)
+// each has 16 waves; beyond that engines of four waves, with several pages of a block per wave in flight, of which
+// two to four times as many are resident.  Two prefetch steps of 4,370 blocks of 16 pages of 16 x 128, us, four-wave
+// engines / wide engines: 64 engines 1081 / 571, 256 engines 399 / 229 (without the window: 175).
+constexpr int kWideWaves = 16;
+constexpr int window_side(int np) { return np <= 4 ? 4 : 2; }
 // large calls: about 64 KB of input per workgroup and one pool-cursor atomic for it
 constexpr int enc_ppw_large(int np) { return np == 1 ? 64 / KVC_ENC_WAVES_1KB : np == 2 ? 8 : np == 3 ? 5 : np == 4 ? 4 : np == 5 ? KVC_PPW5 : np == 6 ? KVC_PPW6 : np == 7 ? KVC_PPW7 : KVC_PPW8; }
 // waves per encoder workgroup in large calls
@@ -1169,18 +1213,20 @@ struct ShapeOps {
         return launch_kernel(k_decompress<P, kCodecWaves, dec_ppw(NP)>, page_grid(a.n_pages, dec_ppw(NP)), dim3(kCodecWaves * 64), s, a);
     }
 
-    static hipError_t decompress_window(const DecodeArgs& a, const WindowArgs& w, unsigned grid, hipStream_t s) {
-        return launch_kernel(k_decompress_window<P, kCodecWaves>, dim3(grid), dim3(kCodecWaves * 64), s, a, w);
+    static hipError_t decompress_window(const DecodeArgs& a, const WindowArgs& w, unsigned grid, bool wide, hipStream_t s) {
+        if (wide) return launch_kernel(k_decompress_window<P, kWideWaves, 1>, dim3(grid), dim3(kWideWaves * 64), s, a, w);
+        return launch_kernel(k_decompress_window<P, kCodecWaves, window_side(NP)>, dim3(grid), dim3(kCodecWaves * 64), s, a, w);
     }
 
     // engines the current device holds at once: a larger grid would only queue workgroups behind the
     // resident ones, which keep taking turns until the queue is empty
-    static int window_capacity() {
+    static int window_capacity(bool wide) {
         int dev = 0, cus = 0, per_cu = 0;
+        const void* k = wide ? reinterpret_cast<const void*>(&k_decompress_window<P, kWideWaves, 1>) : reinterpret_cast<const void*>(&k_decompress_window<P, kCodecWaves, window_side(NP)>);
         if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_decompress_window<P, kCodecWaves>, kCodecWaves * 64, 0) != hipSuccess) {
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, (wide ? kWideWaves : kCodecWaves) * 64, 0) != hipSuccess) {
             (void)hipGetLastError();
-            return 0;  // unknown: no cap
+            return 0;  // unknown: no cap (narrow), never used (wide)
         }
         return cus * per_cu;
     }

@@ -85,7 +85,7 @@ struct PlanArgs {
 struct WindowHdr {
     unsigned int n_issued;  // entries in the queue (constant while the engines run)
     unsigned int engines;   // transfer engines of the call = min(omega, n_issued): the bound on blocks in flight
-    unsigned int chunk;     // queue entries an engine takes per turn (1..8)
+    unsigned int chunk;     // queue entries an engine takes per turn (1..kMaxWindowTurn)
     unsigned int pad0[13];
     unsigned int ticket;    // next queue entry to hand out; the two hot counters sit in cache lines of their own
     unsigned int pad1[15];
@@ -94,6 +94,8 @@ struct WindowHdr {
 };
 static_assert(sizeof(WindowHdr) == 256, "window header is 256 bytes");
 
+constexpr int kMaxWindowTurn = 8;
+
 struct WindowArgs {
     WindowHdr* hdr;
     int32_t* pending;      // [layers of the call]: issued transfers of the layer not yet completed
@@ -101,6 +103,7 @@ struct WindowArgs {
     const int32_t* fetch;  // the call's part of the fetch list: [n_now], pool block or -1
     int32_t n_now;         // slots of the call = layers of the call * per_layer
     int32_t per_layer;     // n_seq * k
+    FastDiv by_per_layer;
     int32_t layer_begin, n_layers_call, n_layers;
     int32_t omega;         // engines the decode launch starts at most
     long long* notify;     // [n_layers + 4], see kvc.h
@@ -125,8 +128,8 @@ inline hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, hip
 
 hipError_t launch_prefetch_plan(const PlanArgs& a, hipStream_t s);
 hipError_t launch_window_build(const WindowArgs& w, hipStream_t s);
-hipError_t launch_decompress_window(const DecodeArgs& a, const WindowArgs& w, int32_t omega, hipStream_t s);
-int window_engine_capacity(const Geometry& g);
+hipError_t launch_decompress_window(const DecodeArgs& a, const WindowArgs& w, int32_t omega, int32_t wide_capacity, hipStream_t s);
+int window_engine_capacity(const Geometry& g, bool wide);
 hipError_t launch_fill_i32(int32_t* p, int32_t v, uint64_t n, hipStream_t s);
 hipError_t launch_compress(const EncodeArgs& a, hipStream_t s);
 hipError_t launch_decompress(const DecodeArgs& a, hipStream_t s);

@@ -413,45 +413,52 @@ struct WindowTurn {
 };
 
 // One turn of an engine: report the blocks of the run `done` as complete -- make them visible, count
-// them, stamp the layers and the call whose last transfer was among them -- and take the next run of up
-// to hdr->chunk queue entries.  Called by all threads of the workgroup; `s_turn` is two words of LDS.
+// them, stamp the layers whose last transfer was among them -- and take the next run of up to hdr->chunk
+// queue entries (the first run needs no ticket: engine b begins with the b-th).  Called by all threads of the
+// workgroup; `s_turn` is two words of LDS, `slots` the run's queue entries, parked in LDS by wave 0, `mine` the
+// blocks this engine has completed; n_issued and chunk are the header's (read once: they share a line with the ticket).
 // An engine decodes the blocks of its run one after the other, so it still holds one block in flight; the
-// run only spaces out the bookkeeping, whose device-wide release (a write-back of the XCD's L2) and
-// same-address atomics cost more than decoding a block when paid per block.
+// run only spaces out the bookkeeping, which the other waves wait for.  It is kept short: the decoder's stores
+// under the window write through to the device's memory (store_out), so that waiting for them is all it takes to
+// publish a block; with a write-back of the XCD's L2 in its place a turn cost about 8 us (256 engines).  And the
+// counters every engine shares serve one atomic every 10 to 20 ns whatever the engines are doing, so a turn spends
+// two (ticket, the layer's pending count); the count of completed blocks is added up per engine and reported when
+// the engine leaves.
 // Thread 0 does the bookkeeping between two barriers, so the single-lane region lies inside the loop
 // body and not across its back edge, and the result comes back in scalar registers: the engines' loop
 // and its exit branch on the scalar unit and every wave meets every barrier with all of its lanes.  (With
 // the single-lane work at both ends of the loop body the compiler merges it across the back edge into
 // an outer loop and lets the other lanes run ahead to the next barrier: the workgroup then never
 // meets.)
-__device__ __forceinline__ WindowTurn window_next(const WindowArgs& w, uint32_t* s_turn, WindowTurn done) {
-    // every wave's stores have reached the XCD's L2 before the workgroup meets ...
-    if (done.count) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+template <bool FIRST>
+__device__ __forceinline__ WindowTurn window_next(const WindowArgs& w, uint32_t* s_turn, WindowTurn done, const int32_t* slots, uint32_t& mine,
+                                                  uint32_t n_issued, uint32_t chunk) {
+    // every wave's stores have reached memory before the workgroup meets, and the counters move after that
+    if (!FIRST) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), the other counters unchanged
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    }
+    mine += done.count;
     __syncthreads();
     if (threadIdx.x == 0) {
         const long long finished = max(wall_clock64(), 1ll);  // read before the blocks are counted
-        const unsigned int n_issued = w.hdr->n_issued;
-        unsigned int dn = 0;
-        if (done.count) {
-            // ... and one device-wide release publishes them before the counters move
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        const unsigned int t = FIRST ? blockIdx.x * chunk : atomicAdd(&w.hdr->ticket, chunk);
+        if (!FIRST) {
             uint32_t i = 0;
             while (i < done.count) {  // the run's entries are in layer order: one decrement per layer met
-                const int32_t l_rel = w.queue[done.first + i] / w.per_layer;
+                const uint32_t l_rel = fast_div((uint32_t)slots[i], w.by_per_layer);
                 uint32_t n = 1;
-                while (i + n < done.count && w.queue[done.first + i + n] / w.per_layer == l_rel) ++n;
+                while (i + n < done.count && fast_div((uint32_t)slots[i + n], w.by_per_layer) == l_rel) ++n;
                 if (atomicSub(&w.pending[l_rel], (int)n) == (int)n)
-                    __hip_atomic_store(&w.notify[w.layer_begin + l_rel], finished, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(&w.notify[w.layer_begin + (int32_t)l_rel], finished, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
                 i += n;
             }
-            dn = atomicAdd(&w.hdr->done, done.count) + done.count;
+            // WaitCompletion returns: NotifyGPU(ready).  The last engine to leave reads this clock after the last
+            // block was counted, and every engine wrote its layer stamps before it reported its blocks: the stamp
+            // is the latest of the call.
+            if (t >= n_issued && atomicAdd(&w.hdr->done, mine) + mine == n_issued)
+                __hip_atomic_store(&w.notify[w.n_layers + 3], max(wall_clock64(), 1ll), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         }
-        const unsigned int chunk = w.hdr->chunk;
-        const unsigned int t = atomicAdd(&w.hdr->ticket, chunk);
-        // WaitCompletion returns: NotifyGPU(ready).  This clock is read after the last block was counted
-        // and every layer stamp before its block was: the stamp is the latest of the call.
-        if (done.count && dn == n_issued)
-            __hip_atomic_store(&w.notify[w.n_layers + 3], max(wall_clock64(), 1ll), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         s_turn[0] = t;
         s_turn[1] = t < n_issued ? min(chunk, n_issued - t) : 0u;
     }
@@ -472,8 +479,8 @@ struct ShapeKernels {
     bool partial;
     hipError_t (*compress)(const EncodeArgs& a, hipStream_t s);
     hipError_t (*decompress)(const DecodeArgs& a, hipStream_t s);
-    hipError_t (*decompress_window)(const DecodeArgs& a, const WindowArgs& w, unsigned grid, hipStream_t s);
-    int (*window_capacity)();  // window engines resident on the current device at once (0: unknown)
+    hipError_t (*decompress_window)(const DecodeArgs& a, const WindowArgs& w, unsigned grid, bool wide, hipStream_t s);
+    int (*window_capacity)(bool wide);  // window engines resident on the current device at once (0: unknown)
 };
 constexpr int kShapeGroups = 16;
 using ShapeLookup = const ShapeKernels* (*)(int d, int np, bool partial);

@@ -227,16 +227,17 @@ __global__ __launch_bounds__(256) void k_window_place(WindowArgs w) {
         w.notify[w.layer_begin + l] = in_layer ? 0ll : now;
         if (l == 0) {
             // Engines at work: at most omega, at most one per transfer -- and beyond 256 of them only as far
-            // as each still has eight transfers to carry out: every turn of every engine is three atomics on
-            // shared counters, and a short queue spread over a thousand engines spends its time there
-            // (5,120 transfers: 0.51 ms with 1,024 engines, 0.33 ms with 256).
+            // as each still has eight transfers to carry out: every turn of every engine is an atomic on a shared
+            // counter, and more engines than that gain nothing (4,370 transfers: 110 us with 256 engines, 105 us
+            // with 512).
             unsigned int engines = min(total, (uint32_t)w.omega);
             if (engines > 256u) engines = min(engines, max(256u, total / 8u));
             w.hdr->n_issued = total;
             w.hdr->engines = engines;
             // entries per turn: long queues space out the bookkeeping, short ones keep every engine busy
-            w.hdr->chunk = engines ? min(max(total / (4u * engines), 1u), 8u) : 1u;
-            w.hdr->ticket = 0;
+            const unsigned int chunk = engines ? min(max(total / (4u * engines), 1u), (uint32_t)kMaxWindowTurn) : 1u;
+            w.hdr->chunk = chunk;
+            w.hdr->ticket = engines * chunk;  // the engines' first turns (engines * chunk <= total) need no ticket
             w.hdr->done = 0;
             w.notify[w.n_layers] = now;                        // window opened
             w.notify[w.n_layers + 1] = (long long)total;       // transfers issued
@@ -311,16 +312,16 @@ hipError_t launch_window_build(const WindowArgs& w, hipStream_t s) {
 
 // At most omega workgroups, one block in flight each; the queue may turn out shorter than the grid, in
 // which case the surplus workgroups leave at their first look.
-hipError_t launch_decompress_window(const DecodeArgs& a, const WindowArgs& w, int32_t omega, hipStream_t s) {
+hipError_t launch_decompress_window(const DecodeArgs& a, const WindowArgs& w, int32_t omega, int32_t wide_capacity, hipStream_t s) {
     if (w.n_now <= 0) return hipSuccess;
     const unsigned grid = (unsigned)std::min<int64_t>(omega, w.n_now);
     const ShapeKernels* f = shape_kernels(a.g.N, a.g.d);
-    return f ? f->decompress_window(a, w, grid, s) : hipErrorInvalidValue;
+    return f ? f->decompress_window(a, w, grid, wide_capacity > 0 && grid <= (unsigned)wide_capacity, s) : hipErrorInvalidValue;
 }
 
-int window_engine_capacity(const Geometry& g) {
+int window_engine_capacity(const Geometry& g, bool wide) {
     const ShapeKernels* f = shape_kernels(g.N, g.d);
-    return f ? f->window_capacity() : 0;
+    return f ? f->window_capacity(wide) : 0;
 }
 
 hipError_t launch_fill_i32(int32_t* p, int32_t v, uint64_t n, hipStream_t s) {
