@@ -212,6 +212,7 @@ static int compress_impl(kvc_ctx* ctx, const void* d_cache, int64_t n_cache_bloc
     a.g = ctx->g;
     a.scheme = ctx->cfg.scheme;
     a.block_scheme = d_block_scheme;
+    a.by_ppb = kvc::make_fast_div((uint32_t)ctx->g.ppb);
     a.pool = ctx->pool;
     a.pool_units = ctx->pool_bytes / 16;
     a.desc = ctx->desc;

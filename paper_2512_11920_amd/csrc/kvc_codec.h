@@ -136,9 +136,10 @@ constexpr int kSchemeAny = -2;
 constexpr float kMagic = 12582912.0f;  // 1.5 * 2^23: adding it rounds to an integer, ties to even
 constexpr uint32_t kMagicBits = 0x4B400000u;
 
-__device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2v, a),
-                                                                 __builtin_bit_cast(ushort2v, b)));
+// max(m, |x|) on two FP16 values, NaN if either is one (as the packed max3 of m, x and -x: one instruction)
+__device__ __forceinline__ half2v max_magnitude(half2v m, uint32_t bits) {
+    const half2v x = __builtin_bit_cast(half2v, bits);
+    return __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, x), -x);
 }
 
 // Quantize step on 8 FP16 values: bits of (x * s_inv + M_k), M_k = 1.5*2^23 + 256*k.  The fused
@@ -182,10 +183,15 @@ __device__ __forceinline__ void store_codes(const uint4 (&raw)[P::kPasses], floa
 }
 
 // Table of the 8-bit wrap + zig-zag map, indexed by delta + 256 (delta in [-254, 254]).
-__device__ __forceinline__ void fill_zigzag_lut(uint8_t* lut) {
-    for (int i = threadIdx.x; i < 512; i += blockDim.x) {
-        const uint32_t b = (uint32_t)(i - 256) & 0xFFu;
-        lut[i] = (uint8_t)(((b << 1) ^ (0u - (b >> 7))) & 0xFFu);
+__device__ __forceinline__ void fill_zigzag_lut(uint32_t* lut) {
+    if (threadIdx.x < 128) {  // four entries per thread
+        uint32_t w = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t b = (4u * threadIdx.x + (uint32_t)e) & 0xFFu;  // (entry - 256) mod 256
+            w |= (((b << 1) ^ (0u - (b >> 7))) & 0xFFu) << (8 * e);
+        }
+        lut[threadIdx.x] = w;
     }
 }
 
@@ -330,17 +336,26 @@ __device__ __forceinline__ uint32_t pass_lane_off(const Geometry& g, const LaneP
     return ((lp.row0 + (wrap ? 1u : 0u)) * (uint32_t)g.row_stride + (wrap ? c - P::kLpr : c) * 8u) * 2u;
 }
 
+// A page's loads, `src` its first element.  Nothing here is behind a branch: the loads of a batch of pages are then in
+// flight together and each page waits for its own only.  (Lanes beyond a short page read the 16 bytes that begin
+// the last pass's first row, and hold zeros.)
 template <class P, bool CHAN>
-__device__ __forceinline__ void load_page(const EncodeArgs& a, const EncTask& task, const LanePos& lp,
-                                          uint4 (&raw)[P::kPasses]) {
-    const char* src = reinterpret_cast<const char*>(a.cache) + wave_uniform((int64_t)task.src_off * 2);
+__device__ __forceinline__ void load_page(const EncodeArgs& a, const char* src, const LanePos& lp, uint4 (&raw)[P::kPasses]) {
     const Extent x = page_extent<P>(a.g);
 #pragma unroll
     for (int p = 0; p < P::kPasses; ++p) {
-        raw[p] = make_uint4(0u, 0u, 0u, 0u);  // lanes beyond a short page hold zeros
-        if (lane_live<P>(x, p))
-            raw[p] = load_stream(reinterpret_cast<const uint4*>(src + pass_base_off<P, CHAN>(a.g, p) + pass_lane_off<P, CHAN>(a.g, lp, p)));
+        const bool live = lane_live<P>(x, p);
+        const uint32_t off = pass_lane_off<P, CHAN>(a.g, lp, p);
+        raw[p] = load_stream(reinterpret_cast<const uint4*>(src + pass_base_off<P, CHAN>(a.g, p) + (live ? off : 0u)));
     }
+}
+// ... once they have arrived: lanes beyond a short page hold zeros
+template <class P>
+__device__ __forceinline__ void clear_beyond(const Extent& x, uint4 (&raw)[P::kPasses]) {
+    if (!P::kPartial) return;
+    constexpr int p = P::kPasses - 1;
+    const uint32_t keep = lane_live<P>(x, p) ? ~0u : 0u;
+    raw[p] = make_uint4(raw[p].x & keep, raw[p].y & keep, raw[p].z & keep, raw[p].w & keep);
 }
 
 // Mode 5: the packets of a page whose 128-bit pieces were dealt to the lanes as piece_index<P, true> says;
@@ -425,15 +440,16 @@ __device__ __forceinline__ PageResult encode_page(const uint4 (&raw)[P::kPasses]
     const int lane = lane_id();
     const uint32_t qi = (uint32_t)lane & 3u;
 
-    // scaling: max |x| on the FP16 bit patterns, two per dword
-    uint32_t m2 = 0;
+    // scaling: max |x|, two values per dword; the magnitudes compare as integers across the lanes
+    half2v mh = {(_Float16)0.0f, (_Float16)0.0f};
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        m2 = pk_max_u16(m2, raw[p].x & 0x7FFF7FFFu);
-        m2 = pk_max_u16(m2, raw[p].y & 0x7FFF7FFFu);
-        m2 = pk_max_u16(m2, raw[p].z & 0x7FFF7FFFu);
-        m2 = pk_max_u16(m2, raw[p].w & 0x7FFF7FFFu);
+        mh = max_magnitude(mh, raw[p].x);
+        mh = max_magnitude(mh, raw[p].y);
+        mh = max_magnitude(mh, raw[p].z);
+        mh = max_magnitude(mh, raw[p].w);
     }
+    const uint32_t m2 = __builtin_bit_cast(uint32_t, mh) & 0x7FFF7FFFu;
     const uint32_t m = wave_max_dpp(max(m2 & 0xFFFFu, m2 >> 16));
     PageResult r;
     if (scheme == KVC_MODE_RAW || m >= 0x7C00u) {  // requested, or NaN/Inf present: bypass
@@ -519,139 +535,165 @@ __device__ __forceinline__ PageResult encode_page(const uint4 (&raw)[P::kPasses]
     return r;
 }
 
-// Encode the page held in `raw` (if the task is live) into LDS slot `slot` and note its result.
-template <class P, int SCHEME, int SLOTS>
-__device__ __forceinline__ void encode_into_slot(const EncodeArgs& a, const uint4 (&raw)[P::kPasses], const LanePos& lp, const EncTask& task,
-                                                 int slot, uint32_t* stage, const uint8_t* lut, EncBook<SLOTS>& book) {
-    PageResult r;
-    r.n16 = 0;
-    r.mode = KVC_MODE_INVALID;
-    r.scale = 0.0f;
-    if (task.desc_idx >= 0) r = encode_page<P, SCHEME>(raw, lp, page_extent<P>(a.g), task.scheme, stage, lut, a.st);
-    if (lane_id() == 0) {
-        book.n16[slot] = r.n16;
-        book.mode[slot] = r.mode;
-        book.scale[slot] = r.scale;
-        book.desc[slot] = task.desc_idx;
-        book.srcoff[slot] = task.src_off;
-    }
+// Encoder launch shape for large calls, by passes per page: waves per workgroup, pages per wave, pages a wave holds in
+// registers at once.  A workgroup takes one atomic on the pool cursor, and the cursor's line serves one every 13 ns
+// whoever asks: with 64 KB of input per workgroup a launch at full bandwidth keeps it busy four fifths of the time,
+// and half of that makes it the bound (a million pages of 16 x 128: 32 KB per workgroup 1725 us, 64 KB 1055, 80 to 128
+// KB 970 to 1000).  The payloads wait in LDS meanwhile, half a byte per byte, so 160 KB per workgroup and more leave
+// a compute unit one workgroup and nothing to overlap its phases with (1475 us).  Between those the shapes are the
+// best of a sweep; compress, us, 64 KB shape -> this one: 16 x 64 272 -> 260, 16 x 96 420 -> 382, 16 x 128 1055 -> 970,
+// 32 x 96 389 -> 371, 16 x 224 509 -> 432, 16 x 256 532 -> 504 (1 KB pages: 96 and 128 KB are slower, 145 -> 172).  The
+// instantiations that read the mode at run time need more registers and have shapes of their own (INT8 at 16 x 128
+// 272 -> 253, 16 x 96 421 -> 388, 32 x 96 381 -> 368, 24 x 96 135 -> 124, 16 x 224 511 -> 475).
+struct EncShape {
+    int waves, ppw, ring;
+};
+constexpr EncShape enc_large(int np, int scheme) {
+    constexpr EncShape fixed[9] = {{0, 0, 0}, {8, 8, 8}, {8, 5, 5}, {8, 3, 3}, {4, 5, 5}, {8, 2, 2}, {8, 2, 2}, {8, 2, 2}, {8, 2, 1}};
+    constexpr EncShape run_time[9] = {{0, 0, 0}, {8, 8, 8}, {4, 8, 8}, {4, 6, 3}, {8, 3, 3}, {8, 2, 2}, {8, 2, 2}, {4, 3, 1}, {4, 2, 1}};
+    return scheme >= 0 ? fixed[np] : run_time[np];
 }
+constexpr int enc_ring(int np, int ppw, int scheme) { return ppw <= enc_large(np, scheme).ring ? ppw : enc_large(np, scheme).ring; }
 
-#ifndef KVC_PPW5
-#define KVC_PPW5 3
-#endif
-#ifndef KVC_PPW6
-#define KVC_PPW6 3
-#endif
-#ifndef KVC_PPW7
-#define KVC_PPW7 2
-#endif
-#ifndef KVC_PPW8
-#define KVC_PPW8 2
-#endif
-#ifndef KVC_RING5
-#define KVC_RING5 3
-#endif
-#ifndef KVC_RING6
-#define KVC_RING6 3
-#endif
-#ifndef KVC_RING7
-#define KVC_RING7 2
-#endif
-#ifndef KVC_ENC_WAVES_LONG
-#define KVC_ENC_WAVES_LONG 4
-#endif
-#ifndef KVC_ENC_MIN_WAVES
-#define KVC_ENC_MIN_WAVES 4
-#endif
-#ifndef KVC_ENC_WAVES_1KB
-#define KVC_ENC_WAVES_1KB 8
-#endif
-
-// Pages a wave holds in registers at once: while one is encoded the loads of the others are in flight.
-// Measured best with the ring as long as the wave's whole share (all loads issued up front, about 16 KB
-// per wave, no loop) for pages of up to four passes; a page is 4 registers per pass, so longer pages
-// take turns in fewer sets, and at eight passes a second page in registers costs occupancy and gains
-// nothing.
-// The run-time-scheme instantiation needs more registers for itself: from six passes on it keeps one page.
-constexpr int enc_ring_max(int np, int scheme) {
-    return np <= 2 ? 8 : np <= 3 ? 5 : np <= 4 ? 4 : np <= 5 ? KVC_RING5 : (np == 6 && scheme >= 0) ? KVC_RING6 : (np == 7 && scheme >= 0) ? KVC_RING7 : 1;
-}
-
-// (four waves per SIMD is what the LDS slots allow anyway: keep every instantiation within 128 VGPRs; the
-// channel-pair encoder at D = 256 holds 32 mapped values beside the page and runs better with three, and
-// so do the run-time-scheme encoders of seven- and eight-pass pages whose rows cross passes or whose last
-// pass may be short, which would spill at four)
+// (four waves per SIMD is about what the LDS slots allow anyway: keep the instantiations within 128 VGPRs; where the
+// slots allow three -- four-pass pages with the mode fixed --, the channel-pair encoder at D = 256 holds 32 mapped
+// values beside the page, and the run-time-scheme encoders of seven- and eight-pass pages whose rows cross passes or
+// whose last pass may be short would spill at four)
 template <class P, int SCHEME>
 constexpr int enc_min_waves() {
-    return ((P::kD == 256 && (SCHEME == KVC_MODE_CHAN || SCHEME == kSchemeAny)) || (P::kPasses >= 7 && (!P::kAligned || P::kPartial) && SCHEME < 0)) ? 3 : KVC_ENC_MIN_WAVES;
+    return ((P::kPasses == 4 && SCHEME >= 0) || (P::kD == 256 && (SCHEME == KVC_MODE_CHAN || SCHEME == kSchemeAny)) || (P::kPasses >= 7 && (!P::kAligned || P::kPartial) && SCHEME < 0)) ? 3 : 4;
 }
+// A page task as it is parked in LDS: what a later turn of the loop, or the end of the kernel, needs to know of it.
+struct EncPlace {
+    uint64_t di;
+    int32_t sb;
+    uint32_t pg;
+    int scheme;
+    uint32_t w;  // once encoded: n16 | mode << 16 ...
+    float s;     // ... and the scale
+};
+
 template <class P, int WAVES, int PPW, int SCHEME>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_min_waves<P, SCHEME>()))) void k_compress(EncodeArgs a) {
-    constexpr int kSlots = WAVES * PPW;
     constexpr int NP = P::kPasses;
     constexpr int kMaxMode = SCHEME == kSchemeAny ? KVC_MODE_CHAN : KVC_MODE_PACK;  // what a per-block request may ask for
-    constexpr int kRing = enc_ring_max(NP, SCHEME) < PPW ? enc_ring_max(NP, SCHEME) : PPW;
-    static_assert(PPW % kRing == 0, "the loop handles pages in groups of kRing");
-    __shared__ __align__(16) uint32_t s_stage[kSlots][Slot<NP>::kWords];
-    __shared__ EncBook<kSlots> s_book;
-    __shared__ uint8_t s_lut[512];
+    constexpr int kRing = enc_ring(NP, PPW, SCHEME);
+    constexpr bool kUniform = PPW == 1;  // one page per wave: resolved on the scalar unit
+    static_assert(PPW % kRing == 0 && PPW <= 16, "the loop handles pages in groups of kRing; a row of lanes scans them");
+    __shared__ __align__(16) uint32_t s_stage[WAVES * PPW][Slot<NP>::kWords];
+    __shared__ uint32_t s_lut[128];
+    __shared__ uint32_t s_total[WAVES];
+    __shared__ unsigned long long s_base;
+    __shared__ EncPlace s_place[WAVES * PPW];
+    const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    fill_zigzag_lut(s_lut);
-    __syncthreads();
-    const int64_t t0 = ((int64_t)task_block_index<0>() * WAVES + wave) * PPW;
-    TaskPos pos = task_pos(t0, a.g.ppb);
+    const uint8_t* lut = reinterpret_cast<const uint8_t*>(s_lut);
+    uint32_t (*slots)[Slot<NP>::kWords] = &s_stage[wave * PPW];
+    const Extent x = page_extent<P>(a.g);
     const LanePos lp = lane_pos<P>(a.g);
-    const int slot0 = wave * PPW;
+    const int64_t t0 = ((int64_t)task_block_index() * WAVES + wave) * PPW;
+    const EncLanes L = kUniform ? enc_locate(a, t0 < a.n_pages, (uint32_t)t0, kMaxMode)
+                                : enc_locate(a, lane < PPW && t0 + lane < a.n_pages, (uint32_t)t0 + (uint32_t)lane, kMaxMode);
+    const uint32_t ok = kUniform ? (L.ok ? 1u : 0u) : (uint32_t)__builtin_amdgcn_ballot_w64(L.ok);
+    if (lane < PPW) s_place[wave * PPW + lane] = EncPlace{L.di, L.sb, L.pg, L.scheme, 0u, 0.0f};  // (not kept in registers meanwhile)
+    wave_sync();
+    uint32_t total = 0;  // payload units of the wave's pages
+    const int any = __builtin_ctz(ok | 0x10000u);  // a page that exists: the loads of those that do not read it again
     // the deal of the page to the lanes follows the mode requested for it
-    auto load = [&](const EncTask& task, uint4 (&raw)[NP]) {
+    constexpr bool kParked = kRing < PPW;  // pages are loaded while others are encoded
+    auto scheme_of = [&](int i) { return kParked ? (int)wave_uniform((int32_t)s_place[wave * PPW + i].scheme) : (int)of_lane<kUniform>((uint32_t)L.scheme, i); };
+    auto load = [&](int i, uint4 (&raw)[NP]) {
+        const int from = (ok >> i) & 1u ? i : any;
+        const EncPlace& parked = s_place[wave * PPW + from];
+        const int32_t sb = kParked ? wave_uniform(parked.sb) : (int32_t)of_lane<kUniform>((uint32_t)L.sb, from);
+        const int32_t pg = kParked ? wave_uniform((int32_t)parked.pg) : (int32_t)of_lane<kUniform>(L.pg, from);
+        const int64_t off = page_base(a.g, sb, pg);
+        const char* src = reinterpret_cast<const char*>(a.cache) + off * 2;
         if constexpr (SCHEME == kSchemeAny) {
-            if (task.scheme == KVC_MODE_CHAN)
-                load_page<P, true>(a, task, lp, raw);
+            if (scheme_of(i) == KVC_MODE_CHAN)
+                load_page<P, true>(a, src, lp, raw);
             else
-                load_page<P, false>(a, task, lp, raw);
+                load_page<P, false>(a, src, lp, raw);
         } else {
-            load_page<P, SCHEME == KVC_MODE_CHAN>(a, task, lp, raw);
+            load_page<P, SCHEME == KVC_MODE_CHAN>(a, src, lp, raw);
         }
     };
-    if (kRing > 1) {
-        // The register sets take turns (the inner loop is unrolled, so every index is a constant):
-        // nothing is copied between them.
-        EncTask t[kRing];
-        uint4 r[kRing][NP];
-#pragma unroll
-        for (int j = 0; j < kRing - 1; ++j) {
-            if (j > 0) task_advance(pos, a.g.ppb);
-            t[j] = resolve_enc_task(a, t0 + j, pos, kMaxMode);
-            if (t[j].desc_idx >= 0) load(t[j], r[j]);
+    auto encode = [&](int i, uint4 (&raw)[NP]) {
+        if (((ok >> i) & 1u) == 0) return;
+        clear_beyond<P>(x, raw);
+        const PageResult r = encode_page<P, SCHEME>(raw, lp, x, scheme_of(i), slots[i], lut, a.st);
+        if (lane == 0) {
+            s_place[wave * PPW + i].w = r.n16 | (r.mode << 16);
+            s_place[wave * PPW + i].s = r.scale;
         }
+        total += r.n16;
+    };
+    // The register sets take turns (the inner loop is unrolled, so every index is a constant): nothing is copied
+    // between them, and up to kRing pages' loads are in flight.
+    uint4 raw[kRing][NP];
+    if (ok) {
+#pragma unroll
+        for (int j = 0; j < kRing - 1; ++j) load(j, raw[j]);
+    }
+    fill_zigzag_lut(s_lut);
+    __syncthreads();
+    if (ok) {
 #pragma unroll 1
         for (int i = 0; i < PPW; i += kRing) {
 #pragma unroll
             for (int j = 0; j < kRing; ++j) {
-                constexpr int kAhead = kRing - 1;
-                const int nb = (j + kAhead) % kRing;
-                task_advance(pos, a.g.ppb);
-                t[nb] = resolve_enc_task(a, i + j + kAhead < PPW ? t0 + i + j + kAhead : a.n_pages, pos, kMaxMode);  // past the end: no task
-                if (t[nb].desc_idx >= 0) load(t[nb], r[nb]);
-                encode_into_slot<P, SCHEME>(a, r[j], lp, t[j], slot0 + i + j, s_stage[slot0 + i + j], s_lut, s_book);
+                const int next = i + j + kRing - 1;
+                if (kRing == PPW ? j == 0 : next < PPW) load(kRing == PPW ? kRing - 1 : next, raw[(j + kRing - 1) % kRing]);
+                encode(i + j, raw[j]);
             }
         }
-    } else {
-#pragma unroll 1
-        for (int i = 0; i < PPW; ++i) {
-            const EncTask task = resolve_enc_task(a, t0 + i, pos, kMaxMode);
-            task_advance(pos, a.g.ppb);
-            uint4 raw[NP];
-            if (task.desc_idx >= 0) load(task, raw);
-            encode_into_slot<P, SCHEME>(a, raw, lp, task, slot0 + i, s_stage[slot0 + i], s_lut, s_book);
-        }
+    }
+    // One atomic on the pool cursor reserves a contiguous span for all pages of the workgroup.
+    if (lane == 0) s_total[wave] = total;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t all = 0;
+#pragma unroll
+        for (int k = 0; k < WAVES; ++k) all += s_total[k];
+        const unsigned long long base = all ? atomicAdd(&a.st->cursor16, (unsigned long long)all) : 0ull;
+        if (base + all > a.pool_units) atomicOr(&a.st->status, KVC_ST_POOL_FULL);
+        s_base = base;
     }
     __syncthreads();
-    if (threadIdx.x == 0) reserve_pool_span<kSlots>(a, s_book);
-    __syncthreads();
+    if (ok == 0) return;
+    // lane i: where page i's payload goes; pages that do not fit become INVALID
+    uint32_t before = 0;  // units of the waves before this one
+#pragma unroll
+    for (int k = 0; k < WAVES - 1; ++k) before += k < wave ? s_total[k] : 0u;
+    wave_sync();
+    const EncPlace& own = s_place[wave * PPW + min(lane, PPW - 1)];
+    const uint32_t w_own = lane < PPW ? own.w : 0u;  // lane i: page i's
+    const uint32_t n_own = w_own & 0xFFFFu;
+    const uint64_t off16 = s_base + before + (kUniform ? 0u : row16_incl_scan_dpp(n_own) - n_own);
+    const bool fits = off16 + n_own <= a.pool_units;
+    if (lane < 32 && ((ok >> (lane & 31)) & 1u)) {
+        const uint64_t off = off16 * 16u;
+        reinterpret_cast<uint4*>(a.desc)[own.di] =
+            fits ? make_uint4((uint32_t)off, (uint32_t)(off >> 32), __float_as_uint(own.s), w_own) : make_uint4(0u, 0u, 0u, (uint32_t)KVC_MODE_INVALID << 16);
+    }
+    const uint32_t store = ok & (uint32_t)__builtin_amdgcn_ballot_w64(fits);
 #pragma unroll 1
-    for (int i = 0; i < PPW; ++i) emit_page<kSlots>(a, s_book, slot0 + i, s_stage[slot0 + i]);
+    for (int i = 0; i < PPW; ++i) {
+        if (((store >> i) & 1u) == 0) continue;
+        const uint32_t w = of_lane<false>(w_own, i), n16 = w & 0xFFFFu;
+        KVC_CHECK(a.st, of_lane<false>(off16, i) + n16 <= a.pool_units && (size_t)n16 * 16 <= sizeof(uint32_t) * Slot<8>::kWords * 2);
+        uint4* dst = reinterpret_cast<uint4*>(a.pool) + of_lane<false>(off16, i);
+        if (w >> 16 == KVC_MODE_RAW) {  // the payload is the dense page
+            const EncPlace pl = s_place[wave * PPW + i];
+            const uint16_t* srcp = a.cache + page_base(a.g, (int64_t)wave_uniform(pl.sb), wave_uniform((int32_t)pl.pg));
+            for (uint32_t o = (uint32_t)lane; o < n16; o += 64) dst[o] = *reinterpret_cast<const uint4*>(srcp + elem_off(a.g, (int)o * 8));
+        } else {  // (written once and not read back by the encoder)
+            const uint4* staged = reinterpret_cast<const uint4*>(slots[i]);
+#pragma unroll
+            for (int z = 0; z < P::kRounds; ++z)
+                if ((uint32_t)lane + 64u * z < n16) store_stream(dst + lane + 64 * z, staged[lane + 64 * z]);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------------- decode
@@ -776,16 +818,6 @@ __device__ __forceinline__ DecLanes dec_open(const DecodeArgs& a, const DecPlace
     if (readable && !ok) st = KVC_ST_CORRUPT;
     if (st) atomicOr(&a.st->status, st);
     return r;
-}
-
-// Lane i's value in scalar registers.  UNIFORM: every lane holds the same page task.
-template <bool UNIFORM>
-__device__ __forceinline__ uint32_t of_lane(uint32_t v, int i) {
-    return (uint32_t)(UNIFORM ? __builtin_amdgcn_readfirstlane((int)v) : __builtin_amdgcn_readlane((int)v, i));
-}
-template <bool UNIFORM>
-__device__ __forceinline__ uint64_t of_lane(uint64_t v, int i) {
-    return (uint64_t)of_lane<UNIFORM>((uint32_t)v, i) | ((uint64_t)of_lane<UNIFORM>((uint32_t)(v >> 32), i) << 32);
 }
 
 // 16 bytes from global memory straight to LDS: lane l's go to lds + 16 l (the destination is wave-uniform).
@@ -1071,7 +1103,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_decompress(DecodeArgs a) {
     __shared__ __align__(16) uint32_t s_stage[WAVES][PPW][Slot<P::kPasses>::kWords];
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t t0 = ((int64_t)task_block_index<1>() * WAVES + wave) * PPW;
+    const int64_t t0 = ((int64_t)task_block_index() * WAVES + wave) * PPW;
     if (t0 >= a.n_pages) return;
     // A page's memory chain is ids -> descriptor -> payload, each a full trip to HBM.  The wave walks it for
     // all of its PPW pages at once: lane i resolves page i, then all payload loads are issued, straight to
@@ -1147,12 +1179,6 @@ constexpr int kCodecWaves = 4;
 // engines / wide engines: 64 engines 1081 / 571, 256 engines 399 / 229 (without the window: 175).
 constexpr int kWideWaves = 16;
 constexpr int window_side(int np) { return np <= 4 ? 4 : 2; }
-// large calls: about 64 KB of input per workgroup and one pool-cursor atomic for it
-constexpr int enc_ppw_large(int np) { return np == 1 ? 64 / KVC_ENC_WAVES_1KB : np == 2 ? 8 : np == 3 ? 5 : np == 4 ? 4 : np == 5 ? KVC_PPW5 : np == 6 ? KVC_PPW6 : np == 7 ? KVC_PPW7 : KVC_PPW8; }
-// waves per encoder workgroup in large calls
-// (one-pass pages: eight waves share the workgroup's 64 slots, so that six waves instead of four fit a SIMD
-// beside the LDS the slots take: 0.41 -> 0.51 of HBM peak at 16 x 32; two-pass pages lose by the same change)
-constexpr int enc_waves_large(int np) { return np >= 5 ? KVC_ENC_WAVES_LONG : np == 1 ? KVC_ENC_WAVES_1KB : 4; }
 // A small call (a decode step's offload of a few blocks) is latency: one page per wave (more only for
 // the smallest pages), so the pages are encoded side by side instead of several in a row.  The cursor
 // then takes an atomic per four pages, which only a large call would feel.
@@ -1163,9 +1189,7 @@ constexpr int enc_ppw_small(int np) { return np == 1 ? 4 : np == 2 ? 2 : 1; }
 // 1109 (a million pages) with 1 / 2 / 4: there the launch moves 5.8 TB/s, what a copy does, with any of them.
 constexpr int dec_ppw(int np) { return np == 1 ? 4 : np == 2 ? 2 : 1; }
 // calls of at most this many pages take the low-latency launch shape
-#ifndef KVC_ENC_SMALL_PAGES
-#define KVC_ENC_SMALL_PAGES 2048
-#endif
+constexpr int kEncSmallPages = 2048;
 
 inline dim3 page_grid(int64_t n_pages, int ppw, int waves = kCodecWaves) {
     const int64_t per_wg = (int64_t)waves * ppw;
@@ -1180,10 +1204,10 @@ struct ShapeOps {
     template <int SCHEME>
     static hipError_t compress_scheme(const EncodeArgs& a, hipStream_t s) {
         const dim3 block(kCodecWaves * 64);
-        if (a.n_pages <= KVC_ENC_SMALL_PAGES)
+        if (a.n_pages <= kEncSmallPages)
             return launch_kernel(k_compress<P, kCodecWaves, enc_ppw_small(NP), SCHEME>, page_grid(a.n_pages, enc_ppw_small(NP)), block, s, a);
-        constexpr int W = enc_waves_large(NP);
-        return launch_kernel(k_compress<P, W, enc_ppw_large(NP), SCHEME>, page_grid(a.n_pages, enc_ppw_large(NP), W), dim3(W * 64), s, a);
+        constexpr EncShape e = enc_large(NP, SCHEME);
+        return launch_kernel(k_compress<P, e.waves, e.ppw, SCHEME>, page_grid(a.n_pages, e.ppw, e.waves), dim3(e.waves * 64), s, a);
     }
 
     static hipError_t compress(const EncodeArgs& a, hipStream_t s) {

@@ -34,6 +34,7 @@ struct EncodeArgs {
     Geometry g;
     int32_t scheme;
     const uint8_t* block_scheme;  // optional: requested mode per block (overrides scheme)
+    FastDiv by_ppb;
     uint8_t* pool;
     uint64_t pool_units;  // pool size in 16-byte units
     kvc_desc* desc;

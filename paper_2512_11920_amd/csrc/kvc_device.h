@@ -5,11 +5,6 @@
 
 namespace kvc {
 
-// payloads are written to the pool once and not read back by the encoder: non-temporal stores
-#ifndef KVC_NT_POOL_STORE
-#define KVC_NT_POOL_STORE 1
-#endif
-
 // Debug build (-DKVC_DEBUG_BOUNDS=1): every LDS slot index and pool span the kernels compute is checked
 // against its bounds; a violation sets status bit 8 instead of being executed silently.  Off by default.
 #ifndef KVC_DEBUG_BOUNDS
@@ -147,26 +142,15 @@ __device__ __forceinline__ int64_t elem_off(const Geometry& g, int e) {
     return (int64_t)row * g.row_stride + ((uint32_t)e - row * (uint32_t)g.d);
 }
 
-// Workgroup index used for task assignment.  Workgroups are dealt round-robin to the 8 XCDs, so with
-// the identity deal (MODE 0) XCD k works on the tasks whose index is k modulo 8 for the whole launch: all
-// XCDs sweep the buffers side by side, 16 KB apart.  MODE 1 gives each XCD one contiguous eighth of the
-// tasks instead, so that it streams through a region of its own.  Measured on the 21 GB cache: the
-// decoder's time falls into one of two clusters from process to process whatever the deal (the buffers'
-// placement by the driver decides: this GPU's HBM behaves as three regions of about 96 GB, and any kernel,
-// a plain copy too, runs 4-7 % slower when it reads and writes inside one of them than when it reads from
-// one and writes to another); with MODE 1 the clusters are 5.0 and 5.45 ms,
-// with MODE 0 5.15 and 5.45 ms, and the decode-gather step gains 7 %.  The encoder is 1-2 % faster with
-// MODE 0.  (Also tried, without gain for either kernel: rotating the tasks inside every run of eight
-// workgroups, shifting all tasks by a workgroup, runs of 3 to 4099 tasks per XCD in turn, and eighths
-// entered at staggered points.)
-template <int MODE>
+// Workgroup index used for task assignment.  Workgroups are dealt round-robin to the 8 XCDs; here each XCD gets one
+// contiguous eighth of the tasks, so that it streams through a region of its own, in both directions: the payloads of
+// eight distant regions then lie side by side in the pool, and the decoder's XCDs read them side by side again.  A
+// million pages of 16 x 128, us: encoder 1075 -> 1051, decoder 1077 -> 1028 on the pool it leaves (with the identity deal
+// in both 1075, with this one in the decoder alone 1077).
 __device__ __forceinline__ unsigned task_block_index() {
     const unsigned b = blockIdx.x;
-    if (MODE == 1) {
-        const unsigned q = gridDim.x >> 3;
-        return b < (q << 3) ? (b & 7u) * q + (b >> 3) : b;
-    }
-    return b;
+    const unsigned q = gridDim.x >> 3;
+    return b < (q << 3) ? (b & 7u) * q + (b >> 3) : b;
 }
 
 // A value every lane of the wave holds the same copy of, moved to scalar registers: index arithmetic
@@ -178,6 +162,16 @@ __device__ __forceinline__ int64_t wave_uniform(int64_t v) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
     return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// Lane i's value in scalar registers.  UNIFORM: every lane holds the same page task.
+template <bool UNIFORM>
+__device__ __forceinline__ uint32_t of_lane(uint32_t v, int i) {
+    return (uint32_t)(UNIFORM ? __builtin_amdgcn_readfirstlane((int)v) : __builtin_amdgcn_readlane((int)v, i));
+}
+template <bool UNIFORM>
+__device__ __forceinline__ uint64_t of_lane(uint64_t v, int i) {
+    return (uint64_t)of_lane<UNIFORM>((uint32_t)v, i) | ((uint64_t)of_lane<UNIFORM>((uint32_t)(v >> 32), i) << 32);
 }
 
 // Scaling step of Algorithm 2 for a page whose largest magnitude is the finite, non-zero FP16 value
@@ -211,57 +205,33 @@ struct PageResult {
     float scale;
 };
 
-// Page task of the encoder: which source page, which descriptor.
-struct EncTask {
-    long long desc_idx;  // -1: nothing to do
-    long long src_off;   // element offset of the source page in the cache buffer
-    int scheme;          // mode requested for this page
+// Page tasks of the encoder, one per lane: lane i of a wave holds page i of the wave's batch, so that the ids and
+// modes of all its pages are fetched by one load each.  (Resolved page by page, a call with block ids waited for every
+// id, and with it for the page loads under way.)
+struct EncLanes {
+    bool ok;      // there is a page to encode
+    int32_t sb;   // source block
+    uint32_t pg;  // page inside the block
+    uint64_t di;  // descriptor index
+    int scheme;   // mode requested for the page
 };
 
-// Position of a wave's first page task as (block, page in block); later tasks advance it by one page.
-// A wave works on one page at a time, so positions and everything derived from them are wave-uniform.
-struct TaskPos {
-    int64_t blk;
-    int pg;
-};
-
-// The host bounds the pages of one call well below 2^31, so task indices divide in 32 bits.
-__device__ __forceinline__ TaskPos task_pos(int64_t t, int ppb) {
-    TaskPos r;
-    const uint32_t blk = (uint32_t)t / (uint32_t)ppb;
-    r.pg = wave_uniform((int32_t)((uint32_t)t - blk * (uint32_t)ppb));
-    r.blk = (int64_t)(uint32_t)wave_uniform((int32_t)blk);
-    return r;
-}
-
-__device__ __forceinline__ void task_advance(TaskPos& p, int ppb) {
-    if (++p.pg == ppb) {
-        p.pg = 0;
-        ++p.blk;
-    }
-}
-
-// max_mode: the highest mode a per-block request may name for this page shape (higher values are read as it)
-__device__ __forceinline__ EncTask resolve_enc_task(const EncodeArgs& a, int64_t t, const TaskPos& pos, int max_mode = KVC_MODE_PACK) {
-    EncTask r;
-    r.desc_idx = -1;
-    r.src_off = -1;
-    r.scheme = a.scheme;
-    if (t >= a.n_pages) return r;
-    const int ppb = a.g.ppb;
-    const int64_t blk = pos.blk;
-    const int pg = pos.pg;
-    const int64_t sb = a.src_ids ? (int64_t)wave_uniform(a.src_ids[blk]) : blk;
-    const int64_t pb = a.pool_ids ? (int64_t)wave_uniform(a.pool_ids[blk]) : blk;
-    if (sb < 0 || pb < 0) return r;
-    const uint64_t d_idx = (uint64_t)pb * (uint64_t)ppb + (uint64_t)pg;
-    if (sb >= a.n_cache_blocks || d_idx >= a.n_desc) {
-        if (lane_id() == 0) atomicOr(&a.st->status, KVC_ST_BAD_INDEX);
-        return r;
-    }
-    r.src_off = page_base(a.g, sb, pg);
-    r.desc_idx = (long long)d_idx;
-    if (a.block_scheme) r.scheme = min(wave_uniform((int32_t)a.block_scheme[blk]), (int32_t)max_mode);
+// lane-wise: page task t of the call (t < 2^31).  max_mode: the highest mode a per-block request may name for this
+// page shape (higher values are read as it)
+__device__ __forceinline__ EncLanes enc_locate(const EncodeArgs& a, bool live, uint32_t t, int max_mode) {
+    EncLanes r;
+    const uint32_t blk = fast_div(t, a.by_ppb);
+    r.pg = t - blk * (uint32_t)a.g.ppb;
+    int32_t sb = (int32_t)blk, pb = (int32_t)blk, scheme = a.scheme;
+    if (live && a.src_ids) sb = a.src_ids[blk];
+    if (live && a.pool_ids) pb = a.pool_ids[blk];
+    if (live && a.block_scheme) scheme = min((int)a.block_scheme[blk], max_mode);
+    r.sb = sb;
+    r.scheme = scheme;
+    const bool wanted = live && sb >= 0 && pb >= 0;
+    r.di = (uint64_t)(uint32_t)pb * (uint32_t)a.g.ppb + r.pg;
+    r.ok = wanted && sb < a.n_cache_blocks && r.di < a.n_desc;
+    if (wanted && !r.ok) atomicOr(&a.st->status, KVC_ST_BAD_INDEX);
     return r;
 }
 
@@ -327,78 +297,6 @@ __device__ __forceinline__ DecPlace dec_locate(const DecodeArgs& a, bool live, u
 __device__ __forceinline__ void zero_page(uint16_t* dst, const Geometry& g) {
     for (int o = lane_id(); o < (g.E >> 3); o += 64)
         *reinterpret_cast<uint4*>(dst + elem_off(g, o * 8)) = make_uint4(0, 0, 0, 0);
-}
-
-// Per-workgroup bookkeeping of the encoder: results of the pages staged in LDS.
-template <int SLOTS>
-struct EncBook {
-    uint32_t n16[SLOTS];
-    uint32_t mode[SLOTS];
-    float scale[SLOTS];
-    unsigned long long off16[SLOTS];
-    long long desc[SLOTS];
-    long long srcoff[SLOTS];
-};
-
-// One thread reserves a contiguous pool span for all staged pages of the workgroup with a single
-// atomic on the pool cursor and hands each page its offset; pages that do not fit become INVALID.
-template <int SLOTS>
-__device__ __forceinline__ void reserve_pool_span(const EncodeArgs& a, EncBook<SLOTS>& b) {
-    uint32_t tot = 0;  // at most SLOTS * 512 units
-    for (int k = 0; k < SLOTS; ++k) tot += b.n16[k];
-    const unsigned long long base = tot ? atomicAdd(&a.st->cursor16, (unsigned long long)tot) : 0ull;
-    const bool all_fit = base + tot <= a.pool_units;
-    uint32_t rel = 0;
-    for (int k = 0; k < SLOTS; ++k) {
-        const uint32_t n = b.n16[k];
-        if (!all_fit && n && base + rel + n > a.pool_units) b.mode[k] = KVC_MODE_INVALID;
-        b.off16[k] = base + rel;
-        rel += n;
-    }
-    if (!all_fit) atomicOr(&a.st->status, KVC_ST_POOL_FULL);
-}
-
-// A wave moves one staged payload (or, for RAW, the source page) to its pool span and writes the
-// 16-byte descriptor.
-template <int SLOTS>
-__device__ __forceinline__ void emit_page(const EncodeArgs& a, const EncBook<SLOTS>& b, int slot, const uint32_t* stage) {
-    const long long di = b.desc[slot];
-    if (di < 0) return;
-    const int lane = lane_id();
-    const uint32_t mode = b.mode[slot];
-    const uint32_t n16 = b.n16[slot];
-    const unsigned long long off16 = b.off16[slot];
-    if (mode != KVC_MODE_INVALID) {
-        KVC_CHECK(a.st, off16 + n16 <= a.pool_units && (size_t)n16 * 16 <= sizeof(uint32_t) * Slot<8>::kWords * 2);
-        uint4* dst = reinterpret_cast<uint4*>(a.pool) + off16;
-        if (mode == KVC_MODE_RAW) {  // the payload is the dense page
-            const uint16_t* srcp = a.cache + b.srcoff[slot];
-            for (uint32_t o = lane; o < n16; o += 64) dst[o] = *reinterpret_cast<const uint4*>(srcp + elem_off(a.g, (int)o * 8));
-        } else {
-            const uint4* srcp = reinterpret_cast<const uint4*>(stage);
-#if KVC_NT_POOL_STORE
-            typedef uint32_t u4v __attribute__((ext_vector_type(4)));
-            for (uint32_t o = lane; o < n16; o += 64) {
-                const uint4 v = srcp[o];
-                u4v w;
-                w.x = v.x; w.y = v.y; w.z = v.z; w.w = v.w;
-                __builtin_nontemporal_store(w, reinterpret_cast<u4v*>(dst + o));
-            }
-#else
-            for (uint32_t o = lane; o < n16; o += 64) dst[o] = srcp[o];
-#endif
-        }
-    }
-    if (lane == 0) {
-        uint4 dw;
-        if (mode == KVC_MODE_INVALID) {
-            dw = make_uint4(0, 0, 0, (uint32_t)KVC_MODE_INVALID << 16);
-        } else {
-            const unsigned long long off = off16 * 16ull;
-            dw = make_uint4((uint32_t)off, (uint32_t)(off >> 32), __float_as_uint(b.scale[slot]), n16 | (mode << 16));
-        }
-        reinterpret_cast<uint4*>(a.desc)[di] = dw;
-    }
 }
 
 // ---- outstanding-request window (Algorithm 1, WaitCompletion over at most Omega_max transfers) ----
