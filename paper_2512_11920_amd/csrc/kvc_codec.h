@@ -1104,13 +1104,12 @@ __global__ __launch_bounds__(WAVES * 64) void k_decompress(DecodeArgs a) {
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t t0 = ((int64_t)task_block_index() * WAVES + wave) * PPW;
-    if (t0 >= a.n_pages) return;
     // A page's memory chain is ids -> descriptor -> payload, each a full trip to HBM.  The wave walks it for
     // all of its PPW pages at once: lane i resolves page i, then all payload loads are issued, straight to
     // LDS, and the pages are decoded one after the other.
     const LanePos lp = lane_pos<P>(a.g);
     // (a batch of one page is resolved on the scalar unit: every lane has the same task)
-    const DecLanes L = dec_open<P>(a, PPW == 1 ? dec_locate(a, true, (uint32_t)t0) : dec_locate(a, lane < PPW && t0 + lane < a.n_pages, (uint32_t)t0 + (uint32_t)lane));
+    const DecLanes L = dec_open<P>(a, PPW == 1 ? dec_locate(a, t0 < a.n_pages, (uint32_t)t0) : dec_locate(a, lane < PPW && t0 + lane < a.n_pages, (uint32_t)t0 + (uint32_t)lane));
     dec_fetch<P, PPW, PPW == 1>(a, L, 0, s_stage[wave]);
     dec_batch<P, PPW, PPW == 1, false>(a, L, 0, lp, s_stage[wave]);
 }
@@ -1190,6 +1189,9 @@ constexpr int enc_ppw_small(int np) { return np == 1 ? 4 : np == 2 ? 2 : 1; }
 constexpr int dec_ppw(int np) { return np == 1 ? 4 : np == 2 ? 2 : 1; }
 // calls of at most this many pages take the low-latency launch shape
 constexpr int kEncSmallPages = 2048;
+// Four-pass pages with the mode fixed: up to this many pages the workgroups of 16 pages are all resident at once (256
+// compute units, four each), while those of 20 would leave a nearly empty last round (16,384 pages: 26 us, 29.7 us).
+constexpr int kEncMidPages = 16384;
 
 inline dim3 page_grid(int64_t n_pages, int ppw, int waves = kCodecWaves) {
     const int64_t per_wg = (int64_t)waves * ppw;
@@ -1206,6 +1208,9 @@ struct ShapeOps {
         const dim3 block(kCodecWaves * 64);
         if (a.n_pages <= kEncSmallPages)
             return launch_kernel(k_compress<P, kCodecWaves, enc_ppw_small(NP), SCHEME>, page_grid(a.n_pages, enc_ppw_small(NP)), block, s, a);
+        if constexpr (NP == 4 && SCHEME >= 0) {
+            if (a.n_pages <= kEncMidPages) return launch_kernel(k_compress<P, 4, 4, SCHEME>, page_grid(a.n_pages, 4, 4), dim3(256), s, a);
+        }
         constexpr EncShape e = enc_large(NP, SCHEME);
         return launch_kernel(k_compress<P, e.waves, e.ppw, SCHEME>, page_grid(a.n_pages, e.ppw, e.waves), dim3(e.waves * 64), s, a);
     }
