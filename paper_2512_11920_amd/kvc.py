@@ -43,11 +43,15 @@ class KvcError(RuntimeError):
 
 
 _lib = None
+# bound when the library is loaded: torch, and the calls that name the current device's current stream.  (A small data
+# call is mostly the way through this module: torch.cuda.current_stream() alone, which makes a stream object, took
+# 1.3 us of 7.)
+_torch = _device_now = _raw_stream_now = None
 
 
 def load():
     """dlopen libkvc.so and declare the prototypes.  Raises if the library is missing."""
-    global _lib
+    global _lib, _torch, _device_now, _raw_stream_now
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -55,8 +59,11 @@ def load():
                           "(there is no fallback implementation)")
     # libkvc.so needs the HIP runtime by soname; importing torch first makes the loader resolve it
     # to the copy torch already mapped, so tensors and kernels share one runtime instance.
-    import torch  # noqa: F401
+    import torch
 
+    _torch = torch
+    _device_now = getattr(torch._C, "_cuda_getDevice", None)
+    _raw_stream_now = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     L = C.CDLL(LIB_PATH)
     vp, i32p = C.c_void_p, C.c_void_p
     L.kvc_create.restype = C.c_int
@@ -126,18 +133,17 @@ def _ptr(t):
 
 
 def _stream(stream):
-    import torch
-
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream_now is not None and _device_now is not None and _torch.cuda.is_initialized():
+        return _raw_stream_now(_device_now())
+    return _torch.cuda.current_stream().cuda_stream
 
 
 def _ids(t):
-    import torch
-
     if t is None:
         return None
-    assert t.is_cuda and t.dtype == torch.int32 and t.is_contiguous(), "block ids: contiguous int32 CUDA tensor"
+    assert t.is_cuda and t.dtype == _torch.int32 and t.is_contiguous(), "block ids: contiguous int32 CUDA tensor"
     return t
 
 
@@ -151,6 +157,7 @@ class Codec:
         _check(self._L.kvc_create(C.byref(self._ctx), C.byref(self.cfg)), "kvc_create")
         self.pool = None
         self.desc = None
+        self._block_stride = self._span = self.block_elems  # of the contiguous layout
 
     # -- geometry
     @property
@@ -216,17 +223,12 @@ class Codec:
     # -- the three data calls
     def _blocks_of(self, t) -> int:
         """Number of whole blocks the tensor's storage covers under the current layout."""
-        import torch
-
-        assert t.is_cuda and t.is_contiguous() and t.dtype == torch.float16
-        bs = getattr(self, "_block_stride", self.block_elems)
-        span = getattr(self, "_span", self.block_elems)
-        return 0 if t.numel() < span else (t.numel() - span) // bs + 1
+        assert t.is_cuda and t.is_contiguous() and t.dtype == _torch.float16
+        n = t.numel()
+        return 0 if n < self._span else (n - self._span) // self._block_stride + 1
 
     def compress_blocks(self, cache, n: int | None = None, src_ids=None, pool_ids=None, block_scheme=None, stream=None):
         """block_scheme: optional uint8 CUDA tensor, requested mode per block of the call."""
-        import torch
-
         nb = self._blocks_of(cache)
         src_ids, pool_ids = _ids(src_ids), _ids(pool_ids)
         if n is None:
@@ -236,7 +238,7 @@ class Codec:
             _check(self._L.kvc_compress_blocks(self._ctx, cache.data_ptr(), nb, _ptr(src_ids), _ptr(pool_ids), int(n),
                                                _stream(stream)), "kvc_compress_blocks")
         else:
-            assert block_scheme.is_cuda and block_scheme.dtype == torch.uint8 and block_scheme.numel() >= n
+            assert block_scheme.is_cuda and block_scheme.dtype == _torch.uint8 and block_scheme.numel() >= n
             _check(self._L.kvc_compress_blocks_mixed(self._ctx, cache.data_ptr(), nb, _ptr(src_ids), _ptr(pool_ids),
                                                      block_scheme.data_ptr(), int(n), _stream(stream)),
                    "kvc_compress_blocks_mixed")
