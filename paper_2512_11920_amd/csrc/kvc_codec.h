@@ -23,7 +23,6 @@ namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
 // Non-temporal hints for the page-sized streams (encoder input, decoder output): measured 4-7 % faster.
@@ -1175,7 +1174,7 @@ constexpr int kCodecWaves = 4;
 // Transfer engines of the prefetch window.  Up to as many engines as the device holds of the wide kind (512 at 16 x 128)
 // each has 16 waves; beyond that engines of four waves, with several pages of a block per wave in flight, of which
 // two to four times as many are resident.  Two prefetch steps of 4,370 blocks of 16 pages of 16 x 128, us, four-wave
-// engines / wide engines: 64 engines 1081 / 571, 256 engines 399 / 229 (without the window: 175).
+// engines / wide engines: 64 engines 1081 / 571, 256 engines 399 / 229.
 constexpr int kWideWaves = 16;
 constexpr int window_side(int np) { return np <= 4 ? 4 : 2; }
 // A small call (a decode step's offload of a few blocks) is latency: one page per wave (more only for

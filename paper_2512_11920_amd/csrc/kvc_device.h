@@ -145,8 +145,8 @@ __device__ __forceinline__ int64_t elem_off(const Geometry& g, int e) {
 // Workgroup index used for task assignment.  Workgroups are dealt round-robin to the 8 XCDs; here each XCD gets one
 // contiguous eighth of the tasks, so that it streams through a region of its own, in both directions: the payloads of
 // eight distant regions then lie side by side in the pool, and the decoder's XCDs read them side by side again.  A
-// million pages of 16 x 128, us: encoder 1075 -> 1051, decoder 1077 -> 1028 on the pool it leaves (with the identity deal
-// in both 1075, with this one in the decoder alone 1077).
+// million pages of 16 x 128, us, with the encoder's tasks dealt in order -> by eighths: encoder 1075 -> 1051, decoder
+// 1077 -> 1048 on the pool it leaves.
 __device__ __forceinline__ unsigned task_block_index() {
     const unsigned b = blockIdx.x;
     const unsigned q = gridDim.x >> 3;
@@ -157,12 +157,6 @@ __device__ __forceinline__ unsigned task_block_index() {
 // on it (64-bit multiplies, bounds checks) then runs on the scalar unit, loads indexed by it become
 // scalar loads, and an access at kernel-argument pointer + such an offset needs no per-lane base.
 __device__ __forceinline__ int32_t wave_uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-
-__device__ __forceinline__ int64_t wave_uniform(int64_t v) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
 
 // Lane i's value in scalar registers.  UNIFORM: every lane holds the same page task.
 template <bool UNIFORM>
