@@ -1046,10 +1046,12 @@ __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L
     dec_fetched();
 #pragma unroll 1
     for (int i0 = 0; i0 < PPW; i0 += kScan) {
-        uint32_t info[H::kRounds];
-        uint64_t bad, special;
-        if (kScan == 1 && (of_lane<UNIFORM>(L.meta, first + i0) >> 24) == kDecSkip) continue;
-        dec_headers<P, UNIFORM, kScan>(x, L, first, i0, slots, info, bad, special);
+        uint32_t info[H::kRounds] = {};
+        uint64_t bad = 0, special = 0;
+        // (a scan for one page is left out where the page has no header: 0.3 us of a small call of INT8 pages)
+        const uint32_t meta0 = of_lane<UNIFORM>(L.meta, first + i0);
+        if (kScan > 1 || ((meta0 >> 24) == kDecPayload && ((meta0 >> 16) & 0xFFu) != KVC_MODE_INT8))
+            dec_headers<P, UNIFORM, kScan>(x, L, first, i0, slots, info, bad, special);
 #pragma unroll 1
         for (int j = 0; j < kScan; ++j) {
             const int i = i0 + j;
