@@ -1117,8 +1117,9 @@ __global__ __launch_bounds__(WAVES * 64) void k_decompress(DecodeArgs a) {
 
 // Transfer engines of the prefetch window (Algorithm 1: at most Omega_max transfers outstanding): a
 // workgroup takes the next issued blocks from the queue (a turn), its waves decode them one block after the other,
-// and the completion is reported before the next turn is taken.  An engine is latency, not bandwidth: few of them
-// are at work, each on one block.  So the waves share a block's pages as far as they go round (wave w takes pages w,
+// meeting after each -- no payload of a block is asked for before the last store of the engine's block before has
+// reached memory --, and the completion is reported before the next turn is taken.  An engine is latency, not
+// bandwidth: few of them are at work, each on one block.  So the waves share a block's pages as far as they go round (wave w takes pages w,
 // w + WAVES, ...; WIDE engines have a wave for each of 16 pages), and what can be known ahead is fetched for the
 // whole turn at once: queue entries, pool blocks and all descriptors, one page task per lane, before the first
 // payload.  SIDE: pages of one block that a wave has in flight together.
@@ -1128,6 +1129,11 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
     __shared__ __align__(16) uint32_t s_stage[WAVES][SIDE][Slot<P::kPasses>::kWords];
     __shared__ uint32_t s_turn[2];
     __shared__ int32_t s_q[WAVES][2][kMaxWindowTurn];
+#if KVC_DEBUG_BOUNDS
+    __shared__ uint32_t s_done;  // waves that have finished a block, summed over the engine's blocks
+    if (threadIdx.x == 0) s_done = 0;
+    uint32_t blocks = 0;  // blocks behind this wave
+#endif
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ppb = a.g.ppb;
@@ -1139,34 +1145,43 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
     const uint32_t n_issued = w.hdr->n_issued, chunk = w.hdr->chunk;
     uint32_t mine = 0;
     WindowTurn none;
-    none.first = none.count = 0;
+    none.first = none.count = none.at = 0;
     WindowTurn turn = window_next<true>(w, s_turn, none, s_q[0][0], mine, n_issued, chunk);
+    DecLanes L = {};  // 64 page tasks of the turn, one per lane
+    int t = 0;        // the wave's page tasks of the turn behind it, in block order
     while (turn.count) {
-        // the turn's queue entries and the pool blocks they name, one per lane, parked in the wave's row of LDS
-        if ((uint32_t)lane < turn.count) {
-            const int32_t slot_l = w.queue[turn.first + lane];
-            s_q[wave][0][lane] = slot_l;
-            s_q[wave][1][lane] = a.pool_ids[slot_l];
-        }
-        wave_sync();
-        const int tasks = (int)turn.count * per_block;  // in block order
-        for (int t0 = 0; t0 < tasks; t0 += 64 / SIDE * SIDE) {
-            const int t = t0 + lane;
-            const uint32_t b = min((uint32_t)t / (uint32_t)per_block, turn.count - 1u);
-            DecPlace pl;
-            pl.pg = (uint32_t)(wave + (t - (int)b * per_block) * WAVES);
-            pl.live = lane < 64 / SIDE * SIDE && t < tasks && (int)pl.pg < ppb;
-            pl.bad_index = false;
-            pl.pb = s_q[wave][1][b];
-            pl.db = s_q[wave][0][b];
-            const DecLanes L = dec_open<P>(a, pl);
-            for (int j = 0; j < 64 / SIDE * SIDE && t0 + j < tasks; j += SIDE) {
-                dec_fetch<P, SIDE, false>(a, L, j, s_stage[wave]);
-                dec_batch<P, SIDE, false, true>(a, L, j, lp, s_stage[wave]);
-                wave_sync();
-                __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the slots have been read before they are filled again
+        if (turn.at == 0) {  // the turn's queue entries and the pool blocks they name, one per lane, parked in the wave's row of LDS
+            if ((uint32_t)lane < turn.count) {
+                const int32_t slot_l = w.queue[turn.first + lane];
+                s_q[wave][0][lane] = slot_l;
+                s_q[wave][1][lane] = a.pool_ids[slot_l];
             }
+            wave_sync();
+            t = 0;
         }
+        for (const int end = t + per_block; t < end; t += SIDE) {  // the pages of block number turn.at
+            if (t % 64 == 0) {
+                const uint32_t b = min((uint32_t)(t + lane) / (uint32_t)per_block, turn.count - 1u);
+                DecPlace pl;
+                pl.pg = (uint32_t)(wave + (t + lane - (int)b * per_block) * WAVES);
+                pl.live = t + lane < (int)turn.count * per_block && (int)pl.pg < ppb;
+                pl.bad_index = false;
+                pl.pb = s_q[wave][1][b];
+                pl.db = s_q[wave][0][b];
+                L = dec_open<P>(a, pl);
+            }
+#if KVC_DEBUG_BOUNDS
+            KVC_CHECK(a.st, *(volatile uint32_t*)&s_done >= blocks * WAVES);
+#endif
+            dec_fetch<P, SIDE, false>(a, L, t % 64, s_stage[wave]);
+            dec_batch<P, SIDE, false, true>(a, L, t % 64, lp, s_stage[wave]);
+            wave_sync();
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the slots have been read before they are filled again
+        }
+#if KVC_DEBUG_BOUNDS
+        if (lane == 0) atomicAdd(&s_done, 1u);
+        ++blocks;
+#endif
         turn = window_next<false>(w, s_turn, turn, s_q[0][0], mine, n_issued, chunk);
     }
 }

@@ -302,15 +302,17 @@ __device__ __forceinline__ void zero_page(uint16_t* dst, const Geometry& g) {
 struct WindowTurn {
     uint32_t first;  // index of the first queue entry
     uint32_t count;  // entries in the run; 0 = the queue is exhausted, the engine leaves
+    uint32_t at;     // the entry at work
 };
 
-// One turn of an engine: report the blocks of the run `done` as complete -- make them visible, count
-// them, stamp the layers whose last transfer was among them -- and take the next run of up to hdr->chunk
-// queue entries (the first run needs no ticket: engine b begins with the b-th).  Called by all threads of the
+// End of a block of an engine: the waves meet with all their stores of it in memory, and only then is the next block's
+// payload asked for -- one block per engine is in flight, which is what bounds the call by Omega.  After the last block
+// of the run `turn`: report the run's blocks as complete -- count them, stamp the layers whose last transfer was among
+// them -- and take the next run of up to hdr->chunk queue entries (the first run needs no ticket: engine b begins with
+// the b-th).  Called by all threads of the
 // workgroup; `s_turn` is two words of LDS, `slots` the run's queue entries, parked in LDS by wave 0, `mine` the
 // blocks this engine has completed; n_issued and chunk are the header's (read once: they share a line with the ticket).
-// An engine decodes the blocks of its run one after the other, so it still holds one block in flight; the
-// run only spaces out the bookkeeping, which the other waves wait for.  It is kept short: the decoder's stores
+// The run spaces out the bookkeeping, which the other waves wait for.  It is kept short: the decoder's stores
 // under the window write through to the device's memory (store_out), so that waiting for them is all it takes to
 // publish a block; with a write-back of the XCD's L2 in its place a turn cost about 8 us (256 engines).  And the
 // counters every engine shares serve one atomic every 10 to 20 ns whatever the engines are doing, so a turn spends
@@ -323,24 +325,25 @@ struct WindowTurn {
 // an outer loop and lets the other lanes run ahead to the next barrier: the workgroup then never
 // meets.)
 template <bool FIRST>
-__device__ __forceinline__ WindowTurn window_next(const WindowArgs& w, uint32_t* s_turn, WindowTurn done, const int32_t* slots, uint32_t& mine,
+__device__ __forceinline__ WindowTurn window_next(const WindowArgs& w, uint32_t* s_turn, WindowTurn turn, const int32_t* slots, uint32_t& mine,
                                                   uint32_t n_issued, uint32_t chunk) {
     // every wave's stores have reached memory before the workgroup meets, and the counters move after that
     if (!FIRST) {
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), the other counters unchanged
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     }
-    mine += done.count;
     __syncthreads();
+    if (!FIRST && ++turn.at < turn.count) return turn;
+    mine += turn.count;
     if (threadIdx.x == 0) {
         const long long finished = max(wall_clock64(), 1ll);  // read before the blocks are counted
         const unsigned int t = FIRST ? blockIdx.x * chunk : atomicAdd(&w.hdr->ticket, chunk);
         if (!FIRST) {
             uint32_t i = 0;
-            while (i < done.count) {  // the run's entries are in layer order: one decrement per layer met
+            while (i < turn.count) {  // the run's entries are in layer order: one decrement per layer met
                 const uint32_t l_rel = fast_div((uint32_t)slots[i], w.by_per_layer);
                 uint32_t n = 1;
-                while (i + n < done.count && fast_div((uint32_t)slots[i + n], w.by_per_layer) == l_rel) ++n;
+                while (i + n < turn.count && fast_div((uint32_t)slots[i + n], w.by_per_layer) == l_rel) ++n;
                 if (atomicSub(&w.pending[l_rel], (int)n) == (int)n)
                     __hip_atomic_store(&w.notify[w.layer_begin + (int32_t)l_rel], finished, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
                 i += n;
@@ -358,6 +361,7 @@ __device__ __forceinline__ WindowTurn window_next(const WindowArgs& w, uint32_t*
     WindowTurn r;
     r.first = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_turn[0]);
     r.count = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_turn[1]);
+    r.at = 0;
     return r;
 }
 

@@ -91,4 +91,11 @@ import test_gpu_prefetch as tpf  # noqa: E402
 for omega, geom in ((5, (16, 128, 4, 5, 8, 4, 48, 200)), (16, (8, 32, 2, 5, 8, 4, 48, 200)), (4096, (16, 32, 1, 48, 16, 5, 400, 800))):
     tpf.test_window_prefetch_matches_unbounded_and_model(omega, geom)
     n_cases += 1
+# ... and with every compute unit busy, wide engines and narrow ones: this build also counts the waves that have finished
+# each block, so a payload asked for while another wave is still at the engine's block before sets bit 8 too
+import test_gpu_window_scale as tws  # noqa: E402
+
+for case in ((16, 128, 16, 3), (16, 128, 8, 5), (16, 64, 3, 5), (24, 96, 6, 2), (16, 256, 4, 1), (16, 32, 8, 0)):
+    tws.test_window_equals_unbounded_call_on_a_busy_gpu(*case)
+    n_cases += 1
 print(f"debug-bounds ok: {n_cases} cases", flush=True)
