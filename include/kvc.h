@@ -223,7 +223,7 @@ int kvc_prefetch_layers(kvc_ctx* ctx, void* d_l2, int32_t* d_tags, int32_t* d_fe
  *             may poll or wait for; a layer that needed no transfer is stamped when the window opens.
  *             [n_layers] = clock when the window opened, [n_layers+1] = transfers issued by the call,
  *             [n_layers+2] = transfer engines the call put to work: at most omega, at most one per transfer
- *             issued, at most what the GPU holds at once (1,024 to 2,048 on MI355X, by page shape), and
+ *             issued, at most what the GPU holds at once (1,024 to 1,792 on MI355X, by page shape), and
  *             beyond 256 only while each engine has at least eight transfers; no more blocks than that are
  *             ever in flight,
  *             [n_layers+3] = 0 until every transfer of the call has completed, then that clock value.
