@@ -98,4 +98,11 @@ import test_gpu_window_scale as tws  # noqa: E402
 for case in ((16, 128, 16, 3), (16, 128, 8, 5), (16, 64, 3, 5), (24, 96, 6, 2), (16, 256, 4, 1), (16, 32, 8, 0)):
     tws.test_window_equals_unbounded_call_on_a_busy_gpu(*case)
     n_cases += 1
+# encoder workgroups of several pages, with skipped and refused ids and a pool that fills
+import test_gpu_encoder_batches as teb  # noqa: E402
+
+for N, d, scheme, pages in ((16, 32, 3, 2049), (16, 64, "mixed", 2100), (16, 96, 3, 2049), (16, 128, 3, 2049), (16, 128, 3, 16400), (16, 128, 5, 16400),
+                            (16, 128, "mixed", 2100), (13, 160, 3, 2100), (21, 192, "mixed", 2049), (17, 224, 1, 2049), (16, 256, 3, 2049)):
+    teb.test_ids_modes_and_a_full_pool(N, d, scheme, pages, 3)
+    n_cases += 1
 print(f"debug-bounds ok: {n_cases} cases", flush=True)
