@@ -130,7 +130,16 @@ def test_every_kernel_instantiation_under_full_occupancy(N, d, scheme):
     """Instantiations of the kernels for exact page shapes (the compile-time scheme, the run-time scheme and
     the per-block scheme) and for pages with a short last pass, on enough pages that several workgroups share
     every compute unit, three launches each, every page compared with the oracle bit for bit."""
-    n = 24576
+    _full_occupancy(N, d, scheme, 24576)
+
+
+# four-pass pages with the mode fixed have an encoder of their own for calls of up to 16,384 pages
+@pytest.mark.parametrize("N,d,scheme", [(16, 128, 3), (16, 128, 5), (32, 64, 3), (8, 256, 3)])
+def test_middle_calls_of_four_pass_pages_under_full_occupancy(N, d, scheme):
+    _full_occupancy(N, d, scheme, 16384)
+
+
+def _full_occupancy(N, d, scheme, n):
     rng = np.random.default_rng(7000 + 31 * N + d + (9 if scheme == "mixed" else scheme) + 100003 * int(os.environ.get("KVC_DIFF_SEED", "0")))
     x = _soak_pages(rng, n, N, d)
     xt = torch.from_numpy(x.reshape(-1, 1, N, d)).to(DEV)
