@@ -13,8 +13,9 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 # one to eight passes, whole and short last passes; the middle (up to 16,384 pages) and the large launch of four-pass
-# pages with the mode fixed
+# pages with the mode fixed; both deals of the tasks of whole eight-pass pages (in order up to 32,768 pages)
 CASES = [(N, d, scheme, pages) for (N, d) in ((16, 32), (16, 64), (16, 96), (16, 128), (16, 160), (16, 192), (16, 224), (16, 256)) for scheme, pages in ((3, 2049), ("mixed", 2100))] + \
+        [(16, 256, 3, 32770), (16, 256, 4, 32770), (32, 128, "mixed", 32770)] + \
         [(16, 64, 5, 2300), (16, 256, 5, 2049), (16, 128, 5, 2049), (16, 128, 3, 16380), (16, 128, 3, 16400), (16, 128, 5, 16400)] + \
         [(7, 32, 3, 2049), (13, 64, "mixed", 2100), (9, 128, 2, 2100), (15, 96, 4, 2049), (13, 160, 3, 2100), (21, 192, "mixed", 2049), (17, 224, 1, 2049), (15, 256, 3, 2100)]
 
