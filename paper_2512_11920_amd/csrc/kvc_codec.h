@@ -1196,15 +1196,19 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
 
 // Launch shapes by page size (NP passes of 1 KB): waves per workgroup, pages per wave.
 constexpr int kCodecWaves = 4;
-// Transfer engines of the prefetch window.  Up to as many engines as the device holds of the wide kind (512 at 16 x 128)
-// each has 16 waves; beyond that engines of four waves, with several pages of a block per wave in flight, of which
-// two to four times as many are resident.  Two prefetch steps of 4,370 blocks of 16 pages of 16 x 128, us, four-wave
-// engines / wide engines: 64 engines 1081 / 571, 256 engines 399 / 229.
+// Transfer engines of the prefetch window.  Calls of at most as many engines (omega, or the slots of the call) as the
+// device holds of the wide kind -- one per compute unit, 256, at 16 x 128; two where the kernel fits 64 vector registers --
+// have engines of 16 waves; the others have engines of four waves, with several pages of a block per wave in flight, of
+// which four to seven fit a compute unit.  Two prefetch steps of 2,048 blocks of 16 pages of 16 x 128, us, four-wave
+// engines / wide engines, all else alike: 64 engines 498 / 320, 256 engines 160 / 121; blocks of two pages, where most
+// waves of a wide engine have none, 735 / 748 with 64 engines.  (The choice is made before the transfers are counted: an
+// omega above the wide kind's number with few transfers runs 256 narrow engines, 161 us in the first example.)
 constexpr int kWideWaves = 16;
 constexpr int window_side(int np) { return np <= 4 ? 4 : 2; }
 // A small call (a decode step's offload of a few blocks) is latency: one page per wave (more only for
 // the smallest pages), so the pages are encoded side by side instead of several in a row.  The cursor
-// then takes an atomic per four pages, which only a large call would feel.
+// then takes an atomic per four pages, 13 ns each: little at 256 pages of 16 x 128 (0.8 of 6.5 us), but 3.3 of 8.8 us at
+// 1,024 and 6.7 of 12 at 2,048.
 constexpr int enc_ppw_small(int np) { return np == 1 ? 4 : np == 2 ? 2 : 1; }
 // Pages per decoder wave: a page of one or two passes is too small to cover its own memory chain, so a wave
 // takes the pages that share a header scan, resolved one per lane.  Measured (half a million pages, us): one
