@@ -23,6 +23,7 @@ namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef float float2v __attribute__((ext_vector_type(2)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
 // Non-temporal hints for the page-sized streams (encoder input, decoder output): measured 4-7 % faster.
@@ -706,90 +707,101 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
 // ---------------------------------------------------------------------------------- decode
 
 // dequantize: x = fp16(fp32(q) * s).  b = (q + 128) mod 256 sits in the low byte of pb; the fused
-// b*s - 128*s rounds q*s once to binary32 (128*s is exact), then one rounding to FP16.
+// b*s - 128*s rounds q*s once to binary32 (128*s is exact), then one rounding to FP16, for two values at once.  (The
+// compiler would rather fuse the product with the conversion, v_fma_mixlo/hi_f16; those issue once in 8.5 cycles each,
+// v_fma_f32 in 2.6 and v_cvt_pk_f16_f32, which converts two, in 4.3: 17 against 9.6 cycles per pair.)
 __device__ __forceinline__ uint4 dequant8_biased(const uint32_t pb[8], float s, float neg128s) {
     half2v h[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        h[k].x = (_Float16)__builtin_fmaf((float)(pb[2 * k] & 0xFFu), s, neg128s);
-        h[k].y = (_Float16)__builtin_fmaf((float)(pb[2 * k + 1] & 0xFFu), s, neg128s);
+        float2v f = {__builtin_fmaf((float)(pb[2 * k] & 0xFFu), s, neg128s), __builtin_fmaf((float)(pb[2 * k + 1] & 0xFFu), s, neg128s)};
+        asm("" : "+v"(f.x), "+v"(f.y));
+        h[k] = __builtin_convertvector(f, half2v);
     }
     return make_uint4(__builtin_bit_cast(uint32_t, h[0]), __builtin_bit_cast(uint32_t, h[1]),
                       __builtin_bit_cast(uint32_t, h[2]), __builtin_bit_cast(uint32_t, h[3]));
 }
 
-// Stores of the decoder's output at base + off (wave-uniform) + lane_off.  Plain launches stream it out; under the
-// prefetch window (WT) the stores write through the XCD's L2 (device scope), so that a block is published by
-// waiting for its stores, without a write-back of the whole L2.
-template <bool WT>
+// Stores of the decoder's output at base + off (wave-uniform) + lane_off.  They write through the XCD's L2 (device scope)
+// and are not kept there.  Under the prefetch window a block is thereby published by waiting for its stores, without a
+// write-back of the whole L2; and every launch is faster so: written back in the L2's own time instead, the pages that
+// 8,000 waves are writing at once reach the memory in no order (a million pages of 16 x 128, us: 1025 -> 1013, half a
+// million of mode 5 515 -> 503, 262,144 raw pages 381 -> 371; without the streaming hint 1063).
 __device__ __forceinline__ void store_out(char* base, int64_t off, uint32_t lane_off, const uint4& v) {
-    if constexpr (WT) {
-        uint4v w;
-        w.x = v.x; w.y = v.y; w.z = v.z; w.w = v.w;
-        // aux: 16 = sc1, device scope; 2 = nt.  The uniform offset goes into the resource and not into the store's scalar
-        // offset: a store of more than 64 bits needs a wait state before its data registers are written again, and
-        // with a scalar offset the compiler leaves it out, taking the store to be safe -- on this chip it is not (one
-        // page in a hundred came out with the first dword of some lanes replaced by what was computed next).
-        __builtin_amdgcn_raw_buffer_store_b128(w, __builtin_amdgcn_make_buffer_rsrc(base + off, 0, -1, 0x00020000), (int)lane_off, 0, 16 | 2);
-    } else {
-        store_stream(reinterpret_cast<uint4*>(base + off + lane_off), v);
-    }
+    uint4v w;
+    w.x = v.x; w.y = v.y; w.z = v.z; w.w = v.w;
+    // aux: 16 = sc1, device scope; 2 = nt.  The uniform offset goes into the resource and not into the store's scalar
+    // offset: a store of more than 64 bits needs a wait state before its data registers are written again, and
+    // with a scalar offset the compiler leaves it out, taking the store to be safe -- on this chip it is not (one
+    // page in a hundred came out with the first dword of some lanes replaced by what was computed next).
+    __builtin_amdgcn_raw_buffer_store_b128(w, __builtin_amdgcn_make_buffer_rsrc(base + off, 0, -1, 0x00020000), (int)lane_off, 0, 16 | 2);
 }
-template <bool WT>
 __device__ __forceinline__ void zero_out(uint16_t* dst, const Geometry& g) {
-    if constexpr (WT) {
-        for (int o = lane_id(); o < (g.E >> 3); o += 64)
-            store_out<true>(reinterpret_cast<char*>(dst), 0, (uint32_t)elem_off(g, o * 8) * 2u, make_uint4(0u, 0u, 0u, 0u));
-    } else {
-        zero_page(dst, g);
-    }
+    for (int o = lane_id(); o < (g.E >> 3); o += 64)
+        store_out(reinterpret_cast<char*>(dst), 0, (uint32_t)elem_off(g, o * 8) * 2u, make_uint4(0u, 0u, 0u, 0u));
 }
 
-// This lane's 8 values of its quad's packet in group set p, read from the staged payload.  gi: the packet's
-// body offset and code, as the header scan left them.  A value's zig-zag code u comes back in two parts,
-// sg = 0 or -1 from its lowest bit, and hb: u >> 1 (delta = hb ^ sg), or u itself if TWICE (2 delta = hb ^ sg;
-// the field then begins at the value's own bit, which saves the four offsets by one).  SPECIAL: the page has
-// zero-run or run packets (few pages do, and the others are decoded without the tests for them).
-template <int NP, bool TWICE, bool SPECIAL>
-__device__ __forceinline__ void unpack8(const DecodeArgs& a, const uint32_t* stage, uint32_t gi, uint32_t hdr,
-                                        uint32_t (&hb)[8], int (&sg)[8]) {
+// What the header scan leaves for a packet group: where its body begins in the slot, its code c, and the byte mask that
+// keeps the upper c - 1 bits of a c-bit field.
+struct GroupInfo {
+    uint32_t at;    // body offset << 12 | c << 8 | 4 (c - 1) mod 32
+    uint32_t high;  // 2^(c-1) - 1 in every byte
+};
+__device__ __forceinline__ GroupInfo group_pack(uint32_t off, uint32_t c) {
+    GroupInfo g;
+    g.at = (off << 12) | (c << 8) | (((c - 1u) << 2) & 31u);
+    g.high = 0x01010101u * ((1u << ((c - 1u) & 7u)) - 1u);
+    return g;
+}
+
+// (m & a) | (~m & b), as the instruction of this chip that takes half the time of a bit-field insert
+__device__ __forceinline__ uint32_t select_bits(uint32_t m, uint32_t a, uint32_t b) { return __builtin_amdgcn_bitop3_b32(m, a, b, 0xCA); }
+
+// Four c-bit fields (the low 4c bits of x, 1 <= c <= 8) to the four bytes of a dword, each undone from its zig-zag code
+// and biased by 128 (mod 256).  sh = 8 - c.  Four values at a time, because the decoder of a whole cache keeps the
+// vector units busy two thirds of its time and a transfer engine of the prefetch window waits for them: a field, its
+// sign and the sum took 2.9 instructions of 4.4 cycles per value one by one, these take 2 of mostly 2.5.
+__device__ __forceinline__ uint32_t fields_to_bytes(uint32_t x, uint32_t sh, uint32_t high) {
+    x = select_bits(0x0000FFFFu, x, x << (sh + sh));  // fields 2 and 3 to the upper half
+    x = select_bits(0x00FF00FFu, x, x << sh);         // fields 1 and 3 to the odd bytes (a byte's bits above c are whatever followed)
+    const uint32_t sign = 0x80808080u - (x & 0x01010101u);  // per byte 0x80, or 0x7F from an odd code: its sign, with the bias
+    return ((x >> 1) & high) ^ sign;
+}
+
+// This lane's 8 values of its quad's packet in group set p, read from the staged payload and undone from their zig-zag
+// codes: value k is byte k of the two dwords, plus 128 (mod 256).  SPECIAL: the page has zero-run or run packets (few
+// pages do, and the others are decoded without the tests for them).
+template <int NP, bool SPECIAL>
+__device__ __forceinline__ void unpack8(const DecodeArgs& a, const uint32_t* stage, const GroupInfo& g, uint32_t hdr, uint32_t (&w)[2]) {
     (void)hdr;
-    (void)a;  // only the bounds-checking build reads it
+    (void)a;  // only the bounds-checking build reads them
     const uint32_t qi = (uint32_t)lane_id() & 3u;
-    uint32_t c = gi & 15u;
-    const uint32_t goff = gi >> 4;
+    uint32_t c = (g.at >> 8) & 15u;
+    const uint32_t goff = g.at >> 12;
+    uint32_t high = g.high;
     uint32_t B = goff + __umul24(qi, c);
     if (SPECIAL && c == 9) B = goff;
-    const uint32_t sh = (B & 3u) << 3;
     const uint32_t* p0 = stage + (B >> 2);
     KVC_CHECK(a.st, (B >> 2) + 2 < (uint32_t)Slot<NP>::kWords && B >= hdr);  // bodies start after the header bytes
     const uint32_t d0 = p0[0], d1 = p0[1], d2 = p0[2];
-    uint32_t lo = __builtin_amdgcn_alignbit(d1, d0, sh);
-    uint32_t hi = __builtin_amdgcn_alignbit(d2, d1, sh);
+    uint32_t lo = __builtin_amdgcn_alignbyte(d1, d0, B);  // (a byte shift is taken mod 4, a bit shift mod 32)
+    const uint32_t up = __builtin_amdgcn_alignbyte(d2, d1, B);
+    // values 0..3 are bits 0 .. 4c - 1 of (up : lo), values 4..7 the 4c bits after those: shifted down by 4, then by 4c - 4
+    uint32_t hi = __builtin_amdgcn_alignbit(up >> 4, __builtin_amdgcn_alignbit(up, lo, 4u), g.at);
     if (SPECIAL) {
         if (c == 9) {  // run packet: the body byte, 32 times
             lo = __builtin_amdgcn_perm(lo, lo, 0u);
             hi = lo;
             c = 8;
+            high = 0x7F7F7F7Fu;
         } else if (c == 0) {  // zero-run packet
             lo = 0;
             hi = 0;
-            c = 1;
         }
     }
-    const uint32_t mid = shr_nibbles(lo, hi, c);  // values 4..7 start at bit 4c
-    // value k sits at bits [k*c, k*c + c)
-    constexpr uint32_t kLow = TWICE ? 0u : 1u;
-    const uint32_t w = c - kLow;
-    const uint32_t o1 = c, o2 = c << 1, o3 = o2 + c;
-    hb[0] = __builtin_amdgcn_ubfe(lo, kLow, w), sg[0] = __builtin_amdgcn_sbfe((int)lo, 0u, 1u);
-    hb[1] = __builtin_amdgcn_ubfe(lo, o1 + kLow, w), sg[1] = __builtin_amdgcn_sbfe((int)lo, o1, 1u);
-    hb[2] = __builtin_amdgcn_ubfe(lo, o2 + kLow, w), sg[2] = __builtin_amdgcn_sbfe((int)lo, o2, 1u);
-    hb[3] = __builtin_amdgcn_ubfe(lo, o3 + kLow, w), sg[3] = __builtin_amdgcn_sbfe((int)lo, o3, 1u);
-    hb[4] = __builtin_amdgcn_ubfe(mid, kLow, w), sg[4] = __builtin_amdgcn_sbfe((int)mid, 0u, 1u);
-    hb[5] = __builtin_amdgcn_ubfe(mid, o1 + kLow, w), sg[5] = __builtin_amdgcn_sbfe((int)mid, o1, 1u);
-    hb[6] = __builtin_amdgcn_ubfe(mid, o2 + kLow, w), sg[6] = __builtin_amdgcn_sbfe((int)mid, o2, 1u);
-    hb[7] = __builtin_amdgcn_ubfe(mid, o3 + kLow, w), sg[7] = __builtin_amdgcn_sbfe((int)mid, o3, 1u);
+    const uint32_t sh = 8u - c;
+    w[0] = fields_to_bytes(lo, sh, high);
+    w[1] = fields_to_bytes(hi, sh, high);
 }
 
 template <class P>
@@ -871,12 +883,12 @@ struct HeaderDeal {
     static constexpr int kRounds = (kG + 63) / 64;       // scans per page
 };
 
-// Scan the headers of SCAN <= HeaderDeal<P>::kPages pages, those of slots i0 .. and lanes first + i0 ..: info = body offset << 4 | code of
-// the lane's group (one per round).  `bad` / `special`: ballots of the lanes whose page fails validation, and of
+// Scan the headers of SCAN <= HeaderDeal<P>::kPages pages, those of slots i0 .. and lanes first + i0 ..: info = what the
+// lane's group needs to be read (one per round).  `bad` / `special`: ballots of the lanes whose page fails validation, and of
 // the lanes whose group is a zero-run or run packet.
 template <class P, bool UNIFORM, int SCAN>
 __device__ __forceinline__ void dec_headers(const Extent& x, const DecLanes& L, int first, int i0, const uint32_t (*slots)[Slot<P::kPasses>::kWords],
-                                            uint32_t (&info)[HeaderDeal<P>::kRounds], uint64_t& bad, uint64_t& special) {
+                                            GroupInfo (&info)[HeaderDeal<P>::kRounds], uint64_t& bad, uint64_t& special) {
     using H = HeaderDeal<P>;
     constexpr int kG = P::kGroups;
     const int lane = lane_id();
@@ -900,7 +912,7 @@ __device__ __forceinline__ void dec_headers(const Extent& x, const DecLanes& L, 
             incl = row16_incl_scan_dpp(size);
             if (H::kSeg == 32) incl += dpp<0x142, 0xA>(0, incl);  // odd rows add the row before
         }
-        info[r] = ((total + incl - size) << 4) | c;
+        info[r] = group_pack(total + incl - size, c);
         wrong = wrong || c > 9 || (mode == KVC_MODE_DELTA && (c == 0 || c == 9));
         rare = rare || c == 0 || c == 9;
         if (r + 1 < H::kRounds)
@@ -914,7 +926,7 @@ __device__ __forceinline__ void dec_headers(const Extent& x, const DecLanes& L, 
 }
 
 // Decode an INT8 payload at src (the staged copy, or the pool itself) into the page at dst_b.
-template <class P, bool WT>
+template <class P>
 __device__ __forceinline__ void dec_int8(const DecodeArgs& a, const Extent& x, const LanePos& lp, float s, char* dst_b, const uint2* src) {
 #pragma unroll
     for (int p = 0; p < P::kPasses; ++p) {
@@ -927,22 +939,25 @@ __device__ __forceinline__ void dec_int8(const DecodeArgs& a, const Extent& x, c
             pb[k] = lo >> (8 * k);
             pb[4 + k] = hi >> (8 * k);
         }
-        store_out<WT>(dst_b, pass_base_off<P, false>(a.g, p), pass_lane_off<P, false>(a.g, lp, p), dequant8_biased(pb, s, -128.0f * s));
+        store_out(dst_b, pass_base_off<P, false>(a.g, p), pass_lane_off<P, false>(a.g, lp, p), dequant8_biased(pb, s, -128.0f * s));
     }
 }
 
 // Decode one staged packed payload into the page at dst_b.  seg0: the first lane of the page's part of `info`.
 // SPECIAL: the page may hold zero-run and run packets.
-template <class P, bool SPECIAL, bool WT>
+template <class P, bool SPECIAL>
 __device__ __forceinline__ void dec_page(const DecodeArgs& a, const Extent& x, const LanePos& lp, uint32_t mode, float s, char* dst_b, const uint32_t* stage,
-                                         const uint32_t (&info)[HeaderDeal<P>::kRounds], int seg0) {
+                                         const GroupInfo (&info)[HeaderDeal<P>::kRounds], int seg0) {
     constexpr int NP = P::kPasses;
     const int lane = lane_id();
     const float neg128s = -128.0f * s;
     // info of the group this lane's quad unpacks in group set p: lane seg0 + (16 p + quad) mod 64 of its scan
     auto group_info = [&](int p) {
         const uint32_t from = (uint32_t)(seg0 + (p * 16) % 64 + (lane >> 2)) << 2;
-        return (uint32_t)__builtin_amdgcn_ds_bpermute((int)from, (int)info[(p * 16) / 64]);
+        GroupInfo g;
+        g.at = (uint32_t)__builtin_amdgcn_ds_bpermute((int)from, (int)info[(p * 16) / 64].at);
+        g.high = (uint32_t)__builtin_amdgcn_ds_bpermute((int)from, (int)info[(p * 16) / 64].high);
+        return g;
     };
     if constexpr (P::kChan && P::kD == 64) {
         if (mode == KVC_MODE_CHAN) {
@@ -955,16 +970,10 @@ __device__ __forceinline__ void dec_page(const DecodeArgs& a, const Extent& x, c
             uint32_t pair_lo[2], pair_hi[2];  // per set: the dwords of pairs 2s and 2s + 1 for this lane's tokens
 #pragma unroll
             for (int sset = 0; sset < 2; ++sset) {
-                uint32_t hb[8];
-                int sg[8];
-                unpack8<NP, false, SPECIAL>(a, stage, group_info(sset), x.hdr, hb, sg);
-                uint32_t b[8];
-#pragma unroll
-                for (int m = 0; m < 8; ++m) b[m] = (hb[m] ^ (uint32_t)sg[m]) + 128u;
-                const uint32_t w0 = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u), __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), 0x05040100u);
-                const uint32_t w1 = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[7], b[6], 0x0c0c0400u), __builtin_amdgcn_perm(b[5], b[4], 0x0c0c0400u), 0x05040100u);
-                const uint32_t own = hi ? w1 : w0;  // values 4h .. 4h + 3: this lane's tokens
-                const uint32_t got = (uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ 32) << 2, (int)(hi ? w0 : w1));
+                uint32_t w[2];
+                unpack8<NP, SPECIAL>(a, stage, group_info(sset), x.hdr, w);
+                const uint32_t own = hi ? w[1] : w[0];  // values 4h .. 4h + 3: this lane's tokens
+                const uint32_t got = (uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ 32) << 2, (int)(hi ? w[0] : w[1]));
                 pair_lo[sset] = hi ? got : own;  // pair 2s: packed by the lower half's lane
                 pair_hi[sset] = hi ? own : got;  // pair 2s + 1: packed by the upper half's lane
             }
@@ -974,7 +983,7 @@ __device__ __forceinline__ void dec_page(const DecodeArgs& a, const Extent& x, c
 #pragma unroll
                 for (int k = 0; k < 8; ++k)  // channel k = pair k / 2 = 2 (k / 4) + (k / 2) % 2, value 2p + k % 2 of the dword
                     pb[k] = (((k >> 1) & 1) ? pair_hi[k >> 2] : pair_lo[k >> 2]) >> (8 * (2 * p + (k & 1)));
-                store_out<WT>(dst_b, pass_base_off<P, true>(a.g, p), pass_lane_off<P, true>(a.g, lp, p), dequant8_biased(pb, s, neg128s));
+                store_out(dst_b, pass_base_off<P, true>(a.g, p), pass_lane_off<P, true>(a.g, lp, p), dequant8_biased(pb, s, neg128s));
             }
             return;
         }
@@ -988,16 +997,7 @@ __device__ __forceinline__ void dec_page(const DecodeArgs& a, const Extent& x, c
             for (int h = 0; h < NP / 4; ++h) {
                 uint32_t packed[4][2];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    uint32_t hb[8];
-                    int sg[8];
-                    unpack8<NP, false, SPECIAL>(a, stage, group_info(4 * h + j), x.hdr, hb, sg);
-                    uint32_t b[8];
-#pragma unroll
-                    for (int m = 0; m < 8; ++m) b[m] = (hb[m] ^ (uint32_t)sg[m]) + 128u;
-                    packed[j][0] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u), __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), 0x05040100u);
-                    packed[j][1] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[7], b[6], 0x0c0c0400u), __builtin_amdgcn_perm(b[5], b[4], 0x0c0c0400u), 0x05040100u);
-                }
+                for (int j = 0; j < 4; ++j) unpack8<NP, SPECIAL>(a, stage, group_info(4 * h + j), x.hdr, packed[j]);
 #pragma unroll
                 for (int p = 0; p < 4; ++p) {
                     uint32_t pb[8];
@@ -1006,7 +1006,7 @@ __device__ __forceinline__ void dec_page(const DecodeArgs& a, const Extent& x, c
                         const int m = 2 * p + (k & 1);  // value index inside group set k / 2
                         pb[k] = packed[k >> 1][m >> 2] >> (8 * (m & 3));
                     }
-                    store_out<WT>(dst_b, pass_base_off<P, true>(a.g, 4 * h + p), pass_lane_off<P, true>(a.g, lp, 4 * h + p), dequant8_biased(pb, s, neg128s));
+                    store_out(dst_b, pass_base_off<P, true>(a.g, 4 * h + p), pass_lane_off<P, true>(a.g, lp, 4 * h + p), dequant8_biased(pb, s, neg128s));
                 }
             }
             return;
@@ -1016,36 +1016,38 @@ __device__ __forceinline__ void dec_page(const DecodeArgs& a, const Extent& x, c
     uint32_t carry = 0;  // what a row that continues from the pass before had summed up there
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        uint32_t hb[8];  // a value's zig-zag code
-        int sg[8];       // 0 or -1 from its sign flag
-        unpack8<NP, true, SPECIAL>(a, stage, group_info(p), x.hdr, hb, sg);
-        uint32_t pb[8];  // biased codes in byte 1: ((2 q) << 7) + (128 << 8)
+        uint32_t w[2];
+        unpack8<NP, SPECIAL>(a, stage, group_info(p), x.hdr, w);
+        uint32_t pb[8];  // codes + 128 in byte 0
         if (no_delta) {  // no delta step was taken: the fields are the codes
 #pragma unroll
-            for (int k = 0; k < 8; ++k) pb[k] = ((hb[k] ^ (uint32_t)sg[k]) << 7) + 0x8000u;
+            for (int k = 0; k < 8; ++k) pb[k] = w[k >> 2] >> (8 * (k & 3));
         } else {
-            // prefix sum along the channel index, of twice the deltas: in the lane first (each step is one
-            // xor-add), then the lanes of the token row before this one
-            uint32_t pre[8];
-            pre[0] = hb[0] ^ (uint32_t)sg[0];
-#pragma unroll
-            for (int k = 1; k < 8; ++k) pre[k] = (hb[k] ^ (uint32_t)sg[k]) + pre[k - 1];
-            const uint32_t tot = pre[7];
+            // prefix sum along the channel index (mod 256): the lanes of the token row before this one, then in the
+            // lane.  Every byte carries a bias of 128, so that 128 times the number of bytes summed is in the sum:
+            // nothing for a whole lane, and 128 too many at every odd k after adding the 128 of the result.
+            const uint32_t t0 = __builtin_amdgcn_udot4(w[0], 0x01010101u, 0u, false);
+            const uint32_t tot = __builtin_amdgcn_udot4(w[1], 0x01010101u, t0, false);
             const uint32_t incl = row_incl_scan<P>(lp, p, tot, carry);
             if (!P::kAligned) carry = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-            const uint32_t base = ((incl - tot) << 7) + 0x8000u;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) pb[k] = (pre[k] << 7) + base;
+            const uint32_t even = incl - tot, odd = even + 128u;
+            pb[0] = even + w[0];
+            pb[1] = __builtin_amdgcn_udot4(w[0], 0x00000101u, odd, false);
+            pb[2] = __builtin_amdgcn_udot4(w[0], 0x00010101u, even, false);
+            pb[3] = odd + t0;
+            const uint32_t even4 = even + t0;
+            pb[4] = even4 + w[1];
+            pb[5] = __builtin_amdgcn_udot4(w[1], 0x00000101u, pb[3], false);
+            pb[6] = __builtin_amdgcn_udot4(w[1], 0x00010101u, even4, false);
+            pb[7] = incl + 128u;
         }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) pb[k] >>= 8;
         if (lane_live<P>(x, p))
-            store_out<WT>(dst_b, pass_base_off<P, false>(a.g, p), pass_lane_off<P, false>(a.g, lp, p), dequant8_biased(pb, s, neg128s));
+            store_out(dst_b, pass_base_off<P, false>(a.g, p), pass_lane_off<P, false>(a.g, lp, p), dequant8_biased(pb, s, neg128s));
     }
 }
 
 // Decode the pages whose payloads dec_fetch has begun to load.
-template <class P, int PPW, bool UNIFORM, bool WT>
+template <class P, int PPW, bool UNIFORM>
 __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L, int first, const LanePos& lp, uint32_t (*slots)[Slot<P::kPasses>::kWords]) {
     using H = HeaderDeal<P>;
     static_assert(PPW % H::kPages == 0 || PPW == 1, "a header scan covers whole pages of the batch");
@@ -1054,7 +1056,7 @@ __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L
     dec_fetched();
 #pragma unroll 1
     for (int i0 = 0; i0 < PPW; i0 += kScan) {
-        uint32_t info[H::kRounds] = {};
+        GroupInfo info[H::kRounds] = {};
         uint64_t bad = 0, special = 0;
         // (a scan for one page is left out where the page has no header: 0.3 us of a small call of INT8 pages)
         const uint32_t meta0 = of_lane<UNIFORM>(L.meta, first + i0);
@@ -1070,7 +1072,7 @@ __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L
             constexpr uint64_t kSegMask = H::kSeg == 64 ? ~0ull : (1ull << (H::kSeg & 63)) - 1;
             const bool bad_header = ((bad >> (j * H::kSeg)) & kSegMask) != 0;
             if (kind == kDecZero || bad_header) {
-                zero_out<WT>(dst, a.g);
+                zero_out(dst, a.g);
                 if (bad_header && lane_id() == 0) atomicOr(&a.st->status, KVC_ST_CORRUPT);
                 continue;
             }
@@ -1083,10 +1085,7 @@ __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L
                 for (int p = 0; p < P::kPasses; ++p)
                     if (lane_live<P>(x, p)) {
                         const uint4 v = src[p * 64 + lane_id()];
-                        if (WT)
-                            store_out<true>(dst_b, pass_base_off<P, false>(a.g, p), pass_lane_off<P, false>(a.g, lp, p), v);
-                        else
-                            *reinterpret_cast<uint4*>(dst_b + pass_base_off<P, false>(a.g, p) + pass_lane_off<P, false>(a.g, lp, p)) = v;
+                        store_out(dst_b, pass_base_off<P, false>(a.g, p), pass_lane_off<P, false>(a.g, lp, p), v);
                     }
                 continue;
             }
@@ -1094,15 +1093,15 @@ __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L
             const float s = __uint_as_float(of_lane<UNIFORM>(__float_as_uint(L.s), first + i));
             if (mode == KVC_MODE_INT8) {
                 if constexpr (kStageInt8<PPW>)
-                    dec_int8<P, WT>(a, x, lp, s, dst_b, reinterpret_cast<const uint2*>(slots[i]));
+                    dec_int8<P>(a, x, lp, s, dst_b, reinterpret_cast<const uint2*>(slots[i]));
                 else
-                    dec_int8<P, WT>(a, x, lp, s, dst_b, reinterpret_cast<const uint2*>(a.pool + of_lane<UNIFORM>(L.off, first + i)));
+                    dec_int8<P>(a, x, lp, s, dst_b, reinterpret_cast<const uint2*>(a.pool + of_lane<UNIFORM>(L.off, first + i)));
                 continue;
             }
             if (((special >> (j * H::kSeg)) & kSegMask) != 0)
-                dec_page<P, true, WT>(a, x, lp, mode, s, dst_b, slots[i], info, j * H::kSeg);
+                dec_page<P, true>(a, x, lp, mode, s, dst_b, slots[i], info, j * H::kSeg);
             else
-                dec_page<P, false, WT>(a, x, lp, mode, s, dst_b, slots[i], info, j * H::kSeg);
+                dec_page<P, false>(a, x, lp, mode, s, dst_b, slots[i], info, j * H::kSeg);
         }
     }
 }
@@ -1120,7 +1119,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_decompress(DecodeArgs a) {
     // (a batch of one page is resolved on the scalar unit: every lane has the same task)
     const DecLanes L = dec_open<P>(a, PPW == 1 ? dec_locate(a, t0 < a.n_pages, (uint32_t)t0) : dec_locate(a, lane < PPW && t0 + lane < a.n_pages, (uint32_t)t0 + (uint32_t)lane));
     dec_fetch<P, PPW, PPW == 1>(a, L, 0, s_stage[wave]);
-    dec_batch<P, PPW, PPW == 1, false>(a, L, 0, lp, s_stage[wave]);
+    dec_batch<P, PPW, PPW == 1>(a, L, 0, lp, s_stage[wave]);
 }
 
 // Transfer engines of the prefetch window (Algorithm 1: at most Omega_max transfers outstanding): a
@@ -1182,7 +1181,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
             KVC_CHECK(a.st, *(volatile uint32_t*)&s_done >= blocks * WAVES);
 #endif
             dec_fetch<P, SIDE, false>(a, L, t % 64, s_stage[wave]);
-            dec_batch<P, SIDE, false, true>(a, L, t % 64, lp, s_stage[wave]);
+            dec_batch<P, SIDE, false>(a, L, t % 64, lp, s_stage[wave]);
             wave_sync();
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the slots have been read before they are filled again
         }

@@ -288,11 +288,6 @@ __device__ __forceinline__ DecPlace dec_locate(const DecodeArgs& a, bool live, u
     return r;
 }
 
-__device__ __forceinline__ void zero_page(uint16_t* dst, const Geometry& g) {
-    for (int o = lane_id(); o < (g.E >> 3); o += 64)
-        *reinterpret_cast<uint4*>(dst + elem_off(g, o * 8)) = make_uint4(0, 0, 0, 0);
-}
-
 // ---- outstanding-request window (Algorithm 1, WaitCompletion over at most Omega_max transfers) ----
 // A workgroup is one transfer engine: it takes the next entry of the issue queue, decodes that block,
 // reports completion and takes the next.  The grid has at most Omega workgroups, so never more than
