@@ -386,9 +386,10 @@ static int prefetch_impl(kvc_ctx* ctx, void* d_l2, int32_t* d_tags, int32_t* d_f
     w.n_layers_call = layer_end - layer_begin;
     w.n_layers = n_layers;
     w.omega = omega;
+    w.wide = ctx->wide_capacity > 0 && std::min<int64_t>(omega, n_now) <= ctx->wide_capacity ? 1 : 0;
     w.notify = d_notify;
     if (!hip_ok(kvc::launch_window_build(w, s))) return KVC_ERR_HIP;
-    return hip_ok(kvc::launch_decompress_window(a, w, omega, ctx->wide_capacity, s)) ? KVC_OK : KVC_ERR_HIP;
+    return hip_ok(kvc::launch_decompress_window(a, w, s)) ? KVC_OK : KVC_ERR_HIP;
 }
 
 int kvc_prefetch_layers(kvc_ctx* ctx, void* d_l2, int32_t* d_tags, int32_t* d_fetch, int32_t* d_loc,

@@ -809,17 +809,31 @@ __device__ __forceinline__ bool is_packed_mode(uint32_t mode) {
     return mode == KVC_MODE_DELTA || mode == KVC_MODE_RLE || mode == KVC_MODE_PACK || (P::kChan && mode == KVC_MODE_CHAN);
 }
 
-// Lane-wise second half of the resolution: fetch the descriptor, validate it against the pool and the page
-// geometry.  Sticky status bits of bad indices and descriptors are set here.
-template <class P>
-__device__ __forceinline__ DecLanes dec_open(const DecodeArgs& a, const DecPlace& t) {
-    const Extent x = page_extent<P>(a.g);
+// Lane-wise second half of the resolution: ask for the descriptor, and -- once it is there -- validate it against the pool
+// and the page geometry.  Sticky status bits of bad indices and descriptors are set in the second part.
+struct DecDue {
+    uint64_t di;                   // descriptor index
+    bool stray, wanted, readable;  // output block out of range; a page is due; its descriptor exists
+};
+__device__ __forceinline__ DecDue dec_due(const DecodeArgs& a, const DecPlace& t) {
     const bool placed = t.live && t.db >= 0 && t.db < a.n_out_blocks;
-    const uint64_t di = (uint64_t)t.pb * (uint64_t)a.g.ppb + t.pg;
-    const bool wanted = placed && (t.bad_index || t.pb >= 0);
-    const bool readable = wanted && !t.bad_index && di < a.n_desc;
+    DecDue r;
+    r.di = (uint64_t)t.pb * (uint64_t)a.g.ppb + t.pg;
+    r.stray = t.live && t.db >= 0 && !placed;
+    r.wanted = placed && (t.bad_index || t.pb >= 0);
+    r.readable = r.wanted && !t.bad_index && r.di < a.n_desc;
+    return r;
+}
+__device__ __forceinline__ uint4 dec_ask(const DecodeArgs& a, const DecPlace& t) {
+    const DecDue due = dec_due(a, t);
     uint4 dw = make_uint4(0u, 0u, 0u, 0u);
-    if (readable) dw = reinterpret_cast<const uint4*>(a.desc)[di];
+    if (due.readable) dw = reinterpret_cast<const uint4*>(a.desc)[due.di];
+    return dw;
+}
+template <class P>
+__device__ __forceinline__ DecLanes dec_check(const DecodeArgs& a, const DecPlace& t, const uint4& dw) {
+    const Extent x = page_extent<P>(a.g);
+    const DecDue due = dec_due(a, t);
     DecLanes r;
     r.db = t.db;
     r.pg = t.pg;
@@ -829,14 +843,18 @@ __device__ __forceinline__ DecLanes dec_open(const DecodeArgs& a, const DecPlace
     const bool raw = mode == KVC_MODE_RAW;
     const bool in_pool = (r.off & 15u) == 0 && (r.off >> 4) + n16 <= a.pool_units;
     const bool sized = raw ? n16 == x.E >> 3 : mode == KVC_MODE_INT8 ? n16 == x.E >> 4 : is_packed_mode<P>(mode) && n16 * 16u >= x.hdr && n16 < x.E >> 4;
-    const bool ok = readable && in_pool && sized;
-    const uint32_t kind = ok ? (raw ? kDecRaw : kDecPayload) : wanted ? kDecZero : kDecSkip;
+    const bool ok = due.readable && in_pool && sized;
+    const uint32_t kind = ok ? (raw ? kDecRaw : kDecPayload) : due.wanted ? kDecZero : kDecSkip;
     r.meta = n16 | (mode << 16) | (kind << 24);
     uint32_t st = 0;
-    if (t.live && ((t.db >= 0 && !placed) || (wanted && !readable))) st = KVC_ST_BAD_INDEX;
-    if (readable && !ok) st = KVC_ST_CORRUPT;
+    if (due.stray || (due.wanted && !due.readable)) st = KVC_ST_BAD_INDEX;
+    if (due.readable && !ok) st = KVC_ST_CORRUPT;
     if (st) atomicOr(&a.st->status, st);
     return r;
+}
+template <class P>
+__device__ __forceinline__ DecLanes dec_open(const DecodeArgs& a, const DecPlace& t) {
+    return dec_check<P>(a, t, dec_ask(a, t));
 }
 
 // 16 bytes from global memory straight to LDS: lane l's go to lds + 16 l (the destination is wave-uniform).
@@ -1046,14 +1064,13 @@ __device__ __forceinline__ void dec_page(const DecodeArgs& a, const Extent& x, c
     }
 }
 
-// Decode the pages whose payloads dec_fetch has begun to load.
+// Decode the pages whose payloads dec_fetch has loaded (dec_fetched: they are there).
 template <class P, int PPW, bool UNIFORM>
 __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L, int first, const LanePos& lp, uint32_t (*slots)[Slot<P::kPasses>::kWords]) {
     using H = HeaderDeal<P>;
     static_assert(PPW % H::kPages == 0 || PPW == 1, "a header scan covers whole pages of the batch");
     constexpr int kScan = PPW < H::kPages ? PPW : H::kPages;  // pages taken from one scan
     const Extent x = page_extent<P>(a.g);
-    dec_fetched();
 #pragma unroll 1
     for (int i0 = 0; i0 < PPW; i0 += kScan) {
         GroupInfo info[H::kRounds] = {};
@@ -1119,17 +1136,18 @@ __global__ __launch_bounds__(WAVES * 64) void k_decompress(DecodeArgs a) {
     // (a batch of one page is resolved on the scalar unit: every lane has the same task)
     const DecLanes L = dec_open<P>(a, PPW == 1 ? dec_locate(a, t0 < a.n_pages, (uint32_t)t0) : dec_locate(a, lane < PPW && t0 + lane < a.n_pages, (uint32_t)t0 + (uint32_t)lane));
     dec_fetch<P, PPW, PPW == 1>(a, L, 0, s_stage[wave]);
+    dec_fetched();
     dec_batch<P, PPW, PPW == 1>(a, L, 0, lp, s_stage[wave]);
 }
 
-// Transfer engines of the prefetch window (Algorithm 1: at most Omega_max transfers outstanding): a
-// workgroup takes the next issued blocks from the queue (a turn), its waves decode them one block after the other,
-// meeting after each -- no payload of a block is asked for before the last store of the engine's block before has
-// reached memory --, and the completion is reported before the next turn is taken.  An engine is latency, not
-// bandwidth: few of them are at work, each on one block.  So the waves share a block's pages as far as they go round (wave w takes pages w,
-// w + WAVES, ...; WIDE engines have a wave for each of 16 pages), and what can be known ahead is fetched for the
-// whole turn at once: queue entries, pool blocks and all descriptors, one page task per lane, before the first
-// payload.  SIDE: pages of one block that a wave has in flight together.
+// Narrow transfer engines of the prefetch window, for calls of many (Algorithm 1: at most Omega_max transfers
+// outstanding): a workgroup takes the next issued blocks from the queue (a turn), its waves decode them one block after
+// the other, meeting after each -- no payload of a block is asked for before the last store of the engine's block before
+// has reached memory --, and the completion is reported before the next turn is taken.  The waves share a block's pages
+// as far as they go round (wave w takes pages w, w + WAVES, ...), and queue entries, pool blocks and all descriptors of a
+// turn are fetched at once, one page task per lane, before its first payload.  (Looked ahead for as wide engines do it,
+// an engine is bound to blocks that an idle one could take: with 546 engines of eight blocks each, on compute units
+// that hold two or three, 216 us became 231.)  SIDE: pages of one block that a wave has in flight together.
 // (pages of up to four passes whose rows do not cross passes: held within 128 VGPRs, so that four waves fit a SIMD)
 template <class P, int WAVES, int SIDE>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::kPasses <= 4 && P::kAligned ? 4 : 1))) void k_decompress_window(DecodeArgs a, WindowArgs w) {
@@ -1181,6 +1199,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
             KVC_CHECK(a.st, *(volatile uint32_t*)&s_done >= blocks * WAVES);
 #endif
             dec_fetch<P, SIDE, false>(a, L, t % 64, s_stage[wave]);
+            dec_fetched();
             dec_batch<P, SIDE, false>(a, L, t % 64, lp, s_stage[wave]);
             wave_sync();
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the slots have been read before they are filled again
@@ -1190,6 +1209,175 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
         ++blocks;
 #endif
         turn = window_next<false>(w, s_turn, turn, s_q[0][0], mine, n_issued, chunk);
+    }
+}
+
+// Wide transfer engines of the prefetch window, for calls of as many as have a compute unit each, or fewer: a
+// workgroup takes issued blocks from the queue in runs, its waves decode them one block after the other,
+// meeting after each -- no payload of a block is asked for before the last store of the engine's block before has
+// reached memory.  An engine is latency, not bandwidth: few of them are at work, each on one block.  So the waves share a
+// block's pages as far as they go round (there is one for each of 16), and what leads to a payload -- ticket, queue entry, pool block, descriptors, four trips one after the other -- is
+// walked ahead of the payloads by one of the waves, the clerk, a trip per block: while block i is decoded it asks for
+// the descriptors of block i + 1 (a page per lane), the pool block of i + 2, the queue entry of i + 3 and, where its run
+// ends, the next run.  It also keeps the books.  (Done by every wave, the few hundred instructions of it cost an engine
+// half a microsecond per block; done for a whole run when the run before had ended, a tenth of the time of 256 engines
+// went into the four trips.)
+// (pages of up to four passes whose rows do not cross passes: held within 128 VGPRs, so that four waves fit a SIMD)
+template <class P, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::kPasses <= 4 && P::kAligned ? 4 : 1))) void k_decompress_window_wide(WindowParams params) {
+    const DecodeArgs& a = params.a;
+    constexpr int kClerkPages = 64;  // pages of a block the clerk looks up; blocks of more are left to the waves
+    constexpr int kClerk = WAVES - 1;
+    __shared__ __align__(16) uint32_t s_stage[WAVES][1][Slot<P::kPasses>::kWords];
+    __shared__ __align__(16) uint4 s_page[kClerkPages];  // the block at work: what the waves need to know of its pages,
+    __shared__ int32_t s_block[2];                       // its slot (-1: there is none) and its pool block
+    __shared__ WindowBooks s_books;                      // the clerk's (in LDS, not in registers of all waves)
+#if KVC_DEBUG_BOUNDS
+    __shared__ uint32_t s_done;  // waves that have finished a block, summed over the engine's blocks
+    if (threadIdx.x == 0) s_done = 0;
+    uint32_t behind = 0;  // blocks behind this wave
+#endif
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool clerk = wave == kClerk;
+    const int ppb = a.g.ppb;
+    const LanePos lp = lane_pos<P>(a.g);
+    const uint32_t engines = params.w.hdr->engines;
+    if (blockIdx.x >= engines) return;  // the window was opened for fewer engines than the grid holds
+    const int per_block = (ppb + WAVES - 1) / WAVES;  // a wave's page tasks of a block (tasks past the block do nothing)
+    const bool looked_up = ppb <= kClerkPages;
+    auto page_task = [&](bool live, int pg, int32_t slot, int32_t pb) {
+        DecPlace pl;
+        pl.pg = (uint32_t)pg;
+        pl.live = live && pg < ppb;
+        pl.bad_index = false;
+        pl.pb = pb;
+        pl.db = slot;
+        return pl;
+    };
+
+    // what the clerk has asked for
+    uint4 asked = make_uint4(0u, 0u, 0u, 0u);
+    uint32_t ticket = 0, was_pending = 0;
+    int32_t slot_asked = -1, pb_asked = -1;
+    long long rep_at = 0;
+    auto clerk_task = [&](int32_t slot, int32_t pb) { return page_task(looked_up && slot >= 0, lane, slot, pb); };
+    // The waves meet with all their stores of the block in memory, the clerk publishes the next, and they meet again.
+    // (The single-wave part lies inside the loop body and not across its back edge, and the loop and its exit branch on
+    // the scalar unit: every wave meets every barrier with all of its lanes.  With single-lane work at both ends of the
+    // loop body the compiler merges it across the back edge into an outer loop and lets the other lanes run ahead to the
+    // next barrier: the workgroup then never meets.)
+    auto publish = [&](const DecLanes& pages, int32_t next_slot, int32_t next_pb) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), the other counters unchanged
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __syncthreads();
+        if (clerk) {
+            s_page[lane] = make_uint4((uint32_t)pages.off, (uint32_t)(pages.off >> 32), __float_as_uint(pages.s), pages.meta);
+            if (lane == 0) {
+                s_block[0] = next_slot;
+                s_block[1] = next_pb;
+            }
+        }
+        __syncthreads();
+    };
+    DecLanes pages = {};
+    int32_t next_slot = -1, next_pb = -1;
+    if (clerk) {
+        __builtin_amdgcn_s_setprio(3);  // whatever it does beside its pages, the others wait for
+        const WindowParams& k = params_again<WindowParams>();
+        auto slot_of = [&](uint32_t i) { return i == kWindowNone ? -1 : wave_uniform(k.w.queue[i]); };
+        auto block_of = [&](int32_t slot) { return slot < 0 ? -1 : wave_uniform(k.a.pool_ids[slot]); };
+        WindowBooks b;
+        b.open_at(k.w.hdr->n_issued, blockIdx.x, engines, k.w.hdr->chunk);
+        next_slot = slot_of(b.take());  // (engines <= n_issued: there is a first)
+        b.slot1 = slot_of(b.take());
+        b.slot2 = slot_of(b.take());
+        next_pb = block_of(next_slot);
+        b.pb1 = block_of(b.slot1);
+        b.layer = b.layer_of(k.w, next_slot);
+        b.put(s_books);
+        pages = dec_open<P>(k.a, clerk_task(next_slot, next_pb));
+    }
+    publish(pages, next_slot, next_pb);
+    int32_t slot = wave_uniform(s_block[0]);
+    while (slot >= 0) {
+        const int32_t pb = wave_uniform(s_block[1]);
+        // page tasks t .. t + 63 of the block, one per lane
+        auto lanes = [&](int t) {
+            const int pg = wave + (t + lane) * WAVES;
+            if (!looked_up) return dec_open<P>(params_again<WindowParams>().a, page_task(t + lane < per_block, pg, slot, pb));
+            const uint4 v = s_page[min(pg, kClerkPages - 1)];
+            DecLanes r;
+            r.off = (uint64_t)v.x | ((uint64_t)v.y << 32);
+            r.s = __uint_as_float(v.z);
+            r.meta = pg < ppb ? v.w : 0u;
+            r.pg = (uint32_t)pg;
+            r.db = slot;
+            return r;
+        };
+        DecLanes L = lanes(0);
+        for (int t = 0;;) {
+#if KVC_DEBUG_BOUNDS
+            KVC_CHECK(a.st, *(volatile uint32_t*)&s_done >= behind * WAVES);
+#endif
+            dec_fetch<P, 1, false>(a, L, t % 64, s_stage[wave]);
+            dec_fetched();
+            if (t == 0 && clerk) {
+                const WindowParams& k = params_again<WindowParams>();
+                WindowBooks b;
+                b.get(s_books);
+                asked = dec_ask(k.a, clerk_task(b.slot1, b.pb1));
+                pb_asked = b.slot2 < 0 ? -1 : k.a.pool_ids[b.slot2];
+                const uint32_t i3 = b.take();
+                slot_asked = i3 == kWindowNone ? -1 : k.w.queue[i3];
+                b.run = b.next_run();
+                if (lane == 0) {
+                    if (b.run) ticket = atomicAdd(&k.w.hdr->ticket, b.run);
+                    if (b.rep) {
+                        rep_at = max(wall_clock64(), 1ll);  // read before the blocks are counted
+                        was_pending = (uint32_t)atomicSub(&k.w.pending[b.rep_layer], (int)b.rep);
+                    }
+                }
+                b.put(s_books);
+            }
+            dec_batch<P, 1, false>(a, L, t % 64, lp, s_stage[wave]);
+            wave_sync();
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the slots have been read before they are filled again
+            if (++t >= per_block) break;
+            if (t % 64 == 0) L = lanes(t);
+        }
+#if KVC_DEBUG_BOUNDS
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        if (lane == 0) atomicAdd(&s_done, 1u);
+#endif
+        if (clerk) {
+            const WindowParams& k = params_again<WindowParams>();
+            WindowBooks b;
+            b.get(s_books);
+            if (lane == 0 && b.rep && was_pending == b.rep) window_stamp(&k.w.notify[k.w.layer_begin + (int32_t)b.rep_layer], rep_at);
+            if (b.run) b.refill((uint32_t)wave_uniform((int32_t)ticket));
+            next_slot = b.slot1;
+            next_pb = b.pb1;
+            b.block_done(k.w);
+            b.slot1 = b.slot2;
+            b.slot2 = wave_uniform(slot_asked);
+            b.pb1 = wave_uniform(pb_asked);
+            b.put(s_books);
+            pages = dec_check<P>(k.a, clerk_task(next_slot, next_pb), asked);
+        }
+        publish(pages, next_slot, next_pb);
+        slot = wave_uniform(s_block[0]);
+#if KVC_DEBUG_BOUNDS
+        ++behind;
+#endif
+    }
+    if (clerk && lane == 0) {
+        const WindowArgs& w = params_again<WindowParams>().w;
+        const WindowBooks& b = s_books;
+        if (b.rep && atomicSub(&w.pending[b.rep_layer], (int)b.rep) == (int)b.rep) window_stamp(&w.notify[w.layer_begin + (int32_t)b.rep_layer], max(wall_clock64(), 1ll));
+        // WaitCompletion returns: NotifyGPU(ready).  The last engine to leave reads this clock after the last block was
+        // counted, and every engine wrote its layer stamps before it reported its blocks: the stamp is the latest of the call.
+        if (atomicAdd(&w.hdr->done, b.mine) + b.mine == w.hdr->n_issued) window_stamp(&w.notify[w.n_layers + 3], max(wall_clock64(), 1ll));
     }
 }
 
@@ -1270,7 +1458,7 @@ struct ShapeOps {
     }
 
     static hipError_t decompress_window(const DecodeArgs& a, const WindowArgs& w, unsigned grid, bool wide, hipStream_t s) {
-        if (wide) return launch_kernel(k_decompress_window<P, kWideWaves, 1>, dim3(grid), dim3(kWideWaves * 64), s, a, w);
+        if (wide) return launch_kernel(k_decompress_window_wide<P, kWideWaves>, dim3(grid), dim3(kWideWaves * 64), s, WindowParams{a, w});
         return launch_kernel(k_decompress_window<P, kCodecWaves, window_side(NP)>, dim3(grid), dim3(kCodecWaves * 64), s, a, w);
     }
 
@@ -1278,7 +1466,7 @@ struct ShapeOps {
     // resident ones, which keep taking turns until the queue is empty
     static int window_capacity(bool wide) {
         int dev = 0, cus = 0, per_cu = 0;
-        const void* k = wide ? reinterpret_cast<const void*>(&k_decompress_window<P, kWideWaves, 1>) : reinterpret_cast<const void*>(&k_decompress_window<P, kCodecWaves, window_side(NP)>);
+        const void* k = wide ? reinterpret_cast<const void*>(&k_decompress_window_wide<P, kWideWaves>) : reinterpret_cast<const void*>(&k_decompress_window<P, kCodecWaves, window_side(NP)>);
         if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, (wide ? kWideWaves : kCodecWaves) * 64, 0) != hipSuccess) {
             (void)hipGetLastError();

@@ -95,7 +95,9 @@ struct WindowHdr {
 };
 static_assert(sizeof(WindowHdr) == 256, "window header is 256 bytes");
 
-constexpr int kMaxWindowTurn = 8;
+constexpr int kMaxWindowTurn = 8;  // queue entries an engine takes in a row, and reports at once, at most
+constexpr int kWindowManyEngines = 256;  // more engines than this are used only as far as each has eight transfers
+constexpr int kWindowAhead = 4;         // queue entries a wide engine knows without asking, at least
 
 struct WindowArgs {
     WindowHdr* hdr;
@@ -107,7 +109,13 @@ struct WindowArgs {
     FastDiv by_per_layer;
     int32_t layer_begin, n_layers_call, n_layers;
     int32_t omega;         // engines the decode launch starts at most
+    int32_t wide;          // they are of the wide kind
     long long* notify;     // [n_layers + 4], see kvc.h
+};
+
+struct WindowParams {
+    DecodeArgs a;
+    WindowArgs w;
 };
 
 inline uint64_t window_workspace_bytes(int64_t n_blocks, int64_t n_layers_call) {
@@ -129,7 +137,7 @@ inline hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, hip
 
 hipError_t launch_prefetch_plan(const PlanArgs& a, hipStream_t s);
 hipError_t launch_window_build(const WindowArgs& w, hipStream_t s);
-hipError_t launch_decompress_window(const DecodeArgs& a, const WindowArgs& w, int32_t omega, int32_t wide_capacity, hipStream_t s);
+hipError_t launch_decompress_window(const DecodeArgs& a, const WindowArgs& w, hipStream_t s);
 int window_engine_capacity(const Geometry& g, bool wide);
 hipError_t launch_fill_i32(int32_t* p, int32_t v, uint64_t n, hipStream_t s);
 hipError_t launch_compress(const EncodeArgs& a, hipStream_t s);

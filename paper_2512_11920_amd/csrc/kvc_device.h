@@ -293,6 +293,15 @@ __device__ __forceinline__ DecPlace dec_locate(const DecodeArgs& a, bool live, u
 // reports completion and takes the next.  The grid has at most Omega workgroups, so never more than
 // Omega blocks are in flight; every workgroup leaves as soon as the queue is exhausted.
 
+// A stamp of the notification array.  It orders nothing behind it and need not: the pages that a stamp speaks of were
+// written through to the device's memory (store_out) and waited for by every wave before the counts moved that led to the
+// stamp.  (A release in its place writes back the XCD's whole L2: 8 us an engine and report, when 256 engines did it.)
+__device__ __forceinline__ void window_stamp(long long* at, long long clock) {
+    __hip_atomic_store(at, clock, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// ---- narrow engines: turn by turn
+
 // What an engine holds between two turns: a run of consecutive queue entries.
 struct WindowTurn {
     uint32_t first;  // index of the first queue entry
@@ -340,14 +349,14 @@ __device__ __forceinline__ WindowTurn window_next(const WindowArgs& w, uint32_t*
                 uint32_t n = 1;
                 while (i + n < turn.count && fast_div((uint32_t)slots[i + n], w.by_per_layer) == l_rel) ++n;
                 if (atomicSub(&w.pending[l_rel], (int)n) == (int)n)
-                    __hip_atomic_store(&w.notify[w.layer_begin + (int32_t)l_rel], finished, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+                    window_stamp(&w.notify[w.layer_begin + (int32_t)l_rel], finished);
                 i += n;
             }
             // WaitCompletion returns: NotifyGPU(ready).  The last engine to leave reads this clock after the last
             // block was counted, and every engine wrote its layer stamps before it reported its blocks: the stamp
             // is the latest of the call.
             if (t >= n_issued && atomicAdd(&w.hdr->done, mine) + mine == n_issued)
-                __hip_atomic_store(&w.notify[w.n_layers + 3], max(wall_clock64(), 1ll), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+                window_stamp(&w.notify[w.n_layers + 3], max(wall_clock64(), 1ll));
         }
         s_turn[0] = t;
         s_turn[1] = t < n_issued ? min(chunk, n_issued - t) : 0u;
@@ -359,6 +368,97 @@ __device__ __forceinline__ WindowTurn window_next(const WindowArgs& w, uint32_t*
     r.at = 0;
     return r;
 }
+
+// ---- wide engines: looked ahead for
+
+constexpr uint32_t kWindowNone = ~0u;
+
+// The kernel's arguments, read from where the launch put them (a kernel of one argument).  What only a rare part of a
+// kernel needs is asked for there and not held in scalar registers meanwhile (an engine has some 80 words of arguments and
+// 30 of books, and 100 scalar registers).
+template <class T>
+__device__ __forceinline__ const T& params_again() {
+    auto p = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const T*)(const void*)p;
+}
+
+// What the clerk of a wide engine knows (wave-uniform): the entries ahead of the engine, and the blocks behind it.
+// Entries come in runs, `left` of them from `next` on, `step` apart, a run asked for before the last entry of the run before
+// is used up.  The first run needs no ticket: entries in a row where the call has eight or more for every engine, else
+// kWindowAhead entries that lie `engines` apart.
+struct WindowBooks {
+    uint32_t n_issued, engines;
+    uint32_t next, left, step, size;
+    uint32_t open;            // the queue may hold more than the known run
+    uint32_t run;             // entries asked for
+    int32_t slot1, slot2;     // slots of the two blocks after the one at work (-1: none),
+    int32_t pb1;              // and the pool block of the first
+    uint32_t mine;            // blocks completed,
+    uint32_t acc, layer;      // those of them not yet reported, all of this layer,
+    uint32_t rep, rep_layer;  // and those to report
+
+    __device__ __forceinline__ void get(const WindowBooks& from) {
+        constexpr int n = sizeof(WindowBooks) / 4;
+        uint32_t v[n];
+#pragma unroll
+        for (int i = 0; i < n; ++i) v[i] = (uint32_t)wave_uniform((int32_t)reinterpret_cast<const uint32_t*>(&from)[i]);
+        *this = __builtin_bit_cast(WindowBooks, v);
+    }
+    __device__ __forceinline__ void put(WindowBooks& to) const {
+        wave_sync();
+        if (lane_id() == 0) to = *this;
+        wave_sync();
+    }
+
+    __device__ __forceinline__ void open_at(uint32_t issued, uint32_t engine, uint32_t n_engines, uint32_t chunk) {
+        const bool rows = chunk > 1;
+        n_issued = issued;
+        engines = n_engines;
+        left = max(chunk, (uint32_t)kWindowAhead);
+        next = rows ? engine * left : engine;
+        step = rows ? 1u : n_engines;
+        size = chunk;
+        open = 1;
+        run = mine = acc = rep = rep_layer = 0;
+    }
+    __device__ __forceinline__ uint32_t take() {
+        if (left == 0) return kWindowNone;
+        const uint32_t i = next;
+        next += step;
+        --left;
+        return i < n_issued ? i : kWindowNone;
+    }
+    // Length of the run to ask for now (0: none): the call's chunk, halved when less than two such runs per engine seem to
+    // be left, so that the engines end within a block of each other.  (Every run is an atomic on one counter, which
+    // serves one every 10 to 20 ns whoever asks: a few hundred engines can ask for every block.)
+    __device__ __forceinline__ uint32_t next_run() {
+        if (left != 0 || open == 0) return 0u;
+        const uint32_t rest = next < n_issued ? n_issued - next : 0u;
+        while (size > 1 && rest < 2u * engines * size) size >>= 1;
+        return size;
+    }
+    __device__ __forceinline__ void refill(uint32_t ticket) {
+        open = ticket < n_issued ? 1u : 0u;
+        next = ticket;
+        left = open ? min(run, n_issued - ticket) : 0u;
+        step = 1;
+    }
+    static __device__ __forceinline__ uint32_t layer_of(const WindowArgs& w, int32_t s) { return s < 0 ? kWindowNone : fast_div((uint32_t)s, w.by_per_layer); }
+    // the block at work is decoded: consecutive blocks of a layer are reported together
+    __device__ __forceinline__ void block_done(const WindowArgs& w) {
+        const uint32_t layer1 = layer_of(w, slot1);
+        ++mine;
+        ++acc;
+        rep = 0;
+        if (layer1 != layer || acc >= (uint32_t)kMaxWindowTurn) {
+            rep = acc;
+            rep_layer = layer;
+            acc = 0;
+            layer = layer1;
+        }
+    }
+};
 
 // The codec kernels are specialised at compile time for the page shape (kvc_codec.h): d channels, np
 // passes of 512 elements, and whether the page fills its last pass (exact: d * N = 512 * np) or not

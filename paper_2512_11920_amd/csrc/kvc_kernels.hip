@@ -231,13 +231,13 @@ __global__ __launch_bounds__(256) void k_window_place(WindowArgs w) {
             // counter, and more engines than that gain little (4,370 transfers of 16 pages of 16 x 128: 121 us with 256
             // engines, 111 us with 512).
             unsigned int engines = min(total, (uint32_t)w.omega);
-            if (engines > 256u) engines = min(engines, max(256u, total / 8u));
+            if (engines > (uint32_t)kWindowManyEngines) engines = min(engines, max((uint32_t)kWindowManyEngines, total / 8u));
             w.hdr->n_issued = total;
             w.hdr->engines = engines;
             // entries per turn: long queues space out the bookkeeping, short ones keep every engine busy
             const unsigned int chunk = engines ? min(max(total / (4u * engines), 1u), (uint32_t)kMaxWindowTurn) : 1u;
             w.hdr->chunk = chunk;
-            w.hdr->ticket = engines * chunk;  // the engines' first turns (engines * chunk <= total) need no ticket
+            w.hdr->ticket = engines * (w.wide ? max(chunk, (unsigned int)kWindowAhead) : chunk);  // the engines' first runs need no ticket
             w.hdr->done = 0;
             w.notify[w.n_layers] = now;                        // window opened
             w.notify[w.n_layers + 1] = (long long)total;       // transfers issued
@@ -312,11 +312,10 @@ hipError_t launch_window_build(const WindowArgs& w, hipStream_t s) {
 
 // At most omega workgroups, one block in flight each; the queue may turn out shorter than the grid, in
 // which case the surplus workgroups leave at their first look.
-hipError_t launch_decompress_window(const DecodeArgs& a, const WindowArgs& w, int32_t omega, int32_t wide_capacity, hipStream_t s) {
+hipError_t launch_decompress_window(const DecodeArgs& a, const WindowArgs& w, hipStream_t s) {
     if (w.n_now <= 0) return hipSuccess;
-    const unsigned grid = (unsigned)std::min<int64_t>(omega, w.n_now);
     const ShapeKernels* f = shape_kernels(a.g.N, a.g.d);
-    return f ? f->decompress_window(a, w, grid, wide_capacity > 0 && grid <= (unsigned)wide_capacity, s) : hipErrorInvalidValue;
+    return f ? f->decompress_window(a, w, (unsigned)std::min<int64_t>(w.omega, w.n_now), w.wide != 0, s) : hipErrorInvalidValue;
 }
 
 int window_engine_capacity(const Geometry& g, bool wide) {

@@ -121,3 +121,27 @@ def test_turns_of_more_page_tasks_than_one_batch_of_descriptors(N, d, ppb, omega
     per_block = -(-(-(-ppb // waves)) // side) * side
     assert min(max(issued // (4 * engines), 1), 8) * per_block > 64
     assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
+# Wide engines: blocks of one page up to more than the clerk looks up (64) and more than a wave resolves at once (1,024
+# pages); from one block per engine and fewer than an engine looks ahead, over runs of one, two and more, to runs of eight.
+@pytest.mark.parametrize("N,d,ppb,omega,layers,n_seq,k", [(16, 64, 1, 256, 3, 29, 8), (16, 128, 3, 200, 2, 31, 7), (16, 32, 17, 96, 3, 32, 5), (8, 64, 16, 128, 5, 32, 8), (16, 128, 5, 100, 8, 32, 8),
+                                                          (5, 96, 64, 60, 2, 16, 8), (5, 96, 65, 33, 2, 16, 8), (1, 32, 1040, 7, 2, 9, 8), (16, 256, 2, 256, 12, 32, 8), (16, 64, 4, 3, 7, 10, 8)])
+def test_wide_engines_over_every_length_of_run(N, d, ppb, omega, layers, n_seq, k):
+    w = Window(N, d, ppb, layers, n_seq, k, 40)
+    want = w.buffer()
+    w.run(want, 0)
+    plan = [t.clone() for t in (w.tags, w.fetch, w.loc)]
+    for om in (omega, 1):
+        got = w.buffer()
+        print(f"[case] wide engines N={N} d={d} ppb={ppb} omega={om}", flush=True)
+        w.run(got, om)
+        torch.cuda.synchronize()
+        nt = w.notify.cpu().numpy()
+        assert nt[layers + 1] == int((w.fetch >= 0).sum()) and nt[layers + 2] == min(om, nt[layers + 1])
+        assert (nt[:layers] >= nt[layers]).all() and (nt[:layers] <= nt[layers + 3]).all()
+        if om == 1:  # one engine completes the layers in order
+            assert (np.diff(nt[:layers]) >= 0).all()
+        assert all(torch.equal(a, b) for a, b in zip(plan, (w.tags, w.fetch, w.loc)))
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    assert w.c.stats()["status"] == kvc.ST_CORRUPT
