@@ -862,6 +862,16 @@ __device__ __forceinline__ void load_to_lds16(const void* g, void* lds) {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g, (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
 }
 
+// Decoder workgroups a compute unit may hold in large calls (0: as many as fit).  With 32 waves on every compute unit and
+// pages of 5 KB and more, 160 to 256 KB per compute unit are being written at once, all over the output, and the memory
+// serves them worse than 128 to 168 KB, which four-pass pages come to by themselves.  262,144 pages, decode, us, eight
+// groups -> the number here: 16 x 160 335 -> 324, 16 x 192 399 -> 389, 16 x 224 473 -> 459, 16 x 256 541 -> 514 (4.5 KB pages
+// 297 -> 301 with six: as many as fit).  The limit is LDS that nothing uses; from 32,768 pages on, below that it
+// neither gains nor loses more than half a microsecond.
+constexpr int kDecLimitPages = 32768;
+constexpr int dec_groups(int np, bool partial) { return np == 8 ? 4 : np >= 6 || (np == 5 && !partial) ? 6 : 0; }
+constexpr int kLdsPerCu = 160 * 1024;
+
 // Whether INT8 payloads go through LDS too.  With several pages per wave their loads have to be under way before
 // the first page is stored; with one page per wave they are read straight from the pool, pass by pass, which is
 // 1.5 % faster for whole launches of INT8 pages (262,144 pages of 4 KB: 285 us, 289 us through LDS).
@@ -946,11 +956,21 @@ __device__ __forceinline__ void dec_headers(const Extent& x, const DecLanes& L, 
 // Decode an INT8 payload at src (the staged copy, or the pool itself) into the page at dst_b.
 template <class P>
 __device__ __forceinline__ void dec_int8(const DecodeArgs& a, const Extent& x, const LanePos& lp, float s, char* dst_b, const uint2* src) {
+    // Where the workgroups of a compute unit are limited, all loads go ahead of all stores (262,144 pages, us: 16 x 256 327 ->
+    // 280, 16 x 192 426 -> 408).  Elsewhere a pass is stored before the next is loaded, which limits what is in flight by
+    // itself (16 x 128 263, all ahead 275).
+    constexpr bool kAhead = dec_groups(P::kPasses, P::kPartial) != 0;
+    uint2 v[P::kPasses];
+    if (kAhead) {
+#pragma unroll
+        for (int p = 0; p < P::kPasses; ++p)
+            if (lane_live<P>(x, p)) v[p] = src[p * 64 + lane_id()];
+    }
 #pragma unroll
     for (int p = 0; p < P::kPasses; ++p) {
         if (!lane_live<P>(x, p)) continue;
-        const uint2 v = src[p * 64 + lane_id()];
-        const uint32_t lo = v.x ^ 0x80808080u, hi = v.y ^ 0x80808080u;  // + 128 in every byte: the sign bits change
+        if (!kAhead) v[p] = src[p * 64 + lane_id()];
+        const uint32_t lo = v[p].x ^ 0x80808080u, hi = v[p].y ^ 0x80808080u;  // + 128 in every byte: the sign bits change
         uint32_t pb[8];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -1454,7 +1474,11 @@ struct ShapeOps {
     }
 
     static hipError_t decompress(const DecodeArgs& a, hipStream_t s) {
-        return launch_kernel(k_decompress<P, kCodecWaves, dec_ppw(NP)>, page_grid(a.n_pages, dec_ppw(NP)), dim3(kCodecWaves * 64), s, a);
+        constexpr int groups = dec_groups(NP, PARTIAL), own = kCodecWaves * dec_ppw(NP) * Slot<NP>::kBytes;
+        constexpr int limit = groups ? kLdsPerCu / groups - 1280 - own : 0;  // (1,280: room for the allocation's granularity)
+        static_assert(limit >= 0 && (groups == 0 || own + limit > kLdsPerCu / (groups + 1)), "one group more does not fit");
+        return launch_kernel_lds(k_decompress<P, kCodecWaves, dec_ppw(NP)>, page_grid(a.n_pages, dec_ppw(NP)), dim3(kCodecWaves * 64),
+                                 a.n_pages >= kDecLimitPages ? limit : 0, s, a);
     }
 
     static hipError_t decompress_window(const DecodeArgs& a, const WindowArgs& w, unsigned grid, bool wide, hipStream_t s) {

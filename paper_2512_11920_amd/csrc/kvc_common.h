@@ -129,10 +129,15 @@ template <typename T>
 struct SameType {
     using type = T;
 };
+// lds: bytes of LDS per workgroup beside the kernel's own.
+template <typename... P>
+inline hipError_t launch_kernel_lds(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t s, typename SameType<P>::type... args) {
+    void* ptrs[] = {static_cast<void*>(&args)...};
+    return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, ptrs, lds, s);
+}
 template <typename... P>
 inline hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t s, typename SameType<P>::type... args) {
-    void* ptrs[] = {static_cast<void*>(&args)...};
-    return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, ptrs, 0, s);
+    return launch_kernel_lds(kernel, grid, block, 0, s, args...);
 }
 
 hipError_t launch_prefetch_plan(const PlanArgs& a, hipStream_t s);
