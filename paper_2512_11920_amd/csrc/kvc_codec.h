@@ -1412,21 +1412,45 @@ constexpr int kCodecWaves = 4;
 // omega above the wide kind's number with few transfers runs 256 narrow engines, 161 us in the first example.)
 constexpr int kWideWaves = 16;
 constexpr int window_side(int np) { return np <= 4 ? 4 : 2; }
-// A small call (a decode step's offload of a few blocks) is latency: one page per wave (more only for
-// the smallest pages), so the pages are encoded side by side instead of several in a row.  The cursor
-// then takes an atomic per four pages, 13 ns each: little at 256 pages of 16 x 128 (0.8 of 6.5 us), but 3.3 of 8.8 us at
-// 1,024 and 6.7 of 12 at 2,048.
-constexpr int enc_ppw_small(int np) { return np == 1 ? 4 : np == 2 ? 2 : 1; }
 // Pages per decoder wave: a page of one or two passes is too small to cover its own memory chain, so a wave
 // takes the pages that share a header scan, resolved one per lane.  Measured (half a million pages, us): one
 // pass 180 / 112 / 117 with 1 / 4 / 8 pages, two passes 283 / 276 / 294 with 1 / 2 / 4, four passes 1075 / 1083 /
 // 1109 (a million pages) with 1 / 2 / 4: there the launch moves 5.8 TB/s, what a copy does, with any of them.
 constexpr int dec_ppw(int np) { return np == 1 ? 4 : np == 2 ? 2 : 1; }
-// calls of at most this many pages take the low-latency launch shape
-constexpr int kEncSmallPages = 2048;
-// Four-pass pages with the mode fixed: up to this many pages the workgroups of 16 pages are all resident at once (256
-// compute units, four each), while those of 20 would leave a nearly empty last round (16,384 pages: 26 us, 29.7 us).
-constexpr int kEncMidPages = 16384;
+// ... unless the call is small: then the memory chain is walked once anyway, and pages side by side are decoded sooner than
+// one after the other (16 x 64, us, two pages per wave -> one: 8 pages 6.4 -> 6.0, 1,024 6.8 -> 6.0, 8,192 9.1 -> 8.8,
+// 16,384 12.3 -> 12.5; 16 x 32, four -> one: 1,024 6.9 -> 6.0, 4,096 7.2 -> 6.3, 16,384 9.3 -> 10.8).
+constexpr int kDecSmallPages(int np) { return 4096 * np; }
+
+// Encoder launch shapes of calls below the large ones: workgroups of `waves` waves with `ppw` pages each, up to `pages`
+// pages.  Such a call (a decode step's offload, a sequence's) is latency: one page per wave while the cursor bears it.
+// It serves an atomic per workgroup every 13 ns, so the more pages there are, the more have to share one -- first by
+// more waves in the workgroup, which are resident anyway, then by more pages per wave, which follow one another.  Compress
+// with a cursor reset before it, us, workgroups of four waves of 1 (up to 2,048) and of 4 or 5 pages -> these, 16 x 128:
+// 1,024 pages 13.8 -> 12.9, 2,048 17.1 -> 14.5, 4,096 18.9 -> 17.0, 8,192 22.9 -> 19.9, 16,384 31.8 -> 28.2, 32,768 50.6 ->
+// 48.8; 16 x 64, two pages per wave -> these: 8 11.3 -> 10.5, 1,024 12.3 -> 11.8, 4,096 16.2 -> 14.5, 16,384 21.3 ->
+// 20.0, 32,768 30.7 -> 27.7; 16 x 32, four -> these: 8 11.7 -> 9.9, 1,024 12.3 -> 11.4, 4,096 15.8 -> 13.2, 16,384 19.3 -> 18.7;
+// 16 x 256: 1,024 15.8 -> 15.0, 4,096 21.9 -> 20.9.
+struct EncTier {
+    int pages, waves, ppw;
+};
+constexpr int kEncTiers = 4;
+constexpr EncTier enc_tier(int np, int scheme, int i) {
+    constexpr EncTier none = {0, 4, 1};
+    constexpr EncTier one[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {16384, 16, 2}, {32768, 16, 4}};  // one pass
+    constexpr EncTier two[kEncTiers] = {{512, 4, 1}, {2048, 8, 1}, {16384, 16, 2}, {32768, 16, 4}};
+    constexpr EncTier four[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {8192, 16, 1}, {32768, 8, 4}};  // three and four
+    constexpr EncTier pairs[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {6144, 16, 1}, {32768, 8, 4}};  // four, mode 5
+    constexpr EncTier six[kEncTiers] = {{512, 4, 1}, {3072, 8, 1}, none, none};                    // five and six
+    constexpr EncTier more[kEncTiers] = {{512, 4, 1}, {4096, 8, 1}, none, none};
+    // (with the mode read at run time the last one is slower at two passes -- 7 x 128, 32,768 pages, 31.9 us, 36.1 --, and the
+    // register sets of three and four do not go four times)
+    if (i == 3 && ((scheme < 0 && np >= 2) || np == 3)) return none;
+    return np == 1 ? one[i] : np == 2 ? two[i] : np == 4 && scheme == KVC_MODE_CHAN ? pairs[i] : np <= 4 ? four[i] : np <= 6 ? six[i] : more[i];
+}
+// Plain INT8 and raw calls encode faster and are at the cursor sooner: from here on they take the large shapes (16 x 128,
+// INT8, 4,096 pages 14.7 us against 15.8, 8,192 18.8 against 20.8; 16 x 32, 16,384 pages 16.7 against 18.0).
+constexpr int enc_plain_pages(int np) { return np <= 2 ? 8192 : 2048; }
 
 inline dim3 page_grid(int64_t n_pages, int ppw, int waves = kCodecWaves) {
     const int64_t per_wg = (int64_t)waves * ppw;
@@ -1438,13 +1462,26 @@ template <int D, int NP, bool PARTIAL>
 struct ShapeOps {
     using P = Page<D, NP, PARTIAL>;
 
+    template <int SCHEME, int TIER>
+    static bool compress_tier(const EncodeArgs& a, hipStream_t s, hipError_t& r) {
+        constexpr EncTier t = enc_tier(NP, SCHEME, TIER);
+        if constexpr (t.pages > 0) {
+            if (a.n_pages <= t.pages) {
+                r = launch_kernel(k_compress<P, t.waves, t.ppw, SCHEME>, page_grid(a.n_pages, t.ppw, t.waves), dim3(t.waves * 64), s, a);
+                return true;
+            }
+        }
+        return false;
+    }
+
     template <int SCHEME>
     static hipError_t compress_scheme(const EncodeArgs& a, hipStream_t s) {
-        const dim3 block(kCodecWaves * 64);
-        if (a.n_pages <= kEncSmallPages)
-            return launch_kernel(k_compress<P, kCodecWaves, enc_ppw_small(NP), SCHEME>, page_grid(a.n_pages, enc_ppw_small(NP)), block, s, a);
-        if constexpr (NP == 4 && SCHEME >= 0) {
-            if (a.n_pages <= kEncMidPages) return launch_kernel(k_compress<P, 4, 4, SCHEME>, page_grid(a.n_pages, 4, 4), dim3(256), s, a);
+        hipError_t r = hipSuccess;
+        const bool plain = SCHEME < 0 && a.block_scheme == nullptr && (a.scheme == KVC_MODE_RAW || a.scheme == KVC_MODE_INT8) && a.n_pages > enc_plain_pages(NP);
+        if (plain) {
+            // large
+        } else if (compress_tier<SCHEME, 0>(a, s, r) || compress_tier<SCHEME, 1>(a, s, r) || compress_tier<SCHEME, 2>(a, s, r) || compress_tier<SCHEME, 3>(a, s, r)) {
+            return r;
         }
         constexpr EncShape e = enc_large(NP, SCHEME);
         return launch_kernel(k_compress<P, e.waves, e.ppw, SCHEME>, page_grid(a.n_pages, e.ppw, e.waves), dim3(e.waves * 64), s, a);
@@ -1474,6 +1511,9 @@ struct ShapeOps {
     }
 
     static hipError_t decompress(const DecodeArgs& a, hipStream_t s) {
+        if constexpr (dec_ppw(NP) > 1) {
+            if (a.n_pages <= kDecSmallPages(NP)) return launch_kernel(k_decompress<P, kCodecWaves, 1>, page_grid(a.n_pages, 1), dim3(kCodecWaves * 64), s, a);
+        }
         constexpr int groups = dec_groups(NP, PARTIAL), own = kCodecWaves * dec_ppw(NP) * Slot<NP>::kBytes;
         constexpr int limit = groups ? kLdsPerCu / groups - 1280 - own : 0;  // (1,280: room for the allocation's granularity)
         static_assert(limit >= 0 && (groups == 0 || own + limit > kLdsPerCu / (groups + 1)), "one group more does not fit");
