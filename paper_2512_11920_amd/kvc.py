@@ -44,14 +44,15 @@ class KvcError(RuntimeError):
 
 _lib = None
 # bound when the library is loaded: torch, and the calls that name the current device's current stream.  (A small data
-# call is mostly the way through this module: torch.cuda.current_stream() alone, which makes a stream object, took
-# 1.3 us of 7.)
-_torch = _device_now = _raw_stream_now = None
+# call is mostly the way to the launch: torch.cuda.current_stream() alone, which makes a stream object, took 1.3 us of 7,
+# and the checks of the id tensors, written with helpers and a generator, 0.9 of 5.4.  The launch itself is 3.3.)
+_torch = _device_now = _raw_stream_now = _half = _int32 = None
+_cuda_ready = False
 
 
 def load():
     """dlopen libkvc.so and declare the prototypes.  Raises if the library is missing."""
-    global _lib, _torch, _device_now, _raw_stream_now
+    global _lib, _torch, _device_now, _raw_stream_now, _half, _int32
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -61,7 +62,7 @@ def load():
     # to the copy torch already mapped, so tensors and kernels share one runtime instance.
     import torch
 
-    _torch = torch
+    _torch, _half, _int32 = torch, torch.float16, torch.int32
     _device_now = getattr(torch._C, "_cuda_getDevice", None)
     _raw_stream_now = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     L = C.CDLL(LIB_PATH)
@@ -135,16 +136,36 @@ def _ptr(t):
 def _stream(stream):
     if stream is not None:
         return stream.cuda_stream
-    if _raw_stream_now is not None and _device_now is not None and _torch.cuda.is_initialized():
+    return _stream_now()
+
+
+def _stream_now():
+    global _cuda_ready
+    if _cuda_ready:
         return _raw_stream_now(_device_now())
+    _cuda_ready = _raw_stream_now is not None and _device_now is not None and _torch.cuda.is_initialized()
     return _torch.cuda.current_stream().cuda_stream
 
 
 def _ids(t):
     if t is None:
         return None
-    assert t.is_cuda and t.dtype == _torch.int32 and t.is_contiguous(), "block ids: contiguous int32 CUDA tensor"
+    assert t.is_cuda and t.dtype == _int32 and t.is_contiguous(), "block ids: contiguous int32 CUDA tensor"
     return t
+
+
+def _id_ptr(t, n):
+    """Address of an id tensor of at least n entries."""
+    assert t.is_cuda and t.dtype == _int32 and t.is_contiguous(), "block ids: contiguous int32 CUDA tensor"
+    assert t.numel() >= n, "id tensors shorter than n"
+    return t.data_ptr()
+
+
+def _id_ptr_of(t, n):
+    """Address of an id tensor of exactly n entries."""
+    assert t.is_cuda and t.dtype == _int32 and t.is_contiguous(), "block ids: contiguous int32 CUDA tensor"
+    assert t.numel() == n
+    return t.data_ptr()
 
 
 class Codec:
@@ -223,34 +244,39 @@ class Codec:
     # -- the three data calls
     def _blocks_of(self, t) -> int:
         """Number of whole blocks the tensor's storage covers under the current layout."""
-        assert t.is_cuda and t.is_contiguous() and t.dtype == _torch.float16
+        assert t.is_cuda and t.is_contiguous() and t.dtype == _half
         n = t.numel()
         return 0 if n < self._span else (n - self._span) // self._block_stride + 1
 
     def compress_blocks(self, cache, n: int | None = None, src_ids=None, pool_ids=None, block_scheme=None, stream=None):
         """block_scheme: optional uint8 CUDA tensor, requested mode per block of the call."""
         nb = self._blocks_of(cache)
-        src_ids, pool_ids = _ids(src_ids), _ids(pool_ids)
         if n is None:
             n = src_ids.numel() if src_ids is not None else (pool_ids.numel() if pool_ids is not None else nb)
-        assert all(t is None or t.numel() >= n for t in (src_ids, pool_ids)), "id tensors shorter than n"
+        n = int(n)
+        src = None if src_ids is None else _id_ptr(src_ids, n)
+        pool = None if pool_ids is None else _id_ptr(pool_ids, n)
+        s = _stream_now() if stream is None else stream.cuda_stream
         if block_scheme is None:
-            _check(self._L.kvc_compress_blocks(self._ctx, cache.data_ptr(), nb, _ptr(src_ids), _ptr(pool_ids), int(n),
-                                               _stream(stream)), "kvc_compress_blocks")
+            rc = self._L.kvc_compress_blocks(self._ctx, cache.data_ptr(), nb, src, pool, n, s)
+            if rc:
+                _check(rc, "kvc_compress_blocks")
         else:
             assert block_scheme.is_cuda and block_scheme.dtype == _torch.uint8 and block_scheme.numel() >= n
-            _check(self._L.kvc_compress_blocks_mixed(self._ctx, cache.data_ptr(), nb, _ptr(src_ids), _ptr(pool_ids),
-                                                     block_scheme.data_ptr(), int(n), _stream(stream)),
-                   "kvc_compress_blocks_mixed")
+            rc = self._L.kvc_compress_blocks_mixed(self._ctx, cache.data_ptr(), nb, src, pool, block_scheme.data_ptr(), n, s)
+            if rc:
+                _check(rc, "kvc_compress_blocks_mixed")
 
     def decompress_blocks(self, out, n: int | None = None, pool_ids=None, dst_ids=None, stream=None):
         nb = self._blocks_of(out)
-        pool_ids, dst_ids = _ids(pool_ids), _ids(dst_ids)
         if n is None:
             n = pool_ids.numel() if pool_ids is not None else (dst_ids.numel() if dst_ids is not None else nb)
-        assert all(t is None or t.numel() >= n for t in (pool_ids, dst_ids)), "id tensors shorter than n"
-        _check(self._L.kvc_decompress_blocks(self._ctx, out.data_ptr(), nb, _ptr(pool_ids), _ptr(dst_ids), int(n),
-                                             _stream(stream)), "kvc_decompress_blocks")
+        n = int(n)
+        pool = None if pool_ids is None else _id_ptr(pool_ids, n)
+        dst = None if dst_ids is None else _id_ptr(dst_ids, n)
+        rc = self._L.kvc_decompress_blocks(self._ctx, out.data_ptr(), nb, pool, dst, n, _stream_now() if stream is None else stream.cuda_stream)
+        if rc:
+            _check(rc, "kvc_decompress_blocks")
 
     def gather_decompress(self, out, block_table, pred, n_layers: int, pool_blocks_per_layer: int, stream=None):
         block_table, pred = _ids(block_table), _ids(pred)
@@ -274,18 +300,16 @@ class Codec:
     def prefetch_layers(self, l2, tags, fetch, loc, block_table, pred, n_layers: int, pool_blocks_per_layer: int,
                         fill_half: int, layer_begin: int = 0, layer_end: int | None = None, l1_first=None, stream=None):
         """l2: float16 [2][n_layers*n_seq*k][ppb][N][d]; tags int32 [2][n_slots]; fetch, loc int32 [n_slots]."""
-        block_table, pred = _ids(block_table), _ids(pred)
         n_seq, max_blocks = block_table.shape
-        k = pred.shape[1]
+        rows, k = pred.shape[:2]
         n_slots = n_layers * n_seq * k
-        assert self._blocks_of(l2) == 2 * n_slots
-        assert _ids(tags).numel() == 2 * n_slots and _ids(fetch).numel() == n_slots and _ids(loc).numel() == n_slots
-        assert pred.shape[0] == n_seq and (l1_first is None or l1_first.numel() == n_seq)
-        layer_end = n_layers if layer_end is None else layer_end
-        _check(self._L.kvc_prefetch_layers(self._ctx, l2.data_ptr(), tags.data_ptr(), fetch.data_ptr(), loc.data_ptr(),
-                                           block_table.data_ptr(), max_blocks, pred.data_ptr(), _ptr(_ids(l1_first)),
-                                           n_seq, k, n_layers, layer_begin, layer_end, int(pool_blocks_per_layer),
-                                           fill_half, _stream(stream)), "kvc_prefetch_layers")
+        assert self._blocks_of(l2) == 2 * n_slots and rows == n_seq
+        rc = self._L.kvc_prefetch_layers(self._ctx, l2.data_ptr(), _id_ptr_of(tags, 2 * n_slots), _id_ptr_of(fetch, n_slots), _id_ptr_of(loc, n_slots),
+                                         _id_ptr(block_table, 0), max_blocks, _id_ptr(pred, 0), None if l1_first is None else _id_ptr_of(l1_first, n_seq),
+                                         n_seq, k, n_layers, layer_begin, n_layers if layer_end is None else layer_end, int(pool_blocks_per_layer),
+                                         fill_half, _stream_now() if stream is None else stream.cuda_stream)
+        if rc:
+            _check(rc, "kvc_prefetch_layers")
 
     def prefetch_layers_window(self, l2, tags, fetch, loc, block_table, pred, n_layers: int, pool_blocks_per_layer: int,
                                fill_half: int, omega: int, notify, work, layer_begin: int = 0, layer_end: int | None = None,
