@@ -862,14 +862,15 @@ __device__ __forceinline__ void load_to_lds16(const void* g, void* lds) {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g, (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
 }
 
-// Decoder workgroups a compute unit may hold in large calls (0: as many as fit).  With 32 waves on every compute unit and
-// pages of 5 KB and more, 160 to 256 KB per compute unit are being written at once, all over the output, and the memory
-// serves them worse than 128 to 168 KB, which four-pass pages come to by themselves.  262,144 pages, decode, us, eight
-// groups -> the number here: 16 x 160 335 -> 324, 16 x 192 399 -> 389, 16 x 224 473 -> 459, 16 x 256 541 -> 514 (4.5 KB pages
-// 297 -> 301 with six: as many as fit).  The limit is LDS that nothing uses; from 32,768 pages on, below that it
-// neither gains nor loses more than half a microsecond.
+// Decoder workgroups a compute unit may hold in large calls (0: as many as fit).  With 32 waves on every compute unit,
+// 128 KB of 4 KB pages and up to 256 KB of 8 KB pages per compute unit are being written at once, all over the output,
+// and the memory serves them worse than 96 to 168 KB.  262,144 pages, decode, us, eight groups -> the number here:
+// 16 x 160 335 -> 324, 16 x 192 399 -> 389, 16 x 224 473 -> 459, 16 x 256 541 -> 514; a million of 16 x 128 1009 -> 987, half a
+// million of mode 5 502 -> 490, a gather of 655,360 674 -> 664 (five groups 1014, seven 1002; 4.5 KB pages 297 -> 301 with
+// six: as many as fit).  The limit is LDS that nothing uses; from 32,768 pages on, below that it neither gains nor
+// loses more than half a microsecond.
 constexpr int kDecLimitPages = 32768;
-constexpr int dec_groups(int np, bool partial) { return np == 8 ? 4 : np >= 6 || (np == 5 && !partial) ? 6 : 0; }
+constexpr int dec_groups(int np, bool partial) { return np == 8 ? 4 : np >= 6 || (np >= 4 && !partial) ? 6 : 0; }
 constexpr int kLdsPerCu = 160 * 1024;
 
 // Whether INT8 payloads go through LDS too.  With several pages per wave their loads have to be under way before
@@ -877,6 +878,21 @@ constexpr int kLdsPerCu = 160 * 1024;
 // 1.5 % faster for whole launches of INT8 pages (262,144 pages of 4 KB: 285 us, 289 us through LDS).
 template <int PPW>
 constexpr bool kStageInt8 = PPW > 1;
+
+// Payloads that are read straight from the pool (INT8 ones with a page per wave, raw ones): how many passes are loaded
+// ahead of their stores.  A load waits for the stores before it, so a page takes a trip per step: all passes in one step are 2.4
+// us for a call of eight raw pages of 16 x 128, one by one 3.1; and in a transfer engine the one INT8 page of a block is
+// what the other fifteen wait for (two steps of 4,370 blocks, of whose pages 6.5 % are INT8: one by one 217 us, all 200).
+// A launch of many more pages than the chip holds moves a little faster with less in flight, but a page that dawdles
+// keeps its wave from the next: 262,144 INT8 pages of 16 x 128 273 us one by one, 264 by two, 274 all; a million pages of mode 3
+// 1008, 996, 997; a gather 686, 666, 666; raw pages 360 one by one, 376 all; INT8 pages of 16 x 256 312 one by one, 280
+// all, of 16 x 192 426 and 408, raw ones of 16 x 256 369 and 377.
+constexpr int kDecFewPages = 8192;  // 256 compute units of 32 waves
+template <class P>
+__device__ __forceinline__ bool dec_few(const DecodeArgs& a) {
+    return a.n_pages <= kDecFewPages;
+}
+constexpr int dec_int8_step(int np) { return np >= 5 ? np : 2; }
 
 // Start the payload loads of PPW pages, those of lanes first .. first + PPW - 1: the i-th goes to LDS slot i, 16
 // bytes per lane and round, without a stop in registers.  Payload bytes past the page's own are not read.
@@ -953,23 +969,18 @@ __device__ __forceinline__ void dec_headers(const Extent& x, const DecLanes& L, 
     special = __builtin_amdgcn_ballot_w64(packed && rare);
 }
 
-// Decode an INT8 payload at src (the staged copy, or the pool itself) into the page at dst_b.
-template <class P>
+// Decode an INT8 payload at src (the staged copy, or the pool itself) into the page at dst_b, STEP passes at a time.
+template <class P, int STEP>
 __device__ __forceinline__ void dec_int8(const DecodeArgs& a, const Extent& x, const LanePos& lp, float s, char* dst_b, const uint2* src) {
-    // Where the workgroups of a compute unit are limited, all loads go ahead of all stores (262,144 pages, us: 16 x 256 327 ->
-    // 280, 16 x 192 426 -> 408).  Elsewhere a pass is stored before the next is loaded, which limits what is in flight by
-    // itself (16 x 128 263, all ahead 275).
-    constexpr bool kAhead = dec_groups(P::kPasses, P::kPartial) != 0;
     uint2 v[P::kPasses];
-    if (kAhead) {
-#pragma unroll
-        for (int p = 0; p < P::kPasses; ++p)
-            if (lane_live<P>(x, p)) v[p] = src[p * 64 + lane_id()];
-    }
 #pragma unroll
     for (int p = 0; p < P::kPasses; ++p) {
+        if (p % STEP == 0) {
+#pragma unroll
+            for (int q = p; q < p + STEP && q < P::kPasses; ++q)
+                if (lane_live<P>(x, q)) v[q] = src[q * 64 + lane_id()];
+        }
         if (!lane_live<P>(x, p)) continue;
-        if (!kAhead) v[p] = src[p * 64 + lane_id()];
         const uint32_t lo = v[p].x ^ 0x80808080u, hi = v[p].y ^ 0x80808080u;  // + 128 in every byte: the sign bits change
         uint32_t pb[8];
 #pragma unroll
@@ -978,6 +989,21 @@ __device__ __forceinline__ void dec_int8(const DecodeArgs& a, const Extent& x, c
             pb[4 + k] = hi >> (8 * k);
         }
         store_out(dst_b, pass_base_off<P, false>(a.g, p), pass_lane_off<P, false>(a.g, lp, p), dequant8_biased(pb, s, -128.0f * s));
+    }
+}
+
+// Copy a raw payload, STEP passes at a time.
+template <class P, int STEP>
+__device__ __forceinline__ void dec_raw(const DecodeArgs& a, const Extent& x, const LanePos& lp, char* dst_b, const uint4* src) {
+    uint4 v[P::kPasses];
+#pragma unroll
+    for (int p = 0; p < P::kPasses; ++p) {
+        if (p % STEP == 0) {
+#pragma unroll
+            for (int q = p; q < p + STEP && q < P::kPasses; ++q)
+                if (lane_live<P>(x, q)) v[q] = src[q * 64 + lane_id()];
+        }
+        if (lane_live<P>(x, p)) store_out(dst_b, pass_base_off<P, false>(a.g, p), pass_lane_off<P, false>(a.g, lp, p), v[p]);
     }
 }
 
@@ -1086,7 +1112,7 @@ __device__ __forceinline__ void dec_page(const DecodeArgs& a, const Extent& x, c
 
 // Decode the pages whose payloads dec_fetch has loaded (dec_fetched: they are there).
 template <class P, int PPW, bool UNIFORM>
-__device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L, int first, const LanePos& lp, uint32_t (*slots)[Slot<P::kPasses>::kWords]) {
+__device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L, int first, const LanePos& lp, uint32_t (*slots)[Slot<P::kPasses>::kWords], bool few) {
     using H = HeaderDeal<P>;
     static_assert(PPW % H::kPages == 0 || PPW == 1, "a header scan covers whole pages of the batch");
     constexpr int kScan = PPW < H::kPages ? PPW : H::kPages;  // pages taken from one scan
@@ -1115,24 +1141,21 @@ __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L
             }
             char* dst_b = reinterpret_cast<char*>(dst);
             if (kind == kDecRaw) {  // stored-uncompressed bypass
-                // (a pass is stored before the next is loaded: whole launches of raw pages are 1.5 % faster so than
-                // with all loads ahead of all stores)
                 const uint4* src = reinterpret_cast<const uint4*>(a.pool + of_lane<UNIFORM>(L.off, first + i));
-#pragma unroll
-                for (int p = 0; p < P::kPasses; ++p)
-                    if (lane_live<P>(x, p)) {
-                        const uint4 v = src[p * 64 + lane_id()];
-                        store_out(dst_b, pass_base_off<P, false>(a.g, p), pass_lane_off<P, false>(a.g, lp, p), v);
-                    }
+                if (few)
+                    dec_raw<P, P::kPasses>(a, x, lp, dst_b, src);
+                else
+                    dec_raw<P, 1>(a, x, lp, dst_b, src);
                 continue;
             }
             const uint32_t mode = (meta >> 16) & 0xFFu;
             const float s = __uint_as_float(of_lane<UNIFORM>(__float_as_uint(L.s), first + i));
             if (mode == KVC_MODE_INT8) {
-                if constexpr (kStageInt8<PPW>)
-                    dec_int8<P>(a, x, lp, s, dst_b, reinterpret_cast<const uint2*>(slots[i]));
+                const uint2* src = kStageInt8<PPW> ? reinterpret_cast<const uint2*>(slots[i]) : reinterpret_cast<const uint2*>(a.pool + of_lane<UNIFORM>(L.off, first + i));
+                if (kStageInt8<PPW> || few || dec_int8_step(P::kPasses) >= P::kPasses)
+                    dec_int8<P, P::kPasses>(a, x, lp, s, dst_b, src);
                 else
-                    dec_int8<P>(a, x, lp, s, dst_b, reinterpret_cast<const uint2*>(a.pool + of_lane<UNIFORM>(L.off, first + i)));
+                    dec_int8<P, dec_int8_step(P::kPasses)>(a, x, lp, s, dst_b, src);
                 continue;
             }
             if (((special >> (j * H::kSeg)) & kSegMask) != 0)
@@ -1157,7 +1180,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_decompress(DecodeArgs a) {
     const DecLanes L = dec_open<P>(a, PPW == 1 ? dec_locate(a, t0 < a.n_pages, (uint32_t)t0) : dec_locate(a, lane < PPW && t0 + lane < a.n_pages, (uint32_t)t0 + (uint32_t)lane));
     dec_fetch<P, PPW, PPW == 1>(a, L, 0, s_stage[wave]);
     dec_fetched();
-    dec_batch<P, PPW, PPW == 1>(a, L, 0, lp, s_stage[wave]);
+    dec_batch<P, PPW, PPW == 1>(a, L, 0, lp, s_stage[wave], dec_few<P>(a));
 }
 
 // Narrow transfer engines of the prefetch window, for calls of many (Algorithm 1: at most Omega_max transfers
@@ -1220,7 +1243,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
 #endif
             dec_fetch<P, SIDE, false>(a, L, t % 64, s_stage[wave]);
             dec_fetched();
-            dec_batch<P, SIDE, false>(a, L, t % 64, lp, s_stage[wave]);
+            dec_batch<P, SIDE, false>(a, L, t % 64, lp, s_stage[wave], true);
             wave_sync();
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the slots have been read before they are filled again
         }
@@ -1360,7 +1383,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
                 }
                 b.put(s_books);
             }
-            dec_batch<P, 1, false>(a, L, t % 64, lp, s_stage[wave]);
+            dec_batch<P, 1, false>(a, L, t % 64, lp, s_stage[wave], true);
             wave_sync();
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the slots have been read before they are filled again
             if (++t >= per_block) break;

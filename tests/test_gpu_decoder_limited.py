@@ -1,4 +1,4 @@
-"""Decode calls of 32,768 pages and more, for which pages of 5 KB and more have a limit on the workgroups of a compute
+"""Decode calls of 32,768 pages and more, for which pages of 4 KB and more have a limit on the workgroups of a compute
 unit: the same bytes as calls just below that size, which have none, and as the oracle for pages of every kind."""
 import numpy as np
 import pytest
@@ -11,7 +11,7 @@ from gpu_util import DEV, fetch_pages
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("N,d", [(16, 160), (32, 96), (11, 256), (16, 224), (13, 256), (16, 256), (15, 256)])
+@pytest.mark.parametrize("N,d", [(16, 128), (32, 64), (15, 128), (16, 96), (16, 160), (32, 96), (11, 256), (16, 224), (13, 256), (16, 256), (15, 256)])
 def test_decode_calls_around_the_limit(N, d):
     n, cut = 32768 + 6, 32767
     top = 5 if N == 16 and d == 256 else 4
