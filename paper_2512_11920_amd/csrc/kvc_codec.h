@@ -868,7 +868,8 @@ __device__ __forceinline__ void load_to_lds16(const void* g, void* lds) {
 // 16 x 160 335 -> 324, 16 x 192 399 -> 389, 16 x 224 473 -> 459, 16 x 256 541 -> 514; a million of 16 x 128 1009 -> 987, half a
 // million of mode 5 502 -> 490, a gather of 655,360 674 -> 664 (five groups 1014, seven 1002; 4.5 KB pages 297 -> 301 with
 // six: as many as fit).  The limit is LDS that nothing uses; from 32,768 pages on, below that it neither gains nor
-// loses more than half a microsecond.
+// loses more than half a microsecond.  A prefetch's list of blocks to fetch leaves waves with nothing to do, and has no
+// limit (two steps of 180,000 pages of 32 x 64 168 us, with the limit 182).
 constexpr int kDecLimitPages = 32768;
 constexpr int dec_groups(int np, bool partial) { return np == 8 ? 4 : np >= 6 || (np >= 4 && !partial) ? 6 : 0; }
 constexpr int kLdsPerCu = 160 * 1024;
@@ -1448,32 +1449,36 @@ constexpr int kDecSmallPages(int np) { return 4096 * np; }
 // Encoder launch shapes of calls below the large ones: workgroups of `waves` waves with `ppw` pages each, up to `pages`
 // pages.  Such a call (a decode step's offload, a sequence's) is latency: one page per wave while the cursor bears it.
 // It serves an atomic per workgroup every 13 ns, so the more pages there are, the more have to share one -- first by
-// more waves in the workgroup, which are resident anyway, then by more pages per wave, which follow one another.  Compress
-// with a cursor reset before it, us, workgroups of four waves of 1 (up to 2,048) and of 4 or 5 pages -> these, 16 x 128:
-// 1,024 pages 13.8 -> 12.9, 2,048 17.1 -> 14.5, 4,096 18.9 -> 17.0, 8,192 22.9 -> 19.9, 16,384 31.8 -> 28.2, 32,768 50.6 ->
-// 48.8; 16 x 64, two pages per wave -> these: 8 11.3 -> 10.5, 1,024 12.3 -> 11.8, 4,096 16.2 -> 14.5, 16,384 21.3 ->
-// 20.0, 32,768 30.7 -> 27.7; 16 x 32, four -> these: 8 11.7 -> 9.9, 1,024 12.3 -> 11.4, 4,096 15.8 -> 13.2, 16,384 19.3 -> 18.7;
-// 16 x 256: 1,024 15.8 -> 15.0, 4,096 21.9 -> 20.9.
+// more waves in the workgroup, then by more pages per wave, which follow one another.  The lines lie where a shape stops
+// being resident at once (16 waves of one page: 4,096 pages, 8,192 where the kernel fits 64 registers; 8 of four pages: 16,384):
+// beyond its line it is slower than what comes next.  Compress with a cursor reset before it, us, workgroups of four
+// waves of 1 (up to 2,048) and of 4 or 5 pages -> these, 16 x 128: 1,024 pages 13.8 -> 12.9, 2,048 17.1 -> 14.5, 4,096
+// 18.9 -> 17.0, 8,192 22.9 -> 19.9, 16,384 31.8 -> 28.2 (12,288 with eight waves of four 26.3, four of four 25.2); 16 x 64, two
+// pages per wave -> these: 8 11.3 -> 10.5, 1,024 12.3 -> 11.8, 4,096 16.2 -> 14.5, 16,384 21.3 -> 20.0; 16 x 32, four ->
+// these: 8 11.7 -> 9.9, 1,024 12.3 -> 11.4, 4,096 15.8 -> 13.2, 16,384 19.3 -> 18.7; 16 x 256: 1,024 15.8 -> 15.0, 4,096
+// 21.9 -> 20.9; a mode per block: 16 x 96 4,096 24.1 -> 15.4, 16 x 64 8,192 25.3 -> 18.2, 16 x 128 8,192 28.3 -> 25.0.
 struct EncTier {
     int pages, waves, ppw;
 };
-constexpr int kEncTiers = 4;
+constexpr int kEncTiers = 5;
 constexpr EncTier enc_tier(int np, int scheme, int i) {
     constexpr EncTier none = {0, 4, 1};
-    constexpr EncTier one[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {16384, 16, 2}, {32768, 16, 4}};  // one pass
-    constexpr EncTier two[kEncTiers] = {{512, 4, 1}, {2048, 8, 1}, {16384, 16, 2}, {32768, 16, 4}};
-    constexpr EncTier four[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {8192, 16, 1}, {32768, 8, 4}};  // three and four
-    constexpr EncTier pairs[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {6144, 16, 1}, {32768, 8, 4}};  // four, mode 5
-    constexpr EncTier six[kEncTiers] = {{512, 4, 1}, {3072, 8, 1}, none, none};                    // five and six
-    constexpr EncTier more[kEncTiers] = {{512, 4, 1}, {4096, 8, 1}, none, none};
-    // (with the mode read at run time the last one is slower at two passes -- 7 x 128, 32,768 pages, 31.9 us, 36.1 --, and the
-    // register sets of three and four do not go four times)
-    if (i == 3 && ((scheme < 0 && np >= 2) || np == 3)) return none;
-    return np == 1 ? one[i] : np == 2 ? two[i] : np == 4 && scheme == KVC_MODE_CHAN ? pairs[i] : np <= 4 ? four[i] : np <= 6 ? six[i] : more[i];
+    constexpr EncTier one[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {16384, 16, 2}, {32768, 16, 4}, none};  // one pass
+    constexpr EncTier two[kEncTiers] = {{512, 4, 1}, {2048, 8, 1}, {16384, 16, 2}, none, none};
+    constexpr EncTier three[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {8192, 16, 1}, none, none};  // and four, the mode read at run time
+    constexpr EncTier four[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {8192, 16, 1}, {13312, 4, 4}, {16384, 8, 4}};
+    constexpr EncTier pairs[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {4096, 16, 1}, {13312, 4, 4}, {32768, 8, 4}};  // four, mode 5
+    constexpr EncTier six[kEncTiers] = {{512, 4, 1}, {3072, 8, 1}, none, none, none};                          // five and six
+    constexpr EncTier more[kEncTiers] = {{512, 4, 1}, {4096, 8, 1}, none, none, none};
+    return np == 1 ? one[i] : np == 2 ? two[i] : np == 3 || (np == 4 && scheme < 0) ? three[i] : np == 4 ? (scheme == KVC_MODE_CHAN ? pairs[i] : four[i]) : np <= 6 ? six[i] : more[i];
 }
-// Plain INT8 and raw calls encode faster and are at the cursor sooner: from here on they take the large shapes (16 x 128,
-// INT8, 4,096 pages 14.7 us against 15.8, 8,192 18.8 against 20.8; 16 x 32, 16,384 pages 16.7 against 18.0).
-constexpr int enc_plain_pages(int np) { return np <= 2 ? 8192 : 2048; }
+// Where the mode is read at run time but is the same for all blocks, the large shapes are reached earlier: the pages of a
+// workgroup are then done together, and plain INT8 and raw ones soon (16 x 128, 4,096 INT8 pages 14.7 us against 15.8, 5,120 of
+// mode 2 or 4 19.0 against 22.0; 16 x 32, 16,384 INT8 pages 16.7 against 18.0).
+constexpr int enc_uniform_pages(int np, int scheme) {
+    const bool plain = scheme == KVC_MODE_RAW || scheme == KVC_MODE_INT8;
+    return plain ? (np <= 2 ? 8192 : 2048) : np == 4 ? 4096 : 1 << 30;
+}
 
 inline dim3 page_grid(int64_t n_pages, int ppw, int waves = kCodecWaves) {
     const int64_t per_wg = (int64_t)waves * ppw;
@@ -1500,10 +1505,9 @@ struct ShapeOps {
     template <int SCHEME>
     static hipError_t compress_scheme(const EncodeArgs& a, hipStream_t s) {
         hipError_t r = hipSuccess;
-        const bool plain = SCHEME < 0 && a.block_scheme == nullptr && (a.scheme == KVC_MODE_RAW || a.scheme == KVC_MODE_INT8) && a.n_pages > enc_plain_pages(NP);
-        if (plain) {
+        if (SCHEME < 0 && a.block_scheme == nullptr && a.n_pages > enc_uniform_pages(NP, a.scheme)) {
             // large
-        } else if (compress_tier<SCHEME, 0>(a, s, r) || compress_tier<SCHEME, 1>(a, s, r) || compress_tier<SCHEME, 2>(a, s, r) || compress_tier<SCHEME, 3>(a, s, r)) {
+        } else if (compress_tier<SCHEME, 0>(a, s, r) || compress_tier<SCHEME, 1>(a, s, r) || compress_tier<SCHEME, 2>(a, s, r) || compress_tier<SCHEME, 3>(a, s, r) || compress_tier<SCHEME, 4>(a, s, r)) {
             return r;
         }
         constexpr EncShape e = enc_large(NP, SCHEME);
@@ -1541,7 +1545,7 @@ struct ShapeOps {
         constexpr int limit = groups ? kLdsPerCu / groups - 1280 - own : 0;  // (1,280: room for the allocation's granularity)
         static_assert(limit >= 0 && (groups == 0 || own + limit > kLdsPerCu / (groups + 1)), "one group more does not fit");
         return launch_kernel_lds(k_decompress<P, kCodecWaves, dec_ppw(NP)>, page_grid(a.n_pages, dec_ppw(NP)), dim3(kCodecWaves * 64),
-                                 a.n_pages >= kDecLimitPages ? limit : 0, s, a);
+                                 a.n_pages >= kDecLimitPages && !a.sparse ? limit : 0, s, a);
     }
 
     static hipError_t decompress_window(const DecodeArgs& a, const WindowArgs& w, unsigned grid, bool wide, hipStream_t s) {
