@@ -1261,11 +1261,13 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
 // meeting after each -- no payload of a block is asked for before the last store of the engine's block before has
 // reached memory.  An engine is latency, not bandwidth: few of them are at work, each on one block.  So the waves share a
 // block's pages as far as they go round (there is one for each of 16), and what leads to a payload -- ticket, queue entry, pool block, descriptors, four trips one after the other -- is
-// walked ahead of the payloads by one of the waves, the clerk, a trip per block: while block i is decoded it asks for
-// the descriptors of block i + 1 (a page per lane), the pool block of i + 2, the queue entry of i + 3 and, where its run
-// ends, the next run.  It also keeps the books.  (Done by every wave, the few hundred instructions of it cost an engine
-// half a microsecond per block; done for a whole run when the run before had ended, a tenth of the time of 256 engines
-// went into the four trips.)
+// walked ahead of the payloads by one of the waves, the clerk, a trip per block: while the payloads of block i are on their
+// way it asks for the descriptors of block i + 1 (a page per lane), the pool block of i + 2, the queue entry of i + 3 and,
+// where its run ends, the next run; while block i is decoded it publishes block i + 1 and keeps the books.  Two steps of
+// 4,370 blocks of 16 pages of 16 x 128, us, 256 / 16 engines: 230 / 2,090 with the trips walked for a run at a time, when the
+// run before had ended; 238 / 2,342 looked ahead for by every wave (a few hundred instructions in 16 waves); 217 / 2,017 by
+// a clerk; and of its last form, with INT8 pages loaded ahead, 200 / 2,009 when it published between the barriers and
+// 196 / 1,909 now.
 // (pages of up to four passes whose rows do not cross passes: held within 128 VGPRs, so that four waves fit a SIMD)
 template <class P, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::kPasses <= 4 && P::kAligned ? 4 : 1))) void k_decompress_window_wide(WindowParams params) {
@@ -1279,7 +1281,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
 #if KVC_DEBUG_BOUNDS
     __shared__ uint32_t s_done;  // waves that have finished a block, summed over the engine's blocks
     if (threadIdx.x == 0) s_done = 0;
-    uint32_t behind = 0;  // blocks behind this wave
+    uint32_t behind = 0;  // meetings behind this wave
 #endif
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1300,120 +1302,106 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
         return pl;
     };
 
-    // what the clerk has asked for
-    uint4 asked = make_uint4(0u, 0u, 0u, 0u);
-    uint32_t ticket = 0, was_pending = 0;
-    int32_t slot_asked = -1, pb_asked = -1;
-    long long rep_at = 0;
     auto clerk_task = [&](int32_t slot, int32_t pb) { return page_task(looked_up && slot >= 0, lane, slot, pb); };
-    // The waves meet with all their stores of the block in memory, the clerk publishes the next, and they meet again.
-    // (The single-wave part lies inside the loop body and not across its back edge, and the loop and its exit branch on
-    // the scalar unit: every wave meets every barrier with all of its lanes.  With single-lane work at both ends of the
-    // loop body the compiler merges it across the back edge into an outer loop and lets the other lanes run ahead to the
-    // next barrier: the workgroup then never meets.)
+    // the clerk: what the waves are to do next
     auto publish = [&](const DecLanes& pages, int32_t next_slot, int32_t next_pb) {
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), the other counters unchanged
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __syncthreads();
-        if (clerk) {
-            s_page[lane] = make_uint4((uint32_t)pages.off, (uint32_t)(pages.off >> 32), __float_as_uint(pages.s), pages.meta);
-            if (lane == 0) {
-                s_block[0] = next_slot;
-                s_block[1] = next_pb;
-            }
+        s_page[lane] = make_uint4((uint32_t)pages.off, (uint32_t)(pages.off >> 32), __float_as_uint(pages.s), pages.meta);
+        if (lane == 0) {
+            s_block[0] = next_slot;
+            s_block[1] = next_pb;
         }
-        __syncthreads();
     };
-    DecLanes pages = {};
-    int32_t next_slot = -1, next_pb = -1;
     if (clerk) {
-        __builtin_amdgcn_s_setprio(3);  // whatever it does beside its pages, the others wait for
+        __builtin_amdgcn_s_setprio(3);  // whatever it does beside its pages, the others wait for (217 us, without 229)
         const WindowParams& k = params_again<WindowParams>();
         auto slot_of = [&](uint32_t i) { return i == kWindowNone ? -1 : wave_uniform(k.w.queue[i]); };
         auto block_of = [&](int32_t slot) { return slot < 0 ? -1 : wave_uniform(k.a.pool_ids[slot]); };
         WindowBooks b;
         b.open_at(k.w.hdr->n_issued, blockIdx.x, engines, k.w.hdr->chunk);
-        next_slot = slot_of(b.take());  // (engines <= n_issued: there is a first)
+        const int32_t slot0 = slot_of(b.take());  // (engines <= n_issued: there is a first)
         b.slot1 = slot_of(b.take());
         b.slot2 = slot_of(b.take());
-        next_pb = block_of(next_slot);
+        const int32_t pb0 = block_of(slot0);
         b.pb1 = block_of(b.slot1);
-        b.layer = b.layer_of(k.w, next_slot);
+        b.layer = b.layer_of(k.w, slot0);
         b.put(s_books);
-        pages = dec_open<P>(k.a, clerk_task(next_slot, next_pb));
+        publish(dec_open<P>(k.a, clerk_task(slot0, pb0)), slot0, pb0);
     }
-    publish(pages, next_slot, next_pb);
-    int32_t slot = wave_uniform(s_block[0]);
+    // The loop and its exit branch on the scalar unit, and the single-wave and single-lane parts lie in the middle of its
+    // body: every wave meets every barrier with all of its lanes.  (With single-lane work at both ends of the loop body the
+    // compiler merges it across the back edge into an outer loop and lets the other lanes run ahead to the next barrier:
+    // the workgroup then never meets.)  Of the two barriers per block the first says that the clerk has published
+    // the next block (and that the block before has been read), the second that all stores of this one are in memory.
+    int32_t slot = -1, pb = -1;
+    DecLanes L;
+    // page tasks t .. t + 63 of the block, one per lane
+    auto lanes = [&](int t) {
+        const int pg = wave + (t + lane) * WAVES;
+        if (!looked_up) return dec_open<P>(params_again<WindowParams>().a, page_task(t + lane < per_block, pg, slot, pb));
+        const uint4 v = s_page[min(pg, kClerkPages - 1)];
+        DecLanes r;
+        r.off = (uint64_t)v.x | ((uint64_t)v.y << 32);
+        r.s = __uint_as_float(v.z);
+        r.meta = pg < ppb && slot >= 0 ? v.w : 0u;
+        r.pg = (uint32_t)pg;
+        r.db = slot;
+        return r;
+    };
+    auto meet = [&]() {
+        __syncthreads();
+        slot = wave_uniform(s_block[0]);
+        pb = wave_uniform(s_block[1]);
+        L = lanes(0);
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), the other counters unchanged
+#if KVC_DEBUG_BOUNDS
+        if (lane == 0) atomicAdd(&s_done, 1u);
+#endif
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __syncthreads();
+    };
+    meet();
     while (slot >= 0) {
-        const int32_t pb = wave_uniform(s_block[1]);
-        // page tasks t .. t + 63 of the block, one per lane
-        auto lanes = [&](int t) {
-            const int pg = wave + (t + lane) * WAVES;
-            if (!looked_up) return dec_open<P>(params_again<WindowParams>().a, page_task(t + lane < per_block, pg, slot, pb));
-            const uint4 v = s_page[min(pg, kClerkPages - 1)];
-            DecLanes r;
-            r.off = (uint64_t)v.x | ((uint64_t)v.y << 32);
-            r.s = __uint_as_float(v.z);
-            r.meta = pg < ppb ? v.w : 0u;
-            r.pg = (uint32_t)pg;
-            r.db = slot;
-            return r;
-        };
-        DecLanes L = lanes(0);
+#if KVC_DEBUG_BOUNDS
+        ++behind;
+#endif
         for (int t = 0;;) {
 #if KVC_DEBUG_BOUNDS
             KVC_CHECK(a.st, *(volatile uint32_t*)&s_done >= behind * WAVES);
 #endif
             dec_fetch<P, 1, false>(a, L, t % 64, s_stage[wave]);
-            dec_fetched();
             if (t == 0 && clerk) {
                 const WindowParams& k = params_again<WindowParams>();
                 WindowBooks b;
                 b.get(s_books);
-                asked = dec_ask(k.a, clerk_task(b.slot1, b.pb1));
-                pb_asked = b.slot2 < 0 ? -1 : k.a.pool_ids[b.slot2];
+                const uint4 asked = dec_ask(k.a, clerk_task(b.slot1, b.pb1));
+                int32_t pb2 = b.slot2 < 0 ? -1 : k.a.pool_ids[b.slot2];
                 const uint32_t i3 = b.take();
-                slot_asked = i3 == kWindowNone ? -1 : k.w.queue[i3];
-                b.run = b.next_run();
+                int32_t slot3 = i3 == kWindowNone ? -1 : k.w.queue[i3];
+                const uint32_t run = b.next_run();
+                uint32_t ticket = 0;
                 if (lane == 0) {
-                    if (b.run) ticket = atomicAdd(&k.w.hdr->ticket, b.run);
+                    if (run) ticket = atomicAdd(&k.w.hdr->ticket, run);
                     if (b.rep) {
-                        rep_at = max(wall_clock64(), 1ll);  // read before the blocks are counted
-                        was_pending = (uint32_t)atomicSub(&k.w.pending[b.rep_layer], (int)b.rep);
+                        const long long now = max(wall_clock64(), 1ll);  // read before the blocks are counted
+                        if (atomicSub(&k.w.pending[b.rep_layer], (int)b.rep) == (int)b.rep) window_stamp(&k.w.notify[k.w.layer_begin + (int32_t)b.rep_layer], now);
                     }
                 }
+                if (run) b.refill((uint32_t)wave_uniform((int32_t)ticket), run);
+                publish(dec_check<P>(k.a, clerk_task(b.slot1, b.pb1), asked), b.slot1, b.pb1);
+                b.block_done(k.w);
+                b.slot1 = b.slot2;
+                b.slot2 = wave_uniform(slot3);
+                b.pb1 = wave_uniform(pb2);
                 b.put(s_books);
             }
+            dec_fetched();
             dec_batch<P, 1, false>(a, L, t % 64, lp, s_stage[wave], true);
             wave_sync();
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the slots have been read before they are filled again
             if (++t >= per_block) break;
             if (t % 64 == 0) L = lanes(t);
         }
-#if KVC_DEBUG_BOUNDS
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-        if (lane == 0) atomicAdd(&s_done, 1u);
-#endif
-        if (clerk) {
-            const WindowParams& k = params_again<WindowParams>();
-            WindowBooks b;
-            b.get(s_books);
-            if (lane == 0 && b.rep && was_pending == b.rep) window_stamp(&k.w.notify[k.w.layer_begin + (int32_t)b.rep_layer], rep_at);
-            if (b.run) b.refill((uint32_t)wave_uniform((int32_t)ticket));
-            next_slot = b.slot1;
-            next_pb = b.pb1;
-            b.block_done(k.w);
-            b.slot1 = b.slot2;
-            b.slot2 = wave_uniform(slot_asked);
-            b.pb1 = wave_uniform(pb_asked);
-            b.put(s_books);
-            pages = dec_check<P>(k.a, clerk_task(next_slot, next_pb), asked);
-        }
-        publish(pages, next_slot, next_pb);
-        slot = wave_uniform(s_block[0]);
-#if KVC_DEBUG_BOUNDS
-        ++behind;
-#endif
+        meet();
     }
     if (clerk && lane == 0) {
         const WindowArgs& w = params_again<WindowParams>().w;

@@ -391,7 +391,6 @@ struct WindowBooks {
     uint32_t n_issued, engines;
     uint32_t next, left, step, size;
     uint32_t open;            // the queue may hold more than the known run
-    uint32_t run;             // entries asked for
     int32_t slot1, slot2;     // slots of the two blocks after the one at work (-1: none),
     int32_t pb1;              // and the pool block of the first
     uint32_t mine;            // blocks completed,
@@ -420,7 +419,7 @@ struct WindowBooks {
         step = rows ? 1u : n_engines;
         size = chunk;
         open = 1;
-        run = mine = acc = rep = rep_layer = 0;
+        mine = acc = rep = rep_layer = 0;
     }
     __device__ __forceinline__ uint32_t take() {
         if (left == 0) return kWindowNone;
@@ -438,7 +437,7 @@ struct WindowBooks {
         while (size > 1 && rest < 2u * engines * size) size >>= 1;
         return size;
     }
-    __device__ __forceinline__ void refill(uint32_t ticket) {
+    __device__ __forceinline__ void refill(uint32_t ticket, uint32_t run) {
         open = ticket < n_issued ? 1u : 0u;
         next = ticket;
         left = open ? min(run, n_issued - ticket) : 0u;
