@@ -361,7 +361,6 @@ static int prefetch_impl(kvc_ctx* ctx, void* d_l2, int32_t* d_tags, int32_t* d_f
     p.fetch = d_fetch;
     p.loc = d_loc;
     p.st = ctx->st;
-    if (!hip_ok(kvc::launch_prefetch_plan(p, s))) return KVC_ERR_HIP;
     // decode the listed pool blocks into their slots of the half being filled; slots are blocks of the
     // cache layout in force (block_stride elements apart)
     const int64_t first = (int64_t)layer_begin * n_seq * k;
@@ -372,7 +371,7 @@ static int prefetch_impl(kvc_ctx* ctx, void* d_l2, int32_t* d_tags, int32_t* d_f
     a.pool_ids = d_fetch + first;
     a.sparse = 1;
     a.n_pages = n_now * ctx->g.ppb;
-    if (omega == 0) return hip_ok(kvc::launch_decompress(a, s)) ? KVC_OK : KVC_ERR_HIP;
+    if (omega == 0) return hip_ok(kvc::launch_prefetch_plan(p, s)) && hip_ok(kvc::launch_decompress(a, s)) ? KVC_OK : KVC_ERR_HIP;
     // engines beyond what the device holds at once would never get a turn: the bound stays "at most omega"
     if (ctx->window_capacity > 0) omega = std::min(omega, ctx->window_capacity);
     kvc::WindowArgs w;
@@ -390,8 +389,7 @@ static int prefetch_impl(kvc_ctx* ctx, void* d_l2, int32_t* d_tags, int32_t* d_f
     w.omega = omega;
     w.wide = ctx->wide_capacity > 0 && std::min<int64_t>(omega, n_now) <= ctx->wide_capacity ? 1 : 0;
     w.notify = d_notify;
-    if (!hip_ok(kvc::launch_window_build(w, s))) return KVC_ERR_HIP;
-    return hip_ok(kvc::launch_decompress_window(a, w, s)) ? KVC_OK : KVC_ERR_HIP;
+    return hip_ok(kvc::launch_window_plan(p, w, s)) && hip_ok(kvc::launch_decompress_window(a, w, s)) ? KVC_OK : KVC_ERR_HIP;
 }
 
 int kvc_prefetch_layers(kvc_ctx* ctx, void* d_l2, int32_t* d_tags, int32_t* d_fetch, int32_t* d_loc,

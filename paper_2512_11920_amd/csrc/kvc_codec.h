@@ -1260,8 +1260,9 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
 // workgroup takes issued blocks from the queue in runs, its waves decode them one block after the other,
 // meeting after each -- no payload of a block is asked for before the last store of the engine's block before has
 // reached memory.  An engine is latency, not bandwidth: few of them are at work, each on one block.  So the waves share a
-// block's pages as far as they go round (there is one for each of 16), and what leads to a payload -- ticket, queue entry, pool block, descriptors, four trips one after the other -- is
-// walked ahead of the payloads by one of the waves, the clerk, a trip per block: while the payloads of block i are on their
+// block's pages as far as they go round (there is one for each of 16), and what leads to a payload -- ticket, queue entry,
+// pool block, descriptors, four trips one after the other -- is walked ahead of the payloads by one of the waves, the clerk,
+// a trip per block: while the payloads of block i are on their
 // way it asks for the descriptors of block i + 1 (a page per lane), the pool block of i + 2, the queue entry of i + 3 and,
 // where its run ends, the next run; while block i is decoded it publishes block i + 1 and keeps the books.  Two steps of
 // 4,370 blocks of 16 pages of 16 x 128, us, 256 / 16 engines: 230 / 2,090 with the trips walked for a run at a time, when the
@@ -1419,9 +1420,10 @@ constexpr int kCodecWaves = 4;
 // device holds of the wide kind -- one per compute unit, 256, at 16 x 128; two where the kernel fits 64 vector registers --
 // have engines of 16 waves; the others have engines of four waves, with several pages of a block per wave in flight, of
 // which four to seven fit a compute unit.  Two prefetch steps of 2,048 blocks of 16 pages of 16 x 128, us, four-wave
-// engines / wide engines, all else alike: 64 engines 498 / 320, 256 engines 160 / 121; blocks of two pages, where most
-// waves of a wide engine have none, 735 / 748 with 64 engines.  (The choice is made before the transfers are counted: an
-// omega above the wide kind's number with few transfers runs 256 narrow engines, 161 us in the first example.)
+// engines / wide engines that fetched a run at a time, all else alike: 64 engines 498 / 320, 256 engines 160 / 121; blocks of
+// two pages, where most waves of a wide engine have none, 735 / 748 with 64 engines (wide engines have gained a sixth
+// to a quarter since).  (The choice is made before the transfers are counted: an omega above the wide kind's number with few
+// transfers runs 256 narrow engines.)
 constexpr int kWideWaves = 16;
 constexpr int window_side(int np) { return np <= 4 ? 4 : 2; }
 // Pages per decoder wave: a page of one or two passes is too small to cover its own memory chain, so a wave

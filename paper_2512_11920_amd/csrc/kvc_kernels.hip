@@ -81,17 +81,14 @@ __global__ __launch_bounds__(kThreads) void k_copy(uint4* __restrict__ dst, cons
 // and tags first, then the table entries.  The walk over the predictions then runs on ballots.  (With a thread per
 // (layer, sequence) that translated its k predictions behind branches the planner took 10.5 us for 64 sequences of
 // 8 -- as long as the decode launch it plans.)
+//
+// plan_row: one row per KMAX lanes, layer l and sequence sq (in range where `there`); -> whether this lane's slot is fetched.
 template <int KMAX>
-__global__ __launch_bounds__(64) void k_prefetch_plan(PlanArgs a) {
+__device__ __forceinline__ bool plan_row(const PlanArgs& a, bool there, int32_t l, int32_t sq) {
     const int lane = lane_id();
     const int j = lane % KMAX;
-    const uint32_t row = blockIdx.x * (64u / KMAX) + (uint32_t)(lane / KMAX);  // rows of one call fit 31 bits
-    const uint32_t rows = (uint32_t)(a.layer_end - a.layer_begin) * (uint32_t)a.n_seq;
     const int k = a.k;
-    const bool live = row < rows && j < k;
-    const uint32_t l_rel = fast_div(row, a.by_n_seq);
-    const int32_t l = a.layer_begin + (int32_t)l_rel;
-    const int32_t sq = (int32_t)(row - l_rel * (uint32_t)a.n_seq);
+    const bool live = there && j < k;
     const int64_t n_slots = (int64_t)a.n_layers * a.n_seq * k;
     const int64_t base = ((int64_t)l * a.n_seq + sq) * k;
     const int64_t fill0 = (int64_t)a.fill_half * n_slots + base, other0 = (int64_t)(1 - a.fill_half) * n_slots + base;
@@ -167,13 +164,39 @@ __global__ __launch_bounds__(64) void k_prefetch_plan(PlanArgs a) {
         if (fetch >= 0) a.tags[fill0 + j] = t_fill;
     }
     if (bad) atomicOr(&a.st->status, KVC_ST_BAD_INDEX);
+    return live && fetch >= 0;
+}
+
+template <int KMAX>
+__global__ __launch_bounds__(64) void k_prefetch_plan(PlanArgs a) {
+    const uint32_t row = blockIdx.x * (64u / KMAX) + (uint32_t)(lane_id() / KMAX);  // rows of one call fit 31 bits
+    const uint32_t rows = (uint32_t)(a.layer_end - a.layer_begin) * (uint32_t)a.n_seq;
+    const uint32_t l_rel = fast_div(row, a.by_n_seq);
+    plan_row<KMAX>(a, row < rows, a.layer_begin + (int32_t)l_rel, (int32_t)(row - l_rel * (uint32_t)a.n_seq));
+}
+
+// The planner of a window call of few sequences: a workgroup per layer, which then knows the layer's transfers and saves the
+// launch that counts them (two steps of 20 layers x 32 sequences x 8, omega 256: 196.5 us, with the count apart, 194; of two
+// layers 42.4 and 40.8).
+template <int KMAX>
+__global__ __launch_bounds__(256) void k_prefetch_plan_count(PlanArgs a, int32_t* pending) {
+    __shared__ uint32_t s_cnt[4];
+    uint32_t n = 0;
+    for (int q0 = 0; q0 < a.n_seq; q0 += 256 / KMAX) {
+        const int32_t sq = q0 + (int32_t)threadIdx.x / KMAX;
+        n += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(plan_row<KMAX>(a, sq < a.n_seq, a.layer_begin + (int32_t)blockIdx.x, sq)));
+    }
+    if (lane_id() == 0) s_cnt[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) pending[blockIdx.x] = (int32_t)(s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3]);
 }
 
 // Opens the outstanding-request window of a prefetch call: the transfers the planner issued (entries
 // >= 0 of the call's part of the fetch list) are queued in issue order -- layer, sequence, slot -- each
 // layer's count becomes its pending counter, and the notification words are reset: a layer with nothing
 // to transfer is ready at once, the others when their last transfer completes.  Two launches, one
-// workgroup per layer each: count, then place (a layer's entries begin where the layers before it end).
+// workgroup per layer each: count (unless the planner has), then place (a layer's entries begin where the layers before
+// it end).
 __global__ __launch_bounds__(256) void k_window_count(WindowArgs w) {
     __shared__ uint32_t s_cnt[4];
     const int l = blockIdx.x;
@@ -303,11 +326,26 @@ hipError_t launch_prefetch_plan(const PlanArgs& a, hipStream_t s) {
     return launch_kernel(k_prefetch_plan<kMaxPrefetchK>, grid(2), dim3(64), s, a);
 }
 
-hipError_t launch_window_build(const WindowArgs& w, hipStream_t s) {
+// Plan a window call and open its window.  The planner counts too where a layer's rows are at most four rounds of its one
+// workgroup; more of them are better spread over the chip.
+hipError_t launch_window_plan(const PlanArgs& a, const WindowArgs& w, hipStream_t s) {
     if (w.n_layers_call <= 0) return hipSuccess;
-    const hipError_t e = launch_kernel(k_window_count, dim3((unsigned)w.n_layers_call), dim3(256), s, w);
+    const dim3 layers((unsigned)w.n_layers_call);
+    const int lanes = a.k <= 8 ? 8 : a.k <= 16 ? 16 : kMaxPrefetchK;
+    hipError_t e;
+    if ((int64_t)a.n_seq * lanes <= 1024) {
+        if (a.k <= 8)
+            e = launch_kernel(k_prefetch_plan_count<8>, layers, dim3(256), s, a, w.pending);
+        else if (a.k <= 16)
+            e = launch_kernel(k_prefetch_plan_count<16>, layers, dim3(256), s, a, w.pending);
+        else
+            e = launch_kernel(k_prefetch_plan_count<kMaxPrefetchK>, layers, dim3(256), s, a, w.pending);
+    } else {
+        e = launch_prefetch_plan(a, s);
+        if (e == hipSuccess) e = launch_kernel(k_window_count, layers, dim3(256), s, w);
+    }
     if (e != hipSuccess) return e;
-    return launch_kernel(k_window_place, dim3((unsigned)w.n_layers_call), dim3(256), s, w);
+    return launch_kernel(k_window_place, layers, dim3(256), s, w);
 }
 
 // At most omega workgroups, one block in flight each; the queue may turn out shorter than the grid, in
