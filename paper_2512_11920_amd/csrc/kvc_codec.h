@@ -1408,9 +1408,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
         const WindowArgs& w = params_again<WindowParams>().w;
         const WindowBooks& b = s_books;
         if (b.rep && atomicSub(&w.pending[b.rep_layer], (int)b.rep) == (int)b.rep) window_stamp(&w.notify[w.layer_begin + (int32_t)b.rep_layer], max(wall_clock64(), 1ll));
-        // WaitCompletion returns: NotifyGPU(ready).  The last engine to leave reads this clock after the last block was
-        // counted, and every engine wrote its layer stamps before it reported its blocks: the stamp is the latest of the call.
-        if (atomicAdd(&w.hdr->done, b.mine) + b.mine == w.hdr->n_issued) window_stamp(&w.notify[w.n_layers + 3], max(wall_clock64(), 1ll));
+        window_leave(w, b.mine, w.hdr->n_issued);
     }
 }
 

@@ -299,6 +299,15 @@ __device__ __forceinline__ DecPlace dec_locate(const DecodeArgs& a, bool live, u
 __device__ __forceinline__ void window_stamp(long long* at, long long clock) {
     __hip_atomic_store(at, clock, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// An engine leaves: it reports its `mine` blocks, its layer stamps being in memory by then, and the last one to leave closes
+// the window (WaitCompletion returns: NotifyGPU(ready)).  So whoever sees the closing stamp sees every layer's, and its clock,
+// read after the last block was counted, is the latest of the call.  (Without the wait the count moved while a stamp
+// of this lane was still on its way, and another engine could close the window ahead of it.)
+__device__ __forceinline__ void window_leave(const WindowArgs& w, uint32_t mine, uint32_t n_issued) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), the other counters unchanged
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    if (atomicAdd(&w.hdr->done, mine) + mine == n_issued) window_stamp(&w.notify[w.n_layers + 3], max(wall_clock64(), 1ll));
+}
 
 // ---- narrow engines: turn by turn
 
@@ -352,11 +361,7 @@ __device__ __forceinline__ WindowTurn window_next(const WindowArgs& w, uint32_t*
                     window_stamp(&w.notify[w.layer_begin + (int32_t)l_rel], finished);
                 i += n;
             }
-            // WaitCompletion returns: NotifyGPU(ready).  The last engine to leave reads this clock after the last
-            // block was counted, and every engine wrote its layer stamps before it reported its blocks: the stamp
-            // is the latest of the call.
-            if (t >= n_issued && atomicAdd(&w.hdr->done, mine) + mine == n_issued)
-                window_stamp(&w.notify[w.n_layers + 3], max(wall_clock64(), 1ll));
+            if (t >= n_issued) window_leave(w, mine, n_issued);
         }
         s_turn[0] = t;
         s_turn[1] = t < n_issued ? min(chunk, n_issued - t) : 0u;

@@ -14,7 +14,10 @@ late, one wait state has to pass before they are written again, and the compiler
 scalar offset; without it lanes store what the next instructions compute.
 
 (4) The window's engines write pages through the XCD's L2 (device scope): a block is published by waiting for its
-stores, and a store without that scope would leave a consumer that polls the ready stamp with stale bytes."""
+stores, and a store without that scope would leave a consumer that polls the ready stamp with stale bytes.
+
+(5) An engine counts itself out of the window only when its layer stamps are in memory: whoever sees the stamp that closes
+the window may read the stamps of all layers."""
 import concurrent.futures
 import os
 import re
@@ -88,6 +91,31 @@ def test_window_engines_write_pages_through_to_memory(asm):
             for op, args in stores:
                 assert op == "buffer_store_dwordx4" and "sc1" in args, f"{kernel}: {op} {' '.join(args)}"
     assert seen >= 2 * (64 + 16), "wide and narrow engines of every page shape"
+
+
+def _waits_for_memory(lines, i):
+    """Whether the instruction at line i stands behind an s_waitcnt vmcnt(0), with no access to memory and no place that is
+    jumped to in between."""
+    for l in reversed(lines[:i]):
+        if re.search(r"^\s*s_waitcnt\b.*vmcnt\(0\)", l):
+            return True
+        if re.match(r"\.LBB", l) or re.match(r"\s*(?:global|buffer|flat|scratch)_", l) or "s_barrier" in l:
+            return False
+    return False
+
+
+def test_engines_leave_the_window_after_their_stamps(asm):
+    seen = 0
+    for name, text in asm.items():
+        for kernel, body in _kernels(text, "k_decompress_window"):
+            lines = body.split("\n")
+            counts = [i for i, l in enumerate(lines) if re.match(r"\s*global_atomic_add v\d+, .*offset:128 sc0", l)]  # hdr->done
+            assert counts, f"{kernel}: no count of completed blocks"
+            stamps = [l for l in lines if re.match(r"\s*global_store_dwordx2 .*sc1", l)]
+            assert len(stamps) >= 2, f"{kernel}: a layer's stamp and the closing one"
+            assert all(_waits_for_memory(lines, i) for i in counts), f"{kernel}: blocks counted with stores in flight"
+            seen += 1
+    assert seen >= 2 * (64 + 16)
 
 
 def test_window_engines_keep_their_barriers_out_of_nested_loops(asm):
