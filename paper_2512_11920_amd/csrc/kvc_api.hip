@@ -241,7 +241,6 @@ static void fill_decode_common(kvc_ctx* ctx, kvc::DecodeArgs& a) {
     a.st = ctx->st;
     a.pool_ids = nullptr;
     a.dst_ids = nullptr;
-    a.sparse = 0;
     a.block_table = nullptr;
     a.pred = nullptr;
     a.max_blocks = a.n_seq = a.k = a.n_layers = 0;
@@ -369,7 +368,6 @@ static int prefetch_impl(kvc_ctx* ctx, void* d_l2, int32_t* d_tags, int32_t* d_f
     a.out = static_cast<uint16_t*>(d_l2) + ((int64_t)fill_half * n_slots + first) * ctx->g.block_stride;
     a.n_out_blocks = n_now;
     a.pool_ids = d_fetch + first;
-    a.sparse = 1;
     a.n_pages = n_now * ctx->g.ppb;
     if (omega == 0) return hip_ok(kvc::launch_prefetch_plan(p, s)) && hip_ok(kvc::launch_decompress(a, s)) ? KVC_OK : KVC_ERR_HIP;
     // engines beyond what the device holds at once would never get a turn: the bound stays "at most omega"

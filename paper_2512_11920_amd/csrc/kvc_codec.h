@@ -866,10 +866,12 @@ __device__ __forceinline__ void load_to_lds16(const void* g, void* lds) {
 // 128 KB of 4 KB pages and up to 256 KB of 8 KB pages per compute unit are being written at once, all over the output,
 // and the memory serves them worse than 96 to 168 KB.  262,144 pages, decode, us, eight groups -> the number here:
 // 16 x 160 335 -> 324, 16 x 192 399 -> 389, 16 x 224 473 -> 459, 16 x 256 541 -> 514; a million of 16 x 128 1009 -> 987, half a
-// million of mode 5 502 -> 490, a gather of 655,360 674 -> 664 (five groups 1014, seven 1002; 4.5 KB pages 297 -> 301 with
-// six: as many as fit).  The limit is LDS that nothing uses; from 32,768 pages on, below that it neither gains nor
-// loses more than half a microsecond.  A prefetch's list of blocks to fetch leaves waves with nothing to do, and has no
-// limit (two steps of 180,000 pages of 32 x 64 168 us, with the limit 182).
+// million of mode 5 502 -> 490 (five groups 1014, seven 1002; 4.5 KB pages 297 -> 301 with six: as many as fit).  The limit is
+// LDS that nothing uses; from 32,768 pages on, below that it neither gains nor loses more than half a microsecond.  It is
+// for calls that decode every block of a range.  Where blocks are named -- id lists, a block table, a prefetch's list of
+// blocks to fetch -- many may be left out, and their waves then come and go through fewer places: 131,072 pages in blocks
+// of one, three quarters of the ids -1, us, without / with the limit: 16 x 128 44.8 / 57.8, 16 x 256 in blocks of eight 56.2 / 70.3;
+// no id -1: 104.3 / 105.8 and 282 / 269; a gather of 655,360 pages that leaves none out 671 / 663.
 constexpr int kDecLimitPages = 32768;
 constexpr int dec_groups(int np, bool partial) { return np == 8 ? 4 : np >= 6 || (np >= 4 && !partial) ? 6 : 0; }
 constexpr int kLdsPerCu = 160 * 1024;
@@ -1533,7 +1535,7 @@ struct ShapeOps {
         constexpr int limit = groups ? kLdsPerCu / groups - 1280 - own : 0;  // (1,280: room for the allocation's granularity)
         static_assert(limit >= 0 && (groups == 0 || own + limit > kLdsPerCu / (groups + 1)), "one group more does not fit");
         return launch_kernel_lds(k_decompress<P, kCodecWaves, dec_ppw(NP)>, page_grid(a.n_pages, dec_ppw(NP)), dim3(kCodecWaves * 64),
-                                 a.n_pages >= kDecLimitPages && !a.sparse ? limit : 0, s, a);
+                                 a.n_pages >= kDecLimitPages && !a.pool_ids && !a.dst_ids && !a.block_table ? limit : 0, s, a);
     }
 
     static hipError_t decompress_window(const DecodeArgs& a, const WindowArgs& w, unsigned grid, bool wide, hipStream_t s) {

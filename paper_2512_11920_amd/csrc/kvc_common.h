@@ -48,7 +48,6 @@ struct DecodeArgs {
     const int32_t* pool_ids;
     const int32_t* dst_ids;
     int64_t n_pages;
-    int32_t sparse;  // many of the blocks may be -1: nothing to do
     Geometry g;
     const uint8_t* pool;
     uint64_t pool_units;

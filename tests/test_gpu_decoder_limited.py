@@ -1,5 +1,5 @@
 """Decode calls of 32,768 pages and more, for which pages of 4 KB and more have a limit on the workgroups of a compute
-unit: the same bytes as calls just below that size, which have none, and as the oracle for pages of every kind."""
+unit: the same bytes as calls that name their blocks, which have none, and as the oracle for pages of every kind."""
 import numpy as np
 import pytest
 import torch
