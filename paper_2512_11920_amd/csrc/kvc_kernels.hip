@@ -176,8 +176,11 @@ __global__ __launch_bounds__(64) void k_prefetch_plan(PlanArgs a) {
 }
 
 // The planner of a window call of few sequences: a workgroup per layer, which then knows the layer's transfers and saves the
-// launch that counts them (two steps of 20 layers x 32 sequences x 8, omega 256: 196.5 us, with the count apart, 194; of two
-// layers 42.4 and 40.8).
+// launch that counts them.  That pays while the layer's rows are done in one round, or two of eight lanes a row; a
+// round is a planner's two trips to memory, and the stores of one keep the loads of the next from being issued ahead.
+// Two steps of one layer, blocks of two pages of 16 x 128, us, count apart / counted here: k = 8, 32 sequences 32.5 / 30.0, 64 37.3 / 37.3, 96
+// 39.6 / 41.7, 128 43.2 / 47.4; k = 16, 16 sequences 34.0 / 31.4, 32 39.8 / 40.9, 64 44.0 / 53.2; k = 32, 8 sequences 36.0 /
+// 34.0, 16 39.8 / 45.2, 32 46.4 / 66.5.  (One step with everything resident, 64 sequences of 8: 15.7 / 13.4.)
 template <int KMAX>
 __global__ __launch_bounds__(256) void k_prefetch_plan_count(PlanArgs a, int32_t* pending) {
     __shared__ uint32_t s_cnt[4];
@@ -326,14 +329,14 @@ hipError_t launch_prefetch_plan(const PlanArgs& a, hipStream_t s) {
     return launch_kernel(k_prefetch_plan<kMaxPrefetchK>, grid(2), dim3(64), s, a);
 }
 
-// Plan a window call and open its window.  The planner counts too where a layer's rows are at most four rounds of its one
-// workgroup; more of them are better spread over the chip.
+// Plan a window call and open its window.  The planner counts too where its one workgroup per layer is quick enough (see
+// there); more rows are better spread over the chip.
 hipError_t launch_window_plan(const PlanArgs& a, const WindowArgs& w, hipStream_t s) {
     if (w.n_layers_call <= 0) return hipSuccess;
     const dim3 layers((unsigned)w.n_layers_call);
     const int lanes = a.k <= 8 ? 8 : a.k <= 16 ? 16 : kMaxPrefetchK;
     hipError_t e;
-    if ((int64_t)a.n_seq * lanes <= 1024) {
+    if ((int64_t)a.n_seq * lanes <= (lanes == 8 ? 512 : 256)) {
         if (a.k <= 8)
             e = launch_kernel(k_prefetch_plan_count<8>, layers, dim3(256), s, a, w.pending);
         else if (a.k <= 16)

@@ -16,3 +16,17 @@ def test_only_calls_that_decode_a_whole_range_limit_their_workgroups():
     named += [dict(op="prefetch", N=N, d=d, ppb=8, seqs=64, k=8, layers=32, omega=0) for N, d in shapes]
     for call, l in zip(named, launches(named)):
         assert l[-1].kernel == "k_decompress" and l[-1].lds == 0, call
+
+
+def test_the_counting_planner_stays_with_few_sequences():
+    """One workgroup per layer plans and counts the transfers of up to two rounds of rows (k <= 8), or one (k <= 32)."""
+    few = [(8, 1), (8, 64), (5, 64), (16, 16), (9, 16), (32, 8), (17, 8)]
+    many = [(8, 65), (8, 128), (1, 65), (16, 17), (16, 64), (32, 9), (17, 32)]
+    calls = [dict(op="prefetch", N=16, d=128, ppb=2, seqs=s, k=k, layers=3, omega=64) for k, s in few + many]
+    for (k, s), l in zip(few + many, launches(calls)):
+        lanes = 8 if k <= 8 else 16 if k <= 16 else 32
+        if (k, s) in few:
+            assert [x.kernel for x in l[:2]] == ["k_prefetch_plan_count", "k_window_place"] and l[0].grid == 3, (k, s)
+        else:
+            assert [x.kernel for x in l[:3]] == ["k_prefetch_plan", "k_window_count", "k_window_place"] and l[0].grid == -(-3 * s // (64 // lanes)), (k, s)
+        assert l[0].params == (lanes,)
