@@ -386,6 +386,7 @@ static int prefetch_impl(kvc_ctx* ctx, void* d_l2, int32_t* d_tags, int32_t* d_f
     w.n_layers = n_layers;
     w.omega = omega;
     w.wide = ctx->wide_capacity > 0 && std::min<int64_t>(omega, n_now) <= ctx->wide_capacity ? 1 : 0;
+    w.ahead = w.wide && kvc::window_looks_ahead(ctx->g) ? kvc::kWindowAhead : 0;
     w.notify = d_notify;
     return hip_ok(kvc::launch_window_plan(p, w, s)) && hip_ok(kvc::launch_decompress_window(a, w, s)) ? KVC_OK : KVC_ERR_HIP;
 }

@@ -1186,8 +1186,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_decompress(DecodeArgs a) {
     dec_batch<P, PPW, PPW == 1>(a, L, 0, lp, s_stage[wave], dec_few<P>(a));
 }
 
-// Narrow transfer engines of the prefetch window, for calls of many (Algorithm 1: at most Omega_max transfers
-// outstanding): a workgroup takes the next issued blocks from the queue (a turn), its waves decode them one block after
+// Transfer engines of the prefetch window that go turn by turn (Algorithm 1: at most Omega_max transfers outstanding):
+// the narrow ones, for calls of many, and wide ones of blocks of few one-pass pages.  A workgroup takes the next issued blocks from the queue (a turn), its waves decode them one block after
 // the other, meeting after each -- no payload of a block is asked for before the last store of the engine's block before
 // has reached memory --, and the completion is reported before the next turn is taken.  The waves share a block's pages
 // as far as they go round (wave w takes pages w, w + WAVES, ...), and queue entries, pool blocks and all descriptors of a
@@ -1258,7 +1258,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
     }
 }
 
-// Wide transfer engines of the prefetch window, for calls of as many as have a compute unit each, or fewer: a
+// Wide transfer engines of the prefetch window that look ahead, for calls of as many as have a compute unit each, or fewer: a
 // workgroup takes issued blocks from the queue in runs, its waves decode them one block after the other,
 // meeting after each -- no payload of a block is asked for before the last store of the engine's block before has
 // reached memory.  An engine is latency, not bandwidth: few of them are at work, each on one block.  So the waves share a
@@ -1425,6 +1425,12 @@ constexpr int kCodecWaves = 4;
 // to a quarter since).  (The choice is made before the transfers are counted: an omega above the wide kind's number with few
 // transfers runs 256 narrow engines.)
 constexpr int kWideWaves = 16;
+// Wide engines of blocks of up to this many one-pass pages go turn by turn like narrow ones.  Such a block is decoded
+// sooner than its clerk has walked ahead, and with a page for every wave the clerk's own comes on top.  Two steps of 20 layers x
+// 64 sequences x 8 blocks, us, with a clerk / turn by turn: 16 x 32, 8 engines, blocks of 1 page 3,155 / 2,745, 4 3,527 / 3,490, 8
+// 3,596 / 3,694, 16 4,709 / 4,104, 24 (8 layers) 2,180 / 2,313; 256 engines 137 / 116, 150 / 144, 154 / 153, 186 / 169, 112 / 121;
+// 7 x 32 in blocks of 16 4,657 / 3,787 and 184 / 155; 16 x 64 in blocks of 16, 32 engines 666 / 723.
+constexpr int kTurnPages = 16;
 constexpr int window_side(int np) { return np <= 4 ? 4 : 2; }
 // Pages per decoder wave: a page of one or two passes is too small to cover its own memory chain, so a wave
 // takes the pages that share a header scan, resolved one per lane.  Measured (half a million pages, us): one
@@ -1538,16 +1544,25 @@ struct ShapeOps {
                                  a.n_pages >= kDecLimitPages && !a.pool_ids && !a.dst_ids && !a.block_table ? limit : 0, s, a);
     }
 
+    // whether the wide engines of blocks of ppb pages are of the kind that looks ahead
+    static bool window_looks_ahead(int ppb) { return NP > 1 || ppb > kTurnPages; }
+
     static hipError_t decompress_window(const DecodeArgs& a, const WindowArgs& w, unsigned grid, bool wide, hipStream_t s) {
+        if constexpr (NP == 1) {
+            if (wide && !window_looks_ahead(a.g.ppb)) return launch_kernel(k_decompress_window<P, kWideWaves, 1>, dim3(grid), dim3(kWideWaves * 64), s, a, w);
+        }
         if (wide) return launch_kernel(k_decompress_window_wide<P, kWideWaves>, dim3(grid), dim3(kWideWaves * 64), s, WindowParams{a, w});
         return launch_kernel(k_decompress_window<P, kCodecWaves, window_side(NP)>, dim3(grid), dim3(kCodecWaves * 64), s, a, w);
     }
 
     // engines the current device holds at once: a larger grid would only queue workgroups behind the
     // resident ones, which keep taking turns until the queue is empty
-    static int window_capacity(bool wide) {
+    static int window_capacity(bool wide, int ppb) {
         int dev = 0, cus = 0, per_cu = 0;
         const void* k = wide ? reinterpret_cast<const void*>(&k_decompress_window_wide<P, kWideWaves>) : reinterpret_cast<const void*>(&k_decompress_window<P, kCodecWaves, window_side(NP)>);
+        if constexpr (NP == 1) {
+            if (wide && !window_looks_ahead(ppb)) k = reinterpret_cast<const void*>(&k_decompress_window<P, kWideWaves, 1>);
+        }
         if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, (wide ? kWideWaves : kCodecWaves) * 64, 0) != hipSuccess) {
             (void)hipGetLastError();
@@ -1556,7 +1571,7 @@ struct ShapeOps {
         return cus * per_cu;
     }
 
-    static constexpr ShapeKernels kTable = {D, NP, PARTIAL, &compress, &decompress, &decompress_window, &window_capacity};
+    static constexpr ShapeKernels kTable = {D, NP, PARTIAL, &compress, &decompress, &decompress_window, &window_capacity, &window_looks_ahead};
 };
 
 }  // namespace

@@ -97,7 +97,7 @@ static_assert(sizeof(WindowHdr) == 256, "window header is 256 bytes");
 
 constexpr int kMaxWindowTurn = 8;  // queue entries an engine takes in a row, and reports at once, at most
 constexpr int kWindowManyEngines = 256;  // more engines than this are used only as far as each has eight transfers
-constexpr int kWindowAhead = 4;         // queue entries a wide engine knows without asking, at least
+constexpr int kWindowAhead = 4;         // queue entries an engine that looks ahead knows without asking, at least
 
 struct WindowArgs {
     WindowHdr* hdr;
@@ -110,6 +110,7 @@ struct WindowArgs {
     int32_t layer_begin, n_layers_call, n_layers;
     int32_t omega;         // engines the decode launch starts at most
     int32_t wide;          // they are of the wide kind
+    int32_t ahead;         // queue entries that each of them knows without asking, at least
     long long* notify;     // [n_layers + 4], see kvc.h
 };
 
@@ -144,6 +145,7 @@ hipError_t launch_prefetch_plan(const PlanArgs& a, hipStream_t s);
 hipError_t launch_window_plan(const PlanArgs& a, const WindowArgs& w, hipStream_t s);
 hipError_t launch_decompress_window(const DecodeArgs& a, const WindowArgs& w, hipStream_t s);
 int window_engine_capacity(const Geometry& g, bool wide);
+bool window_looks_ahead(const Geometry& g);  // whether the wide engines look ahead, or go turn by turn
 hipError_t launch_fill_i32(int32_t* p, int32_t v, uint64_t n, hipStream_t s);
 hipError_t launch_compress(const EncodeArgs& a, hipStream_t s);
 hipError_t launch_decompress(const DecodeArgs& a, hipStream_t s);

@@ -309,7 +309,7 @@ __device__ __forceinline__ void window_leave(const WindowArgs& w, uint32_t mine,
     if (atomicAdd(&w.hdr->done, mine) + mine == n_issued) window_stamp(&w.notify[w.n_layers + 3], max(wall_clock64(), 1ll));
 }
 
-// ---- narrow engines: turn by turn
+// ---- narrow engines, and wide ones of small blocks: turn by turn
 
 // What an engine holds between two turns: a run of consecutive queue entries.
 struct WindowTurn {
@@ -374,7 +374,7 @@ __device__ __forceinline__ WindowTurn window_next(const WindowArgs& w, uint32_t*
     return r;
 }
 
-// ---- wide engines: looked ahead for
+// ---- the other wide engines: looked ahead for
 
 constexpr uint32_t kWindowNone = ~0u;
 
@@ -475,7 +475,8 @@ struct ShapeKernels {
     hipError_t (*compress)(const EncodeArgs& a, hipStream_t s);
     hipError_t (*decompress)(const DecodeArgs& a, hipStream_t s);
     hipError_t (*decompress_window)(const DecodeArgs& a, const WindowArgs& w, unsigned grid, bool wide, hipStream_t s);
-    int (*window_capacity)(bool wide);  // window engines resident on the current device at once (0: unknown)
+    int (*window_capacity)(bool wide, int ppb);  // window engines resident on the current device at once (0: unknown)
+    bool (*window_looks_ahead)(int ppb);         // whether the wide ones look ahead
 };
 constexpr int kShapeGroups = 16;
 using ShapeLookup = const ShapeKernels* (*)(int d, int np, bool partial);

@@ -263,7 +263,7 @@ __global__ __launch_bounds__(256) void k_window_place(WindowArgs w) {
             // entries per turn: long queues space out the bookkeeping, short ones keep every engine busy
             const unsigned int chunk = engines ? min(max(total / (4u * engines), 1u), (uint32_t)kMaxWindowTurn) : 1u;
             w.hdr->chunk = chunk;
-            w.hdr->ticket = engines * (w.wide ? max(chunk, (unsigned int)kWindowAhead) : chunk);  // the engines' first runs need no ticket
+            w.hdr->ticket = engines * max(chunk, (unsigned int)w.ahead);  // the engines' first runs need no ticket
             w.hdr->done = 0;
             w.notify[w.n_layers] = now;                        // window opened
             w.notify[w.n_layers + 1] = (long long)total;       // transfers issued
@@ -361,7 +361,12 @@ hipError_t launch_decompress_window(const DecodeArgs& a, const WindowArgs& w, hi
 
 int window_engine_capacity(const Geometry& g, bool wide) {
     const ShapeKernels* f = shape_kernels(g.N, g.d);
-    return f ? f->window_capacity(wide) : 0;
+    return f ? f->window_capacity(wide, g.ppb) : 0;
+}
+
+bool window_looks_ahead(const Geometry& g) {
+    const ShapeKernels* f = shape_kernels(g.N, g.d);
+    return f && f->window_looks_ahead(g.ppb);
 }
 
 hipError_t launch_fill_i32(int32_t* p, int32_t v, uint64_t n, hipStream_t s) {

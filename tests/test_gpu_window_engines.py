@@ -126,7 +126,8 @@ def test_turns_of_more_page_tasks_than_one_batch_of_descriptors(N, d, ppb, omega
 # Wide engines: blocks of one page up to more than the clerk looks up (64) and more than a wave resolves at once (1,024
 # pages); from one block per engine and fewer than an engine looks ahead, over runs of one, two and more, to runs of eight.
 @pytest.mark.parametrize("N,d,ppb,omega,layers,n_seq,k", [(16, 64, 1, 256, 3, 29, 8), (16, 128, 3, 200, 2, 31, 7), (16, 32, 17, 96, 3, 32, 5), (8, 64, 16, 128, 5, 32, 8), (16, 128, 5, 100, 8, 32, 8),
-                                                          (5, 96, 64, 60, 2, 16, 8), (5, 96, 65, 33, 2, 16, 8), (1, 32, 1040, 7, 2, 9, 8), (16, 256, 2, 256, 12, 32, 8), (16, 64, 4, 3, 7, 10, 8)])
+                                                          (5, 96, 64, 60, 2, 16, 8), (5, 96, 65, 33, 2, 16, 8), (1, 32, 1040, 7, 2, 9, 8), (16, 256, 2, 256, 12, 32, 8), (16, 64, 4, 3, 7, 10, 8),
+                                                          (16, 32, 1, 256, 3, 29, 8), (16, 32, 16, 96, 12, 32, 5), (7, 32, 16, 30, 4, 32, 8), (3, 128, 9, 200, 2, 31, 7), (5, 96, 2, 256, 12, 32, 8)])  # one-pass pages, few a block: turn by turn
 def test_wide_engines_over_every_length_of_run(N, d, ppb, omega, layers, n_seq, k):
     w = Window(N, d, ppb, layers, n_seq, k, 40)
     want = w.buffer()

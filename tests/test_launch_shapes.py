@@ -30,3 +30,15 @@ def test_the_counting_planner_stays_with_few_sequences():
         else:
             assert [x.kernel for x in l[:3]] == ["k_prefetch_plan", "k_window_count", "k_window_place"] and l[0].grid == -(-3 * s // (64 // lanes)), (k, s)
         assert l[0].params == (lanes,)
+
+
+def test_wide_engines_of_small_blocks_go_turn_by_turn():
+    """Up to 16 one-pass pages a block; blocks of more, and of larger pages, have engines that look ahead."""
+    small = [(16, 32, 1), (16, 32, 16), (7, 32, 8), (8, 64, 16), (5, 96, 2), (3, 128, 16), (2, 256, 16)]
+    other = [(16, 32, 17), (7, 32, 64), (32, 32, 1), (16, 64, 16), (6, 96, 16), (16, 128, 1), (16, 256, 16)]
+    calls = [dict(op="prefetch", N=N, d=d, ppb=ppb, seqs=32, k=8, layers=3, omega=64) for N, d, ppb in small + other]
+    for (N, d, ppb), l in zip(small + other, launches(calls)):
+        want = "k_decompress_window" if (N, d, ppb) in small else "k_decompress_window_wide"
+        assert l[-1].kernel == want and l[-1].block == 1024 and l[-1].grid == 64, (N, d, ppb, l[-1])
+    many = launches([dict(c, omega=600) for c in calls])  # more than the device holds of the wide kind
+    assert all(l[-1].kernel == "k_decompress_window" and l[-1].block == 256 for l in many)
