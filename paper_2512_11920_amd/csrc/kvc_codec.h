@@ -1291,7 +1291,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
     const bool clerk = wave == kClerk;
     const int ppb = a.g.ppb;
     const LanePos lp = lane_pos<P>(a.g);
-    const uint32_t engines = params.w.hdr->engines;
+    const uint32_t engines = params.w.hdr->engines, n_issued = params.w.hdr->n_issued, chunk = params.w.hdr->chunk;
     if (blockIdx.x >= engines) return;  // the window was opened for fewer engines than the grid holds
     const int per_block = (ppb + WAVES - 1) / WAVES;  // a wave's page tasks of a block (tasks past the block do nothing)
     const bool looked_up = ppb <= kClerkPages;
@@ -1317,15 +1317,18 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(P::k
     if (clerk) {
         __builtin_amdgcn_s_setprio(3);  // whatever it does beside its pages, the others wait for (217 us, without 229)
         const WindowParams& k = params_again<WindowParams>();
-        auto slot_of = [&](uint32_t i) { return i == kWindowNone ? -1 : wave_uniform(k.w.queue[i]); };
-        auto block_of = [&](int32_t slot) { return slot < 0 ? -1 : wave_uniform(k.a.pool_ids[slot]); };
         WindowBooks b;
-        b.open_at(k.w.hdr->n_issued, blockIdx.x, engines, k.w.hdr->chunk);
-        const int32_t slot0 = slot_of(b.take());  // (engines <= n_issued: there is a first)
-        b.slot1 = slot_of(b.take());
-        b.slot2 = slot_of(b.take());
-        const int32_t pb0 = block_of(slot0);
-        b.pb1 = block_of(b.slot1);
+        b.open_at(n_issued, blockIdx.x, engines, chunk);
+        // the first three entries, one per lane: a trip for all queue entries and one for all pool blocks
+        const uint32_t i0 = b.take(), i1 = b.take(), i2 = b.take();  // (engines <= n_issued: there is a first)
+        const uint32_t i = lane == 0 ? i0 : lane == 1 ? i1 : lane == 2 ? i2 : kWindowNone;
+        int32_t slot_i = -1, pb_i = -1;
+        if (i != kWindowNone) slot_i = k.w.queue[i];
+        if (slot_i >= 0) pb_i = k.a.pool_ids[slot_i];
+        const int32_t slot0 = __builtin_amdgcn_readlane(slot_i, 0), pb0 = __builtin_amdgcn_readlane(pb_i, 0);
+        b.slot1 = __builtin_amdgcn_readlane(slot_i, 1);
+        b.slot2 = __builtin_amdgcn_readlane(slot_i, 2);
+        b.pb1 = __builtin_amdgcn_readlane(pb_i, 1);
         b.layer = b.layer_of(k.w, slot0);
         b.put(s_books);
         publish(dec_open<P>(k.a, clerk_task(slot0, pb0)), slot0, pb0);

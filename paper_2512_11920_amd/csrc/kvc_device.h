@@ -390,8 +390,10 @@ __device__ __forceinline__ const T& params_again() {
 
 // What the clerk of a wide engine knows (wave-uniform): the entries ahead of the engine, and the blocks behind it.
 // Entries come in runs, `left` of them from `next` on, `step` apart, a run asked for before the last entry of the run before
-// is used up.  The first run needs no ticket: entries in a row where the call has eight or more for every engine, else
-// kWindowAhead entries that lie `engines` apart.
+// is used up.  The first run needs no ticket: entries in a row where the call's runs are that long anyway, else kWindowAhead
+// entries that lie `engines` apart: in a row, the first layers would wait for a few engines' fourth block while the others are
+// at work on later ones.  (256 engines, first layer ready and whole call, us, in a row / apart: 2,560 blocks of 32 pages of 16 x 256
+// in ten layers 71 and 142.7 / 32 and 138.8; 2,048 of eight in eight layers 23.5 and 44.5 / 12.8 and 45.5.)
 struct WindowBooks {
     uint32_t n_issued, engines;
     uint32_t next, left, step, size;
@@ -416,7 +418,7 @@ struct WindowBooks {
     }
 
     __device__ __forceinline__ void open_at(uint32_t issued, uint32_t engine, uint32_t n_engines, uint32_t chunk) {
-        const bool rows = chunk > 1;
+        const bool rows = chunk >= (uint32_t)kWindowAhead;
         n_issued = issued;
         engines = n_engines;
         left = max(chunk, (uint32_t)kWindowAhead);

@@ -146,3 +146,22 @@ def test_wide_engines_over_every_length_of_run(N, d, ppb, omega, layers, n_seq, 
         assert all(torch.equal(a, b) for a, b in zip(plan, (w.tags, w.fetch, w.loc)))
         assert torch.equal(got.view(torch.int16), want.view(torch.int16))
     assert w.c.stats()["status"] == kvc.ST_CORRUPT
+
+
+# About ten blocks per engine, and two to an engine's run by the call's own measure: the blocks of the first layer are dealt to
+# all 256 engines, one each, and no layer waits for an engine's fourth block.
+@pytest.mark.parametrize("N,d,ppb,layers,n_seq,k", [(16, 256, 32, 10, 32, 8), (16, 64, 64, 9, 32, 8)])
+def test_the_first_layer_is_ready_in_its_turn(N, d, ppb, layers, n_seq, k):
+    w = Window(N, d, ppb, layers, n_seq, k, 40)
+    got = w.buffer()
+    print(f"[case] first layer N={N} d={d} ppb={ppb}", flush=True)
+    first = []
+    for _ in range(5):
+        w.run(got, 256)
+        torch.cuda.synchronize()
+        nt = w.notify.cpu().numpy()
+        issued, engines = int(nt[layers + 1]), int(nt[layers + 2])
+        assert engines == 256 and 2 <= issued // (4 * engines) < 4
+        first.append((nt[0] - nt[layers]) / (nt[layers + 3] - nt[layers]))
+    # one block of an engine's nine or ten, and the way there; with four in a row it is at least 0.4
+    assert np.median(first) < 0.3, first
