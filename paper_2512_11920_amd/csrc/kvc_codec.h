@@ -867,14 +867,20 @@ __device__ __forceinline__ void load_to_lds16(const void* g, void* lds) {
 // and the memory serves them worse than 96 to 168 KB.  262,144 pages, decode, us, eight groups -> the number here:
 // 16 x 160 335 -> 324, 16 x 192 399 -> 389, 16 x 224 473 -> 459, 16 x 256 541 -> 514; a million of 16 x 128 1009 -> 987, half a
 // million of mode 5 502 -> 490 (five groups 1014, seven 1002; 4.5 KB pages 297 -> 301 with six: as many as fit).  The limit is
-// LDS that nothing uses; from 32,768 pages on, below that it neither gains nor loses more than half a microsecond.  It is
+// LDS that nothing uses.  It holds from 24,576 pages on (16 x 160 30.7 -> 29.6, 16 x 256 45.9 -> 44.7; at 16,384 within half a
+// microsecond), and for pages of 6 and 7 KB, five groups, from 8,192 on, where all waves of a call are resident at once or nearly
+// so: mode 4, 16 x 192, 9,216 and 10,240 pages 13.3 -> 12.1 and 14.1 -> 12.9, 13 x 256 13.6 -> 12.7 and 15.2 -> 13.9; mode 3, cold, 16 x
+// 224, 8,192 and 12,288 18.1 -> 16.7 and 23.7 -> 22.8 (16 x 192 at 8,192, where nothing waits for memory, 10.5 -> 10.9).  It is
 // for calls that decode every block of a range.  Where blocks are named -- id lists, a block table, a prefetch's list of
 // blocks to fetch -- many may be left out, and their waves then come and go through fewer places: 131,072 pages in blocks
 // of one, three quarters of the ids -1, us, without / with the limit: 16 x 128 44.8 / 57.8, 16 x 256 in blocks of eight 56.2 / 70.3;
 // no id -1: 104.3 / 105.8 and 282 / 269; a gather of 655,360 pages that leaves none out 671 / 663.
-constexpr int kDecLimitPages = 32768;
+constexpr int kDecLimitPages = 24576, kDecMiddlePages = 8192;
 constexpr int dec_groups(int np, bool partial) { return np == 8 ? 4 : np >= 6 || (np >= 4 && !partial) ? 6 : 0; }
+constexpr int dec_groups_middle(int np) { return np == 6 || np == 7 ? 5 : 0; }
 constexpr int kLdsPerCu = 160 * 1024;
+// unused LDS per workgroup, beside the kernel's own, that leaves room for `groups` of them
+constexpr int dec_spare_lds(int groups, int own) { return groups ? kLdsPerCu / groups - 1280 - own : 0; }  // (1,280: room for the allocation's granularity)
 
 // Whether INT8 payloads go through LDS too.  With several pages per wave their loads have to be under way before
 // the first page is stored; with one page per wave they are read straight from the pool, pass by pass, which is
@@ -1540,11 +1546,13 @@ struct ShapeOps {
         if constexpr (dec_ppw(NP) > 1) {
             if (a.n_pages <= kDecSmallPages(NP)) return launch_kernel(k_decompress<P, kCodecWaves, 1>, page_grid(a.n_pages, 1), dim3(kCodecWaves * 64), s, a);
         }
-        constexpr int groups = dec_groups(NP, PARTIAL), own = kCodecWaves * dec_ppw(NP) * Slot<NP>::kBytes;
-        constexpr int limit = groups ? kLdsPerCu / groups - 1280 - own : 0;  // (1,280: room for the allocation's granularity)
-        static_assert(limit >= 0 && (groups == 0 || own + limit > kLdsPerCu / (groups + 1)), "one group more does not fit");
-        return launch_kernel_lds(k_decompress<P, kCodecWaves, dec_ppw(NP)>, page_grid(a.n_pages, dec_ppw(NP)), dim3(kCodecWaves * 64),
-                                 a.n_pages >= kDecLimitPages && !a.pool_ids && !a.dst_ids && !a.block_table ? limit : 0, s, a);
+        constexpr int own = kCodecWaves * dec_ppw(NP) * Slot<NP>::kBytes, groups = dec_groups(NP, PARTIAL), middle = dec_groups_middle(NP);
+        constexpr int spare = dec_spare_lds(groups, own), spare_middle = dec_spare_lds(middle, own);
+        static_assert(spare >= 0 && (groups == 0 || own + spare > kLdsPerCu / (groups + 1)), "one group more does not fit");
+        static_assert(spare_middle >= 0 && (middle == 0 || own + spare_middle > kLdsPerCu / (middle + 1)), "one group more does not fit");
+        const bool whole = !a.pool_ids && !a.dst_ids && !a.block_table;
+        const int lds = !whole || a.n_pages < kDecMiddlePages ? 0 : a.n_pages < kDecLimitPages ? spare_middle : spare;
+        return launch_kernel_lds(k_decompress<P, kCodecWaves, dec_ppw(NP)>, page_grid(a.n_pages, dec_ppw(NP)), dim3(kCodecWaves * 64), lds, s, a);
     }
 
     // whether the wide engines of blocks of ppb pages are of the kind that looks ahead
