@@ -868,16 +868,16 @@ __device__ __forceinline__ void load_to_lds16(const void* g, void* lds) {
 // 16 x 160 335 -> 324, 16 x 192 399 -> 389, 16 x 224 473 -> 459, 16 x 256 541 -> 514; a million of 16 x 128 1009 -> 987, half a
 // million of mode 5 502 -> 490 (five groups 1014, seven 1002; 4.5 KB pages 297 -> 301 with six: as many as fit).  The limit is
 // LDS that nothing uses.  It holds from 24,576 pages on (16 x 160 30.7 -> 29.6, 16 x 256 45.9 -> 44.7; at 16,384 within half a
-// microsecond), and for pages of 6 and 7 KB, five groups, from 8,192 on, where all waves of a call are resident at once or nearly
-// so: mode 4, 16 x 192, 9,216 and 10,240 pages 13.3 -> 12.1 and 14.1 -> 12.9, 13 x 256 13.6 -> 12.7 and 15.2 -> 13.9; mode 3, cold, 16 x
-// 224, 8,192 and 12,288 18.1 -> 16.7 and 23.7 -> 22.8 (16 x 192 at 8,192, where nothing waits for memory, 10.5 -> 10.9).  It is
-// for calls that decode every block of a range.  Where blocks are named -- id lists, a block table, a prefetch's list of
+// microsecond).  Pages of 6 to 8 KB have one of six groups from 8,192 on, where a call's waves would all be resident at once, or
+// nearly, and reach their stores together: 9,216 and 10,240 pages, mode 4, 16 x 192 13.2 -> 12.3 and 14.1 -> 12.8, 13 x 256 13.7 -> 12.8 and
+// 14.9 -> 13.8; in cold calls, mode 3, 16 x 192, 8,192 pages 16.7 -> 15.8, 16 x 224, 20,480 36.0 -> 35.0.
+// The large calls' limit is for those that decode every block of a range.  Where blocks are named -- id lists, a block table, a prefetch's list of
 // blocks to fetch -- many may be left out, and their waves then come and go through fewer places: 131,072 pages in blocks
 // of one, three quarters of the ids -1, us, without / with the limit: 16 x 128 44.8 / 57.8, 16 x 256 in blocks of eight 56.2 / 70.3;
 // no id -1: 104.3 / 105.8 and 282 / 269; a gather of 655,360 pages that leaves none out 671 / 663.
 constexpr int kDecLimitPages = 24576, kDecMiddlePages = 8192;
 constexpr int dec_groups(int np, bool partial) { return np == 8 ? 4 : np >= 6 || (np >= 4 && !partial) ? 6 : 0; }
-constexpr int dec_groups_middle(int np) { return np == 6 || np == 7 ? 5 : 0; }
+constexpr int dec_groups_middle(int np) { return np >= 6 ? 6 : 0; }
 constexpr int kLdsPerCu = 160 * 1024;
 // unused LDS per workgroup, beside the kernel's own, that leaves room for `groups` of them
 constexpr int dec_spare_lds(int groups, int own) { return groups ? kLdsPerCu / groups - 1280 - own : 0; }  // (1,280: room for the allocation's granularity)
@@ -1551,7 +1551,7 @@ struct ShapeOps {
         static_assert(spare >= 0 && (groups == 0 || own + spare > kLdsPerCu / (groups + 1)), "one group more does not fit");
         static_assert(spare_middle >= 0 && (middle == 0 || own + spare_middle > kLdsPerCu / (middle + 1)), "one group more does not fit");
         const bool whole = !a.pool_ids && !a.dst_ids && !a.block_table;
-        const int lds = !whole || a.n_pages < kDecMiddlePages ? 0 : a.n_pages < kDecLimitPages ? spare_middle : spare;
+        const int lds = a.n_pages < kDecMiddlePages ? 0 : a.n_pages < kDecLimitPages ? spare_middle : whole ? spare : 0;
         return launch_kernel_lds(k_decompress<P, kCodecWaves, dec_ppw(NP)>, page_grid(a.n_pages, dec_ppw(NP)), dim3(kCodecWaves * 64), lds, s, a);
     }
 
