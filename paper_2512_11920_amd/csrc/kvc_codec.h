@@ -1461,7 +1461,9 @@ constexpr int kDecSmallPages(int np) { return 4096 * np; }
 // 18.9 -> 17.0, 8,192 22.9 -> 19.9, 16,384 31.8 -> 28.2 (12,288 with eight waves of four 26.3, four of four 25.2); 16 x 64, two
 // pages per wave -> these: 8 11.3 -> 10.5, 1,024 12.3 -> 11.8, 4,096 16.2 -> 14.5, 16,384 21.3 -> 20.0; 16 x 32, four ->
 // these: 8 11.7 -> 9.9, 1,024 12.3 -> 11.4, 4,096 15.8 -> 13.2, 16,384 19.3 -> 18.7; 16 x 256: 1,024 15.8 -> 15.0, 4,096
-// 21.9 -> 20.9; a mode per block: 16 x 96 4,096 24.1 -> 15.4, 16 x 64 8,192 25.3 -> 18.2, 16 x 128 8,192 28.3 -> 25.0.
+// 21.9 -> 20.9; a mode per block: 16 x 96 4,096 24.1 -> 15.4, 16 x 64 8,192 25.3 -> 18.2, 16 x 128 4,096 22.6 -> 17.7
+// (beyond that the waves of 16 are no longer resident at once: 5,120 to 8,192 pages 5 to 14 % faster in cold calls with modes that
+// change from block to block, but 7 to 18 % slower with modes that don't and with blocks of one page).
 struct EncTier {
     int pages, waves, ppw;
 };
@@ -1470,19 +1472,20 @@ constexpr EncTier enc_tier(int np, int scheme, int i) {
     constexpr EncTier none = {0, 4, 1};
     constexpr EncTier one[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {16384, 16, 2}, {32768, 16, 4}, none};  // one pass
     constexpr EncTier two[kEncTiers] = {{512, 4, 1}, {2048, 8, 1}, {16384, 16, 2}, none, none};
-    constexpr EncTier three[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {8192, 16, 1}, none, none};  // and four, the mode read at run time
+    constexpr EncTier three[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {8192, 16, 1}, none, none};
+    constexpr EncTier any_four[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {4096, 16, 1}, none, none};  // four, the mode read at run time
     constexpr EncTier four[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {8192, 16, 1}, {13312, 4, 4}, {16384, 8, 4}};
     constexpr EncTier pairs[kEncTiers] = {{512, 4, 1}, {1024, 8, 1}, {4096, 16, 1}, {13312, 4, 4}, {32768, 8, 4}};  // four, mode 5
     constexpr EncTier six[kEncTiers] = {{512, 4, 1}, {3072, 8, 1}, none, none, none};                          // five and six
     constexpr EncTier more[kEncTiers] = {{512, 4, 1}, {4096, 8, 1}, none, none, none};
-    return np == 1 ? one[i] : np == 2 ? two[i] : np == 3 || (np == 4 && scheme < 0) ? three[i] : np == 4 ? (scheme == KVC_MODE_CHAN ? pairs[i] : four[i]) : np <= 6 ? six[i] : more[i];
+    return np == 1 ? one[i] : np == 2 ? two[i] : np == 3 ? three[i] : np == 4 ? (scheme < 0 ? any_four[i] : scheme == KVC_MODE_CHAN ? pairs[i] : four[i]) : np <= 6 ? six[i] : more[i];
 }
 // Where the mode is read at run time but is the same for all blocks, the large shapes are reached earlier: the pages of a
-// workgroup are then done together, and plain INT8 and raw ones soon (16 x 128, 4,096 INT8 pages 14.7 us against 15.8, 5,120 of
-// mode 2 or 4 19.0 against 22.0; 16 x 32, 16,384 INT8 pages 16.7 against 18.0).
+// workgroup are then done together, and plain INT8 and raw ones soon (16 x 128, 4,096 INT8 pages 14.7 us against 15.8; 16 x 32,
+// 16,384 INT8 pages 16.7 against 18.0).
 constexpr int enc_uniform_pages(int np, int scheme) {
     const bool plain = scheme == KVC_MODE_RAW || scheme == KVC_MODE_INT8;
-    return plain ? (np <= 2 ? 8192 : 2048) : np == 4 ? 4096 : 1 << 30;
+    return plain ? (np <= 2 ? 8192 : 2048) : 1 << 30;
 }
 
 inline dim3 page_grid(int64_t n_pages, int ppw, int waves = kCodecWaves) {

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 CASES = [(N, d, scheme, pages) for N, d in ((16, 32), (13, 64), (16, 64), (16, 96), (15, 96), (16, 128), (13, 160), (16, 192), (17, 224), (16, 256)) for scheme, pages in ((3, 7), (3, 509), ("mixed", 516), (3, 1023), ("mixed", 1029))] + \
         [(16, 32, 3, 16380), (16, 32, "mixed", 32764), (7, 32, 3, 16400), (7, 32, 3, 32780), (16, 64, 3, 2046), (16, 64, 5, 2052), (16, 64, 3, 16395), (16, 64, "mixed", 16395), (9, 128, "mixed", 2046), (9, 128, 2, 16383)] + \
         [(16, 96, 3, 8190), (16, 96, "mixed", 8196), (13, 96, 3, 8190), (16, 128, 3, 8190), (16, 128, 3, 8196), (16, 128, 3, 13311), (16, 128, 3, 13317), (16, 128, 3, 16386), (16, 128, 5, 4095), (16, 128, 5, 4101), (16, 128, 5, 13314), (16, 128, 5, 32766)] + \
-        [(16, 128, "mixed", 8190), (15, 128, 4, 4095), (15, 128, 4, 4101), (16, 128, 2, 4101), (32, 64, 4, 4095)] + \
+        [(16, 128, "mixed", 4095), (16, 128, "mixed", 4101), (16, 128, "mixed", 8190), (15, 128, 4, 4095), (15, 128, 4, 4101), (16, 128, 2, 4101), (32, 64, 4, 4095)] + \
         [(16, 128, 1, 2046), (16, 128, 1, 2052), (16, 64, 1, 8190), (16, 64, 0, 8196), (16, 256, 0, 2046), (13, 160, 3, 3069), (16, 192, "mixed", 3075), (16, 192, 3, 3069), (17, 224, 3, 4095), (16, 256, 3, 4095), (16, 256, 5, 4092), (16, 256, "mixed", 4101)]
 
 

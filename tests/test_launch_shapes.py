@@ -50,3 +50,11 @@ def test_wide_engines_of_small_blocks_go_turn_by_turn():
         assert l[-1].kernel == want and l[-1].block == 1024 and l[-1].grid == 64, (N, d, ppb, l[-1])
     many = launches([dict(c, omega=600) for c in calls])  # more than the device holds of the wide kind
     assert all(l[-1].kernel == "k_decompress_window" and l[-1].block == 256 for l in many)
+
+
+def test_encoder_workgroups_of_16_waves_end_where_they_stop_being_resident():
+    """Four-pass pages with the mode read at run time: 4,096 pages of a wave each fill the chip."""
+    calls = [dict(op="compress", N=N, d=d, ppb=1, n=n, **kw) for N, d in ((16, 128), (15, 128), (32, 64), (8, 256)) for n in (4096, 4097) for kw in (dict(mixed=True), dict(scheme=2), dict(scheme=4))]
+    for c, l in zip(calls, launches(calls)):
+        D, NP, partial, waves, ppw, scheme = l[0].params
+        assert scheme < 0 and ((waves, ppw) == (16, 1)) == (c["n"] == 4096), (c, l[0])
