@@ -16,7 +16,10 @@ scalar offset; without it lanes store what the next instructions compute.
 (4) The window's engines write pages through the XCD's L2 (device scope): a block is published by waiting for its
 stores, and a store without that scope would leave a consumer that polls the ready stamp with stale bytes.
 
-(5) An engine counts itself out of the window only when its layer stamps are in memory: whoever sees the stamp that closes
+(5) A block of the window is published by counters that move after all waves of its engine have waited for their stores
+and met: the wait stands right before that meeting.
+
+(6) An engine counts itself out of the window only when its layer stamps are in memory: whoever sees the stamp that closes
 the window may read the stamps of all layers."""
 import concurrent.futures
 import os
@@ -116,6 +119,27 @@ def test_engines_leave_the_window_after_their_stamps(asm):
             assert all(_waits_for_memory(lines, i) for i in counts), f"{kernel}: blocks counted with stores in flight"
             seen += 1
     assert seen >= 2 * (64 + 16)
+
+
+def test_window_engines_meet_with_their_stores_in_memory(asm):
+    seen = {"turn": 0, "ahead": 0}
+    for name, text in asm.items():
+        for kernel, body in _kernels(text, "k_decompress_window"):
+            lines = body.split("\n")
+            stores = [i for i, l in enumerate(lines) if re.match(r"\s*buffer_store_dwordx4 ", l)]
+            barriers = [i for i, l in enumerate(lines) if "s_barrier" in l]
+            counters = [i for i, l in enumerate(lines) if re.match(r"\s*global_atomic_add ", l)]  # ticket, a layer's pending blocks, done
+            if "window_wide" in kernel:
+                # two meetings (before the loop and in it) of two barriers each, and the second of each is behind the wait
+                assert len(barriers) == 4 and sum(_waits_for_memory(lines, i) for i in barriers) == 2, kernel
+                seen["ahead"] += 1
+            else:
+                # the barrier between the page stores and the counters
+                first = min(i for i in counters if i > stores[-1])
+                between = [i for i in barriers if stores[-1] < i < first]
+                assert between and _waits_for_memory(lines, between[0]), kernel
+                seen["turn"] += 1
+    assert seen["turn"] >= 64 + 16 + 10 and seen["ahead"] >= 64 + 16, seen
 
 
 def test_window_engines_keep_their_barriers_out_of_nested_loops(asm):
