@@ -98,11 +98,36 @@ import test_gpu_window_scale as tws  # noqa: E402
 for case in ((16, 128, 16, 3), (16, 128, 8, 5), (16, 64, 3, 5), (24, 96, 6, 2), (16, 256, 4, 1), (16, 32, 8, 0)):
     tws.test_window_equals_unbounded_call_on_a_busy_gpu(*case)
     n_cases += 1
-# encoder workgroups of several pages, with skipped and refused ids and a pool that fills
+# encoder workgroups of several pages, with skipped and refused ids and a pool that fills: middle calls and large ones
 import test_gpu_encoder_batches as teb  # noqa: E402
+from launch_shapes import large_decoder_pages, large_encoder_pages  # noqa: E402
 
 for N, d, scheme, pages in ((16, 32, 3, 2049), (16, 64, "mixed", 2100), (16, 96, 3, 2049), (16, 128, 3, 2049), (16, 128, 3, 16400), (16, 128, 5, 16400),
                             (16, 128, "mixed", 2100), (13, 160, 3, 2100), (21, 192, "mixed", 2049), (17, 224, 1, 2049), (16, 256, 3, 2049)):
     teb.test_ids_modes_and_a_full_pool(N, d, scheme, pages, 3)
+    n_cases += 1
+for N, d, scheme in ((16, 32, 3), (7, 32, "mixed"), (16, 64, 3), (16, 64, "mixed"), (16, 96, 3), (16, 128, 3), (16, 128, 5), (16, 128, "mixed"),
+                     (13, 160, 3), (21, 192, "mixed"), (17, 224, 1), (16, 256, 3), (16, 256, 5)):
+    teb.test_ids_modes_and_a_full_pool(N, d, scheme, large_encoder_pages(N, d, scheme) + 20, 3)
+    n_cases += 1
+# plain decoder waves of several pages: pages of one and two passes, packets of every kind
+for N, d in ((16, 32), (7, 32), (8, 64), (16, 64), (13, 64), (32, 32)):
+    rng = np.random.default_rng(1700 + N + d)
+    x = td._soak_pages(rng, large_decoder_pages(N, d) + 7, N, d)
+    x[5::41] = 0
+    x[9::53].view(np.uint16)[:, N // 2, 3] = 0x7E00  # raw pages
+    per_block = rng.integers(0, 6 if (N, d) == (16, 64) else 5, x.shape[0]).astype(np.uint8)
+    print(f"[case] bounds-checking build, waves of several pages N={N} d={d} pages={x.shape[0]}", flush=True)
+    xt = torch.from_numpy(x.reshape(-1, 1, N, d)).to(DEV)
+    c = kvc.Codec(N, d, 1, 3)
+    c.alloc_pool(x.shape[0], x.shape[0] * N * d * 2 + 64, DEV)
+    c.compress_blocks(xt, block_scheme=torch.from_numpy(per_block).to(DEV))
+    out = torch.empty_like(xt)
+    c.decompress_blocks(out)
+    st = c.stats()
+    assert st["status"] == 0, f"status {st['status']:#x}: bit 8 = an index or span left its bounds"
+    od, op = teb.oracle_pages(x, N, d, per_block)
+    want, bad = o.decompress_pages(op, od, N, d, n_threads=8)
+    assert bad == 0 and np.array_equal(out.cpu().numpy().view(np.uint16).reshape(-1, N, d), want)
     n_cases += 1
 print(f"debug-bounds ok: {n_cases} cases", flush=True)

@@ -15,6 +15,25 @@ import sys
 import tempfile
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def large_encoder_pages(N, d, scheme):
+    """The smallest call that takes the encoder's large launch shape (scheme: 0..5 for the call, or "mixed": one per block)."""
+    passes = -(-N * d // 512)
+    if scheme in (0, 1):  # plain: no packets to wait for
+        return 8193 if passes <= 2 else 2049
+    if passes == 4:
+        whole = N * d == 2048 and (N, d) in ((16, 128), (32, 64), (8, 256))  # these have encoders of their own for modes 3 and 5
+        return 32769 if whole and scheme == 5 else 16385 if whole and scheme == 3 else 4097
+    return {1: 32769, 2: 16385, 3: 8193, 5: 3073, 6: 3073, 7: 4097, 8: 4097}[passes]
+
+
+def large_decoder_pages(N, d):
+    """The smallest call whose decoder waves take several pages (pages of one or two passes; None: there is none)."""
+    passes = -(-N * d // 512)
+    return 4096 * passes + 1 if passes <= 2 else None
+
+
 Launch = collections.namedtuple("Launch", "kernel params grid block lds")  # params: the kernel's template arguments
 
 

@@ -1,5 +1,5 @@
-"""Decoder waves that take several pages at once: every kind of page task beside every other in one wave, in calls
-whose last wave is not full, and the division the tasks are resolved with."""
+"""Decoder waves: every kind of page task beside every other, in small calls, whose waves take a page each, and in calls
+whose waves take several pages (the last wave not full), and the division the tasks are resolved with."""
 import os
 import subprocess
 
@@ -9,6 +9,7 @@ import torch
 
 from oracle import kvc_oracle as o
 from paper_2512_11920_amd import kvc
+from launch_shapes import large_decoder_pages
 
 DEV = "cuda:0"
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -46,11 +47,24 @@ int main() {
     assert r.returncode == 0 and r.stdout.startswith("0 of "), r.stdout
 
 
-# one, two, three, four passes (waves of 4, 2, 1, 1 pages), with and without a short last pass, and one of more than 64 groups
+# one, two, three, four passes, with and without a short last pass, and one of more than 64 groups: a page per wave
 @pytest.mark.gpu
 @pytest.mark.parametrize("N,d", [(16, 32), (8, 64), (7, 32), (16, 64), (13, 64), (16, 96), (16, 128), (20, 192)])
 @pytest.mark.parametrize("ppb,n", [(1, 61), (3, 22)])
 def test_every_kind_of_task_in_one_wave(N, d, ppb, n):
+    task_kinds(N, d, ppb, n)
+
+
+# pages of one and two passes in calls whose waves take four and two pages, from several blocks and from one and a part of another
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,d", [(16, 32), (8, 64), (7, 32), (3, 96), (16, 64), (13, 64), (32, 32), (7, 128)])
+@pytest.mark.parametrize("ppb", [1, 3, 5])
+def test_every_kind_of_task_in_waves_of_several_pages(N, d, ppb):
+    pages = large_decoder_pages(N, d) + 5  # the last wave is not full
+    task_kinds(N, d, ppb, -(-pages // ppb), n_hits=pages // 23)
+
+
+def task_kinds(N, d, ppb, n, n_hits=7):
     rng = np.random.default_rng(1000 * N + d + ppb)
     pages = n * ppb
     x = (rng.standard_normal((pages, N, d)) * np.exp(0.7 * rng.standard_normal((pages, 1, d)))).astype(np.float16)
@@ -69,14 +83,14 @@ def test_every_kind_of_task_in_one_wave(N, d, ppb, n):
     pool = c.pool.cpu().numpy()
     # damage: an unknown mode, a wrong size, a span outside the pool, a first packet code no packet has
     packed = np.nonzero((desc["mode"] >= 2) & (desc["mode"] <= 5))[0]
-    hit = rng.permutation(packed)[:7]
-    desc["mode"][hit[0]] = 9
-    desc["n16"][hit[1]] += 1
-    desc["off"][hit[2]] = pool.size
-    desc["off"][hit[3]] += 8
-    for h in hit[4:6]:
+    hit = rng.permutation(packed)[:n_hits]
+    desc["mode"][hit[0::7]] = 9
+    desc["n16"][hit[1::7]] += 1
+    desc["off"][hit[2::7]] = pool.size
+    desc["off"][hit[3::7]] += 8
+    for h in np.concatenate([hit[4::7], hit[5::7]]):
         pool[int(desc["off"][h])] |= 0x0F
-    desc["mode"][hit[6]] = 0xFF
+    desc["mode"][hit[6::7]] = 0xFF
     c.desc.copy_(torch.from_numpy(desc.view(np.uint8)).to(DEV))
     c.pool.copy_(torch.from_numpy(pool).to(DEV))
     want, bad = o.decompress_pages(pool, desc, N, d)
@@ -85,7 +99,7 @@ def test_every_kind_of_task_in_one_wave(N, d, ppb, n):
     src, dst = rng.permutation(n).astype(np.int32), rng.permutation(n).astype(np.int32)
     src[1::6] = -1
     dst[2::8] = -1
-    src[9], dst[12] = n, n
+    src[9::83], dst[12::97] = n, n
     expect = np.full((n, ppb, N, d), 0x4700, np.uint16)
     for i in range(n):
         if 0 <= dst[i] < n and src[i] >= 0:
@@ -96,5 +110,5 @@ def test_every_kind_of_task_in_one_wave(N, d, ppb, n):
     status = c.stats()["status"]
     assert np.array_equal(out.cpu().numpy().view(np.uint16), expect)
     used = [src[i] for i in range(n) if 0 <= dst[i] < n and 0 <= src[i] < n]
-    refused = {int(h) // ppb for h in hit[:7]} & {int(u) for u in used}
+    refused = {int(h) // ppb for h in hit} & {int(u) for u in used}
     assert bool(status & kvc.ST_CORRUPT) == bool(refused) and status & kvc.ST_BAD_INDEX

@@ -7,6 +7,7 @@ import torch
 
 from oracle import kvc_oracle as o
 from gpu_util import DEV, make_codec, upload_oracle_pool
+from launch_shapes import large_decoder_pages
 
 pytestmark = pytest.mark.gpu
 
@@ -53,5 +54,25 @@ def test_random_packets_decode_as_the_oracle_decodes_them(N, d):
         got = out.cpu().numpy().view(np.uint16).reshape(n, N, d)
         wrong = np.nonzero((got != want).any((1, 2)))[0]
         assert wrong.size == 0, f"{wrong.size} of {n} pages differ, first {wrong[:5]}"
+        assert c.stats()["status"] == 0
+        del keep
+
+
+# the same payloads many times over, in calls whose waves take four and two pages of one and two passes, which share their header scans
+@pytest.mark.parametrize("N,d", [(16, 32), (7, 32), (3, 128), (16, 64), (13, 64), (5, 192)])
+def test_random_packets_in_waves_of_several_pages(N, d):
+    rng = np.random.default_rng(N * 1000 + d + 1)
+    for mode in (2, 3, 4) + ((5,) if N == 16 and d == 64 else ()):
+        some, pool = random_payloads(rng, 420, N, d, mode)
+        desc = some[rng.integers(0, 420, large_decoder_pages(N, d) + 6)]
+        want, bad = o.decompress_pages(pool, desc, N, d, n_threads=8)
+        assert bad == 0
+        c = make_codec(N, d, 1, 3, 1)
+        keep = upload_oracle_pool(c, desc, pool)
+        out = torch.empty((desc.size, 1, N, d), dtype=torch.float16, device=DEV)
+        print(f"[case] random packets N={N} d={d} mode={mode} pages={desc.size}", flush=True)
+        c.decompress_blocks(out)
+        wrong = np.nonzero((out.cpu().numpy().view(np.uint16).reshape(-1, N, d) != want).any((1, 2)))[0]
+        assert wrong.size == 0, f"{wrong.size} of {desc.size} pages differ, first {wrong[:5]}"
         assert c.stats()["status"] == 0
         del keep

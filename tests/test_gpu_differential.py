@@ -9,6 +9,7 @@ import torch
 from oracle import kvc_oracle as o
 from paper_2512_11920_amd import kvc
 from gpu_util import DEV, check_pool_invariants, compare_pages_with_oracle
+from launch_shapes import large_encoder_pages
 
 pytestmark = pytest.mark.gpu
 
@@ -130,7 +131,7 @@ def test_every_kernel_instantiation_under_full_occupancy(N, d, scheme):
     """Instantiations of the kernels for exact page shapes (the compile-time scheme, the run-time scheme and
     the per-block scheme) and for pages with a short last pass, on enough pages that several workgroups share
     every compute unit, three launches each, every page compared with the oracle bit for bit."""
-    _full_occupancy(N, d, scheme, 24576)
+    _full_occupancy(N, d, scheme, max(24576, large_encoder_pages(N, d, scheme) + 31))
 
 
 # four-pass pages with the mode fixed have an encoder of their own for calls of up to 16,384 pages
@@ -201,13 +202,13 @@ def _shape_pages(rng, n, N, d):
 def test_every_page_shape(d):
     """Every accepted token count for this channel count (N * d <= 4096): pages that fill their last pass of
     512 elements and pages that do not, with one to eight passes, an odd and an even number of packet
-    groups.  Two requested modes per shape, both launch shapes of the encoder over the sweep."""
+    groups.  Two requested modes per shape, small calls and the large launch shapes of the encoder over the sweep."""
     for N in range(1, 4096 // d + 1):
         rng = np.random.default_rng(50000 + 97 * N + d)
-        n = 2100 if N % 7 == 3 else 160  # some shapes with more than 2048 pages: the large-call launch shape
-        x = _shape_pages(rng, n, N, d)
-        xt = torch.from_numpy(x.reshape(-1, 1, N, d)).to(DEV)
         for scheme in (3, (N + d // 32) % 5):
+            n = large_encoder_pages(N, d, scheme) + 51 if N % 7 == 3 else 160  # some shapes with the large-call launch shape
+            x = _shape_pages(rng, n, N, d)
+            xt = torch.from_numpy(x.reshape(-1, 1, N, d)).to(DEV)
             print(f"[case] page shape N={N} d={d} pages={n} scheme={scheme}", flush=True)
             c = kvc.Codec(N, d, 1, scheme)
             c.alloc_pool(n, n * N * d * 2 + 64, DEV)

@@ -1,23 +1,29 @@
 """Encoder workgroups that hold several pages: everything that is not the plain case -- block ids that skip or leave
 their range inside a wave and over whole waves, a descriptor table that ends inside a block, a last workgroup that is
 not full, one mode per block, a pool that fills inside a workgroup -- against the oracle, at call sizes that take the
-large-call shapes."""
+large-call shapes (large_encoder_pages, which a test on the recorded launches holds to the library) and some below."""
 import numpy as np
 import pytest
 import torch
 
 from oracle import kvc_oracle as o
 from paper_2512_11920_amd import kvc
+from launch_shapes import large_encoder_pages
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
-# one to eight passes, whole and short last passes; the middle (up to 16,384 pages) and the large launch of four-pass
-# pages with the mode fixed; both deals of the tasks of whole eight-pass pages (in order up to 32,768 pages)
-CASES = [(N, d, scheme, pages) for (N, d) in ((16, 32), (16, 64), (16, 96), (16, 128), (16, 160), (16, 192), (16, 224), (16, 256)) for scheme, pages in ((3, 2049), ("mixed", 2100))] + \
+def large(N, d, scheme, more=0):
+    return N, d, scheme, large_encoder_pages(N, d, scheme) + more
+
+
+# one to eight passes, whole and short last passes; the middle and the large launch of four-pass pages with the mode fixed;
+# both deals of the tasks of whole eight-pass pages (in order up to 32,768 pages)
+CASES = [large(N, d, scheme, more) for (N, d) in ((16, 32), (16, 64), (16, 96), (16, 128), (16, 160), (16, 192), (16, 224), (16, 256)) for scheme, more in ((3, 0), ("mixed", 51))] + \
         [(16, 256, 3, 32770), (16, 256, 4, 32770), (32, 128, "mixed", 32770)] + \
-        [(16, 64, 5, 2300), (16, 256, 5, 2049), (16, 128, 5, 2049), (16, 128, 3, 16380), (16, 128, 3, 16400), (16, 128, 5, 16400)] + \
-        [(7, 32, 3, 2049), (13, 64, "mixed", 2100), (9, 128, 2, 2100), (15, 96, 4, 2049), (13, 160, 3, 2100), (21, 192, "mixed", 2049), (17, 224, 1, 2049), (15, 256, 3, 2100)]
+        [large(16, 64, 5, 200), large(16, 256, 5), large(16, 128, 5), (16, 64, 5, 2300), (16, 256, 5, 2049), (16, 128, 5, 2049), (16, 128, 3, 16380), (16, 128, 3, 16400), (16, 128, 5, 16400)] + \
+        [large(7, 32, 3), large(13, 64, "mixed", 51), large(9, 128, 2, 51), large(15, 96, 4), large(13, 160, 3, 51), large(21, 192, "mixed"), large(17, 224, 1), large(15, 256, 3, 51)] + \
+        [(16, 32, 3, 2049), (16, 64, "mixed", 2100), (16, 96, 3, 2049), (16, 128, "mixed", 2100), (16, 224, 3, 2049), (7, 32, 3, 2049), (21, 192, "mixed", 2049)]
 
 
 def make_pages(rng, n, N, d):

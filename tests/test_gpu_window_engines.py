@@ -53,10 +53,10 @@ class Window:
             self.c.prefetch_layers(*args, stream=stream)
 
 
-# Few engines on a queue that keeps them busy for milliseconds, of the wide kind (16 waves, up to 256 or 512 engines by
-# page shape); and the narrow kind, which more engines than that take, on queues long enough for the same.
+# Engines on a queue that keeps them busy for milliseconds: few and many of the wide kind (16 waves, up to 256 or 512 engines by
+# page shape), with a clerk and turn by turn; and the narrow kind, which more engines than that take.
 @pytest.mark.parametrize("N,d,ppb,omega,layers,n_seq,k", [(16, 128, 4, 2, 8, 16, 8), (16, 64, 16, 4, 8, 16, 8), (16, 256, 3, 3, 8, 16, 8), (24, 96, 5, 2, 8, 16, 8),
-                                                          (16, 32, 16, 1, 8, 16, 8), (16, 128, 1, 1024, 16, 1024, 32), (16, 64, 2, 1024, 32, 1024, 32)])
+                                                          (16, 32, 16, 1, 8, 16, 8), (16, 128, 16, 256, 24, 64, 32), (16, 32, 16, 200, 32, 128, 32), (16, 128, 1, 1024, 16, 1024, 32), (16, 64, 2, 1024, 32, 1024, 32)])
 def test_a_layer_stamped_ready_can_be_read_while_the_window_is_open(N, d, ppb, omega, layers, n_seq, k):
     w = Window(N, d, ppb, layers, n_seq, k, 96)
     want = w.buffer()

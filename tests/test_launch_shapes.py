@@ -1,5 +1,5 @@
 """Rules of the launches, found without a GPU (tests/launch_shapes.py): which kernel a call gets, in which shape."""
-from launch_shapes import launches
+from launch_shapes import large_decoder_pages, large_encoder_pages, launches
 
 
 def decode(N, d, ppb, n, **kw):
@@ -58,3 +58,19 @@ def test_encoder_workgroups_of_16_waves_end_where_they_stop_being_resident():
     for c, l in zip(calls, launches(calls)):
         D, NP, partial, waves, ppw, scheme = l[0].params
         assert scheme < 0 and ((waves, ppw) == (16, 1)) == (c["n"] == 4096), (c, l[0])
+
+
+def test_where_the_large_launch_shapes_begin():
+    """large_encoder_pages and large_decoder_pages, from which tests take their sizes, say what the library does."""
+    shapes = [(N, d) for d in range(32, 257, 32) for N in sorted({16, 1, 8, 32, *(512 * p // d + e for p in range(1, 9) for e in (0, 1))}) if 1 <= N <= 4096 // d]
+    kinds = [(N, d, sc) for N, d in shapes for sc in (0, 1, 2, 3, 4, "mixed")] + [(16, d, 5) for d in (64, 128, 256)]
+    encode = lambda N, d, sc, n: dict(op="compress", N=N, d=d, ppb=1, n=n, scheme=3 if sc == "mixed" else sc, mixed=sc == "mixed")
+    calls = [encode(N, d, sc, n) for N, d, sc in kinds for n in (large_encoder_pages(N, d, sc) - 1, large_encoder_pages(N, d, sc), 1 << 20)]
+    got = [l[0] for l in launches(calls)]
+    for i, kind in enumerate(kinds):
+        below, first, large = got[3 * i:3 * i + 3]
+        assert first.params == large.params != below.params, (kind, below, first, large)
+    several = [(N, d) for N, d in shapes if large_decoder_pages(N, d)]
+    for N, d in several:
+        below, first = (l[0] for l in launches([decode(N, d, 1, n) for n in (large_decoder_pages(N, d) - 1, large_decoder_pages(N, d))]))
+        assert below.params[-1] == 1 and first.params[-1] == (4 if N * d <= 512 else 2), (N, d)
