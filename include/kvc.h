@@ -211,22 +211,27 @@ int kvc_prefetch_layers(kvc_ctx* ctx, void* d_l2, int32_t* d_tags, int32_t* d_fe
 /* kvc_prefetch_layers with Algorithm 1's outstanding-request window (WaitCompletion over at most
  * Omega_max concurrent transfers; Section 3.4.2 gives the paper's controller a window of 16): the
  * transfers the planner issues are queued in issue order (layer, sequence, slot) and carried out by at
- * most `omega` transfer engines (workgroups), each holding one block in flight: an engine takes the next
- * queue entries, up to eight in a row, and asks for no payload of a block before the block it carried out
- * before that is complete in memory.  omega >= 1; a small omega leaves most of the GPU to the computation
+ * most `omega` transfer engines (workgroups), each holding one block in flight: an engine asks for no
+ * payload of a block before the block it carried out before that is complete in memory.  An engine carries
+ * out its entries in queue order.  Which ones it takes is unspecified: the first few of every engine are
+ * dealt in advance (in a row, or one to each engine in turn), the others are taken as they come, up to
+ * eight in a row.  omega >= 1; a small omega leaves most of the GPU to the computation
  * the prefetch hides behind, a large one approaches kvc_prefetch_layers.  Plan arrays (tags, fetch, loc)
  * and buffer contents are those of kvc_prefetch_layers.
  *   d_notify  int64 [n_layers + 4], device, out.  Entry l (layers of the call only): 0 while transfers
  *             of layer l are outstanding, then the device's wall clock (hipDeviceAttributeWallClockRate
- *             ticks, never 0) at which its last transfer was reported complete (engines report at the end
- *             of the entries they took in a row) -- the ready notification a consumer
- *             may poll or wait for; a layer that needed no transfer is stamped when the window opens.
+ *             ticks, never 0) at which its last transfer was reported complete -- the ready notification
+ *             a consumer may poll or wait for; a layer that needed no transfer is stamped when the window
+ *             opens.  Engines report up to eight blocks at a time: at the end of the entries they took in a
+ *             row, or, looking ahead, when the next block is one of another layer and has been asked for.
+ *             A layer may thus be complete up to seven blocks of one engine before its stamp.
  *             [n_layers] = clock when the window opened, [n_layers+1] = transfers issued by the call,
  *             [n_layers+2] = transfer engines the call put to work: at most omega, at most one per transfer
  *             issued, at most what the GPU holds at once (1,024 to 1,792 on MI355X, by page shape), and
  *             beyond 256 only while each engine has at least eight transfers; no more blocks than that are
  *             ever in flight,
- *             [n_layers+3] = 0 until every transfer of the call has completed, then that clock value.
+ *             [n_layers+3] = 0 until every transfer of the call has completed, then that clock value; who
+ *             sees it finds all layers stamped.
  *   d_work    device workspace of at least kvc_prefetch_window_workspace(n_blocks, n_layers_call) bytes,
  *             256-byte aligned, n_blocks = (layer_end - layer_begin) * n_seq * k, n_layers_call =
  *             layer_end - layer_begin; caller-owned, contents meaningless between calls.  Calls that

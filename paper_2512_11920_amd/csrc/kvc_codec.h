@@ -26,7 +26,8 @@ typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float2v __attribute__((ext_vector_type(2)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
-// Non-temporal hints for the page-sized streams (encoder input, decoder output): measured 4-7 % faster.
+// Non-temporal hints for the encoder's streams (its input, and the payloads it stores): measured 4-7 % faster.  (The
+// decoder's stores have their own, see store_out.)
 #ifndef KVC_NT_LOAD
 #define KVC_NT_LOAD 1
 #endif
@@ -883,8 +884,9 @@ constexpr int kLdsPerCu = 160 * 1024;
 constexpr int dec_spare_lds(int groups, int own) { return groups ? kLdsPerCu / groups - 1280 - own : 0; }  // (1,280: room for the allocation's granularity)
 
 // Whether INT8 payloads go through LDS too.  With several pages per wave their loads have to be under way before
-// the first page is stored; with one page per wave they are read straight from the pool, pass by pass, which is
-// 1.5 % faster for whole launches of INT8 pages (262,144 pages of 4 KB: 285 us, 289 us through LDS).
+// the first page is stored; with one page per wave they are read straight from the pool, which is 1.5 % faster for
+// whole launches of INT8 pages even one pass at a time (262,144 pages of 4 KB: 285 us, 289 us through LDS; more passes
+// at a time see below).
 template <int PPW>
 constexpr bool kStageInt8 = PPW > 1;
 
@@ -897,10 +899,6 @@ constexpr bool kStageInt8 = PPW > 1;
 // 1008, 996, 997; a gather 686, 666, 666; raw pages 360 one by one, 376 all; INT8 pages of 16 x 256 312 one by one, 280
 // all, of 16 x 192 426 and 408, raw ones of 16 x 256 369 and 377.
 constexpr int kDecFewPages = 8192;  // 256 compute units of 32 waves
-template <class P>
-__device__ __forceinline__ bool dec_few(const DecodeArgs& a) {
-    return a.n_pages <= kDecFewPages;
-}
 constexpr int dec_int8_step(int np) { return np >= 5 ? np : 2; }
 
 // Start the payload loads of PPW pages, those of lanes first .. first + PPW - 1: the i-th goes to LDS slot i, 16
@@ -1189,7 +1187,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_decompress(DecodeArgs a) {
     const DecLanes L = dec_open<P>(a, PPW == 1 ? dec_locate(a, t0 < a.n_pages, (uint32_t)t0) : dec_locate(a, lane < PPW && t0 + lane < a.n_pages, (uint32_t)t0 + (uint32_t)lane));
     dec_fetch<P, PPW, PPW == 1>(a, L, 0, s_stage[wave]);
     dec_fetched();
-    dec_batch<P, PPW, PPW == 1>(a, L, 0, lp, s_stage[wave], dec_few<P>(a));
+    dec_batch<P, PPW, PPW == 1>(a, L, 0, lp, s_stage[wave], a.n_pages <= kDecFewPages);
 }
 
 // Transfer engines of the prefetch window that go turn by turn (Algorithm 1: at most Omega_max transfers outstanding):
@@ -1432,7 +1430,8 @@ constexpr int kCodecWaves = 4;
 // engines / wide engines that fetched a run at a time, all else alike: 64 engines 498 / 320, 256 engines 160 / 121; blocks of
 // two pages, where most waves of a wide engine have none, 735 / 748 with 64 engines (wide engines have gained a sixth
 // to a quarter since).  (The choice is made before the transfers are counted: an omega above the wide kind's number with few
-// transfers runs 256 narrow engines.)
+// transfers runs 256 narrow engines; and as wide engines are now, more engines than the device holds of them can be
+// slower than as many as it does: 4,370 blocks of 16 pages of 16 x 128 a step, two steps, omega 256 / 512 / 1,024 180 / 198 / 187 us.)
 constexpr int kWideWaves = 16;
 // Wide engines of blocks of up to this many one-pass pages go turn by turn like narrow ones.  Such a block is decoded
 // sooner than its clerk has walked ahead, and with a page for every wave the clerk's own comes on top.  Two steps of 20 layers x

@@ -124,12 +124,6 @@ __device__ __forceinline__ void shl_bytes(uint2 W, uint32_t B, uint32_t& d0, uin
     d2 = __builtin_amdgcn_perm(0u, W.y, sel);
 }
 
-// Low 32 bits of (hi : lo) >> 4c for 1 <= c <= 8.
-__device__ __forceinline__ uint32_t shr_nibbles(uint32_t lo, uint32_t hi, uint32_t c) {
-    const uint32_t v = __builtin_amdgcn_alignbit(hi, lo, c << 2);  // the shift is taken mod 32
-    return c == 8u ? hi : v;
-}
-
 // element offset of a page inside a cache buffer
 __device__ __forceinline__ int64_t page_base(const Geometry& g, int64_t blk, int pg) {
     return blk * g.block_stride + (int64_t)pg * g.page_stride;
