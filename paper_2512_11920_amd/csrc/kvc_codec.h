@@ -581,6 +581,10 @@ struct EncPlace {
 // larger calls the encoder gains less than the decoder loses on the pool it leaves (2 to 3 % from 131,072 pages on).
 constexpr int kEncInOrder8Kb = 32768;
 
+// LDS words of a wave's payloads: they follow one another as the pages are encoded, an encoded page holds at most the 512
+// bytes per pass of its INT8 form, and the one at work has a whole slot.
+constexpr int enc_stage_words(int np, int ppw) { return (ppw - 1) * np * 128 + ((np * 520 + 16 + 15) / 16) * 4; }
+
 template <class P, int WAVES, int PPW, int SCHEME>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_min_waves<P, SCHEME>()))) void k_compress(EncodeArgs a) {
     constexpr int NP = P::kPasses;
@@ -588,7 +592,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
     constexpr int kRing = enc_ring(NP, PPW, SCHEME);
     constexpr bool kUniform = PPW == 1;  // one page per wave: resolved on the scalar unit
     static_assert(PPW % kRing == 0 && PPW <= 16, "the loop handles pages in groups of kRing; a row of lanes scans them");
-    __shared__ __align__(16) uint32_t s_stage[WAVES * PPW][Slot<NP>::kWords];
+    __shared__ __align__(16) uint32_t s_stage[WAVES][enc_stage_words(NP, PPW)];
     __shared__ uint32_t s_lut[128];
     __shared__ uint32_t s_total[WAVES];
     __shared__ unsigned long long s_base;
@@ -596,7 +600,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint8_t* lut = reinterpret_cast<const uint8_t*>(s_lut);
-    uint32_t (*slots)[Slot<NP>::kWords] = &s_stage[wave * PPW];
+    uint32_t* const staged = s_stage[wave];  // the wave's payloads, one after the other
     const Extent x = page_extent<P>(a.g);
     const LanePos lp = lane_pos<P>(a.g);
     constexpr unsigned kInOrder = P::kPasses == 8 && !P::kPartial && PPW > 1 ? kEncInOrder8Kb / (WAVES * PPW) : 0;  // workgroups
@@ -606,7 +610,8 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
     const uint32_t ok = kUniform ? (L.ok ? 1u : 0u) : (uint32_t)__builtin_amdgcn_ballot_w64(L.ok);
     if (lane < PPW) s_place[wave * PPW + lane] = EncPlace{L.di, L.sb, L.pg, L.scheme, 0u, 0.0f};  // (not kept in registers meanwhile)
     wave_sync();
-    uint32_t total = 0;  // payload units of the wave's pages
+    uint32_t total = 0;  // payload units of the wave's pages,
+    uint32_t held = 0;   // and those of them that are staged (raw payloads are not)
     const int any = __builtin_ctz(ok | 0x10000u);  // a page that exists: the loads of those that do not read it again
     // the deal of the page to the lanes follows the mode requested for it
     constexpr bool kParked = kRing < PPW;  // pages are loaded while others are encoded
@@ -630,12 +635,13 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
     auto encode = [&](int i, uint4 (&raw)[NP]) {
         if (((ok >> i) & 1u) == 0) return;
         clear_beyond<P>(x, raw);
-        const PageResult r = encode_page<P, SCHEME>(raw, lp, x, scheme_of(i), slots[i], lut, a.st);
+        const PageResult r = encode_page<P, SCHEME>(raw, lp, x, scheme_of(i), staged + 4u * held, lut, a.st);
         if (lane == 0) {
             s_place[wave * PPW + i].w = r.n16 | (r.mode << 16);
             s_place[wave * PPW + i].s = r.scale;
         }
         total += r.n16;
+        held += r.mode == KVC_MODE_RAW ? 0u : r.n16;
     };
     // The register sets take turns (the inner loop is unrolled, so every index is a constant): nothing is copied
     // between them, and up to kRing pages' loads are in flight.
@@ -685,23 +691,58 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
         reinterpret_cast<uint4*>(a.desc)[own.di] =
             fits ? make_uint4((uint32_t)off, (uint32_t)(off >> 32), __float_as_uint(own.s), w_own) : make_uint4(0u, 0u, 0u, (uint32_t)KVC_MODE_INVALID << 16);
     }
-    const uint32_t store = ok & (uint32_t)__builtin_amdgcn_ballot_w64(fits);
+    // The staged payloads are one run in LDS and, but for raw pages, in the pool.  They are copied as one, and by lines of the
+    // pool: every round of lanes but the first and the last stores eight whole lines, and a line belongs to one store unless
+    // it is shared with another wave.  (Page by page, each with rounds of its own, every page split a line in two stores,
+    // which the streaming hint often sends to the memory one by one.  Compress, us: half a million pages of 16 x 128, mode
+    // 5, 484 -> 477, a million of mode 3 973 -> 966, 524,288 of 16 x 96 378 -> 368, of 16 x 64 257 -> 250, of 16 x 32 by
+    // block ids 151 -> 142; up to 16,384 pages the same.)  A wave of one page does without the lines.
+    const uint32_t unfit = ok & (uint32_t)__builtin_amdgcn_ballot_w64(!fits);  // (the wave's last pages, if any)
+    const uint32_t raws = ok & (uint32_t)__builtin_amdgcn_ballot_w64(w_own >> 16 == KVC_MODE_RAW);
+    const uint64_t base16 = of_lane<false>(off16, 0);
+    auto copy_out = [&](uint64_t to16, uint32_t from, uint32_t n) {  // n units from unit `from` of the stage to unit `to16` of the pool
+        if (n == 0) return;
+        const uint4* src = reinterpret_cast<const uint4*>(staged) + from;
+        KVC_CHECK(a.st, to16 + n <= a.pool_units && (from + n) * 4u <= (uint32_t)enc_stage_words(NP, PPW));
+        const uint32_t skew = kUniform ? 0u : (uint32_t)to16 & 7u;  // units of the first line that are not the wave's
+        const __amdgpu_buffer_rsrc_t dst = __builtin_amdgcn_make_buffer_rsrc(a.pool + (to16 - skew) * 16u, 0, (int)((skew + n) * 16u), 0x00020000);
+        constexpr int kAhead = PPW * 32 * NP >= 256 ? 4 : (PPW * 32 * NP + 63) / 64;
+        for (uint32_t u0 = 0; u0 < skew + n; u0 += 64u * kAhead) {
+            uint4v v[kAhead];
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                const uint4 t = src[min((uint32_t)max((int)(u0 + lane + 64u * k - skew), 0), n - 1u)];
+                v[k].x = t.x; v[k].y = t.y; v[k].z = t.z; v[k].w = t.w;
+            }
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {  // (units beyond the last are out of the resource's range, and so are those before the first made to be: not stored)
+                uint32_t at = (u0 + lane + 64u * k) * 16u;
+                if (k == 0) at = u0 + lane < skew ? ~15u : at;
+                __builtin_amdgcn_raw_buffer_store_b128(v[k], dst, (int)at, 0, 2);
+            }
+        }
+    };
+    if (raws == 0) {
+        copy_out(base16, 0u, unfit ? (uint32_t)(of_lane<false>(off16, __builtin_ctz(unfit)) - base16) : total);
+        return;
+    }
+    uint32_t from = 0;
 #pragma unroll 1
     for (int i = 0; i < PPW; ++i) {
-        if (((store >> i) & 1u) == 0) continue;
+        if (((ok & ~unfit) >> i & 1u) == 0) continue;
         const uint32_t w = of_lane<false>(w_own, i), n16 = w & 0xFFFFu;
-        KVC_CHECK(a.st, of_lane<false>(off16, i) + n16 <= a.pool_units && (size_t)n16 * 16 <= sizeof(uint32_t) * Slot<8>::kWords * 2);
-        uint4* dst = reinterpret_cast<uint4*>(a.pool) + of_lane<false>(off16, i);
-        if (w >> 16 == KVC_MODE_RAW) {  // the payload is the dense page
-            const EncPlace pl = s_place[wave * PPW + i];
-            const uint16_t* srcp = a.cache + page_base(a.g, (int64_t)wave_uniform(pl.sb), wave_uniform((int32_t)pl.pg));
-            for (uint32_t o = (uint32_t)lane; o < n16; o += 64) dst[o] = *reinterpret_cast<const uint4*>(srcp + elem_off(a.g, (int)o * 8));
-        } else {  // (written once and not read back by the encoder)
-            const uint4* staged = reinterpret_cast<const uint4*>(slots[i]);
-#pragma unroll
-            for (int z = 0; z < P::kRounds; ++z)
-                if ((uint32_t)lane + 64u * z < n16) store_stream(dst + lane + 64 * z, staged[lane + 64 * z]);
+        const uint64_t to16 = of_lane<false>(off16, i);
+        if (w >> 16 != KVC_MODE_RAW) {
+            copy_out(to16, from, n16);
+            from += n16;
+            continue;
         }
+        // the payload is the dense page
+        KVC_CHECK(a.st, to16 + n16 <= a.pool_units);
+        uint4* dst = reinterpret_cast<uint4*>(a.pool) + to16;
+        const EncPlace pl = s_place[wave * PPW + i];
+        const uint16_t* srcp = a.cache + page_base(a.g, (int64_t)wave_uniform(pl.sb), wave_uniform((int32_t)pl.pg));
+        for (uint32_t o = (uint32_t)lane; o < n16; o += 64) dst[o] = *reinterpret_cast<const uint4*>(srcp + elem_off(a.g, (int)o * 8));
     }
 }
 
