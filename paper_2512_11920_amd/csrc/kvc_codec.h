@@ -16,6 +16,8 @@
 // Encode: Algorithm 2 of the paper (scaling, quantize, delta, run-length encode).
 // Decode: Section 3.5.3 (undo run-length coding, prefix sum, dequantize; bypass for raw pages).
 #pragma once
+#include <type_traits>
+
 #include "kvc_device.h"
 
 namespace kvc {
@@ -24,6 +26,7 @@ namespace {
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float2v __attribute__((ext_vector_type(2)));
+typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
 // Non-temporal hints for the encoder's streams (its input, and the payloads it stores): measured 4-7 % faster.  (The
@@ -700,7 +703,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
     const uint32_t unfit = ok & (uint32_t)__builtin_amdgcn_ballot_w64(!fits);  // (the wave's last pages, if any)
     const uint32_t raws = ok & (uint32_t)__builtin_amdgcn_ballot_w64(w_own >> 16 == KVC_MODE_RAW);
     const uint64_t base16 = of_lane<false>(off16, 0);
-    auto copy_out = [&](uint64_t to16, uint32_t from, uint32_t n) {  // n units from unit `from` of the stage to unit `to16` of the pool
+    auto copy_units = [&](auto aux, uint64_t to16, uint32_t from, uint32_t n) {  // n units from unit `from` of the stage to unit `to16` of the pool
         if (n == 0) return;
         const uint4* src = reinterpret_cast<const uint4*>(staged) + from;
         KVC_CHECK(a.st, to16 + n <= a.pool_units && (from + n) * 4u <= (uint32_t)enc_stage_words(NP, PPW));
@@ -718,9 +721,16 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
             for (int k = 0; k < kAhead; ++k) {  // (units beyond the last are out of the resource's range, and so are those before the first made to be: not stored)
                 uint32_t at = (u0 + lane + 64u * k) * 16u;
                 if (k == 0) at = u0 + lane < skew ? ~15u : at;
-                __builtin_amdgcn_raw_buffer_store_b128(v[k], dst, (int)at, 0, 2);
+                __builtin_amdgcn_raw_buffer_store_b128(v[k], dst, (int)at, 0, decltype(aux)::value);
             }
         }
+    };
+    const bool kept = of_lane<true>((uint64_t)s_base, 0) < a.kept_units;  // (one answer for a workgroup)
+    auto copy_out = [&](uint64_t to16, uint32_t from, uint32_t n) {
+        if (kept)
+            copy_units(std::integral_constant<int, 16>{}, to16, from, n);  // sc1: through the L2, to stay in the last-level cache
+        else
+            copy_units(std::integral_constant<int, 2>{}, to16, from, n);  // nt
     };
     if (raws == 0) {
         copy_out(base16, 0u, unfit ? (uint32_t)(of_lane<false>(off16, __builtin_ctz(unfit)) - base16) : total);
@@ -900,8 +910,10 @@ __device__ __forceinline__ DecLanes dec_open(const DecodeArgs& a, const DecPlace
 }
 
 // 16 bytes from global memory straight to LDS: lane l's go to lds + 16 l (the destination is wave-uniform).
+// STREAM: and leave what the last-level cache holds where it is (nt).
+template <bool STREAM = false>
 __device__ __forceinline__ void load_to_lds16(const void* g, void* lds) {
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g, (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g, (__attribute__((address_space(3))) void*)lds, 16, 0, STREAM ? 2 : 0);
 }
 
 // Decoder workgroups a compute unit may hold in large calls (0: as many as fit).  With 32 waves on every compute unit,
@@ -944,7 +956,7 @@ constexpr int dec_int8_step(int np) { return np >= 5 ? np : 2; }
 
 // Start the payload loads of PPW pages, those of lanes first .. first + PPW - 1: the i-th goes to LDS slot i, 16
 // bytes per lane and round, without a stop in registers.  Payload bytes past the page's own are not read.
-template <class P, int PPW, bool UNIFORM>
+template <class P, int PPW, bool UNIFORM, bool MAY_STREAM = false>
 __device__ __forceinline__ void dec_fetch(const DecodeArgs& a, const DecLanes& L, int first, uint32_t (*slots)[Slot<P::kPasses>::kWords]) {
     const uint32_t lane = (uint32_t)lane_id();
     const bool staged = (L.meta >> 24) == kDecPayload && (kStageInt8<PPW> || ((L.meta >> 16) & 0xFFu) != KVC_MODE_INT8);
@@ -952,11 +964,36 @@ __device__ __forceinline__ void dec_fetch(const DecodeArgs& a, const DecLanes& L
 #pragma unroll
     for (int i = 0; i < PPW; ++i) {
         const uint32_t n16 = of_lane<UNIFORM>(n_own, first + i);
-        const uint8_t* src = a.pool + of_lane<UNIFORM>(L.off, first + i);
+        const uint64_t off = of_lane<UNIFORM>(L.off, first + i);
+        const uint8_t* src = a.pool + off;
+        if (MAY_STREAM && off >= a.near_bytes) {
+#pragma unroll
+            for (int z = 0; z < P::kRounds; ++z)
+                if (lane + 64u * z < n16) load_to_lds16<true>(src + (lane + 64u * z) * 16u, reinterpret_cast<uint4*>(slots[i]) + 64 * z);
+            continue;
+        }
 #pragma unroll
         for (int z = 0; z < P::kRounds; ++z)
             if (lane + 64u * z < n16) load_to_lds16(src + (lane + 64u * z) * 16u, reinterpret_cast<uint4*>(slots[i]) + 64 * z);
     }
+}
+
+// A lane's part of a payload that is read straight from the pool (or, INT8, from its staged copy).
+template <bool STREAM>
+__device__ __forceinline__ uint2 load_payload(const uint2* p) {
+    if constexpr (STREAM) {
+        const uint2v v = __builtin_nontemporal_load(reinterpret_cast<const uint2v*>(p));
+        return make_uint2(v.x, v.y);
+    } else {
+        return *p;
+    }
+}
+template <bool STREAM>
+__device__ __forceinline__ uint4 load_payload(const uint4* p) {
+    if constexpr (STREAM)
+        return load_stream(p);
+    else
+        return *p;
 }
 
 // The fetched payloads of this wave are in LDS.  (Waited for before the first output store is issued: loads
@@ -1018,7 +1055,7 @@ __device__ __forceinline__ void dec_headers(const Extent& x, const DecLanes& L, 
 }
 
 // Decode an INT8 payload at src (the staged copy, or the pool itself) into the page at dst_b, STEP passes at a time.
-template <class P, int STEP>
+template <class P, int STEP, bool STREAM = false>
 __device__ __forceinline__ void dec_int8(const DecodeArgs& a, const Extent& x, const LanePos& lp, float s, char* dst_b, const uint2* src) {
     uint2 v[P::kPasses];
 #pragma unroll
@@ -1026,7 +1063,7 @@ __device__ __forceinline__ void dec_int8(const DecodeArgs& a, const Extent& x, c
         if (p % STEP == 0) {
 #pragma unroll
             for (int q = p; q < p + STEP && q < P::kPasses; ++q)
-                if (lane_live<P>(x, q)) v[q] = src[q * 64 + lane_id()];
+                if (lane_live<P>(x, q)) v[q] = load_payload<STREAM>(src + q * 64 + lane_id());
         }
         if (!lane_live<P>(x, p)) continue;
         const uint32_t lo = v[p].x ^ 0x80808080u, hi = v[p].y ^ 0x80808080u;  // + 128 in every byte: the sign bits change
@@ -1041,7 +1078,7 @@ __device__ __forceinline__ void dec_int8(const DecodeArgs& a, const Extent& x, c
 }
 
 // Copy a raw payload, STEP passes at a time.
-template <class P, int STEP>
+template <class P, int STEP, bool STREAM = false>
 __device__ __forceinline__ void dec_raw(const DecodeArgs& a, const Extent& x, const LanePos& lp, char* dst_b, const uint4* src) {
     uint4 v[P::kPasses];
 #pragma unroll
@@ -1049,7 +1086,7 @@ __device__ __forceinline__ void dec_raw(const DecodeArgs& a, const Extent& x, co
         if (p % STEP == 0) {
 #pragma unroll
             for (int q = p; q < p + STEP && q < P::kPasses; ++q)
-                if (lane_live<P>(x, q)) v[q] = src[q * 64 + lane_id()];
+                if (lane_live<P>(x, q)) v[q] = load_payload<STREAM>(src + q * 64 + lane_id());
         }
         if (lane_live<P>(x, p)) store_out(dst_b, pass_base_off<P, false>(a.g, p), pass_lane_off<P, false>(a.g, lp, p), v[p]);
     }
@@ -1159,7 +1196,7 @@ __device__ __forceinline__ void dec_page(const DecodeArgs& a, const Extent& x, c
 }
 
 // Decode the pages whose payloads dec_fetch has loaded (dec_fetched: they are there).
-template <class P, int PPW, bool UNIFORM>
+template <class P, int PPW, bool UNIFORM, bool MAY_STREAM = false>
 __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L, int first, const LanePos& lp, uint32_t (*slots)[Slot<P::kPasses>::kWords], bool few) {
     using H = HeaderDeal<P>;
     static_assert(PPW % H::kPages == 0 || PPW == 1, "a header scan covers whole pages of the batch");
@@ -1189,8 +1226,11 @@ __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L
             }
             char* dst_b = reinterpret_cast<char*>(dst);
             if (kind == kDecRaw) {  // stored-uncompressed bypass
-                const uint4* src = reinterpret_cast<const uint4*>(a.pool + of_lane<UNIFORM>(L.off, first + i));
-                if (few)
+                const uint64_t off = of_lane<UNIFORM>(L.off, first + i);
+                const uint4* src = reinterpret_cast<const uint4*>(a.pool + off);
+                if (MAY_STREAM && off >= a.near_bytes)
+                    dec_raw<P, 1, true>(a, x, lp, dst_b, src);
+                else if (few)
                     dec_raw<P, P::kPasses>(a, x, lp, dst_b, src);
                 else
                     dec_raw<P, 1>(a, x, lp, dst_b, src);
@@ -1200,7 +1240,9 @@ __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L
             const float s = __uint_as_float(of_lane<UNIFORM>(__float_as_uint(L.s), first + i));
             if (mode == KVC_MODE_INT8) {
                 const uint2* src = kStageInt8<PPW> ? reinterpret_cast<const uint2*>(slots[i]) : reinterpret_cast<const uint2*>(a.pool + of_lane<UNIFORM>(L.off, first + i));
-                if (kStageInt8<PPW> || few || dec_int8_step(P::kPasses) >= P::kPasses)
+                if (MAY_STREAM && !kStageInt8<PPW> && of_lane<UNIFORM>(L.off, first + i) >= a.near_bytes)
+                    dec_int8<P, dec_int8_step(P::kPasses), true>(a, x, lp, s, dst_b, src);
+                else if (kStageInt8<PPW> || few || dec_int8_step(P::kPasses) >= P::kPasses)
                     dec_int8<P, P::kPasses>(a, x, lp, s, dst_b, src);
                 else
                     dec_int8<P, dec_int8_step(P::kPasses)>(a, x, lp, s, dst_b, src);
@@ -1226,9 +1268,9 @@ __global__ __launch_bounds__(WAVES * 64) void k_decompress(DecodeArgs a) {
     const LanePos lp = lane_pos<P>(a.g);
     // (a batch of one page is resolved on the scalar unit: every lane has the same task)
     const DecLanes L = dec_open<P>(a, PPW == 1 ? dec_locate(a, t0 < a.n_pages, (uint32_t)t0) : dec_locate(a, lane < PPW && t0 + lane < a.n_pages, (uint32_t)t0 + (uint32_t)lane));
-    dec_fetch<P, PPW, PPW == 1>(a, L, 0, s_stage[wave]);
+    dec_fetch<P, PPW, PPW == 1, true>(a, L, 0, s_stage[wave]);
     dec_fetched();
-    dec_batch<P, PPW, PPW == 1>(a, L, 0, lp, s_stage[wave], a.n_pages <= kDecFewPages);
+    dec_batch<P, PPW, PPW == 1, true>(a, L, 0, lp, s_stage[wave], a.n_pages <= kDecFewPages);
 }
 
 // Transfer engines of the prefetch window that go turn by turn (Algorithm 1: at most Omega_max transfers outstanding):

@@ -37,6 +37,7 @@ struct EncodeArgs {
     FastDiv by_ppb;
     uint8_t* pool;
     uint64_t pool_units;  // pool size in 16-byte units
+    uint64_t kept_units;  // payloads below this unit of the pool are stored to stay in the last-level cache (see kPoolKeptBytes)
     kvc_desc* desc;
     uint64_t n_desc;
     DevState* st;
@@ -54,6 +55,7 @@ struct DecodeArgs {
     const kvc_desc* desc;
     uint64_t n_desc;
     DevState* st;
+    uint64_t near_bytes;  // payloads from this byte of the pool on are read past the last-level cache (see kDecStreamFrom)
     // gather form (block_table != nullptr): page task t = ((l*n_seq + s)*k + j)*ppb + pg
     const int32_t* block_table;
     const int32_t* pred;
@@ -62,6 +64,23 @@ struct DecodeArgs {
     // divisions of the task resolution: by ppb, and in the gather form by n_seq * k and by k
     FastDiv by_ppb, by_per_layer, by_k;
 };
+
+// The last-level cache (256 MB, memory side) keeps what is stored without a streaming hint.  Payloads that go to the
+// beginning of a pool are stored so, and a call that brings the blocks back finds them there: compress and decompress of
+// one set of blocks, us, with every payload stored past the cache -> so: 65,536 pages of 16 x 128 138 -> 127, half a million
+// of 16 x 32 280 -> 253, of 16 x 64 517 -> 503, 98,304 of 24 x 96 226 -> 212; sixteen calls of 65,536 pages, each followed by
+// its decode, 2,240 -> 2,216.  Only the beginning, because payloads that push others out of the cache reach the memory in no
+// order: with no limit half a million pages of 16 x 128, mode 5, are encoded in 512 us (484 with the hint), and fetched back
+// no sooner.  Limits of 128, 192, 208, 224 and 256 MB: 16 x 64 510, 502, 502, 500, 520; 65,536 pages of 16 x 256, a mode per
+// block, 274, 268, 268, 271, 282 (278 with the hint).
+constexpr uint64_t kPoolKeptBytes = 208ull << 20;
+// Calls that decode a whole range of more payload than the cache holds read what lies beyond that beginning with the
+// hint: read plainly, it pushes out the beginning, and then itself, before either is read again.  By the size of the
+// pages, as the payloads' is not known here: 768 MiB are 256 MB of payload at a ratio of three.  Decode, us, read plainly ->
+// so, repeated / after 2 GB of other traffic: 768 MiB of 16 x 128 187 -> 169 / 218 -> 213, 2 GiB 507 -> 481 / 535 -> 533, 4 GiB
+// 1,003 -> 985 / 1,033 -> 1,033, 8 GiB 1,993 -> 1,988 / 2,023 -> 2,048, 16 GiB 4,001 -> 4,068 / 4,033 -> 4,067: above 4 GiB
+// what is kept is too small a part to pay for lines that two payloads share and that are then read twice.
+constexpr uint64_t kDecStreamFrom = 768ull << 20, kDecStreamTo = 4096ull << 20;
 
 constexpr int kMaxPrefetchK = 32;  // predictions per sequence the slot-reuse policy can plan
 
