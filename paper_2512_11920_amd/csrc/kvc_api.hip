@@ -376,7 +376,7 @@ static int prefetch_impl(kvc_ctx* ctx, void* d_l2, int32_t* d_tags, int32_t* d_f
     a.n_out_blocks = n_now;
     a.pool_ids = d_fetch + first;
     a.n_pages = n_now * ctx->g.ppb;
-    if (omega == 0) return hip_ok(kvc::launch_prefetch_plan(p, s)) && hip_ok(kvc::launch_decompress(a, s)) ? KVC_OK : KVC_ERR_HIP;
+    if (omega == 0) return hip_ok(kvc::launch_prefetch(p, a, s)) ? KVC_OK : KVC_ERR_HIP;
     // engines beyond what the device holds at once would never get a turn: the bound stays "at most omega"
     if (ctx->window_capacity > 0) omega = std::min(omega, ctx->window_capacity);
     kvc::WindowArgs w;
