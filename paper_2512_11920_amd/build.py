@@ -79,6 +79,29 @@ def build_debug(verbose: bool = False) -> str:
     return build(force=True, verbose=verbose, extra_flags=("-DKVC_DEBUG_BOUNDS=1",), lib=LIB_DEBUG)
 
 
+BINDING_SRC = os.path.join(_CSRC, "kvc_py.cpp")
+BINDING = os.path.join(_PKG, "_kvc_py.so")
+
+
+def build_binding(force: bool = True, verbose: bool = False) -> str:
+    """Compile the extension module that kvc.py makes its data calls through (host code, against torch's headers)."""
+    if not force and os.path.exists(BINDING) and all(os.path.getmtime(p) <= os.path.getmtime(BINDING) for p in (BINDING_SRC, HEADERS[-1])):
+        return BINDING
+    import sysconfig
+
+    import torch
+
+    at = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(_ROOT, "include"), "-isystem", os.path.join(at, "include"), "-isystem", os.path.join(at, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-o", BINDING, BINDING_SRC,
+           "-L", os.path.join(at, "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), file=sys.stderr)
+    subprocess.run(cmd, check=True)
+    return BINDING
+
+
 CLIENT_SRC = os.path.join(_ROOT, "tests", "abi_client.cpp")
 CLIENT_BIN = os.path.join(_ROOT, "tests", "abi_client")
 
@@ -94,6 +117,7 @@ def build_client(verbose: bool = False) -> str:
 
 
 if __name__ == "__main__":
+    print(build_binding(verbose=True))
     print(build(force=True, verbose=True))
     print(build_debug(verbose=True))
     print(build_client(verbose=True))

@@ -1,5 +1,6 @@
-"""Thin ctypes binding of libkvc.so (see include/kvc.h).  Argument marshalling only: every step
-of the codec runs in the HIP kernels.  PyTorch supplies device memory and streams.
+"""Thin binding of libkvc.so (see include/kvc.h).  Argument marshalling only: every step
+of the codec runs in the HIP kernels.  PyTorch supplies device memory and streams.  The data calls go through a
+small extension module (csrc/kvc_py.cpp), everything else through ctypes.
 
 There is no CPU fallback: if the library has not been built (``python -m paper_2512_11920_amd.build``)
 loading raises."""
@@ -43,16 +44,16 @@ class KvcError(RuntimeError):
 
 
 _lib = None
-# bound when the library is loaded: torch, and the calls that name the current device's current stream.  (A small data
-# call is mostly the way to the launch: torch.cuda.current_stream() alone, which makes a stream object, took 1.3 us of 7,
-# and the checks of the id tensors, written with helpers and a generator, 0.9 of 5.4.  The launch itself is 3.3.)
-_torch = _device_now = _raw_stream_now = _half = _int32 = None
+# bound when the library is loaded: torch, the calls that name the current device's current stream, and the data calls.  (A small
+# data call is mostly the way to the launch, which is 2.8 us: torch.cuda.current_stream() alone, which makes a stream object,
+# takes 1.3, and the checks of the tensors and the call, in Python and through ctypes, took 1.4.)
+_torch = _device_now = _raw_stream_now = _half = _int32 = _call = None
 _cuda_ready = False
 
 
 def load():
     """dlopen libkvc.so and declare the prototypes.  Raises if the library is missing."""
-    global _lib, _torch, _device_now, _raw_stream_now, _half, _int32
+    global _lib, _torch, _device_now, _raw_stream_now, _half, _int32, _call
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -116,6 +117,10 @@ def load():
     L.kvc_copy_bytes.argtypes = [vp, vp, C.c_uint64, vp]
     L.kvc_strerror.restype = C.c_char_p
     L.kvc_strerror.argtypes = [C.c_int]
+    from . import _kvc_py
+
+    _kvc_py.init(*(C.cast(f, vp).value for f in (L.kvc_compress_blocks, L.kvc_compress_blocks_mixed, L.kvc_decompress_blocks, L.kvc_gather_decompress, L.kvc_prefetch_layers)))
+    _call = _kvc_py
     _lib = L
     return L
 
@@ -152,20 +157,6 @@ def _ids(t):
         return None
     assert t.is_cuda and t.dtype == _int32 and t.is_contiguous(), "block ids: contiguous int32 CUDA tensor"
     return t
-
-
-def _id_ptr(t, n):
-    """Address of an id tensor of at least n entries."""
-    assert t.is_cuda and t.dtype == _int32 and t.is_contiguous(), "block ids: contiguous int32 CUDA tensor"
-    assert t.numel() >= n, "id tensors shorter than n"
-    return t.data_ptr()
-
-
-def _id_ptr_of(t, n):
-    """Address of an id tensor of exactly n entries."""
-    assert t.is_cuda and t.dtype == _int32 and t.is_contiguous(), "block ids: contiguous int32 CUDA tensor"
-    assert t.numel() == n
-    return t.data_ptr()
 
 
 class Codec:
@@ -250,43 +241,22 @@ class Codec:
 
     def compress_blocks(self, cache, n: int | None = None, src_ids=None, pool_ids=None, block_scheme=None, stream=None):
         """block_scheme: optional uint8 CUDA tensor, requested mode per block of the call."""
-        nb = self._blocks_of(cache)
-        if n is None:
-            n = src_ids.numel() if src_ids is not None else (pool_ids.numel() if pool_ids is not None else nb)
-        n = int(n)
-        src = None if src_ids is None else _id_ptr(src_ids, n)
-        pool = None if pool_ids is None else _id_ptr(pool_ids, n)
-        s = _stream_now() if stream is None else stream.cuda_stream
-        if block_scheme is None:
-            rc = self._L.kvc_compress_blocks(self._ctx, cache.data_ptr(), nb, src, pool, n, s)
-            if rc:
-                _check(rc, "kvc_compress_blocks")
-        else:
-            assert block_scheme.is_cuda and block_scheme.dtype == _torch.uint8 and block_scheme.numel() >= n
-            rc = self._L.kvc_compress_blocks_mixed(self._ctx, cache.data_ptr(), nb, src, pool, block_scheme.data_ptr(), n, s)
-            if rc:
-                _check(rc, "kvc_compress_blocks_mixed")
+        rc = _call.compress(self._ctx.value, cache, self._block_stride, self._span, n, src_ids, pool_ids, block_scheme,
+                            _stream_now() if stream is None else stream.cuda_stream)
+        if rc:
+            _check(rc, "kvc_compress_blocks" if block_scheme is None else "kvc_compress_blocks_mixed")
 
     def decompress_blocks(self, out, n: int | None = None, pool_ids=None, dst_ids=None, stream=None):
-        nb = self._blocks_of(out)
-        if n is None:
-            n = pool_ids.numel() if pool_ids is not None else (dst_ids.numel() if dst_ids is not None else nb)
-        n = int(n)
-        pool = None if pool_ids is None else _id_ptr(pool_ids, n)
-        dst = None if dst_ids is None else _id_ptr(dst_ids, n)
-        rc = self._L.kvc_decompress_blocks(self._ctx, out.data_ptr(), nb, pool, dst, n, _stream_now() if stream is None else stream.cuda_stream)
+        rc = _call.decompress(self._ctx.value, out, self._block_stride, self._span, n, pool_ids, dst_ids,
+                              _stream_now() if stream is None else stream.cuda_stream)
         if rc:
             _check(rc, "kvc_decompress_blocks")
 
     def gather_decompress(self, out, block_table, pred, n_layers: int, pool_blocks_per_layer: int, stream=None):
-        block_table, pred = _ids(block_table), _ids(pred)
-        n_seq, max_blocks = block_table.shape
-        assert pred.shape[0] == n_seq
-        k = pred.shape[1]
-        assert self._blocks_of(out) == n_layers * n_seq * k
-        _check(self._L.kvc_gather_decompress(self._ctx, out.data_ptr(), block_table.data_ptr(), max_blocks,
-                                             pred.data_ptr(), n_seq, k, n_layers, int(pool_blocks_per_layer),
-                                             _stream(stream)), "kvc_gather_decompress")
+        rc = _call.gather(self._ctx.value, out, self._block_stride, self._span, block_table, pred, n_layers, int(pool_blocks_per_layer),
+                          _stream_now() if stream is None else stream.cuda_stream)
+        if rc:
+            _check(rc, "kvc_gather_decompress")
 
     def set_prefetch_policy(self, policy: int):
         """0: prediction j uses slot j; 1: wanted blocks stay put, missing ones take unwanted slots."""
@@ -300,14 +270,8 @@ class Codec:
     def prefetch_layers(self, l2, tags, fetch, loc, block_table, pred, n_layers: int, pool_blocks_per_layer: int,
                         fill_half: int, layer_begin: int = 0, layer_end: int | None = None, l1_first=None, stream=None):
         """l2: float16 [2][n_layers*n_seq*k][ppb][N][d]; tags int32 [2][n_slots]; fetch, loc int32 [n_slots]."""
-        n_seq, max_blocks = block_table.shape
-        rows, k = pred.shape[:2]
-        n_slots = n_layers * n_seq * k
-        assert self._blocks_of(l2) == 2 * n_slots and rows == n_seq
-        rc = self._L.kvc_prefetch_layers(self._ctx, l2.data_ptr(), _id_ptr_of(tags, 2 * n_slots), _id_ptr_of(fetch, n_slots), _id_ptr_of(loc, n_slots),
-                                         _id_ptr(block_table, 0), max_blocks, _id_ptr(pred, 0), None if l1_first is None else _id_ptr_of(l1_first, n_seq),
-                                         n_seq, k, n_layers, layer_begin, n_layers if layer_end is None else layer_end, int(pool_blocks_per_layer),
-                                         fill_half, _stream_now() if stream is None else stream.cuda_stream)
+        rc = _call.prefetch(self._ctx.value, l2, self._block_stride, self._span, tags, fetch, loc, block_table, pred, l1_first, n_layers,
+                            layer_begin, layer_end, int(pool_blocks_per_layer), fill_half, _stream_now() if stream is None else stream.cuda_stream)
         if rc:
             _check(rc, "kvc_prefetch_layers")
 

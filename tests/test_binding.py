@@ -1,0 +1,64 @@
+"""The checks of the Python binding's data calls: what a tensor has to be, and which blocks a call without a count means."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2512_11920_amd import kvc
+from gpu_util import DEV
+
+
+def test_tensors_off_the_gpu_are_refused():
+    kvc.load()
+    half, ids = torch.zeros(64, dtype=torch.float16), torch.zeros((2, 2), dtype=torch.int32)
+    for call in (lambda: kvc._call.compress(0, half, 64, 64, None, None, None, None, 0), lambda: kvc._call.decompress(0, half, 64, 64, 1, None, None, 0),
+                 lambda: kvc._call.gather(0, half, 64, 64, ids, ids, 1, 4, 0), lambda: kvc._call.prefetch(0, half, 64, 64, ids, ids, ids, ids, ids, None, 1, 0, None, 4, 0, 0)):
+        with pytest.raises(AssertionError):
+            call()
+    for other in (np.zeros(64, np.float16), None, 0):
+        with pytest.raises(TypeError):
+            kvc._call.compress(0, other, 64, 64, None, None, None, None, 0)
+    with pytest.raises(TypeError):
+        kvc._call.compress(0, half)
+
+
+@pytest.mark.gpu
+def test_calls_with_and_without_a_count():
+    N, d, ppb = 16, 64, 2
+    x = torch.randn((6, ppb, N, d), device=DEV).half()
+    c = kvc.Codec(N, d, ppb, 3)
+    c.alloc_pool(6, x.numel() * 2 + 64, DEV)
+    c.compress_blocks(x)
+    assert sum(c.stats()["pages"]) == 6 * ppb  # all there are
+    want = torch.empty_like(x)
+    c.decompress_blocks(want)
+    ids = torch.tensor([4, 1, 3], dtype=torch.int32, device=DEV)
+    for kw, n in (({}, 6), ({"n": 2}, 2), ({"n": np.int64(2)}, 2), ({"pool_ids": ids}, 3), ({"pool_ids": ids, "n": 1}, 1), ({"dst_ids": ids}, 3)):
+        out = torch.full_like(x, 9.0)
+        c.decompress_blocks(out, **kw)
+        src = ids[:n].long() if "pool_ids" in kw else torch.arange(n, device=DEV)
+        dst = ids[:n].long() if "dst_ids" in kw else torch.arange(n, device=DEV)
+        rest = torch.ones(6, dtype=torch.bool, device=DEV)
+        rest[dst] = False
+        assert torch.equal(out[dst], want[src]) and (out[rest] == 9.0).all(), kw
+    out = torch.empty_like(x)
+    for bad in (dict(pool_ids=ids.long()), dict(pool_ids=ids.cpu()), dict(pool_ids=ids, n=4), dict(dst_ids=torch.stack((ids, ids), 1)[:, 0], n=2)):
+        with pytest.raises(AssertionError):
+            c.decompress_blocks(out, **bad)
+        with pytest.raises(AssertionError):
+            c.compress_blocks(x, **{"src_ids" if k == "dst_ids" else k: v for k, v in bad.items()})
+    for t in (x.float(), x.cpu(), x.transpose(2, 3)):
+        with pytest.raises(AssertionError):
+            c.compress_blocks(t)
+    for modes in (torch.zeros(6, dtype=torch.int32, device=DEV), torch.zeros(5, dtype=torch.uint8, device=DEV)):
+        with pytest.raises(AssertionError):
+            c.compress_blocks(x, block_scheme=modes)
+    table = torch.zeros((3, 2), dtype=torch.int32, device=DEV)
+    with pytest.raises(AssertionError):  # six slots, not five
+        c.gather_decompress(x[:5], table, torch.zeros((3, 2), dtype=torch.int32, device=DEV), 1, 6)
+    c.gather_decompress(out, table, torch.zeros((3, 2), dtype=torch.int32, device=DEV), 1, 6)
+    assert torch.equal(out, want[:1].expand_as(out))
+    with pytest.raises(kvc.KvcError):  # more blocks than the cache has
+        c.compress_blocks(x, n=1 << 30)
+    c.close()
+    with pytest.raises(kvc.KvcError):
+        c.compress_blocks(x)
