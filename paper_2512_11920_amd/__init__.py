@@ -1,6 +1,6 @@
 """MI355X-native KV-cache page codec (compression / decompression engine of CXL-SpecKV).
 
-``kvc``   ctypes binding of the HIP library (libkvc.so); no fallback path.
+``kvc``   binding of the HIP library (libkvc.so); no fallback path.
 ``synth`` seeded synthetic KV caches and access patterns.
 ``build`` compiles the library in-tree with hipcc for gfx950.
 """
