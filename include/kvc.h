@@ -184,7 +184,6 @@ int kvc_gather_decompress(kvc_ctx* ctx, void* d_out, const int32_t* d_block_tabl
  *           kvc_set_cache_layout a slot is a block of that layout: slot i of half h starts at element
  *           (h*n_layers*n_seq*k + i) * block_stride.
  *   d_tags  int32 [2][n_layers*n_seq*k]: pool block held by every slot, -1 = empty (kvc_prefetch_reset).
- *           While a call runs, what it holds for the call's layers of the half being filled is the library's.
  *   d_fetch int32 [n_layers*n_seq*k], out: pool block decoded into slot (l,s,j) by this call, or -1.
  *   d_loc   int32 [n_layers*n_seq*k], out: where the consumer finds predicted block (l,s,j):
  *           half*n_slots + slot (>= 0), -2 = resident in the GPU-local cache (logical block >=

@@ -17,7 +17,7 @@ SHAPE_GROUPS = 16  # see csrc/kvc_codec.hip
 UNITS = [("kvc_kernels.hip", (), "kvc_kernels.o"), ("kvc_api.hip", (), "kvc_api.o")] + \
         [("kvc_codec.hip", (f"-DKVC_SHAPE_GROUP={g}",), f"kvc_codec_{g}.o") for g in range(SHAPE_GROUPS)]
 SOURCES = [os.path.join(_CSRC, f) for f in ("kvc_kernels.hip", "kvc_codec.hip", "kvc_api.hip")]
-HEADERS = [os.path.join(_CSRC, f) for f in ("kvc_common.h", "kvc_fastdiv.h", "kvc_device.h", "kvc_plan.h", "kvc_codec.h")] + [os.path.join(_ROOT, "include", "kvc.h")]
+HEADERS = [os.path.join(_CSRC, f) for f in ("kvc_common.h", "kvc_fastdiv.h", "kvc_device.h", "kvc_codec.h")] + [os.path.join(_ROOT, "include", "kvc.h")]
 LIB = os.path.join(_PKG, "libkvc.so")
 #: the same library with every LDS index and pool span the kernels compute checked against its bounds
 #: (a violation sets status bit 8); a GPU test runs the parity cases through it

@@ -376,7 +376,13 @@ static int prefetch_impl(kvc_ctx* ctx, void* d_l2, int32_t* d_tags, int32_t* d_f
     a.n_out_blocks = n_now;
     a.pool_ids = d_fetch + first;
     a.n_pages = n_now * ctx->g.ppb;
-    if (omega == 0) return hip_ok(kvc::launch_prefetch(p, a, s)) ? KVC_OK : KVC_ERR_HIP;
+    // Two launches, also where a step has few pages.  In one, whose workgroups each plan the row they decode a part of, a step that
+    // has the chip to itself is shorter (a layer of 8,192 pages of 16 x 128, us: 12.7 instead of 14.6), but beside a layer's compute
+    // workgroups that only find that nothing is to be fetched wait for a place on the chip with all their waves: what such steps
+    // add to a GEMM on another stream, predictions that slide over their blocks, is 13.2 instead of 7.6, 1,024 pages 7.3 / 6.4, and
+    // of 8,192 rows of one page, alone, 35.9 / 15.8.  Whichever workgroup of a row is the last to have read its tags would also have
+    // to be counted somewhere, and a caller's tags leave no room for a count.
+    if (omega == 0) return hip_ok(kvc::launch_prefetch_plan(p, s)) && hip_ok(kvc::launch_decompress(a, s)) ? KVC_OK : KVC_ERR_HIP;
     // engines beyond what the device holds at once would never get a turn: the bound stays "at most omega"
     if (ctx->window_capacity > 0) omega = std::min(omega, ctx->window_capacity);
     kvc::WindowArgs w;

@@ -18,7 +18,7 @@
 #pragma once
 #include <type_traits>
 
-#include "kvc_plan.h"
+#include "kvc_device.h"
 
 namespace kvc {
 namespace {
@@ -1273,59 +1273,6 @@ __global__ __launch_bounds__(WAVES * 64) void k_decompress(DecodeArgs a) {
     dec_batch<P, PPW, PPW == 1, true>(a, L, 0, lp, s_stage[wave], a.n_pages <= kDecFewPages);
 }
 
-// A prefetch step of few pages in one launch: every workgroup plans the row (layer, sequence) that its pages belong to, and
-// decodes those of them that are to be fetched.  Such a step is two chains of memory trips, planner and decoder, and the end
-// of one launch and the beginning of the next lie between them; here the descriptors are asked for as soon as the plan is there.
-// One wave plans, the others wait for it: a few hundred instructions, once for eight pages.  Reset and two steps of one layer,
-// blocks of 16 pages of 16 x 128, us, two launches a step -> one: 64 sequences of 8 (8,192 pages) 23.8 -> 21.4, 32 18.5 ->
-// 16.1, 4 13.9 -> 12.5 (with the host's launches, eager, 20.5 -> 16.6); 16 x 256 40.9 -> 38.3, 16 x 64 in blocks of eight 16.7 ->
-// 14.4.  Workgroups of 4 / 8 / 16 waves 24.0 / 21.4 / 21.5 with 64 sequences, 13.1 / 12.5 / 14.3 with four.
-//
-// The workgroups of a row all read its tags, and one of them has to write them.  It is the last to have read them, and
-// which that is the upper bits of the tag of the row's first slot tell: they count, and the last one leaves the slot's tag
-// there.  (A count anywhere else would have to be cleared by an earlier launch, or be shared by calls on several
-// streams.)  It is counted when the payloads are there, so that nothing waits for the count: asked for with the payloads, 22.6
-// us instead of 21.4.
-constexpr int kPrefetchWaves = 8;
-template <class P, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void k_prefetch_decompress(PrefetchParams f) {
-    const DecodeArgs& a = f.a;
-    const PlanArgs& p = f.p;
-    __shared__ __align__(16) uint32_t s_stage[WAVES][1][Slot<P::kPasses>::kWords];
-    __shared__ int32_t s_fetch[kPrefetchOneK];
-    const int lane = lane_id();
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t b = task_block_index(), row = fast_div(b, f.by_groups), part = b - row * f.groups;
-    const LanePos lp = lane_pos<P>(a.g);
-    PlanSlot slot = {};
-    if (wave == 0) {
-        const uint32_t l = fast_div(row, p.by_n_seq);
-        slot = plan_row<kPrefetchOneK>(p, lane < kPrefetchOneK, p.layer_begin + (int32_t)l, (int32_t)(row - l * (uint32_t)p.n_seq), f.tag_bits);
-        if (lane < kPrefetchOneK) s_fetch[lane] = slot.live ? slot.fetch : -1;
-    }
-    __syncthreads();
-    const uint32_t t = part * WAVES + (uint32_t)wave, j = fast_div(t, a.by_ppb);
-    DecPlace pl;
-    pl.live = j < (uint32_t)p.k;
-    pl.bad_index = false;
-    pl.pb = wave_uniform(s_fetch[min(j, kPrefetchOneK - 1u)]);
-    pl.db = (int32_t)(row * (uint32_t)p.k + j);
-    pl.pg = t - j * (uint32_t)a.g.ppb;
-    const DecLanes L = dec_open<P>(a, pl);
-    dec_fetch<P, 1, true>(a, L, 0, s_stage[wave]);
-    dec_fetched();
-    // this workgroup has read the row's tags
-    uint32_t before = 0;  // and so had this many
-    if (wave == 0 && lane == 0 && f.tag_bits != 0)
-        before = (atomicAdd(reinterpret_cast<uint32_t*>(&p.tags[slot.tag_at]), 1u << (32 - f.tag_bits)) - (uint32_t)slot.had) >> (32 - f.tag_bits);
-    dec_batch<P, 1, true>(a, L, 0, lp, s_stage[wave], true);
-    if (wave == 0 && (uint32_t)wave_uniform((int32_t)before) + 1u == f.groups && slot.live) {
-        p.loc[slot.at] = slot.loc;
-        p.fetch[slot.at] = slot.fetch;
-        if (slot.fetch >= 0 || lane == 0) __hip_atomic_store(&p.tags[slot.tag_at], slot.tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-
 // Transfer engines of the prefetch window that go turn by turn (Algorithm 1: at most Omega_max transfers outstanding):
 // the narrow ones, for calls of many, and wide ones of blocks of few one-pass pages.  A workgroup takes the next issued blocks from the queue (a turn), its waves decode them one block after
 // the other, meeting after each -- no payload of a block is asked for before the last store of the engine's block before
@@ -1693,19 +1640,6 @@ struct ShapeOps {
         return launch_kernel_lds(k_decompress<P, kCodecWaves, dec_ppw(NP)>, page_grid(a.n_pages, dec_ppw(NP)), dim3(kCodecWaves * 64), lds, s, a);
     }
 
-    // a prefetch step in one launch
-    static hipError_t prefetch(const PlanArgs& p, const DecodeArgs& a, hipStream_t s) {
-        const int64_t row_pages = (int64_t)p.k * a.g.ppb;
-        PrefetchParams f;
-        f.a = a;
-        f.p = p;
-        f.groups = (uint32_t)((row_pages + kPrefetchWaves - 1) / kPrefetchWaves);
-        f.by_groups = make_fast_div(f.groups);
-        f.tag_bits = 0;
-        while ((1u << f.tag_bits) < f.groups) ++f.tag_bits;
-        return launch_kernel(k_prefetch_decompress<P, kPrefetchWaves>, dim3((unsigned)(a.n_pages / row_pages) * f.groups), dim3(kPrefetchWaves * 64), s, f);
-    }
-
     // whether the wide engines of blocks of ppb pages are of the kind that looks ahead
     static bool window_looks_ahead(int ppb) { return NP > 1 || ppb > kTurnPages; }
 
@@ -1733,7 +1667,7 @@ struct ShapeOps {
         return cus * per_cu;
     }
 
-    static constexpr ShapeKernels kTable = {D, NP, PARTIAL, &compress, &decompress, &prefetch, &decompress_window, &window_capacity, &window_looks_ahead};
+    static constexpr ShapeKernels kTable = {D, NP, PARTIAL, &compress, &decompress, &decompress_window, &window_capacity, &window_looks_ahead};
 };
 
 }  // namespace

@@ -99,21 +99,6 @@ struct PlanArgs {
     DevState* st;
 };
 
-// A prefetch step in one launch: the workgroups of a row (a sequence of a layer) each plan it and decode a part of it.
-struct PrefetchParams {
-    DecodeArgs a;
-    PlanArgs p;
-    uint32_t groups;  // workgroups of a row
-    FastDiv by_groups;
-    int32_t tag_bits;  // upper bits of the tag of a row's first slot in which they are counted
-};
-// Steps of one launch: of as many pages as the chip holds waves at once (every workgroup of a row plans it, which only pays while
-// they are all resident: reset and two steps, us, two launches / one, 16,384 pages of 16 x 128 38.9 / 41.5, of 16 x 32 20.0 / 30.9),
-// with at most eight predictions, a lane each of the planning wave, and of rows and pools whose count and tags share 32 bits:
-// 32 workgroups of a row and 2^26 blocks of the bound descriptor table.
-constexpr int64_t kPrefetchOnePages = 8192, kPrefetchOneRow = 256, kPrefetchOneBlocks = 1 << 26;
-constexpr int kPrefetchOneK = 8;
-
 // Outstanding-request window of the prefetch path (Algorithm 1: WaitCompletion over at most Omega_max
 // concurrent transfers).  The workspace of one call: this header, then one pending counter per layer of
 // the call, then the queue of issued transfers (slot indices relative to the call's first slot).
@@ -175,7 +160,7 @@ inline hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, hip
     return launch_kernel_lds(kernel, grid, block, 0, s, args...);
 }
 
-hipError_t launch_prefetch(const PlanArgs& p, const DecodeArgs& a, hipStream_t s);
+hipError_t launch_prefetch_plan(const PlanArgs& a, hipStream_t s);
 hipError_t launch_window_plan(const PlanArgs& a, const WindowArgs& w, hipStream_t s);
 hipError_t launch_decompress_window(const DecodeArgs& a, const WindowArgs& w, hipStream_t s);
 int window_engine_capacity(const Geometry& g, bool wide);

@@ -470,7 +470,6 @@ struct ShapeKernels {
     bool partial;
     hipError_t (*compress)(const EncodeArgs& a, hipStream_t s);
     hipError_t (*decompress)(const DecodeArgs& a, hipStream_t s);
-    hipError_t (*prefetch)(const PlanArgs& p, const DecodeArgs& a, hipStream_t s);
     hipError_t (*decompress_window)(const DecodeArgs& a, const WindowArgs& w, unsigned grid, bool wide, hipStream_t s);
     int (*window_capacity)(bool wide, int ppb);  // window engines resident on the current device at once (0: unknown)
     bool (*window_looks_ahead)(int ppb);         // whether the wide ones look ahead

@@ -4,7 +4,7 @@ its launches down (tests/launch_recorder.cpp), in a process of its own, and call
     launches([call, ...]) -> [[Launch, ...], ...]
 
 A call is a dict: op ("compress", "decompress", "gather", "prefetch"), N, d, ppb, scheme, n (blocks) and, by op, lists
-(names of the id lists it passes), mixed (a mode per block), layers, seqs, k, omega."""
+(names of the id lists it passes), mixed (a mode per block), layers, seqs, k, omega; desc: pages of its descriptor table, where that is not to be a huge one."""
 import collections
 import ctypes as C
 import json
@@ -76,7 +76,7 @@ def _main(recorder, lib):
     for c in json.load(sys.stdin):
         cfg, ctx = (i32 * 4)(c["N"], c["d"], c["ppb"], c.get("scheme", 3)), C.c_void_p()
         n, lists = c.get("n", 0), c.get("lists", ())
-        assert L.kvc_create(C.byref(ctx), cfg) == 0 and L.kvc_bind_pool(ctx, at, big, at, big) == 0
+        assert L.kvc_create(C.byref(ctx), cfg) == 0 and L.kvc_bind_pool(ctx, at, big, at, C.c_uint64(c.get("desc", 1 << 40))) == 0
         rec.rec_clear()
         opt = lambda name: at if name in lists else None
         if c["op"] == "compress" and c.get("mixed"):

@@ -1,6 +1,7 @@
-"""A prefetch step that plans and decodes in one launch, where its rows, its calls and its tags end: rows of one workgroup,
-of a part of one and of 32, calls of 8,192 pages, eight predictions, tags of the largest blocks -- and beyond each line, where the
-planner is a launch of its own.  Tags, fetch list, places and buffer are the model's at every step."""
+"""Prefetch steps of few pages: rows of a part of a workgroup, of one and of many, calls around the pages that the chip holds
+waves for, eight predictions and more -- over tags of every kind: blocks of the pool, empty, the largest and smallest of an int32,
+blocks of a larger table that was bound before.  A tag that is no block of the step is a slot without one of its blocks, whatever
+it is.  Tags, fetch list, places and buffer are the model's at every step."""
 import numpy as np
 import pytest
 import torch
@@ -12,7 +13,7 @@ from gpu_util import DEV, gpu_compress
 
 pytestmark = pytest.mark.gpu
 
-LARGEST = (1 << 26) - 1  # the last block of the largest descriptor table whose steps are one launch
+STRANGE = [-2, -(1 << 31), (1 << 31) - 1, -(1 << 26) - 1, 1 << 26, (1 << 27) - 1, 0x68000000]  # tags no block of the pool has
 
 
 @pytest.mark.parametrize("policy", [0, 1])
@@ -35,7 +36,7 @@ def test_steps_match_the_model(N, d, ppb, n_seq, k, layers, policy):
     full = o.decompress_pages(op, od, N, d, n_threads=8)[0].reshape(layers * pbl, ppb, N, d)
     c.set_prefetch_policy(policy)
     model_step = pm.prefetch_step_reuse if policy else pm.prefetch_step
-    m_tags = rng.choice(np.array([-1, LARGEST, LARGEST - 1, 0, layers * pbl - 1], np.int32), (2, layers, n_seq, k))
+    m_tags = rng.choice(np.array([-1, 0, 1, layers * pbl - 1] + STRANGE, np.int64).astype(np.int32), (2, layers, n_seq, k))
     tags = torch.from_numpy(m_tags.reshape(-1).copy()).to(DEV)
     fetch, loc = (torch.full((n_slots,), 7, dtype=torch.int32, device=DEV) for _ in range(2))
     l2 = torch.full((2 * n_slots, ppb, N, d), 5.0, dtype=torch.float16, device=DEV)
@@ -47,7 +48,7 @@ def test_steps_match_the_model(N, d, ppb, n_seq, k, layers, policy):
         if step == 4:
             pred[n_seq // 2, 0] = 10  # beyond the table
         l1 = np.maximum(nb - 1, 1).astype(np.int32) if step % 3 == 2 else None
-        print(f"[case] one launch N={N} d={d} ppb={ppb} seqs={n_seq} k={k} layers={layers} policy={policy} step {step}", flush=True)
+        print(f"[case] prefetch steps N={N} d={d} ppb={ppb} seqs={n_seq} k={k} layers={layers} policy={policy} step {step}", flush=True)
         for lo, hi in ((0, 1), (1, layers)):  # (the second is a call over no layers where there is one)
             c.prefetch_layers(l2, tags, fetch, loc, dev_table, torch.from_numpy(pred).to(DEV), layers, pbl, step % 2, layer_begin=lo, layer_end=hi,
                               l1_first=None if l1 is None else torch.from_numpy(l1).to(DEV))

@@ -40,6 +40,15 @@ def test_the_counting_planner_stays_with_few_sequences():
         assert l[0].params == (lanes,)
 
 
+def test_a_prefetch_step_is_planned_by_rows_and_decoded_by_pages():
+    """Whatever the rows: the decoder gets a wave per page, also where a row has one, or one more than fill a workgroup."""
+    for k, ppb, seqs, layers in ((1, 1, 1, 1), (1, 1, 8192, 1), (1, 9, 910, 1), (4, 1, 2048, 1), (8, 1, 1024, 1), (8, 16, 64, 1), (8, 16, 4, 2), (8, 33, 3, 1), (9, 4, 6, 2), (32, 2, 5, 1)):
+        plan, decoder = launches([dict(op="prefetch", N=16, d=128, ppb=ppb, seqs=seqs, k=k, layers=layers, omega=0, desc=layers * 64 * ppb)])[0]
+        lanes = 8 if k <= 8 else 16 if k <= 16 else 32
+        assert plan.kernel == "k_prefetch_plan" and plan.params == (lanes,) and plan.grid == -(-layers * seqs // (64 // lanes))
+        assert decoder.kernel == "k_decompress" and decoder.grid == -(-layers * seqs * k * ppb // (decoder.block // 64))
+
+
 def test_wide_engines_of_small_blocks_go_turn_by_turn():
     """Up to 16 one-pass pages a block; blocks of more, and of larger pages, have engines that look ahead."""
     small = [(16, 32, 1), (16, 32, 16), (7, 32, 8), (8, 64, 16), (5, 96, 2), (3, 128, 16), (2, 256, 16)]
