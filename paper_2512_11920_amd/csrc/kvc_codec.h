@@ -31,30 +31,16 @@ typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
 // Non-temporal hints for the encoder's streams (its input, and the payloads it stores): measured 4-7 % faster.  (The
 // decoder's stores have their own, see store_out.)
-#ifndef KVC_NT_LOAD
-#define KVC_NT_LOAD 1
-#endif
-#ifndef KVC_NT_STORE
-#define KVC_NT_STORE 1
-#endif
 
 // 128-bit global accesses of streamed data (each byte is touched once)
 __device__ __forceinline__ uint4 load_stream(const uint4* p) {
-#if KVC_NT_LOAD
     const uint4v v = __builtin_nontemporal_load(reinterpret_cast<const uint4v*>(p));
     return make_uint4(v.x, v.y, v.z, v.w);
-#else
-    return *p;
-#endif
 }
 __device__ __forceinline__ void store_stream(uint4* p, const uint4& v) {
-#if KVC_NT_STORE
     uint4v w;
     w.x = v.x; w.y = v.y; w.z = v.z; w.w = v.w;
     __builtin_nontemporal_store(w, reinterpret_cast<uint4v*>(p));
-#else
-    *p = v;
-#endif
 }
 
 // Compile-time shape of a page of NP passes with D channels per token.  PARTIAL: the page has fewer
