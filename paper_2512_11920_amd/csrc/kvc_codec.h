@@ -583,8 +583,10 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
     static_assert(PPW % kRing == 0 && PPW <= 16, "the loop handles pages in groups of kRing; a row of lanes scans them");
     __shared__ __align__(16) uint32_t s_stage[WAVES][enc_stage_words(NP, PPW)];
     __shared__ uint32_t s_lut[128];
-    __shared__ uint32_t s_total[WAVES];
+    __shared__ uint32_t s_total[WAVES];  // units of each wave's payloads; kHasRaw: raw pages among them
     __shared__ unsigned long long s_base;
+    __shared__ uint32_t s_kept;
+    constexpr uint32_t kHasRaw = 1u << 24;
     __shared__ EncPlace s_place[WAVES * PPW];
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -653,22 +655,26 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
         }
     }
     // One atomic on the pool cursor reserves a contiguous span for all pages of the workgroup.
-    if (lane == 0) s_total[wave] = total;
+    if (lane == 0) s_total[wave] = total | (held != total ? kHasRaw : 0u);
     __syncthreads();
     if (threadIdx.x == 0) {
-        uint32_t all = 0;
+        uint32_t all = 0, raw_too = 0;
 #pragma unroll
-        for (int k = 0; k < WAVES; ++k) all += s_total[k];
+        for (int k = 0; k < WAVES; ++k) {
+            all += s_total[k] & (kHasRaw - 1u);
+            raw_too |= s_total[k] & kHasRaw;
+        }
         const unsigned long long base = all ? atomicAdd(&a.st->cursor16, (unsigned long long)all) : 0ull;
         if (base + all > a.pool_units) atomicOr(&a.st->status, KVC_ST_POOL_FULL);
         s_base = base;
+        s_kept = raw_too == 0 && base < a.kept_units;
     }
     __syncthreads();
     if (ok == 0) return;
     // lane i: where page i's payload goes; pages that do not fit become INVALID
     uint32_t before = 0;  // units of the waves before this one
 #pragma unroll
-    for (int k = 0; k < WAVES - 1; ++k) before += k < wave ? s_total[k] : 0u;
+    for (int k = 0; k < WAVES - 1; ++k) before += k < wave ? s_total[k] & (kHasRaw - 1u) : 0u;
     wave_sync();
     const EncPlace& own = s_place[wave * PPW + min(lane, PPW - 1)];
     const uint32_t w_own = lane < PPW ? own.w : 0u;  // lane i: page i's
@@ -680,8 +686,8 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
         reinterpret_cast<uint4*>(a.desc)[own.di] =
             fits ? make_uint4((uint32_t)off, (uint32_t)(off >> 32), __float_as_uint(own.s), w_own) : make_uint4(0u, 0u, 0u, (uint32_t)KVC_MODE_INVALID << 16);
     }
-    // The staged payloads are one run in LDS and, but for raw pages, in the pool.  They are copied as one, and by lines of the
-    // pool: every round of lanes but the first and the last stores eight whole lines, and a line belongs to one store unless
+    // The staged payloads are one run in LDS and, where the wave has no raw pages, in the pool.  That is copied as one, and by lines
+    // of the pool: every round of lanes but the first and the last stores eight whole lines, and a line belongs to one store unless
     // it is shared with another wave.  (Page by page, each with rounds of its own, every page split a line in two stores,
     // which the streaming hint often sends to the memory one by one.  Compress, us: half a million pages of 16 x 128, mode
     // 5, 484 -> 477, a million of mode 3 973 -> 966, 524,288 of 16 x 96 378 -> 368, of 16 x 64 257 -> 250, of 16 x 32 by
@@ -689,10 +695,10 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
     const uint32_t unfit = ok & (uint32_t)__builtin_amdgcn_ballot_w64(!fits);  // (the wave's last pages, if any)
     const uint32_t raws = ok & (uint32_t)__builtin_amdgcn_ballot_w64(w_own >> 16 == KVC_MODE_RAW);
     const uint64_t base16 = of_lane<false>(off16, 0);
-    auto copy_units = [&](auto aux, uint64_t to16, uint32_t from, uint32_t n) {  // n units from unit `from` of the stage to unit `to16` of the pool
+    auto copy_out = [&](auto aux, uint64_t to16, uint32_t n) {  // n units from the beginning of the stage to unit `to16` of the pool
         if (n == 0) return;
-        const uint4* src = reinterpret_cast<const uint4*>(staged) + from;
-        KVC_CHECK(a.st, to16 + n <= a.pool_units && (from + n) * 4u <= (uint32_t)enc_stage_words(NP, PPW));
+        const uint4* src = reinterpret_cast<const uint4*>(staged);
+        KVC_CHECK(a.st, to16 + n <= a.pool_units && n * 4u <= (uint32_t)enc_stage_words(NP, PPW));
         const uint32_t skew = kUniform ? 0u : (uint32_t)to16 & 7u;  // units of the first line that are not the wave's
         const __amdgpu_buffer_rsrc_t dst = __builtin_amdgcn_make_buffer_rsrc(a.pool + (to16 - skew) * 16u, 0, (int)((skew + n) * 16u), 0x00020000);
         constexpr int kAhead = PPW * 32 * NP >= 256 ? 4 : (PPW * 32 * NP + 63) / 64;
@@ -711,15 +717,17 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
             }
         }
     };
-    const bool kept = of_lane<true>((uint64_t)s_base, 0) < a.kept_units;  // (one answer for a workgroup)
-    auto copy_out = [&](uint64_t to16, uint32_t from, uint32_t n) {
-        if (kept)
-            copy_units(std::integral_constant<int, 16>{}, to16, from, n);  // sc1: through the L2, to stay in the last-level cache
-        else
-            copy_units(std::integral_constant<int, 2>{}, to16, from, n);  // nt
-    };
+    // (One answer for a workgroup, and no where it holds raw pages: those are read again and stored plainly, they need the cache
+    // for themselves.  Compress / compress and decompress, us, every payload stored past the cache, those of clean waves kept, those
+    // of clean workgroups: 256 MiB of 16 x 64, every second page raw, 104 / 180, 103 / 182, 103 / 181, of 16 x 256 116 / 203,
+    // 119 / 217, 116 / 203; one page in 64 raw 75 / 145, 73 / 130, 74 / 136.)
+    const bool kept = wave_uniform((int)s_kept) != 0;
     if (raws == 0) {
-        copy_out(base16, 0u, unfit ? (uint32_t)(of_lane<false>(off16, __builtin_ctz(unfit)) - base16) : total);
+        const uint32_t n = unfit ? (uint32_t)(of_lane<false>(off16, __builtin_ctz(unfit)) - base16) : total;
+        if (kept)
+            copy_out(std::integral_constant<int, 16>{}, base16, n);  // sc1: through the L2, to stay in the last-level cache
+        else
+            copy_out(std::integral_constant<int, 2>{}, base16, n);  // nt
         return;
     }
     uint32_t from = 0;
@@ -729,7 +737,14 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
         const uint32_t w = of_lane<false>(w_own, i), n16 = w & 0xFFFFu;
         const uint64_t to16 = of_lane<false>(off16, i);
         if (w >> 16 != KVC_MODE_RAW) {
-            copy_out(to16, from, n16);
+            // page by page, in plain rounds: the rounds by lines cost more than they save on so short runs (compress, us, 256 MiB
+            // with every second page raw: 16 x 64 134 -> 104, 16 x 128 134 -> 117; 1 GiB of 16 x 32, one in 16: 327 -> 290)
+            KVC_CHECK(a.st, to16 + n16 <= a.pool_units && (from + n16) * 4u <= (uint32_t)enc_stage_words(NP, PPW));
+            uint4* to = reinterpret_cast<uint4*>(a.pool) + to16;
+            const uint4* src = reinterpret_cast<const uint4*>(staged) + from;
+#pragma unroll
+            for (int z = 0; z < P::kRounds; ++z)
+                if ((uint32_t)lane + 64u * z < n16) store_stream(to + lane + 64 * z, src[lane + 64 * z]);
             from += n16;
             continue;
         }
