@@ -24,7 +24,7 @@ struct kvc_ctx {
     kvc::DevState* st;  // device
     uint8_t* pool;
     uint64_t pool_bytes;
-    bool pool_in_hbm;  // plain device memory
+    bool pool_in_hbm, desc_in_hbm;  // plain device memory
     kvc_desc* desc;
     uint64_t n_desc;
 };
@@ -94,7 +94,7 @@ int kvc_create(kvc_ctx** out, const kvc_config* cfg) {
     c->g.block_stride = (int64_t)c->g.E * cfg->pages_per_block;
     c->pool = nullptr;
     c->pool_bytes = 0;
-    c->pool_in_hbm = false;
+    c->pool_in_hbm = c->desc_in_hbm = false;
     c->desc = nullptr;
     c->n_desc = 0;
     if (!hip_ok(hipGetDevice(&c->device)) || !hip_ok(hipMalloc(&c->st, sizeof(kvc::DevState)))) {
@@ -173,6 +173,7 @@ int kvc_bind_pool(kvc_ctx* ctx, void* d_pool, uint64_t pool_bytes, kvc_desc* d_d
     ctx->pool = static_cast<uint8_t*>(d_pool);
     ctx->pool_bytes = pool_bytes;
     ctx->pool_in_hbm = attr.type == hipMemoryTypeDevice;
+    ctx->desc_in_hbm = dattr.type == hipMemoryTypeDevice;
     ctx->desc = d_desc;
     ctx->n_desc = n_desc_pages;
     return KVC_OK;
@@ -272,7 +273,8 @@ int kvc_decompress_blocks(kvc_ctx* ctx, void* d_cache_out, int64_t n_out_blocks,
     a.dst_ids = d_dst_block_ids;
     a.n_pages = (int64_t)n * ctx->g.ppb;
     const uint64_t page_bytes = (uint64_t)a.n_pages * (uint64_t)ctx->g.E * 2u;
-    if (!d_pool_block_ids && !d_dst_block_ids && ctx->pool_in_hbm && page_bytes >= kvc::kDecStreamFrom && page_bytes <= kvc::kDecStreamTo) a.near_bytes = kvc::kPoolKeptBytes;
+    if (!d_pool_block_ids && !d_dst_block_ids && ctx->pool_in_hbm && ctx->desc_in_hbm && page_bytes >= kvc::kDecStreamFrom && page_bytes <= kvc::kDecStreamTo)
+        a.near_bytes = kvc::kPoolKeptBytes;
     return hip_ok(kvc::launch_decompress(a, static_cast<hipStream_t>(stream))) ? KVC_OK : KVC_ERR_HIP;
 }
 

@@ -55,7 +55,7 @@ struct DecodeArgs {
     const kvc_desc* desc;
     uint64_t n_desc;
     DevState* st;
-    uint64_t near_bytes;  // payloads from this byte of the pool on are read past the last-level cache (see kDecStreamFrom)
+    uint64_t near_bytes;  // where the range's first payload lies below this byte of the pool, those from it on are read past the last-level cache (see kDecStreamFrom)
     // gather form (block_table != nullptr): page task t = ((l*n_seq + s)*k + j)*ppb + pg
     const int32_t* block_table;
     const int32_t* pred;
@@ -76,11 +76,22 @@ struct DecodeArgs {
 constexpr uint64_t kPoolKeptBytes = 208ull << 20;
 // Calls that decode a whole range of more payload than the cache holds read what lies beyond that beginning with the
 // hint: read plainly, it pushes out the beginning, and then itself, before either is read again.  By the size of the
-// pages, as the payloads' is not known here: 768 MiB are 256 MB of payload at a ratio of three.  Decode, us, read plainly ->
-// so, repeated / after 2 GB of other traffic: 768 MiB of 16 x 128 187 -> 169 / 218 -> 213, 2 GiB 507 -> 481 / 535 -> 533, 4 GiB
-// 1,003 -> 985 / 1,033 -> 1,033, 8 GiB 1,993 -> 1,988 / 2,023 -> 2,048, 16 GiB 4,001 -> 4,068 / 4,033 -> 4,067: above 4 GiB
-// what is kept is too small a part to pay for lines that two payloads share and that are then read twice.
-constexpr uint64_t kDecStreamFrom = 768ull << 20, kDecStreamTo = 4096ull << 20;
+// pages, as the payloads' (a half to a third of it) is not known here; and only where the range's first payload lies in
+// the beginning, which the kernel looks up: a range beyond it has nothing there to protect, and lines that two payloads share
+// would be read twice.  16 x 128, mode 3, us, read plainly / with the hint: decode repeated; compress and decompress; decode
+// after 2 GB of other traffic; decode repeated of a range that begins 256 MB into the pool (in the last, the hint is not taken):
+//   512 MiB   109 / 110      239 / 239      154 / 152      109 / 128
+//   576 MiB   134 / 126      269 / 269      177 / 171      136 / 146
+//   640 MiB   155 / 141      300 / 299      191 / 185      158 / 160
+//     1 GiB   254 / 242      502 / 489      287 / 279      255 / 258
+//     2 GiB   510 / 495      994 / 981      542 / 541      512 / 519
+//     4 GiB 1,015 / 1,002  1,972 / 1,964  1,044 / 1,050  1,014 / 1,031
+//   4.5 GiB 1,144 / 1,132  2,228 / 2,214  1,179 / 1,179  1,138 / 1,158
+//     5 GiB 1,272 / 1,255  2,473 / 2,460  1,298 / 1,313  1,273 / 1,290
+// The other shapes turn at much the same sizes.  16 x 32, 16 x 64, 24 x 96, 16 x 256 and mode 5 of 16 x 128 win 6 to 12 % of a
+// repeated decode at 640 MiB; at 576 16 x 256 loses 3 % and mode 5 2 %.  At 4 GiB they win 0 to 3 % and lose less than 1 % after other
+// traffic; at 4.5 GiB 16 x 32, 16 x 256 and mode 5 win nothing and lose 1 % after other traffic.  Raw pages win 2 to 10 % at every size.
+constexpr uint64_t kDecStreamFrom = 608ull << 20, kDecStreamTo = 4352ull << 20;
 
 constexpr int kMaxPrefetchK = 32;  // predictions per sequence the slot-reuse policy can plan
 

@@ -4,7 +4,8 @@ its launches down (tests/launch_recorder.cpp), in a process of its own, and call
     launches([call, ...]) -> [[Launch, ...], ...]
 
 A call is a dict: op ("compress", "decompress", "gather", "prefetch"), N, d, ppb, scheme, n (blocks) and, by op, lists
-(names of the id lists it passes), mixed (a mode per block), layers, seqs, k, omega; desc: pages of its descriptor table, where that is not to be a huge one."""
+(names of the id lists it passes), mixed (a mode per block), layers, seqs, k, omega; desc: pages of its descriptor table, where that is not to be a
+huge one; memory: (hipMemoryType, device) of its pool.  Launch.line: kept_units or near_bytes of an encoder or decoder, in bytes of the pool."""
 import collections
 import ctypes as C
 import json
@@ -34,7 +35,7 @@ def large_decoder_pages(N, d):
     return 4096 * passes + 1 if passes <= 2 else None
 
 
-Launch = collections.namedtuple("Launch", "kernel params grid block lds")  # params: the kernel's template arguments
+Launch = collections.namedtuple("Launch", "kernel params grid block lds line")  # params: the kernel's template arguments
 
 
 def _recorder():
@@ -46,6 +47,7 @@ def _recorder():
         with open(versions, "w") as f:
             f.write("hip_4.2 { global: *; };\n")
         subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-Wno-attributes",
+                        "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(ROOT, "paper_2512_11920_amd", "csrc"),
                         "-Wl,-soname,libamdhip64.so.7", f"-Wl,--version-script={versions}", "-o", os.path.join(_dir.name, "rec.so"),
                         os.path.join(ROOT, "tests", "launch_recorder.cpp")], check=True)
     return os.path.join(_dir.name, "rec.so")
@@ -59,23 +61,24 @@ def launches(calls):
     out = []
     for rows in json.loads(p.stdout):
         out.append([])
-        for mangled, grid, block, lds in rows:
+        for mangled, grid, block, lds, line in rows:
             name = re.search(r"\d(k_[a-z_]+?)(?:I|E|PK|PN|P[a-z]|N\d|v)", mangled).group(1)
             args = re.search(re.escape(name) + r"I(.*?)EEv", mangled)
             nums = re.findall(r"L[ib](n?)(\d+)E", args.group(1) + "E") if args else []
-            out[-1].append(Launch(name, tuple(-int(v) if s else int(v) for s, v in nums), grid, block, lds))
+            out[-1].append(Launch(name, tuple(-int(v) if s else int(v) for s, v in nums), grid, block, lds, line))
     return out
 
 
 def _main(recorder, lib):
     rec = C.CDLL(recorder, mode=C.RTLD_GLOBAL)
-    rec.rec_kernel.restype = C.c_char_p
+    rec.rec_kernel.restype, rec.rec_line.restype = C.c_char_p, C.c_ulonglong
     L = C.CDLL(lib)
     at, big, i32, i64 = C.c_void_p(1 << 20), C.c_uint64(1 << 40), C.c_int32, C.c_int64
     out = []
     for c in json.load(sys.stdin):
         cfg, ctx = (i32 * 4)(c["N"], c["d"], c["ppb"], c.get("scheme", 3)), C.c_void_p()
         n, lists = c.get("n", 0), c.get("lists", ())
+        rec.rec_memory(*c.get("memory", (2, 0)))
         assert L.kvc_create(C.byref(ctx), cfg) == 0 and L.kvc_bind_pool(ctx, at, big, at, C.c_uint64(c.get("desc", 1 << 40))) == 0
         rec.rec_clear()
         opt = lambda name: at if name in lists else None
@@ -98,7 +101,7 @@ def _main(recorder, lib):
         for i in range(rec.rec_count()):
             g, b, l = C.c_uint(), C.c_uint(), C.c_uint()
             rec.rec_shape(i, C.byref(g), C.byref(b), C.byref(l))
-            rows.append((rec.rec_kernel(i).decode(), g.value, b.value, l.value))
+            rows.append((rec.rec_kernel(i).decode(), g.value, b.value, l.value, rec.rec_line(i)))
         out.append(rows)
         L.kvc_destroy(ctx)
     print(json.dumps(out))

@@ -83,3 +83,28 @@ def test_where_the_large_launch_shapes_begin():
     for N, d in several:
         below, first = (l[0] for l in launches([decode(N, d, 1, n) for n in (large_decoder_pages(N, d) - 1, large_decoder_pages(N, d))]))
         assert below.params[-1] == 1 and first.params[-1] == (4 if N * d <= 512 else 2), (N, d)
+
+
+def test_which_calls_read_past_the_last_level_cache():
+    """Decoders of a whole range of 608 MiB to 4.25 GiB of pages, whatever their shape, from a pool in device memory; no call that
+    names its blocks.  Encoders keep the first 208 MB of such a pool, every call."""
+    plain, kept = (1 << 64) - 1, 208 << 20
+    calls, want = [], []
+    for N, d, ppb in ((16, 128, 8), (16, 128, 1), (16, 32, 8), (24, 96, 6), (7, 32, 3), (16, 256, 16)):
+        block = 2 * N * d * ppb
+        first, last = -(-(608 << 20) // block), (4352 << 20) // block
+        for n, line in ((1, plain), (first - 1, plain), (first, kept), (last, kept), (last + 1, plain)):
+            calls.append(decode(N, d, ppb, n))
+            want.append(line)
+        for lists in (["pool"], ["dst"], ["pool", "dst"]):
+            calls.append(decode(N, d, ppb, first, lists=lists))
+            want.append(plain)
+        calls.append(decode(N, d, ppb, first, memory=(1, 0)))  # behind the host link
+        want.append(plain)
+        for lists in ([], ["pool"], ["src", "pool"]):
+            calls += [dict(op="compress", N=N, d=d, ppb=ppb, n=first, lists=lists, scheme=s, memory=m) for s in (0, 3) for m in ((2, 0), (1, 0))]
+            want += [kept, 0] * 2
+    calls += [dict(op="gather", N=16, d=128, ppb=16, seqs=64, k=8, layers=32), dict(op="prefetch", N=16, d=128, ppb=16, seqs=64, k=8, layers=32, omega=0)]
+    want += [plain] * 2
+    for call, line, l in zip(calls, want, launches(calls)):
+        assert l[-1].kernel == ("k_compress" if call["op"] == "compress" else "k_decompress") and l[-1].line == line, (call, l)
