@@ -24,7 +24,7 @@ struct kvc_ctx {
     kvc::DevState* st;  // device
     uint8_t* pool;
     uint64_t pool_bytes;
-    bool pool_in_hbm, desc_in_hbm;  // plain device memory
+    bool pool_in_hbm, desc_in_hbm;  // plain memory of this device
     kvc_desc* desc;
     uint64_t n_desc;
 };
@@ -172,8 +172,8 @@ int kvc_bind_pool(kvc_ctx* ctx, void* d_pool, uint64_t pool_bytes, kvc_desc* d_d
     }
     ctx->pool = static_cast<uint8_t*>(d_pool);
     ctx->pool_bytes = pool_bytes;
-    ctx->pool_in_hbm = attr.type == hipMemoryTypeDevice;
-    ctx->desc_in_hbm = dattr.type == hipMemoryTypeDevice;
+    ctx->pool_in_hbm = attr.type == hipMemoryTypeDevice && attr.device == ctx->device;
+    ctx->desc_in_hbm = dattr.type == hipMemoryTypeDevice && dattr.device == ctx->device;
     ctx->desc = d_desc;
     ctx->n_desc = n_desc_pages;
     return KVC_OK;

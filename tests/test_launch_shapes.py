@@ -86,7 +86,7 @@ def test_where_the_large_launch_shapes_begin():
 
 
 def test_which_calls_read_past_the_last_level_cache():
-    """Decoders of a whole range of 608 MiB to 4.25 GiB of pages, whatever their shape, from a pool in device memory; no call that
+    """Decoders of a whole range of 608 MiB to 4.25 GiB of pages, whatever their shape, from a pool in the device's own memory; no call that
     names its blocks.  Encoders keep the first 208 MB of such a pool, every call."""
     plain, kept = (1 << 64) - 1, 208 << 20
     calls, want = [], []
@@ -99,11 +99,11 @@ def test_which_calls_read_past_the_last_level_cache():
         for lists in (["pool"], ["dst"], ["pool", "dst"]):
             calls.append(decode(N, d, ppb, first, lists=lists))
             want.append(plain)
-        calls.append(decode(N, d, ppb, first, memory=(1, 0)))  # behind the host link
-        want.append(plain)
+        calls += [decode(N, d, ppb, first, memory=m) for m in ((1, 0), (2, 1))]  # behind the host link, or the link to another device
+        want += [plain] * 2
         for lists in ([], ["pool"], ["src", "pool"]):
-            calls += [dict(op="compress", N=N, d=d, ppb=ppb, n=first, lists=lists, scheme=s, memory=m) for s in (0, 3) for m in ((2, 0), (1, 0))]
-            want += [kept, 0] * 2
+            calls += [dict(op="compress", N=N, d=d, ppb=ppb, n=first, lists=lists, scheme=s, memory=m) for s in (0, 3) for m in ((2, 0), (1, 0), (2, 1))]
+            want += [kept, 0, 0] * 2
     calls += [dict(op="gather", N=16, d=128, ppb=16, seqs=64, k=8, layers=32), dict(op="prefetch", N=16, d=128, ppb=16, seqs=64, k=8, layers=32, omega=0)]
     want += [plain] * 2
     for call, line, l in zip(calls, want, launches(calls)):
