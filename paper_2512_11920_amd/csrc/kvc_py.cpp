@@ -5,6 +5,7 @@
 #include <Python.h>
 
 #include <ATen/core/Tensor.h>
+#include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <exception>
@@ -33,14 +34,6 @@ void require(bool c, const char* what = nullptr) {
     throw Raised();
 }
 
-const at::Tensor& tensor(PyObject* o) {
-    if (!THPVariable_Check(o)) {
-        PyErr_Format(PyExc_TypeError, "a tensor, not %s", Py_TYPE(o)->tp_name);
-        throw Raised();
-    }
-    return THPVariable_Unpack(o);
-}
-
 long long integer(PyObject* o) {
     const long long v = PyLong_AsLongLong(o);
     if (v == -1 && PyErr_Occurred()) throw Raised();
@@ -56,20 +49,71 @@ T address(PyObject* o) {
     return reinterpret_cast<T>(p);
 }
 
+// A reference that is given back.
+struct Ref {
+    PyObject* o;
+    explicit Ref(PyObject* o) : o(o) {
+        if (!o) throw Raised();
+    }
+    ~Ref() { Py_DECREF(o); }
+    Ref(const Ref&) = delete;
+};
+
+// An argument that is to be a tensor.  torch's own are looked at directly; a subclass, or any other object with a tensor's attributes (a
+// wrapper of one), is asked as Python code would ask it.
+class Tensor {
+    const at::Tensor* t = nullptr;
+    PyObject* o;
+
+    Ref get(const char* what) const { return Ref(PyObject_GetAttrString(o, what)); }
+    Ref call(const char* what) const { return Ref(PyObject_CallMethod(o, what, nullptr)); }
+    static bool truth(const Ref& r) {
+        const int v = PyObject_IsTrue(r.o);
+        if (v < 0) throw Raised();
+        return v != 0;
+    }
+
+public:
+    explicit Tensor(PyObject* o) : o(o) {
+        if (THPVariable_CheckExact(o)) {
+            t = &THPVariable_Unpack(o);
+        } else if (!PyObject_HasAttrString(o, "is_cuda")) {
+            PyErr_Format(PyExc_TypeError, "a tensor, not %s", Py_TYPE(o)->tp_name);
+            throw Raised();
+        }
+    }
+    bool is_cuda() const { return t ? t->is_cuda() : truth(get("is_cuda")); }
+    bool is_contiguous() const { return t ? t->is_contiguous() : truth(call("is_contiguous")); }
+    bool holds(at::ScalarType type) const {
+        if (t) return t->scalar_type() == type;
+        const Ref d = get("dtype");
+        return THPDtype_Check(d.o) && reinterpret_cast<THPDtype*>(d.o)->scalar_type == type;
+    }
+    long long numel() const { return t ? t->numel() : integer(call("numel").o); }
+    void* data_ptr() const { return t ? t->data_ptr() : address<void*>(call("data_ptr").o); }
+    long long dim() const {
+        if (t) return t->dim();
+        const Py_ssize_t n = PyObject_Length(get("shape").o);
+        if (n < 0) throw Raised();
+        return n;
+    }
+    long long size(int i) const { return t ? t->size(i) : integer(Ref(PySequence_GetItem(get("shape").o, i)).o); }
+};
+
 const char kIds[] = "block ids: contiguous int32 CUDA tensor";
-void check_ids(const at::Tensor& t) { require(t.is_cuda() && t.scalar_type() == at::kInt && t.is_contiguous(), kIds); }
+void check_ids(const Tensor& t) { require(t.is_cuda() && t.holds(at::kInt) && t.is_contiguous(), kIds); }
 
 // address of an id tensor of at least n entries; None: no list
 int32_t* ids_at_least(PyObject* o, long long n) {
     if (o == Py_None) return nullptr;
-    const at::Tensor& t = tensor(o);
+    const Tensor t(o);
     check_ids(t);
     require(t.numel() >= n, "id tensors shorter than n");
     return static_cast<int32_t*>(t.data_ptr());
 }
 // ... of exactly n
 int32_t* ids_of(PyObject* o, long long n) {
-    const at::Tensor& t = tensor(o);
+    const Tensor t(o);
     check_ids(t);
     require(t.numel() == n);
     return static_cast<int32_t*>(t.data_ptr());
@@ -81,21 +125,26 @@ struct Blocks {
     long long n;
 };
 Blocks blocks(PyObject* o, PyObject* stride, PyObject* span) {
-    const at::Tensor& t = tensor(o);
-    require(t.is_cuda() && t.is_contiguous() && t.scalar_type() == at::kHalf);
+    const Tensor t(o);
+    require(t.is_cuda() && t.is_contiguous() && t.holds(at::kHalf));
     const long long have = t.numel(), need = integer(span);
     return {t.data_ptr(), have < need ? 0 : (have - need) / integer(stride) + 1};
 }
 
 // blocks of a call: as asked for, else of its first list, else all there are
 long long count(PyObject* n, PyObject* first, PyObject* second, long long all) {
-    if (n == Py_None) return first != Py_None ? tensor(first).numel() : second != Py_None ? tensor(second).numel() : all;
-    PyObject* v = PyNumber_Long(n);
-    if (!v) throw Raised();
-    const long long r = PyLong_AsLongLong(v);
-    Py_DECREF(v);
-    if (r == -1 && PyErr_Occurred()) throw Raised();
-    return r;
+    if (n == Py_None) return first != Py_None ? Tensor(first).numel() : second != Py_None ? Tensor(second).numel() : all;
+    return integer(Ref(PyNumber_Long(n)).o);
+}
+
+// rows and columns of a table
+struct Rows {
+    long long n, each;
+};
+Rows rows(const Tensor& t, bool more_allowed) {
+    const long long dim = t.dim();
+    require(dim == 2 || (dim > 2 && more_allowed), "block table and predictions: a row per sequence");
+    return {t.size(0), t.size(1)};
 }
 
 template <class F>
@@ -142,8 +191,8 @@ PyObject* py_compress(PyObject*, PyObject* const* a, Py_ssize_t given) {
         const int32_t *src = ids_at_least(a[5], n), *pool = ids_at_least(a[6], n);
         void* stream = address<void*>(a[8]);
         if (a[7] == Py_None) return unlocked([&] { return e.compress(ctx, b.at, b.n, src, pool, (int32_t)n, stream); });
-        const at::Tensor& modes = tensor(a[7]);
-        require(modes.is_cuda() && modes.scalar_type() == at::kByte && modes.numel() >= n);
+        const Tensor modes(a[7]);
+        require(modes.is_cuda() && modes.holds(at::kByte) && modes.numel() >= n);
         const uint8_t* m = static_cast<const uint8_t*>(modes.data_ptr());
         return unlocked([&] { return e.compress_mixed(ctx, b.at, b.n, src, pool, m, (int32_t)n, stream); });
     });
@@ -161,25 +210,21 @@ PyObject* py_decompress(PyObject*, PyObject* const* a, Py_ssize_t given) {
     });
 }
 
-void check_pairs(const at::Tensor& table, const at::Tensor& pred) {
-    require(table.dim() == 2 && pred.dim() >= 2, "block table and predictions: a row per sequence");
-}
-
 // gather(ctx, out, stride, span, block_table, pred, n_layers, pool_blocks_per_layer, stream)
 PyObject* py_gather(PyObject*, PyObject* const* a, Py_ssize_t given) {
     return guarded(given, 9, [&] {
         kvc_ctx* ctx = address<kvc_ctx*>(a[0]);
-        const at::Tensor &table = tensor(a[4]), &pred = tensor(a[5]);
+        const Tensor table(a[4]), pred(a[5]);
         check_ids(table);
         check_ids(pred);
-        check_pairs(table, pred);
-        const long long n_seq = table.size(0), k = pred.size(1), layers = integer(a[6]), per_layer = integer(a[7]);
-        require(pred.size(0) == n_seq);
+        const Rows tr = rows(table, false), pr = rows(pred, true);
+        const long long n_seq = tr.n, k = pr.each, layers = integer(a[6]), per_layer = integer(a[7]);
+        require(pr.n == n_seq);
         const Blocks b = blocks(a[1], a[2], a[3]);
         require(b.n == layers * n_seq * k);
         void* stream = address<void*>(a[8]);
         const int32_t *t = static_cast<const int32_t*>(table.data_ptr()), *p = static_cast<const int32_t*>(pred.data_ptr());
-        const int32_t max_blocks = (int32_t)table.size(1);
+        const int32_t max_blocks = (int32_t)tr.each;
         return unlocked([&] { return e.gather(ctx, b.at, t, max_blocks, p, (int32_t)n_seq, (int32_t)k, (int32_t)layers, per_layer, stream); });
     });
 }
@@ -189,12 +234,11 @@ PyObject* py_gather(PyObject*, PyObject* const* a, Py_ssize_t given) {
 PyObject* py_prefetch(PyObject*, PyObject* const* a, Py_ssize_t given) {
     return guarded(given, 16, [&] {
         kvc_ctx* ctx = address<kvc_ctx*>(a[0]);
-        const at::Tensor &table = tensor(a[7]), &pred = tensor(a[8]);
-        check_pairs(table, pred);
-        const long long n_seq = table.size(0), max_blocks = table.size(1), k = pred.size(1), layers = integer(a[10]);
-        const long long n_slots = layers * n_seq * k;
+        const Rows tr = rows(Tensor(a[7]), false), pr = rows(Tensor(a[8]), true);
+        const long long n_seq = tr.n, max_blocks = tr.each, k = pr.each, layers = integer(a[10]);
         const Blocks b = blocks(a[1], a[2], a[3]);
-        require(b.n == 2 * n_slots && pred.size(0) == n_seq);
+        require(b.n == 2 * (layers * n_seq * k) && pr.n == n_seq);
+        const long long n_slots = b.n / 2;
         int32_t *tags = ids_of(a[4], 2 * n_slots), *fetch = ids_of(a[5], n_slots), *loc = ids_of(a[6], n_slots);
         const int32_t *t = ids_at_least(a[7], 0), *p = ids_at_least(a[8], 0), *l1 = a[9] == Py_None ? nullptr : ids_of(a[9], n_seq);
         const long long begin = integer(a[11]), end = a[12] == Py_None ? layers : integer(a[12]), per_layer = integer(a[13]), half = integer(a[14]);

@@ -62,3 +62,53 @@ def test_calls_with_and_without_a_count():
     c.close()
     with pytest.raises(kvc.KvcError):
         c.compress_blocks(x)
+
+
+class Wrapper:
+    """An object that answers for the tensor it holds, as a paged cache's own class may; says it is on the GPU."""
+
+    is_cuda = True
+
+    def __init__(self, t):
+        self._t = t
+
+    def __getattr__(self, name):
+        return getattr(self._t, name)
+
+
+class Subclass(torch.Tensor):
+    is_cuda = True
+
+
+def all_calls(ctx, wrap, layers=1, table=(3, 2), pred=(3, 2), blocks=6):
+    """The data calls, over blocks of 64 elements, with arguments the checks take when a row per sequence is given."""
+    half, ids = (lambda n: wrap(torch.zeros(64 * n, dtype=torch.float16))), (lambda *s: wrap(torch.zeros(s, dtype=torch.int32)))
+    return {
+        "compress": lambda: kvc._call.compress(ctx, half(blocks), 64, 64, None, ids(blocks), None, None, 0),
+        "mixed": lambda: kvc._call.compress(ctx, half(blocks), 64, 64, None, None, ids(blocks), wrap(torch.zeros(blocks, dtype=torch.uint8)), 0),
+        "decompress": lambda: kvc._call.decompress(ctx, half(blocks), 64, 64, 2, ids(blocks), ids(2), 0),
+        "gather": lambda: kvc._call.gather(ctx, half(blocks), 64, 64, ids(*table), ids(*pred), layers, 4, 0),
+        "prefetch": lambda: kvc._call.prefetch(ctx, half(2 * blocks), 64, 64, ids(2 * blocks), ids(blocks), ids(blocks), ids(*table), ids(*pred), ids(table[0]), layers, 0, None, 4, 0, 0),
+    }
+
+
+@pytest.mark.parametrize("wrap", [Wrapper, lambda t: t.as_subclass(Subclass)])
+def test_objects_with_a_tensors_attributes(wrap):
+    """They are asked, and pass or fail as their answers do.  (No context: the library refuses the call after the checks.)"""
+    kvc.load()
+    for name, call in all_calls(None, wrap).items():
+        assert call() == kvc.ERR_ARG, name
+    for name, call in all_calls(None, lambda t: wrap(t.double())).items():
+        with pytest.raises(AssertionError):
+            call()
+    strided = wrap(torch.zeros((64, 2), dtype=torch.float16).t())
+    with pytest.raises(AssertionError):
+        kvc._call.compress(None, strided, 64, 64, None, None, None, None, 0)
+    with pytest.raises(AssertionError, match="shorter"):
+        kvc._call.decompress(None, wrap(torch.zeros(64, dtype=torch.float16)), 64, 64, 3, wrap(torch.zeros(2, dtype=torch.int32)), None, 0)
+
+    class Half:
+        is_cuda = True
+
+    with pytest.raises(AttributeError):  # what it lacks is named
+        kvc._call.compress(None, Half(), 64, 64, None, None, None, None, 0)
