@@ -147,6 +147,9 @@ Rows rows(const Tensor& t, bool more_allowed) {
     return {t.size(0), t.size(1)};
 }
 
+// (products of sizes that a caller may have got wrong: wide enough not to wrap round to the right number)
+typedef __int128 wide;
+
 template <class F>
 PyObject* guarded(Py_ssize_t given, Py_ssize_t want, F f) {
     if (given != want) {
@@ -221,7 +224,7 @@ PyObject* py_gather(PyObject*, PyObject* const* a, Py_ssize_t given) {
         const long long n_seq = tr.n, k = pr.each, layers = integer(a[6]), per_layer = integer(a[7]);
         require(pr.n == n_seq);
         const Blocks b = blocks(a[1], a[2], a[3]);
-        require(b.n == layers * n_seq * k);
+        require(b.n == (wide)layers * n_seq * k);
         void* stream = address<void*>(a[8]);
         const int32_t *t = static_cast<const int32_t*>(table.data_ptr()), *p = static_cast<const int32_t*>(pred.data_ptr());
         const int32_t max_blocks = (int32_t)tr.each;
@@ -237,7 +240,7 @@ PyObject* py_prefetch(PyObject*, PyObject* const* a, Py_ssize_t given) {
         const Rows tr = rows(Tensor(a[7]), false), pr = rows(Tensor(a[8]), true);
         const long long n_seq = tr.n, max_blocks = tr.each, k = pr.each, layers = integer(a[10]);
         const Blocks b = blocks(a[1], a[2], a[3]);
-        require(b.n == 2 * (layers * n_seq * k) && pr.n == n_seq);
+        require(b.n == 2 * ((wide)layers * n_seq * k) && pr.n == n_seq);
         const long long n_slots = b.n / 2;
         int32_t *tags = ids_of(a[4], 2 * n_slots), *fetch = ids_of(a[5], n_slots), *loc = ids_of(a[6], n_slots);
         const int32_t *t = ids_at_least(a[7], 0), *p = ids_at_least(a[8], 0), *l1 = a[9] == Py_None ? nullptr : ids_of(a[9], n_seq);

@@ -112,3 +112,12 @@ def test_objects_with_a_tensors_attributes(wrap):
 
     with pytest.raises(AttributeError):  # what it lacks is named
         kvc._call.compress(None, Half(), 64, 64, None, None, None, None, 0)
+
+
+def test_sizes_whose_product_wraps_round():
+    """One layer of six blocks is right; this many layers are not, though their blocks are six modulo 2^64."""
+    kvc.load()
+    for layers in (1 + (1 << 63) - (1 << 64), 1 + (1 << 62), 1 - (1 << 62)):
+        for name in ("gather", "prefetch"):
+            with pytest.raises(AssertionError):
+                all_calls(None, Wrapper, layers=layers, table=(4, 2), pred=(4, 4), blocks=16)[name]()
