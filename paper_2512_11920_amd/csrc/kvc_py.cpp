@@ -137,13 +137,16 @@ long long count(PyObject* n, PyObject* first, PyObject* second, long long all) {
     return integer(Ref(PyNumber_Long(n)).o);
 }
 
-// rows and columns of a table
+// rows and columns of a table; an object of another shape cannot be unpacked to them
 struct Rows {
     long long n, each;
 };
-Rows rows(const Tensor& t, bool more_allowed) {
+Rows rows(const Tensor& t, bool more_allowed, PyObject* error = PyExc_ValueError) {
     const long long dim = t.dim();
-    require(dim == 2 || (dim > 2 && more_allowed), "block table and predictions: a row per sequence");
+    if (dim < 2 || (dim > 2 && !more_allowed)) {
+        PyErr_Format(error, "block table and predictions: a row per sequence, not %lld dimensions", dim);
+        throw Raised();
+    }
     return {t.size(0), t.size(1)};
 }
 
@@ -220,7 +223,7 @@ PyObject* py_gather(PyObject*, PyObject* const* a, Py_ssize_t given) {
         const Tensor table(a[4]), pred(a[5]);
         check_ids(table);
         check_ids(pred);
-        const Rows tr = rows(table, false), pr = rows(pred, true);
+        const Rows tr = rows(table, false), pr = rows(pred, true, PyExc_IndexError);
         const long long n_seq = tr.n, k = pr.each, layers = integer(a[6]), per_layer = integer(a[7]);
         require(pr.n == n_seq);
         const Blocks b = blocks(a[1], a[2], a[3]);

@@ -114,6 +114,18 @@ def test_objects_with_a_tensors_attributes(wrap):
         kvc._call.compress(None, Half(), 64, 64, None, None, None, None, 0)
 
 
+def test_tables_without_a_row_per_sequence():
+    kvc.load()
+    for table, pred, gather, prefetch in (((6,), (3, 2), ValueError, ValueError), ((3, 2, 1), (3, 2), ValueError, ValueError), ((3, 2), (3,), IndexError, ValueError),
+                                          ((3, 2), (4, 2), AssertionError, AssertionError)):
+        calls = all_calls(None, Wrapper, table=table, pred=pred)
+        with pytest.raises(gather):
+            calls["gather"]()
+        with pytest.raises(prefetch):
+            calls["prefetch"]()
+    assert all_calls(None, Wrapper, pred=(3, 2, 1))["gather"]() == kvc.ERR_ARG
+
+
 def test_sizes_whose_product_wraps_round():
     """One layer of six blocks is right; this many layers are not, though their blocks are six modulo 2^64."""
     kvc.load()
