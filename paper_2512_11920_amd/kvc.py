@@ -2,7 +2,7 @@
 of the codec runs in the HIP kernels.  PyTorch supplies device memory and streams.  The data calls go through a
 small extension module (csrc/kvc_py.cpp), everything else through ctypes.
 
-There is no CPU fallback: if the library has not been built (``python -m paper_2512_11920_amd.build``)
+There is no CPU fallback: if the library and the module have not been built (``python -m paper_2512_11920_amd.build``)
 loading raises."""
 from __future__ import annotations
 
@@ -13,6 +13,8 @@ import numpy as np
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libkvc.so")
+#: the extension module of the data calls
+BINDING_PATH = os.path.join(_PKG, "_kvc_py.so")
 
 OK, ERR_ARG, ERR_NOT_BOUND, ERR_HIP, ERR_POOL_FULL, ERR_CORRUPT, ERR_UNSUPPORTED, ERR_TOO_LARGE = 0, -1, -2, -3, -4, -5, -6, -7
 MODE_RAW, MODE_INT8, MODE_DELTA, MODE_RLE, MODE_PACK, MODE_CHAN, MODE_INVALID = 0, 1, 2, 3, 4, 5, 0xFF
@@ -52,13 +54,14 @@ _cuda_ready = False
 
 
 def load():
-    """dlopen libkvc.so and declare the prototypes.  Raises if the library is missing."""
+    """dlopen libkvc.so and declare the prototypes.  Raises if the library or the extension module is missing."""
     global _lib, _torch, _device_now, _raw_stream_now, _half, _int32, _call
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise ImportError(f"{LIB_PATH} is not built; run `python -m paper_2512_11920_amd.build` "
-                          "(there is no fallback implementation)")
+    for path in (LIB_PATH, BINDING_PATH):
+        if not os.path.exists(path):
+            raise ImportError(f"{path} is not built; run `python -m paper_2512_11920_amd.build` "
+                              "(there is no fallback implementation)")
     # libkvc.so needs the HIP runtime by soname; importing torch first makes the loader resolve it
     # to the copy torch already mapped, so tensors and kernels share one runtime instance.
     import torch

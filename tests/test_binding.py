@@ -133,3 +133,12 @@ def test_sizes_whose_product_wraps_round():
         for name in ("gather", "prefetch"):
             with pytest.raises(AssertionError):
                 all_calls(None, Wrapper, layers=layers, table=(4, 2), pred=(4, 4), blocks=16)[name]()
+
+
+def test_a_missing_extension_module_is_named(monkeypatch, tmp_path):
+    monkeypatch.setattr(kvc, "_lib", None)
+    for name in ("LIB_PATH", "BINDING_PATH"):
+        with monkeypatch.context() as m:
+            m.setattr(kvc, name, str(tmp_path / "nothing.so"))
+            with pytest.raises(ImportError, match="nothing.so is not built; run `python -m paper_2512_11920_amd.build`"):
+                kvc.load()
