@@ -584,9 +584,10 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
     __shared__ __align__(16) uint32_t s_stage[WAVES][enc_stage_words(NP, PPW)];
     __shared__ uint32_t s_lut[128];
     __shared__ uint32_t s_total[WAVES];  // units of each wave's payloads; kHasRaw: raw pages among them
-    __shared__ unsigned long long s_base;
-    __shared__ uint32_t s_kept;
+    __shared__ unsigned long long s_base;  // its span of the pool begins at this unit; kKept: and is to stay in the last-level cache
+    constexpr unsigned long long kKept = 1ull << 63;
     constexpr uint32_t kHasRaw = 1u << 24;
+    static_assert(WAVES * PPW * NP * 64 < (1 << 24) && WAVES < 128, "the sum over a workgroup keeps both parts apart");
     __shared__ EncPlace s_place[WAVES * PPW];
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -658,28 +659,26 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
     if (lane == 0) s_total[wave] = total | (held != total ? kHasRaw : 0u);
     __syncthreads();
     if (threadIdx.x == 0) {
-        uint32_t all = 0, raw_too = 0;
+        uint32_t sum = 0;  // (units of all waves, and above them how many have raw pages)
 #pragma unroll
-        for (int k = 0; k < WAVES; ++k) {
-            all += s_total[k] & (kHasRaw - 1u);
-            raw_too |= s_total[k] & kHasRaw;
-        }
+        for (int k = 0; k < WAVES; ++k) sum += s_total[k];
+        const uint32_t all = sum % kHasRaw;
         const unsigned long long base = all ? atomicAdd(&a.st->cursor16, (unsigned long long)all) : 0ull;
         if (base + all > a.pool_units) atomicOr(&a.st->status, KVC_ST_POOL_FULL);
-        s_base = base;
-        s_kept = raw_too == 0 && base < a.kept_units;
+        s_base = sum < kHasRaw && base < a.kept_units ? base | kKept : base;
     }
     __syncthreads();
     if (ok == 0) return;
     // lane i: where page i's payload goes; pages that do not fit become INVALID
     uint32_t before = 0;  // units of the waves before this one
 #pragma unroll
-    for (int k = 0; k < WAVES - 1; ++k) before += k < wave ? s_total[k] & (kHasRaw - 1u) : 0u;
+    for (int k = 0; k < WAVES - 1; ++k) before += k < wave ? s_total[k] : 0u;
+    before %= kHasRaw;
     wave_sync();
     const EncPlace& own = s_place[wave * PPW + min(lane, PPW - 1)];
     const uint32_t w_own = lane < PPW ? own.w : 0u;  // lane i: page i's
     const uint32_t n_own = w_own & 0xFFFFu;
-    const uint64_t off16 = s_base + before + (kUniform ? 0u : row16_incl_scan_dpp(n_own) - n_own);
+    const uint64_t off16 = s_base % kKept + before + (kUniform ? 0u : row16_incl_scan_dpp(n_own) - n_own);
     const bool fits = off16 + n_own <= a.pool_units;
     if (lane < 32 && ((ok >> (lane & 31)) & 1u)) {
         const uint64_t off = off16 * 16u;
@@ -721,7 +720,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(enc_
     // for themselves.  Compress / compress and decompress, us, every payload stored past the cache, those of clean waves kept, those
     // of clean workgroups: 256 MiB of 16 x 64, every second page raw, 104 / 180, 103 / 182, 103 / 181, of 16 x 256 116 / 203,
     // 119 / 217, 116 / 203; one page in 64 raw 75 / 145, 73 / 130, 74 / 136.)
-    const bool kept = wave_uniform((int)s_kept) != 0;
+    const bool kept = wave_uniform((int32_t)(s_base >> 32)) < 0;
     if (raws == 0) {
         const uint32_t n = unfit ? (uint32_t)(of_lane<false>(off16, __builtin_ctz(unfit)) - base16) : total;
         if (kept)
