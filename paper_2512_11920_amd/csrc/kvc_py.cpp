@@ -40,15 +40,6 @@ long long integer(PyObject* o) {
     return v;
 }
 
-// (None: a codec that has been closed; the library refuses it)
-template <class T>
-T address(PyObject* o) {
-    if (o == Py_None) return nullptr;
-    void* p = PyLong_AsVoidPtr(o);
-    if (!p && PyErr_Occurred()) throw Raised();
-    return reinterpret_cast<T>(p);
-}
-
 // A reference that is given back.
 struct Ref {
     PyObject* o;
@@ -58,6 +49,31 @@ struct Ref {
     ~Ref() { Py_DECREF(o); }
     Ref(const Ref&) = delete;
 };
+
+// An integer that goes straight to a C entry point, where ctypes also took its own integers and what an object names in
+// _as_parameter_.
+long long passed(PyObject* o) {
+    if (PyIndex_Check(o)) return integer(o);
+    for (const char* what : {"_as_parameter_", "value"})
+        if (PyObject_HasAttrString(o, what)) return passed(Ref(PyObject_GetAttrString(o, what)).o);
+    return integer(o);
+}
+
+// (None: a codec that has been closed; the library refuses it.  A stream may be one of ctypes' pointers, from a program that made it
+// with the runtime.)
+template <class T>
+T address(PyObject* o) {
+    if (o == Py_None) return nullptr;
+    if (!PyLong_Check(o)) {
+        const Ref ctypes(PyImport_ImportModule("ctypes")), type(PyObject_GetAttrString(ctypes.o, "c_void_p"));
+        const Ref pointer(PyObject_CallMethod(ctypes.o, "cast", "OO", o, type.o));
+        const Ref value(PyObject_GetAttrString(pointer.o, "value"));
+        return address<T>(value.o);
+    }
+    void* p = PyLong_AsVoidPtr(o);
+    if (!p && PyErr_Occurred()) throw Raised();
+    return reinterpret_cast<T>(p);
+}
 
 // An argument that is to be a tensor.  torch's own are looked at directly; a subclass, or any other object with a tensor's attributes (a
 // wrapper of one), is asked as Python code would ask it.
@@ -247,7 +263,7 @@ PyObject* py_prefetch(PyObject*, PyObject* const* a, Py_ssize_t given) {
         const long long n_slots = b.n / 2;
         int32_t *tags = ids_of(a[4], 2 * n_slots), *fetch = ids_of(a[5], n_slots), *loc = ids_of(a[6], n_slots);
         const int32_t *t = ids_at_least(a[7], 0), *p = ids_at_least(a[8], 0), *l1 = a[9] == Py_None ? nullptr : ids_of(a[9], n_seq);
-        const long long begin = integer(a[11]), end = a[12] == Py_None ? layers : integer(a[12]), per_layer = integer(a[13]), half = integer(a[14]);
+        const long long begin = passed(a[11]), end = a[12] == Py_None ? layers : passed(a[12]), per_layer = integer(a[13]), half = passed(a[14]);
         void* stream = address<void*>(a[15]);
         return unlocked([&] {
             return e.prefetch(ctx, b.at, tags, fetch, loc, t, (int32_t)max_blocks, p, l1, (int32_t)n_seq, (int32_t)k, (int32_t)layers, (int32_t)begin, (int32_t)end,

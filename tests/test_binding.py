@@ -1,4 +1,6 @@
 """The checks of the Python binding's data calls: what a tensor has to be, and which blocks a call without a count means."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -142,3 +144,26 @@ def test_a_missing_extension_module_is_named(monkeypatch, tmp_path):
             m.setattr(kvc, name, str(tmp_path / "nothing.so"))
             with pytest.raises(ImportError, match="nothing.so is not built; run `python -m paper_2512_11920_amd.build`"):
                 kvc.load()
+
+
+class Named:
+    def __init__(self, v):
+        self._as_parameter_ = v
+
+
+@pytest.mark.parametrize("integer", [int, C.c_int32, np.int64, lambda v: Named(v), lambda v: Named(C.c_int32(v))])
+@pytest.mark.parametrize("pointer", [int, C.c_void_p, lambda v: Named(v), lambda v: C.cast(v, C.POINTER(C.c_char))])
+def test_streams_and_layers_as_ctypes_took_them(integer, pointer):
+    """The first and last layer, the half and the stream of a call are handed on as they are: what ctypes takes for an integer or an address."""
+    kvc.load()
+    half, ids = (lambda n: Wrapper(torch.zeros(64 * n, dtype=torch.float16))), (lambda *s: Wrapper(torch.zeros(s, dtype=torch.int32)))
+    for stream in (pointer(0), pointer(1 << 40)):
+        assert kvc._call.compress(None, half(6), 64, 64, None, None, None, None, stream) == kvc.ERR_ARG
+        assert kvc._call.decompress(None, half(6), 64, 64, None, None, None, stream) == kvc.ERR_ARG
+        assert kvc._call.gather(None, half(6), 64, 64, ids(3, 2), ids(3, 2), 1, 4, stream) == kvc.ERR_ARG
+        for end in (None, integer(1)):
+            assert kvc._call.prefetch(None, half(12), 64, 64, ids(12), ids(6), ids(6), ids(3, 2), ids(3, 2), None, 1, integer(0), end, 4, integer(1), stream) == kvc.ERR_ARG
+    with pytest.raises((TypeError, C.ArgumentError)):
+        kvc._call.compress(None, half(6), 64, 64, None, None, None, None, 1.5)
+    with pytest.raises(TypeError):
+        kvc._call.prefetch(None, half(12), 64, 64, ids(12), ids(6), ids(6), ids(3, 2), ids(3, 2), None, 1, 0.5, None, 4, 0, 0)
