@@ -1,5 +1,6 @@
 // C ABI of libkvc (see include/kvc.h): argument checks and kernel launches only.
 #include <algorithm>
+#include <atomic>
 #include <new>
 
 #include "kvc_common.h"
@@ -27,7 +28,30 @@ struct kvc_ctx {
     bool pool_in_hbm, desc_in_hbm;  // plain memory of this device
     kvc_desc* desc;
     uint64_t n_desc;
+    std::atomic<uint64_t> waiting{0};  // its part of g_waiting
 };
+
+// Bytes of payload that contexts have stored to stay in each device's last-level cache and not fetched yet, and their number is
+// bounded: what does not fit beside another context's is stored past the cache (see kPoolKeptBytes).  A bound on what
+// an encoded page takes is counted, as the payloads' size is not known here.  It decides where payloads are cached, nothing else.
+static constexpr int kWaitingDevices = 64;
+static std::atomic<uint64_t> g_waiting[kWaitingDevices];
+
+// The context's payloads have been asked for, or given up.
+static void none_waiting(kvc_ctx* ctx) {
+    if (const uint64_t b = ctx->waiting.exchange(0, std::memory_order_relaxed)) g_waiting[ctx->device].fetch_sub(b, std::memory_order_relaxed);
+}
+
+// Whether payloads of at most so many bytes are to stay in the cache until they are fetched.
+static bool may_wait(kvc_ctx* ctx, uint64_t bytes) {
+    if (!ctx->pool_in_hbm || ctx->device >= kWaitingDevices) return false;
+    const uint64_t own = ctx->waiting.load(std::memory_order_relaxed), all = g_waiting[ctx->device].load(std::memory_order_relaxed);
+    const uint64_t more = std::min(bytes, kvc::kPoolKeptBytes - std::min(own, kvc::kPoolKeptBytes));  // (no more of a pool is kept)
+    if (all > own && all + more > kvc::kPoolKeptBytes) return false;
+    ctx->waiting.fetch_add(more, std::memory_order_relaxed);
+    g_waiting[ctx->device].fetch_add(more, std::memory_order_relaxed);
+    return true;
+}
 
 static_assert(sizeof(kvc_desc) == 16, "descriptor is 16 bytes");
 
@@ -115,6 +139,7 @@ int kvc_create(kvc_ctx** out, const kvc_config* cfg) {
 
 void kvc_destroy(kvc_ctx* ctx) {
     if (!ctx) return;
+    none_waiting(ctx);
     (void)hipFree(ctx->st);
     delete ctx;
 }
@@ -170,6 +195,7 @@ int kvc_bind_pool(kvc_ctx* ctx, void* d_pool, uint64_t pool_bytes, kvc_desc* d_d
         if (!dattr.devicePointer) return KVC_ERR_ARG;
         d_desc = static_cast<kvc_desc*>(dattr.devicePointer);
     }
+    none_waiting(ctx);
     ctx->pool = static_cast<uint8_t*>(d_pool);
     ctx->pool_bytes = pool_bytes;
     ctx->pool_in_hbm = attr.type == hipMemoryTypeDevice && attr.device == ctx->device;
@@ -183,6 +209,7 @@ int kvc_reset_pool(kvc_ctx* ctx, void* stream) {
     if (!ctx) return KVC_ERR_ARG;
     if (!ctx->pool) return KVC_ERR_NOT_BOUND;
     if (!on_ctx_device(ctx)) return KVC_ERR_ARG;
+    none_waiting(ctx);
     return hip_ok(kvc::launch_reset(ctx->st, ctx->desc, ctx->n_desc, static_cast<hipStream_t>(stream)))
                ? KVC_OK
                : KVC_ERR_HIP;
@@ -193,6 +220,7 @@ int kvc_restore_pool(kvc_ctx* ctx, uint64_t used_bytes, void* stream) {
     if (!ctx->pool) return KVC_ERR_NOT_BOUND;
     if ((used_bytes & 15u) || used_bytes > ctx->pool_bytes) return KVC_ERR_ARG;
     if (!on_ctx_device(ctx)) return KVC_ERR_ARG;
+    none_waiting(ctx);
     return hip_ok(kvc::launch_set_cursor(ctx->st, used_bytes / 16, static_cast<hipStream_t>(stream))) ? KVC_OK : KVC_ERR_HIP;
 }
 
@@ -219,7 +247,7 @@ static int compress_impl(kvc_ctx* ctx, const void* d_cache, int64_t n_cache_bloc
     a.by_ppb = kvc::make_fast_div((uint32_t)ctx->g.ppb);
     a.pool = ctx->pool;
     a.pool_units = ctx->pool_bytes / 16;
-    a.kept_units = ctx->pool_in_hbm ? kvc::kPoolKeptBytes / 16 : 0;
+    a.kept_units = may_wait(ctx, (uint64_t)a.n_pages * (uint64_t)ctx->g.E) ? kvc::kPoolKeptBytes / 16 : 0;
     a.desc = ctx->desc;
     a.n_desc = ctx->n_desc;
     a.st = ctx->st;
@@ -238,6 +266,7 @@ int kvc_compress_blocks_mixed(kvc_ctx* ctx, const void* d_cache, int64_t n_cache
 }
 
 static void fill_decode_common(kvc_ctx* ctx, kvc::DecodeArgs& a) {
+    none_waiting(ctx);
     a.g = ctx->g;
     a.pool = ctx->pool;
     a.pool_units = ctx->pool_bytes / 16;

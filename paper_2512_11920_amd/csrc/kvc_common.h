@@ -73,6 +73,13 @@ struct DecodeArgs {
 // order: with no limit half a million pages of 16 x 128, mode 5, are encoded in 512 us (484 with the hint), and fetched back
 // no sooner.  Limits of 128, 192, 208, 224 and 256 MB: 16 x 64 510, 502, 502, 500, 520; 65,536 pages of 16 x 256, a mode per
 // block, 274, 268, 268, 271, 282 (278 with the hint).
+// What it takes to gain: the blocks come back before much else is stored or read, and the pool is young or was reset.  So the payloads
+// that contexts keep, and have not fetched, are that many bytes in all; others' are stored past the cache, or they would push
+// each other out.  Sixteen pools of 256 MiB of 16 x 128, all offloaded, then all fetched, us a pool, none kept / each pool's
+// beginning / what fits: 141.3 / 144.1 / 139.9, 32 of 64 MiB 44.2 / 46.4 / 43.6 (offload 22.3 / 24.2 / 22.5), 64 of 16 MiB 18.6 / 19.0 / 18.2
+// (11.2 / 12.3 / 11.7); each fetched right after its offload 142.4 / 130.9 / 130.7, 44.8 / 41.8 / 41.7, 18.7 / 18.5 / 18.6.  16 x 32, 16 x 64, 16 x 256
+// and mode 5 the same.  What it costs others: two reads of 224 MB that the cache would hold, after a compress of 256 MiB, take with
+// it 151 -> 158, of 160 MB 134 -> 135, of 96 MB 117 -> 113.
 constexpr uint64_t kPoolKeptBytes = 208ull << 20;
 // Calls that decode a whole range of more payload than the cache holds read what lies beyond that beginning with the
 // hint: read plainly, it pushes out the beginning, and then itself, before either is read again.  By the size of the

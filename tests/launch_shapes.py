@@ -5,7 +5,8 @@ its launches down (tests/launch_recorder.cpp), in a process of its own, and call
 
 A call is a dict: op ("compress", "decompress", "gather", "prefetch"), N, d, ppb, scheme, n (blocks) and, by op, lists
 (names of the id lists it passes), mixed (a mode per block), layers, seqs, k, omega; desc: pages of its descriptor table, where that is not to be a
-huge one; memory: (hipMemoryType, device) of its pool.  Launch.line: kept_units or near_bytes of an encoder or decoder, in bytes of the pool."""
+huge one; memory: (hipMemoryType, device) of its pool; context: a name, where calls share one (the first says what it is; it lives as
+long as its process).  "reset" and "restore" are calls too.  Launch.line: kept_units or near_bytes of an encoder or decoder, in bytes of the pool."""
 import collections
 import ctypes as C
 import json
@@ -74,12 +75,15 @@ def _main(recorder, lib):
     rec.rec_kernel.restype, rec.rec_line.restype = C.c_char_p, C.c_ulonglong
     L = C.CDLL(lib)
     at, big, i32, i64 = C.c_void_p(1 << 20), C.c_uint64(1 << 40), C.c_int32, C.c_int64
-    out = []
+    out, kept = [], {}
     for c in json.load(sys.stdin):
         cfg, ctx = (i32 * 4)(c["N"], c["d"], c["ppb"], c.get("scheme", 3)), C.c_void_p()
         n, lists = c.get("n", 0), c.get("lists", ())
         rec.rec_memory(*c.get("memory", (2, 0)))
-        assert L.kvc_create(C.byref(ctx), cfg) == 0 and L.kvc_bind_pool(ctx, at, big, at, C.c_uint64(c.get("desc", 1 << 40))) == 0
+        ctx = kept.get(c.get("context"), ctx)
+        assert ctx or L.kvc_create(C.byref(ctx), cfg) == 0 and L.kvc_bind_pool(ctx, at, big, at, C.c_uint64(c.get("desc", 1 << 40))) == 0
+        if "context" in c:
+            kept[c["context"]] = ctx
         rec.rec_clear()
         opt = lambda name: at if name in lists else None
         if c["op"] == "compress" and c.get("mixed"):
@@ -88,6 +92,10 @@ def _main(recorder, lib):
             rc = L.kvc_compress_blocks(ctx, at, i64(n), opt("src"), opt("pool"), i32(n), None)
         elif c["op"] == "decompress":
             rc = L.kvc_decompress_blocks(ctx, at, i64(n), opt("pool"), opt("dst"), i32(n), None)
+        elif c["op"] == "reset":
+            rc = L.kvc_reset_pool(ctx, None)
+        elif c["op"] == "restore":
+            rc = L.kvc_restore_pool(ctx, C.c_uint64(1 << 20), None)
         elif c["op"] == "gather":
             rc = L.kvc_gather_decompress(ctx, at, at, i32(64), at, i32(c["seqs"]), i32(c["k"]), i32(c["layers"]), i64(64), None)
         else:
@@ -103,7 +111,8 @@ def _main(recorder, lib):
             rec.rec_shape(i, C.byref(g), C.byref(b), C.byref(l))
             rows.append((rec.rec_kernel(i).decode(), g.value, b.value, l.value, rec.rec_line(i)))
         out.append(rows)
-        L.kvc_destroy(ctx)
+        if "context" not in c:
+            L.kvc_destroy(ctx)
     print(json.dumps(out))
 
 

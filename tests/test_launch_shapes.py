@@ -108,3 +108,51 @@ def test_which_calls_read_past_the_last_level_cache():
     want += [plain] * 2
     for call, line, l in zip(calls, want, launches(calls)):
         assert l[-1].kernel == ("k_compress" if call["op"] == "compress" else "k_decompress") and l[-1].line == line, (call, l)
+
+
+def test_what_waits_in_the_last_level_cache_is_bounded():
+    """Payloads wait there until their context fetches or gives them up.  Those of another are stored past it unless both fit: 208 MB, of
+    which a block of 8 pages of 16 x 128 is counted as 16 KB."""
+    all_of_it = (208 << 20) // (8 * 2048)
+    shape = dict(N=16, d=128, ppb=8)
+
+    def compress(context, n, **kw):
+        return dict(op="compress", context=context, n=n, **shape, **kw)
+
+    fetches = [decode(16, 128, 8, 1), decode(16, 128, 8, 1, lists=["pool"]), dict(op="gather", seqs=1, k=1, layers=1, **shape), dict(op="prefetch", seqs=1, k=1, layers=1, omega=0, **shape),
+               dict(op="prefetch", seqs=1, k=1, layers=1, omega=4, **shape), dict(op="reset", **shape), dict(op="restore", **shape)]
+    calls, want = [], []
+
+    def then(call, keeps=None):
+        calls.append(call)
+        want.append(keeps)
+
+    for f in fetches:
+        then(compress("a", 4 * all_of_it), True)  # one context: all calls, whatever their size
+        then(compress("a", 1), True)
+        then(compress("b", 1), False)
+        then(compress("b", 1), False)
+        then(dict(f, context="a"))
+        then(compress("b", all_of_it - 64), True)  # a and b beside one another
+        then(compress("a", 64, lists=["src", "pool"]), True)
+        then(compress("a", 1), False)
+        then(compress("b", 1), False)
+        then(compress("c", 1, memory=(1, 0)), False)  # c is behind the host link: takes no part
+        then(dict(f, context="c"))
+        then(compress("d", 1), False)
+        then(dict(f, context="b"))
+        then(compress("d", all_of_it - 64), True)
+        then(dict(f, context="a"))
+        then(compress("d", 1), True)
+        then(compress("a", 64), False)
+        then(dict(f, context="d"))
+    for call, keeps, l in zip(calls, want, launches(calls)):
+        if keeps is not None:
+            assert l[-1].line == (208 << 20 if keeps else 0), call
+    # a context that ends gives its part back
+    ended = [compress("a", 1), dict(compress("", all_of_it)), compress("a", 1), compress("b", 1)]
+    del ended[1]["context"]
+    assert [l[-1].line for l in launches(ended)] == [208 << 20, 0, 208 << 20, 208 << 20]
+    ended = [dict(compress("", all_of_it)), compress("a", all_of_it)]
+    del ended[0]["context"]
+    assert [l[-1].line for l in launches(ended)] == [208 << 20] * 2
