@@ -956,7 +956,7 @@ constexpr int dec_int8_step(int np) { return np >= 5 ? np : 2; }
 
 // Start the payload loads of PPW pages, those of lanes first .. first + PPW - 1: the i-th goes to LDS slot i, 16
 // bytes per lane and round, without a stop in registers.  Payload bytes past the page's own are not read.
-template <class P, int PPW, bool UNIFORM, bool MAY_STREAM = false>
+template <class P, int PPW, bool UNIFORM, bool PAST = false>
 __device__ __forceinline__ void dec_fetch(const DecodeArgs& a, const DecLanes& L, int first, uint32_t (*slots)[Slot<P::kPasses>::kWords], uint64_t near = ~0ull) {
     const uint32_t lane = (uint32_t)lane_id();
     const bool staged = (L.meta >> 24) == kDecPayload && (kStageInt8<PPW> || ((L.meta >> 16) & 0xFFu) != KVC_MODE_INT8);
@@ -966,7 +966,7 @@ __device__ __forceinline__ void dec_fetch(const DecodeArgs& a, const DecLanes& L
         const uint32_t n16 = of_lane<UNIFORM>(n_own, first + i);
         const uint64_t off = of_lane<UNIFORM>(L.off, first + i);
         const uint8_t* src = a.pool + off;
-        if (MAY_STREAM && off >= near) {
+        if (PAST && off >= near) {
 #pragma unroll
             for (int z = 0; z < P::kRounds; ++z)
                 if (lane + 64u * z < n16) load_to_lds16<true>(src + (lane + 64u * z) * 16u, reinterpret_cast<uint4*>(slots[i]) + 64 * z);
@@ -1196,7 +1196,7 @@ __device__ __forceinline__ void dec_page(const DecodeArgs& a, const Extent& x, c
 }
 
 // Decode the pages whose payloads dec_fetch has loaded (dec_fetched: they are there).
-template <class P, int PPW, bool UNIFORM, bool MAY_STREAM = false>
+template <class P, int PPW, bool UNIFORM, bool PAST = false>
 __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L, int first, const LanePos& lp, uint32_t (*slots)[Slot<P::kPasses>::kWords], bool few,
                                           uint64_t near = ~0ull) {
     using H = HeaderDeal<P>;
@@ -1229,7 +1229,7 @@ __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L
             if (kind == kDecRaw) {  // stored-uncompressed bypass
                 const uint64_t off = of_lane<UNIFORM>(L.off, first + i);
                 const uint4* src = reinterpret_cast<const uint4*>(a.pool + off);
-                if (MAY_STREAM && off >= near)
+                if (PAST && off >= near)
                     dec_raw<P, 1, true>(a, x, lp, dst_b, src);
                 else if (few)
                     dec_raw<P, P::kPasses>(a, x, lp, dst_b, src);
@@ -1241,7 +1241,7 @@ __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L
             const float s = __uint_as_float(of_lane<UNIFORM>(__float_as_uint(L.s), first + i));
             if (mode == KVC_MODE_INT8) {
                 const uint2* src = kStageInt8<PPW> ? reinterpret_cast<const uint2*>(slots[i]) : reinterpret_cast<const uint2*>(a.pool + of_lane<UNIFORM>(L.off, first + i));
-                if (MAY_STREAM && !kStageInt8<PPW> && of_lane<UNIFORM>(L.off, first + i) >= near)
+                if (PAST && !kStageInt8<PPW> && of_lane<UNIFORM>(L.off, first + i) >= near)
                     dec_int8<P, dec_int8_step(P::kPasses), true>(a, x, lp, s, dst_b, src);
                 else if (kStageInt8<PPW> || few || dec_int8_step(P::kPasses) >= P::kPasses)
                     dec_int8<P, P::kPasses>(a, x, lp, s, dst_b, src);
@@ -1257,7 +1257,9 @@ __device__ __forceinline__ void dec_batch(const DecodeArgs& a, const DecLanes& L
     }
 }
 
-template <class P, int WAVES, int PPW>
+// PAST: of a call with near_bytes.  (A kernel of its own: asked page by page in the others too, gathers of 51,520 raw pages of 16 x 32 took 18.6
+// us, 18.0 without.)
+template <class P, bool PAST, int WAVES, int PPW>
 __global__ __launch_bounds__(WAVES * 64) void k_decompress(DecodeArgs a) {
     __shared__ __align__(16) uint32_t s_stage[WAVES][PPW][Slot<P::kPasses>::kWords];
     const int lane = lane_id();
@@ -1269,13 +1271,14 @@ __global__ __launch_bounds__(WAVES * 64) void k_decompress(DecodeArgs a) {
     const LanePos lp = lane_pos<P>(a.g);
     // (a batch of one page is resolved on the scalar unit: every lane has the same task)
     const DecLanes L = dec_open<P>(a, PPW == 1 ? dec_locate(a, t0 < a.n_pages, (uint32_t)t0) : dec_locate(a, lane < PPW && t0 + lane < a.n_pages, (uint32_t)t0 + (uint32_t)lane));
-    // (a call with near_bytes decodes blocks 0, 1, ... of the pool: its first descriptor says where its payloads begin.  Read by the
-    // scalar unit: a vector load of one line by every wave costs 2 %.)
-    uint64_t near = a.near_bytes;
-    if (near != ~0ull && *(const __attribute__((address_space(4))) uint64_t*)&a.desc[0].off >= near) near = ~0ull;
-    dec_fetch<P, PPW, PPW == 1, true>(a, L, 0, s_stage[wave], near);
+    uint64_t near = ~0ull;
+    if constexpr (PAST) {  // (blocks 0, 1, ... of the pool: the first descriptor says where the payloads begin.  Read by the
+        near = a.near_bytes;  // scalar unit: a vector load of one line by every wave costs 2 %.)
+        if (*(const __attribute__((address_space(4))) uint64_t*)&a.desc[0].off >= near) near = ~0ull;
+    }
+    dec_fetch<P, PPW, PPW == 1, PAST>(a, L, 0, s_stage[wave], near);
     dec_fetched();
-    dec_batch<P, PPW, PPW == 1, true>(a, L, 0, lp, s_stage[wave], a.n_pages <= kDecFewPages, near);
+    dec_batch<P, PPW, PPW == 1, PAST>(a, L, 0, lp, s_stage[wave], a.n_pages <= kDecFewPages, near);
 }
 
 // Transfer engines of the prefetch window that go turn by turn (Algorithm 1: at most Omega_max transfers outstanding):
@@ -1634,7 +1637,7 @@ struct ShapeOps {
 
     static hipError_t decompress(const DecodeArgs& a, hipStream_t s) {
         if constexpr (dec_ppw(NP) > 1) {
-            if (a.n_pages <= kDecSmallPages(NP)) return launch_kernel(k_decompress<P, kCodecWaves, 1>, page_grid(a.n_pages, 1), dim3(kCodecWaves * 64), s, a);
+            if (a.n_pages <= kDecSmallPages(NP)) return launch_kernel(k_decompress<P, false, kCodecWaves, 1>, page_grid(a.n_pages, 1), dim3(kCodecWaves * 64), s, a);
         }
         constexpr int own = kCodecWaves * dec_ppw(NP) * Slot<NP>::kBytes, groups = dec_groups(NP, PARTIAL), middle = dec_groups_middle(NP);
         constexpr int spare = dec_spare_lds(groups, own), spare_middle = dec_spare_lds(middle, own);
@@ -1642,7 +1645,8 @@ struct ShapeOps {
         static_assert(spare_middle >= 0 && (middle == 0 || own + spare_middle > kLdsPerCu / (middle + 1)), "one group more does not fit");
         const bool whole = !a.pool_ids && !a.dst_ids && !a.block_table;
         const int lds = a.n_pages < kDecMiddlePages ? 0 : a.n_pages < kDecLimitPages ? spare_middle : whole ? spare : 0;
-        return launch_kernel_lds(k_decompress<P, kCodecWaves, dec_ppw(NP)>, page_grid(a.n_pages, dec_ppw(NP)), dim3(kCodecWaves * 64), lds, s, a);
+        const auto kernel = a.near_bytes != ~0ull ? k_decompress<P, true, kCodecWaves, dec_ppw(NP)> : k_decompress<P, false, kCodecWaves, dec_ppw(NP)>;
+        return launch_kernel_lds(kernel, page_grid(a.n_pages, dec_ppw(NP)), dim3(kCodecWaves * 64), lds, s, a);
     }
 
     // whether the wide engines of blocks of ppb pages are of the kind that looks ahead

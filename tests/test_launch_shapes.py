@@ -108,6 +108,8 @@ def test_which_calls_read_past_the_last_level_cache():
     want += [plain] * 2
     for call, line, l in zip(calls, want, launches(calls)):
         assert l[-1].kernel == ("k_compress" if call["op"] == "compress" else "k_decompress") and l[-1].line == line, (call, l)
+        if l[-1].kernel == "k_decompress":  # the kernel that asks where a payload lies, for these calls alone
+            assert l[-1].params[3] == (line == kept), (call, l)
 
 
 def test_what_waits_in_the_last_level_cache_is_bounded():
