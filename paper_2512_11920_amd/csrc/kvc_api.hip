@@ -247,7 +247,7 @@ static int compress_impl(kvc_ctx* ctx, const void* d_cache, int64_t n_cache_bloc
     a.by_ppb = kvc::make_fast_div((uint32_t)ctx->g.ppb);
     a.pool = ctx->pool;
     a.pool_units = ctx->pool_bytes / 16;
-    a.kept_units = may_wait(ctx, (uint64_t)a.n_pages * (uint64_t)ctx->g.E) ? kvc::kPoolKeptBytes / 16 : 0;
+    a.kept_units = a.n_pages >= kvc::kKeptFromPages && may_wait(ctx, (uint64_t)a.n_pages * (uint64_t)ctx->g.E) ? kvc::kPoolKeptBytes / 16 : 0;
     a.desc = ctx->desc;
     a.n_desc = ctx->n_desc;
     a.st = ctx->st;

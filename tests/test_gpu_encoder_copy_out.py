@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 
 # a wave of one page, of several, and of the large shapes; payloads of one round of lanes and of many
-@pytest.mark.parametrize("N,d,scheme,pages", [(16, 32, 3, 40), (16, 32, 3, 1030), (16, 32, 3, 0), (7, 32, 4, 0), (16, 64, 5, 0), (24, 96, 2, 0), (16, 128, 3, 600), (16, 128, 3, 0), (16, 128, 1, 0), (16, 256, 3, 0)])
+@pytest.mark.parametrize("N,d,scheme,pages", [(16, 32, 3, 40), (16, 32, 3, 1030), (16, 32, 3, 0), (7, 32, 4, 0), (16, 64, 5, 0), (24, 96, 2, 0), (16, 128, 3, 600), (16, 128, 3, 0), (16, 128, 1, 0), (16, 256, 3, 0),
+                                                (16, 32, 3, 127), (16, 32, 3, 128), (16, 64, 5, 128), (7, 128, 4, 200), (16, 128, 3, 127), (16, 128, 1, 300), (24, 96, 2, 512), (16, 256, 3, 512), (16, 256, 3, 513)])
 def test_nothing_beside_the_payloads_changes(N, d, scheme, pages):
     n = pages or large_encoder_pages(N, d, scheme) + 9
     x = make_pages(np.random.default_rng(N * d + n), n, N, d)

@@ -114,14 +114,14 @@ def test_which_calls_read_past_the_last_level_cache():
 
 def test_what_waits_in_the_last_level_cache_is_bounded():
     """Payloads wait there until their context fetches or gives them up.  Those of another are stored past it unless both fit: 208 MB, of
-    which a block of 8 pages of 16 x 128 is counted as 16 KB."""
-    all_of_it = (208 << 20) // (8 * 2048)
-    shape = dict(N=16, d=128, ppb=8)
+    which a block of 128 pages of 16 x 128 is counted as 256 KB."""
+    all_of_it = (208 << 20) // (128 * 2048)
+    shape = dict(N=16, d=128, ppb=128)
 
     def compress(context, n, **kw):
         return dict(op="compress", context=context, n=n, **shape, **kw)
 
-    fetches = [decode(16, 128, 8, 1), decode(16, 128, 8, 1, lists=["pool"]), dict(op="gather", seqs=1, k=1, layers=1, **shape), dict(op="prefetch", seqs=1, k=1, layers=1, omega=0, **shape),
+    fetches = [decode(16, 128, 128, 1), decode(16, 128, 128, 1, lists=["pool"]), dict(op="gather", seqs=1, k=1, layers=1, **shape), dict(op="prefetch", seqs=1, k=1, layers=1, omega=0, **shape),
                dict(op="prefetch", seqs=1, k=1, layers=1, omega=4, **shape), dict(op="reset", **shape), dict(op="restore", **shape)]
     calls, want = [], []
 
@@ -135,18 +135,18 @@ def test_what_waits_in_the_last_level_cache_is_bounded():
         then(compress("b", 1), False)
         then(compress("b", 1), False)
         then(dict(f, context="a"))
-        then(compress("b", all_of_it - 64), True)  # a and b beside one another
-        then(compress("a", 64, lists=["src", "pool"]), True)
+        then(compress("b", all_of_it - 4), True)  # a and b beside one another
+        then(compress("a", 4, lists=["src", "pool"]), True)
         then(compress("a", 1), False)
         then(compress("b", 1), False)
         then(compress("c", 1, memory=(1, 0)), False)  # c is behind the host link: takes no part
         then(dict(f, context="c"))
         then(compress("d", 1), False)
         then(dict(f, context="b"))
-        then(compress("d", all_of_it - 64), True)
+        then(compress("d", all_of_it - 4), True)
         then(dict(f, context="a"))
         then(compress("d", 1), True)
-        then(compress("a", 64), False)
+        then(compress("a", 4), False)
         then(dict(f, context="d"))
     for call, keeps, l in zip(calls, want, launches(calls)):
         if keeps is not None:
@@ -158,3 +158,8 @@ def test_what_waits_in_the_last_level_cache_is_bounded():
     ended = [dict(compress("", all_of_it)), compress("a", all_of_it)]
     del ended[0]["context"]
     assert [l[-1].line for l in launches(ended)] == [208 << 20] * 2
+    # and calls of fewer than 128 pages leave none there
+    few = [dict(op="compress", N=N, d=d, ppb=1, n=n, lists=lists, scheme=scheme) for N, d in ((16, 32), (16, 128), (7, 96), (16, 256)) for scheme in (1, 3)
+           for lists in ([], ["src", "pool"]) for n in (1, 64, 127, 128, 129)]
+    for call, l in zip(few, launches(few)):
+        assert l[-1].line == (208 << 20 if call["n"] >= 128 else 0), call
