@@ -31,9 +31,10 @@ struct kvc_ctx {
     std::atomic<uint64_t> waiting{0};  // its part of g_waiting
 };
 
-// Bytes of payload that contexts have stored to stay in each device's last-level cache and not fetched yet, and their number is
-// bounded: what does not fit beside another context's is stored past the cache (see kPoolKeptBytes).  A bound on what
-// an encoded page takes is counted, as the payloads' size is not known here.  It decides where payloads are cached, nothing else.
+// Bytes of payload that the contexts of this process have stored to stay in each device's last-level cache and not fetched yet.
+// They are bounded: what does not fit beside another context's is stored past the cache (see kPoolKeptBytes).  Counted when a
+// call is made, or captured, with the most an encoded page takes, as the payloads' size is not known here.  It decides where
+// payloads are cached, nothing else: calls of several threads that read it at once may keep a little more.
 static constexpr int kWaitingDevices = 64;
 static std::atomic<uint64_t> g_waiting[kWaitingDevices];
 
@@ -48,8 +49,8 @@ static bool may_wait(kvc_ctx* ctx, uint64_t bytes) {
     const uint64_t own = ctx->waiting.load(std::memory_order_relaxed), all = g_waiting[ctx->device].load(std::memory_order_relaxed);
     const uint64_t more = std::min(bytes, kvc::kPoolKeptBytes - std::min(own, kvc::kPoolKeptBytes));  // (no more of a pool is kept)
     if (all > own && all + more > kvc::kPoolKeptBytes) return false;
+    g_waiting[ctx->device].fetch_add(more, std::memory_order_relaxed);  // (first: the sum of the parts never exceeds it)
     ctx->waiting.fetch_add(more, std::memory_order_relaxed);
-    g_waiting[ctx->device].fetch_add(more, std::memory_order_relaxed);
     return true;
 }
 
